@@ -59,13 +59,13 @@ __global__ __launch_bounds__(NT, 2) void k_spmm_t(const uint32_t *__restrict__ A
     const int bh = item / kblocks;
     const int nq = Lq / QB;
 
-    // X tile in LDS: row = query, chunk c at row * CPR + (c ^ ((row & 3) << 1))
+    // X tile in LDS: row = query, chunk c at row * CPR + (c ^ tr_row_swizzle(row))
     const __bf16 *Xh = X + (size_t)bh * LqR * D;
     int src_off[LPT];
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
         const int p = i * NT + tid;
-        const int row = p / CPR, c = (p % CPR) ^ ((row & 3) << 1);
+        const int row = p / CPR, c = (p % CPR) ^ tr_row_swizzle<CPR>(row);
         src_off[i] = row * D + c * 8;
     }
     const uint32_t lds_x = lds_address(&Xs[0][w * 64]);
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(NT, 2) void k_spmm_t(const uint32_t *__restrict__ A
 #pragma unroll
             for (int i = 0; i < LPT; ++i) {
                 const int p = i * NT + tid;
-                const int row = p / CPR, c = (p % CPR) ^ ((row & 3) << 1);
+                const int row = p / CPR, c = (p % CPR) ^ tr_row_swizzle<CPR>(row);
                 async_copy16(src, 2u * ((row < real ? row : real - 1) * D + c * 8), lds_x + 16u * (buf * XT + i * NT));
             }
             return;
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(NT, 2) void k_spmm_t(const uint32_t *__restrict__ A
 
     // transposing reads: lane li of a 16-lane group addresses element [row0 + li/4][col0 + 4 (li%4)]
     const int tr_row = li >> 2;
-    const int tr_sub = (li >> 1) & 1, tr_byte = 8 * (li & 1), tr_xor = tr_row << 1;
+    const int tr_sub = (li >> 1) & 1, tr_byte = 8 * (li & 1);
 
     // One step = 64 queries.  The compressed operand is loaded two steps ahead into registers (r0 for
     // even steps, r1 for odd ones: fixed names, so no register is copied while its load is in flight),
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(NT, 2) void k_spmm_t(const uint32_t *__restrict__ A
         };
         auto tr_x = [&](int q0, int nt) {
             const int row = q0 + tr_row;
-            const int chunk = (2 * nt + tr_sub) ^ tr_xor;   // (row & 3) == tr_row: q0 is a multiple of 4
+            const int chunk = (2 * nt + tr_sub) ^ tr_row_swizzle<CPR>(row);
             return lds_read_tr16(xbase + (row * CPR + chunk) * 16 + tr_byte);
         };
 #pragma unroll
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(NT, 2) void k_masked_sddmm_ds(const __bf16 *__restr
     constexpr int TQ = 64 * NQ;          // queries per workgroup
     static_assert(!DQ || D == 64, "the fused dQ needs two LDS tiles per block");
     __shared__ u32x4 Vs[2][TILE];
-    __shared__ u32x4 Kr[DQ ? 2 : 1][DQ ? TILE : 1];   // K block, row = key, chunk c at row * CPR + (c ^ ((row & 3) << 1))
+    __shared__ u32x4 Kr[DQ ? 2 : 1][DQ ? TILE : 1];   // K block, row = key, chunk c at row * CPR + (c ^ tr_row_swizzle(row))
 
     const int tid = threadIdx.x;
     const int w = tid >> 6, l = tid & 63, li = l & 15, kb = l >> 4;
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(NT, 2) void k_masked_sddmm_ds(const __bf16 *__restr
     const int jb0 = ks_id * blocks_per_wg;
     const int q0 = qt * TQ + w * 16 * NQ;
 
-    // LDS position p (16-byte units) = slot * CPR + (c ^ (slot & 7)) holds chunk c of the key stored in row
+    // LDS position p (16-byte units) = slot * CPR + (c ^ operand_row_swizzle(slot)) holds chunk c of the key stored in row
     // slot `slot`; slot 16 t' + i (MFMA tile t', row i) holds key 32 (i/4) + 4 t' + i%4 ... in the order that
     // gives a lane 16 consecutive keys per half
     const __bf16 *Vh = V + (size_t)bh * LkR * D;
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(NT, 2) void k_masked_sddmm_ds(const __bf16 *__restr
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
         const int p = i * NT + tid;
-        const int slot = p / CPR, c = (p % CPR) ^ (slot & 7);
+        const int slot = p / CPR, c = (p % CPR) ^ operand_row_swizzle<CPR, 16>(slot);
         const int key = (slot & 3) | (((slot >> 4) & 7) << 2) | (((slot >> 2) & 3) << 5);
         src_off[i] = key * D + c * 8;
     }
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(NT, 2) void k_masked_sddmm_ds(const __bf16 *__restr
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
         const int p = i * NT + tid;
-        const int row = p / CPR, c = (p % CPR) ^ ((row & 3) << 1);
+        const int row = p / CPR, c = (p % CPR) ^ tr_row_swizzle<CPR>(row);
         k_off[i] = row * D + c * 8;
     }
     const uint32_t lds_k = lds_address(&Kr[0][DQ ? w * 64 : 0]);
@@ -276,7 +276,7 @@ __global__ __launch_bounds__(NT, 2) void k_masked_sddmm_ds(const __bf16 *__restr
 #pragma unroll
             for (int i = 0; i < LPT; ++i) {
                 const int p = i * NT + tid;
-                const int slot = p / CPR, c = (p % CPR) ^ (slot & 7);
+                const int slot = p / CPR, c = (p % CPR) ^ operand_row_swizzle<CPR, 16>(slot);
                 const int key = (slot & 3) | (((slot >> 4) & 7) << 2) | (((slot >> 2) & 3) << 5);
                 async_copy16(src, 2u * ((key < real ? key : real - 1) * D + c * 8), lds_v + 16u * (buf * TILE + i * NT));
             }
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(NT, 2) void k_masked_sddmm_ds(const __bf16 *__restr
 #pragma unroll
                 for (int i = 0; i < LPT; ++i) {
                     const int p = i * NT + tid;
-                    const int row = p / CPR, c = (p % CPR) ^ ((row & 3) << 1);
+                    const int row = p / CPR, c = (p % CPR) ^ tr_row_swizzle<CPR>(row);
                     async_copy16(ksrc, 2u * ((row < real ? row : real - 1) * D + c * 8), lds_k + 16u * (buf * TILE + i * NT));
                 }
             }
@@ -335,7 +335,7 @@ __global__ __launch_bounds__(NT, 2) void k_masked_sddmm_ds(const __bf16 *__restr
     for (int qs = 0; qs < NQ; ++qs)
 #pragma unroll
         for (int ds = 0; ds < DS; ++ds) acc_dq[qs][ds] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int tr_row = li >> 2, tr_sub = (li >> 1) & 1, tr_byte = 8 * (li & 1), tr_xor = tr_row << 1;
+    const int tr_row = li >> 2, tr_sub = (li >> 1) & 1, tr_byte = 8 * (li & 1);
 
     for (int it = 0; it < blocks_per_wg; ++it) {
         const int jb = jb0 + it;
@@ -372,7 +372,7 @@ __global__ __launch_bounds__(NT, 2) void k_masked_sddmm_ds(const __bf16 *__restr
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     const int slot = 16 * (4 * half + t) + li;
-                    av[t] = __builtin_bit_cast(bf16x8, Vs[buf][slot * CPR + ((4 * s + kb) ^ (li & 7))]);
+                    av[t] = __builtin_bit_cast(bf16x8, Vs[buf][slot * CPR + ((4 * s + kb) ^ operand_row_swizzle<CPR, 16>(li))]);
                 }
 #pragma unroll
                 for (int qs = 0; qs < NQ; ++qs)
@@ -401,7 +401,7 @@ __global__ __launch_bounds__(NT, 2) void k_masked_sddmm_ds(const __bf16 *__restr
                     const char *kbase_lds = reinterpret_cast<const char *>(&Kr[buf][0]);
                     auto tr = [&](int key0, int ds) {
                         const int krow = key0 + tr_row;
-                        const int chunk = (2 * ds + tr_sub) ^ tr_xor;
+                        const int chunk = (2 * ds + tr_sub) ^ tr_row_swizzle<CPR>(krow);
                         return lds_read_tr16(kbase_lds + (krow * CPR + chunk) * 16 + tr_byte);
                     };
                     const int k0 = 32 * (kb >> 1) + 16 * half + 8 * (kb & 1);

@@ -94,6 +94,18 @@ __device__ __forceinline__ void wait_async_copies_keep() {
     __builtin_amdgcn_s_waitcnt(0x0F70 | (YOUNGER & 15) | ((YOUNGER >> 4) << 14));
 }
 
+// XOR pattern for the 16-byte chunks of row slot `slot` of a tile that is read as matrix operand, 16 bytes per lane and
+// one row per lane: ROWS = 32 (lane = row l % 32, chunk 2 s + l / 32) or 16 (row l % 16, chunk 4 s + l / 16).  LDS serves
+// 16 lanes per cycle from 64 banks of 4 bytes, which have to be 16 different groups of four banks: with rows of 256 bytes
+// that takes the four low row bits; of 128-byte rows two make up the 64 banks, so with ROWS = 32 it takes the bits from
+// bit 1 up (ROWS = 16: the three low bits do).  Measured, cycles per read and compute unit: 8.3 with the three low bits
+// where the rule says otherwise (two lanes meet in every group), 4.3 with the rule.
+template <int CPR, int ROWS>
+__device__ __forceinline__ int operand_row_swizzle(int slot) {
+    static_assert((CPR == 8 || CPR == 16) && (ROWS == 16 || ROWS == 32), "rows of 128 or 256 bytes, tiles of 16 or 32 rows");
+    return CPR == 16 ? slot & 15 : ROWS == 32 ? (slot >> 1) & 7 : slot & 7;
+}
+
 // XOR pattern for the 16-byte chunks of row `row` of a tile that is read with the transposing 8-byte LDS read
 // (lane (li, g): row = row0(g) + li / 4, chunk 2 x + (li / 2) % 2, half li % 2, where row0 differs between the lane
 // groups g by a multiple of 8): the 32 lanes served together (two groups) then fall into 32 different pairs of banks.

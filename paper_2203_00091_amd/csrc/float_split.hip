@@ -134,7 +134,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_scores_split(const float *__rest
         const int idx = i * NT + tid;
         const int key = idx / CPR, c = idx % CPR;
         const int slot = 16 * ((key >> 2) & 3) + 4 * (key >> 4) + (key & 3);
-        dst[i] = slot * CPR + (c ^ (slot & 7));
+        dst[i] = slot * CPR + (c ^ operand_row_swizzle<CPR, 16>(slot));
     }
     auto convert = [&](const RawBlock<NCONV, NT> &raw, int buf) {
 #pragma unroll
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_scores_split(const float *__rest
             const int slot = 16 * t + n;
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
-                const int pos = slot * CPR + ((4 * s + g) ^ (n & 7));
+                const int pos = slot * CPR + ((4 * s + g) ^ operand_row_swizzle<CPR, 16>(n));
                 const u32x4 ah = Kh[buf][pos], al = Kl[buf][pos];
 #pragma unroll
                 for (int j = 0; j < NQ; ++j) acc[j][t] = mfma_split(ah, al, qh[j][s], ql[j][s], acc[j][t]);
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(NT, 2) void k_ds_split(const float *__restrict__ dO
         const int idx = i * NT + tid;
         const int key = idx / CPR, c = idx % CPR;
         const int slot = 16 * ((key >> 2) & 3) + 4 * (key >> 4) + (key & 3);     // as in k_scores_split
-        dst[i] = slot * CPR + (c ^ (slot & 7));
+        dst[i] = slot * CPR + (c ^ operand_row_swizzle<CPR, 16>(slot));
     }
     auto convert = [&](const RawBlock<NCONV> &raw, int buf) {
 #pragma unroll
@@ -445,7 +445,7 @@ __global__ __launch_bounds__(NT, 2) void k_ds_split(const float *__restrict__ dO
             const int slot = 16 * t + n;
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
-                const int pos = slot * CPR + ((4 * s + g) ^ (n & 7));
+                const int pos = slot * CPR + ((4 * s + g) ^ operand_row_swizzle<CPR, 16>(n));
                 acc[t] = mfma_split(Vh[buf][pos], Vl[buf][pos], gh[s], gl[s], acc[t]);
             }
         }
@@ -661,7 +661,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 && NW == 8) ? 4 : 2) void k_fused
         const int idx = i * NT + tid;
         const int key = idx / CPR, c = idx % CPR;
         const int slot = 16 * ((key >> 2) & 3) + 4 * (key >> 4) + (key & 3);
-        dst_k[i] = slot * CPR + (c ^ (slot & 7));
+        dst_k[i] = slot * CPR + (c ^ operand_row_swizzle<CPR, 16>(slot));
         dst_v[i] = key * CPR + (c ^ tr_row_swizzle<CPR>(key));
     }
     auto convert = [&](const RawBlock<NCONV, NT> &rk, const RawBlock<NCONV, NT> &rv) {
@@ -741,7 +741,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 && NW == 8) ? 4 : 2) void k_fused
             const int slot = 16 * t + n;
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
-                const int pos = slot * CPR + ((4 * s + g) ^ (n & 7));
+                const int pos = slot * CPR + ((4 * s + g) ^ operand_row_swizzle<CPR, 16>(n));
                 acc[t] = mfma_split(Kh[pos], Kl[pos], qh[s], ql[s], acc[t]);
             }
         }

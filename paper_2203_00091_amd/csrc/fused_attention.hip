@@ -231,14 +231,14 @@ __global__ __launch_bounds__(NT * G, 2) void k_fused(const __bf16 *__restrict__ 
     const __bf16 *Vh = V + (size_t)bh * Lk * D;
 
     // K block in LDS: row slot 16 t + i holds key 16 (i/4) + 4 t + i%4 (tile t, MFMA row i), chunk c
-    // at position slot * CPR + (c ^ (slot & 7)).  V block: row = key, chunk c at row * CPR + (c ^ tr_row_swizzle(row)).
+    // at position slot * CPR + (c ^ operand_row_swizzle(slot)).  V block: row = key, chunk c at row * CPR + (c ^ tr_row_swizzle(row)).
     int k_off[LPT], v_off[LPT];
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
         const int p = i * NT + tid;
         const int slot = p / CPR;
         const int key = (slot & 3) | (((slot >> 4) & 3) << 2) | (((slot >> 2) & 3) << 4);
-        k_off[i] = key * D + ((p % CPR) ^ (slot & 7)) * 8;
+        k_off[i] = key * D + ((p % CPR) ^ operand_row_swizzle<CPR, 16>(slot)) * 8;
         v_off[i] = slot * D + ((p % CPR) ^ tr_row_swizzle<CPR>(slot)) * 8;
     }
     const uint32_t lds_k = lds_address(&Ks[w * 64]), lds_v = lds_address(&Vs[w * 64]);
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(NT * G, 2) void k_fused(const __bf16 *__restrict__ 
                 const int p = i * NT + tid, slot = p / CPR;
                 const int key = (slot & 3) | (((slot >> 4) & 3) << 2) | (((slot >> 2) & 3) << 4);
                 const int kc = key < tail_keys ? key : tail_keys - 1, vc = slot < tail_keys ? slot : tail_keys - 1;
-                async_copy16(ks, 2u * (kc * D + ((p % CPR) ^ (slot & 7)) * 8), lds_k + 16u * (buf * TILE + i * NT));
+                async_copy16(ks, 2u * (kc * D + ((p % CPR) ^ operand_row_swizzle<CPR, 16>(slot)) * 8), lds_k + 16u * (buf * TILE + i * NT));
                 async_copy16(vs, 2u * (vc * D + ((p % CPR) ^ tr_row_swizzle<CPR>(slot)) * 8), lds_v + 16u * (buf * TILE + i * NT));
             }
             return;
@@ -407,7 +407,7 @@ __global__ __launch_bounds__(NT * G, 2) void k_fused(const __bf16 *__restrict__ 
                 bf16x8 ak[4];
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
-                    ak[t] = __builtin_bit_cast(bf16x8, Ks[buf * TILE + (16 * t + li) * CPR + ((4 * s + kb) ^ (li & 7))]);
+                    ak[t] = __builtin_bit_cast(bf16x8, Ks[buf * TILE + (16 * t + li) * CPR + ((4 * s + kb) ^ operand_row_swizzle<CPR, 16>(li))]);
 #pragma unroll
                 for (int qs = 0; qs < NQ; ++qs)
 #pragma unroll

@@ -65,6 +65,13 @@ __device__ __forceinline__ uint32_t push_position(uint32_t idx, float v) {
     return __builtin_amdgcn_alignbit(__float_as_uint(v), idx, 2);
 }
 
+// XOR pattern for the 16-byte chunks of V row `row` (transposing read of a 32-column tile: the 32 lanes served together
+// read 64 bytes of each of four consecutive rows, which have to fall into different quarters of the 64 banks)
+template <int CPR>
+__device__ __forceinline__ int tr32_swizzle(int row) {
+    return CPR == 8 ? (row & 3) << 1 : (row & 3) << 2;
+}
+
 // NW waves per workgroup = NW / KS query tiles of 32 queries x KS waves per tile.  With KS = 2 the two
 // waves of a query tile share its keys: of every 64-key block, wave ks takes the 32-key tile ks (its own
 // reference value, row sums and partial O, merged at the end through LDS).  Smaller work items, more
@@ -154,16 +161,20 @@ __global__ __launch_bounds__(64 * NW, OCC * 4 / NW) void k_fused32(const __bf16 
     [[maybe_unused]] const int tail_keys = Lk - (nblocks - 1) * KB;   // RAGGED: keys of the last block
 
     // K block in LDS: row slot 32 kt + i (key tile kt, MFMA row i = 8g + 4h' + x) holds key
-    // 32 kt + 16 h' + 4 g + x; chunk c sits at slot * CPR + (c ^ (slot & 7)).
-    // V block: row = key, chunk c at row * CPR + (c ^ ((row & 3) << 1)).
-    // Copy i of a thread handles LDS position p = i * NT + tid: NT / CPR row slots further on, which moves
-    // neither the swizzle (low slot bits) nor the low key bits: source = that of copy 0 + a constant.
+    // 32 kt + 16 h' + 4 g + x; chunk c sits at slot * CPR + (c ^ operand_row_swizzle(slot)).
+    // V block: row = key, chunk c at row * CPR + (c ^ tr32_swizzle(row)).
+    // Copy i of a thread handles LDS position p = i * NT + tid: NT / CPR row slots further on, which does not
+    // move the low key bits nor, unless the step is 8 slots of 256 bytes, the swizzle: source = that of copy 0 + a
+    // constant; with the step of 8 every second copy takes the other half of the row (chunk bit 3).
     constexpr int SPC = NT / CPR;       // row slots between consecutive copies of a thread
     static_assert(SPC % 8 == 0, "the slot bits that a thread's copies differ in are bits 3, 4 and 5");
     const int slot0 = tid / CPR;
     const int key0 = (slot0 & 32) | (((slot0 >> 2) & 1) << 4) | (((slot0 >> 3) & 3) << 2) | (slot0 & 3);
-    const int k_chunk = ((tid % CPR) ^ (slot0 & 7)) * 8, v_chunk = ((tid % CPR) ^ ((slot0 & 3) << 1)) * 8;
-    const uint32_t k_off = 2u * (key0 * D + k_chunk);
+    const int k_chunk = ((tid % CPR) ^ operand_row_swizzle<CPR, 32>(slot0)) * 8;
+    const int v_chunk = ((tid % CPR) ^ tr32_swizzle<CPR>(slot0)) * 8;
+    constexpr bool FLIP = CPR == 16 && SPC % 16 != 0;
+    auto k_flip = [](int i) { return FLIP && ((i * SPC) & 8) ? 64 : 0; };   // what copy i adds to the chunk by XOR (elements)
+    const uint32_t k_off = 2u * (key0 * D + k_chunk), k_off_flip = 2u * (key0 * D + (k_chunk ^ 64));
     const uint32_t v_off = 2u * (slot0 * D + v_chunk);
     const uint32_t lds_k = lds_address(&Ks[0][w * 64]), lds_v = lds_address(&Vs[0][w * 64]);
     const uint64_t k_base = uniform_address(K + (size_t)bh * Lk * D), v_base = uniform_address(V + (size_t)bh * Lk * D);
@@ -193,7 +204,7 @@ __global__ __launch_bounds__(64 * NW, OCC * 4 / NW) void k_fused32(const __bf16 
 
     // transposing LDS read (per group of 16 lanes): lane s addresses V[key0 + s/4][col0 + 4 (s%4)]
     const int s16 = l & 15;
-    const int tr_row = s16 >> 2, tr_sub = (s16 >> 1) & 1, tr_byte = 8 * (s16 & 1), tr_xor = tr_row << 1;
+    const int tr_row = s16 >> 2, tr_sub = (s16 >> 1) & 1, tr_byte = 8 * (s16 & 1), tr_xor = tr32_swizzle<CPR>(tr_row);
     const int tr_colgrp = (l >> 4) & 1;   // which 16 of the 32 columns of a tile this lane group reads
     const int kt0 = KS == 2 ? ks : 0;     // first (only, if KS = 2) key tile of this wave
 
@@ -205,14 +216,14 @@ __global__ __launch_bounds__(64 * NW, OCC * 4 / NW) void k_fused32(const __bf16 
             for (int i = 0; i < LPT; ++i) {
                 const int key = key0 + (((i * SPC) >> 3) & 1) * 4 + (((i * SPC) >> 4) & 1) * 8 + ((i * SPC) & 32);
                 const int row = slot0 + i * SPC;
-                async_copy16(ks_, 2u * ((key < tail_keys ? key : tail_keys - 1) * D + k_chunk), lds_k + 16u * (buf * TILE + i * NT));
+                async_copy16(ks_, 2u * ((key < tail_keys ? key : tail_keys - 1) * D + (k_chunk ^ k_flip(i))), lds_k + 16u * (buf * TILE + i * NT));
                 async_copy16(vs_, 2u * ((row < tail_keys ? row : tail_keys - 1) * D + v_chunk), lds_v + 16u * (buf * TILE + i * NT));
             }
             return;
         }
 #pragma unroll
         for (int i = 0; i < LPT; ++i)
-            async_copy16(ks_ + (uint64_t)((((i * SPC) >> 3) & 1) * 4 + (((i * SPC) >> 4) & 1) * 8 + ((i * SPC) & 32)) * D * 2, k_off,
+            async_copy16(ks_ + (uint64_t)((((i * SPC) >> 3) & 1) * 4 + (((i * SPC) >> 4) & 1) * 8 + ((i * SPC) & 32)) * D * 2, k_flip(i) ? k_off_flip : k_off,
                          lds_k + 16u * (buf * TILE + i * NT));
 #pragma unroll
         for (int i = 0; i < LPT; ++i)
@@ -256,7 +267,7 @@ __global__ __launch_bounds__(64 * NW, OCC * 4 / NW) void k_fused32(const __bf16 
 #pragma unroll
                 for (int s = 0; s < STEPS; ++s) {
                     const bf16x8 ak =
-                        __builtin_bit_cast(bf16x8, Ks[buf][(32 * t + lj) * CPR + ((2 * s + h) ^ (lj & 7))]);
+                        __builtin_bit_cast(bf16x8, Ks[buf][(32 * t + lj) * CPR + ((2 * s + h) ^ operand_row_swizzle<CPR, 32>(lj))]);
                     acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak, bq[s], s == 0 ? cb : acc[t], 0, 0, 0);
                 }
             }
@@ -266,7 +277,7 @@ __global__ __launch_bounds__(64 * NW, OCC * 4 / NW) void k_fused32(const __bf16 
 #pragma unroll
                 for (int s = 0; s < STEPS; ++s) {
                     const bf16x8 ak =
-                        __builtin_bit_cast(bf16x8, Ks[buf][(32 * (kt0 + t) + lj) * CPR + ((2 * s + h) ^ (lj & 7))]);
+                        __builtin_bit_cast(bf16x8, Ks[buf][(32 * (kt0 + t) + lj) * CPR + ((2 * s + h) ^ operand_row_swizzle<CPR, 32>(lj))]);
                     acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak, bq[s], s == 0 ? cneg : acc[t], 0, 0, 0);
                 }
             }

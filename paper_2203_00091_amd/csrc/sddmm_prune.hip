@@ -69,12 +69,12 @@ __global__ __launch_bounds__(NT, 2) void k_sddmm(const __bf16 *__restrict__ Q, c
     const __bf16 *Kh = K + (size_t)bh * Lk * D;
 
     // per-thread source offsets of the direct-to-LDS copies: LDS position p (16-byte units)
-    // = slot * CPR + (c ^ (slot & 7)) holds chunk c of the key stored in row slot `slot`
+    // = slot * CPR + (c ^ operand_row_swizzle(slot)) holds chunk c of the key stored in row slot `slot`
     int src_off[LPT];
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
         const int p = i * NT + tid;
-        const int slot = p / CPR, c = (p % CPR) ^ (slot & 7);
+        const int slot = p / CPR, c = (p % CPR) ^ operand_row_swizzle<CPR, 16>(slot);
         const int key = (slot & 3) | (((slot >> 4) & 7) << 2) | (((slot >> 2) & 3) << 5);
         src_off[i] = key * D + c * 8;
     }
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(NT, 2) void k_sddmm(const __bf16 *__restrict__ Q, c
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     const int slot = 16 * (4 * half + t) + li;
-                    ak[t] = __builtin_bit_cast(bf16x8, Ks[buf][slot * CPR + ((4 * s + kb) ^ (li & 7))]);
+                    ak[t] = __builtin_bit_cast(bf16x8, Ks[buf][slot * CPR + ((4 * s + kb) ^ operand_row_swizzle<CPR, 16>(li))]);
                 }
 #pragma unroll
                 for (int qs = 0; qs < NQ; ++qs)
@@ -304,12 +304,12 @@ __global__ __launch_bounds__(NT, 2) void k_sddmm32(const __bf16 *__restrict__ Q,
 
     const __bf16 *Kh = K + (size_t)bh * LkR * D;
 
-    // LDS position p (16-byte units) = slot * CPR + (c ^ (slot & 7)) holds chunk c of the key of row slot `slot`
+    // LDS position p (16-byte units) = slot * CPR + (c ^ operand_row_swizzle(slot)) holds chunk c of the key of row slot `slot`
     int src_off[LPT];
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
         const int p = i * NT + tid;
-        const int slot = p / CPR, c = (p % CPR) ^ (slot & 7);
+        const int slot = p / CPR, c = (p % CPR) ^ operand_row_swizzle<CPR, 32>(slot);
         const int t = slot >> 5, r = slot & 31;          // tile, MFMA row = 8 g + 4 h' + x
         const int key = 64 * (t >> 1) + 32 * ((r >> 2) & 1) + 16 * (t & 1) + 4 * (r >> 3) + (r & 3);
         src_off[i] = key * D + c * 8;
@@ -327,7 +327,7 @@ __global__ __launch_bounds__(NT, 2) void k_sddmm32(const __bf16 *__restrict__ Q,
 #pragma unroll
             for (int i = 0; i < LPT; ++i) {
                 const int p = i * NT + tid;
-                const int slot = p / CPR, c = (p % CPR) ^ (slot & 7);
+                const int slot = p / CPR, c = (p % CPR) ^ operand_row_swizzle<CPR, 32>(slot);
                 const int t = slot >> 5, r = slot & 31;
                 const int key = 64 * (t >> 1) + 32 * ((r >> 2) & 1) + 16 * (t & 1) + 4 * (r >> 3) + (r & 3);
                 async_copy16(src, 2u * ((key < real ? key : real - 1) * D + c * 8), lds_k + 16u * (buf * TILE + i * NT));
@@ -431,7 +431,7 @@ __global__ __launch_bounds__(NT, 2) void k_sddmm32(const __bf16 *__restrict__ Q,
 #pragma unroll
                 for (int s = 0; s < STEPS; ++s) {
                     const bf16x8 ak =
-                        __builtin_bit_cast(bf16x8, Ks[buf][(32 * t + lj) * CPR + ((2 * s + h) ^ (lj & 7))]);
+                        __builtin_bit_cast(bf16x8, Ks[buf][(32 * t + lj) * CPR + ((2 * s + h) ^ operand_row_swizzle<CPR, 32>(lj))]);
                     acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak, bq[s], acc[u], 0, 0, 0);
                 }
             }

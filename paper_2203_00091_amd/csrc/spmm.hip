@@ -58,13 +58,13 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
     const int nblocks = Lk / KB;
     const int meta_slot = ((kb & 1) << 1) | (kb >> 1);   // where the word of 32-key chunk kb sits in a row's 16 bytes
 
-    // LDS position p (16-byte units) = row * CPR + (c ^ ((row & 3) << 1)) holds chunk c of key `row`
+    // LDS position p (16-byte units) = row * CPR + (c ^ tr_row_swizzle(row)) holds chunk c of key `row`
     const __bf16 *Vh = V + (size_t)bh * LkR * D;
     int src_off[LPT];
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
         const int p = i * NT + tid;
-        const int row = p / CPR, c = (p % CPR) ^ ((row & 3) << 1);
+        const int row = p / CPR, c = (p % CPR) ^ tr_row_swizzle<CPR>(row);
         src_off[i] = row * D + c * 8;
     }
     const uint32_t lds_v = lds_address(&Vs[0][w * 64]);   // this wave's 1 KB slice of copy 0, buffer 0
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
 #pragma unroll
             for (int i = 0; i < LPT; ++i) {
                 const int p = i * NT + tid;
-                const int row = p / CPR, c = (p % CPR) ^ ((row & 3) << 1);
+                const int row = p / CPR, c = (p % CPR) ^ tr_row_swizzle<CPR>(row);
                 async_copy16(src, 2u * ((row < real ? row : real - 1) * D + c * 8), lds_v + 16u * (buf * TILE + i * NT));
             }
             return;
@@ -119,7 +119,6 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
     const int tr_row = li >> 2;
     const int tr_sub = (li >> 1) & 1;      // which 16-byte chunk of the 32-byte column group
     const int tr_byte = 8 * (li & 1);
-    const int tr_xor = tr_row << 1;        // (row & 3) << 1, key0 is a multiple of 4
 
     // SOFTMAX: reference value of row li of each row block (the same in the four lane groups kb of a row)
     static_assert(!SOFTMAX || SPARSE, "the softmax is folded into the sparse product only");
@@ -200,7 +199,7 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
         const char *vbase = reinterpret_cast<const char *>(&Vs[buf][0]);
         auto tr = [&](int key0, int ds) {
             const int row = key0 + tr_row;
-            const int chunk = (2 * ds + tr_sub) ^ tr_xor;
+            const int chunk = (2 * ds + tr_sub) ^ tr_row_swizzle<CPR>(row);
             return lds_read_tr16(vbase + (row * CPR + chunk) * 16 + tr_byte);
         };
         if constexpr (SPARSE) {
