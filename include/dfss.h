@@ -302,7 +302,7 @@ dfss_status dense_attention_fused_blocked_split(const void *Q, const void *K, co
  * comparison (as under a key bias of -inf), so a run of M keys that is entirely absent emits N
  * entries of weight exactly 0.  The rows Lq .. LqP-1 of vals and meta hold valid but meaningless
  * entries, and no such row of O is written; nothing is read or written past the caller's arrays.
- * The backward calls take P, meta (and dS in the workspace) in the same padded layout, whatever the
+ * The backward calls take P and meta in the same padded layout, whatever the
  * rows past Lq hold: those rows take no part in dK and dV, the absent keys (weight 0) none in dQ,
  * and dQ [B*H, Lq, d], dK, dV [B*H, Lk, d] are written for the real rows only.
  * The causal calls and the block-pattern calls take tile multiples only (DFSS_ERR_UNSUPPORTED /
@@ -340,10 +340,10 @@ dfss_status dfss_spmm_t(const void *vals, const void *meta, const void *X, const
  * the vals buffer after dfss_sparse_softmax and the metadata of dfss_sddmm_prune of the SAME forward pass
  * (run the three stage calls to keep them; they compose to dfss_attention).  Outputs: dQ [B*H, Lq, d],
  * dK, dV [B*H, Lk, d], bfloat16.  ws: device scratch of at least dfss_backward_workspace_bytes(),
- * 256-byte aligned (holds dS).  A key bias of the forward pass needs no extra argument: masked
- * entries have weight 0 and so receive and pass on no gradient.  Kernels: the stage-1 mainloop with the stored
- * position codes in the place of the selection (dS; at d = 64 it forms dQ in the same pass, at d = 128 the
- * stage-3 SpMM does), and the transposed sparse product twice (dV, dK). */
+ * 256-byte aligned (2-byte dtype: the row terms delta; 4-byte dtype: dS).  A key bias of the forward pass needs no extra
+ * argument: masked entries have weight 0 and so receive and pass on no gradient.  Two kernels with the 2-byte dtype: dQ and
+ * delta over the keys of a query, then dV and dK over the queries of a key; each forms dS from P, the stored position codes
+ * and dO V^T in registers. */
 size_t dfss_backward_workspace_bytes(const dfss_shape *s);
 dfss_status dfss_attention_backward(const void *dO, const void *Q, const void *K, const void *V, const void *O,
                                     const void *P, const void *meta, const dfss_shape *s, float scale, void *dQ,

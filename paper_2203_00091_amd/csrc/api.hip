@@ -604,25 +604,16 @@ dfss_status dfss_attention_backward(const void *dO, const void *Q, const void *K
     if (D.f32 && !D.split) return DFSS_ERR_UNSUPPORTED;
     if (ws_bytes < align_up(dfss_vals_bytes(s))) return DFSS_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    void *dS = ws;   // scale * dS in the compressed layout of P
     if (D.f32) {
+        void *dS = ws;   // scale * dS in the compressed layout of P
         hipError_t e = dfss::launch_masked_sddmm_ds_split(dO, V, O, P, meta, D.BH, D.Lq, D.Lk, D.d, scale, dS, st);
         if (e == hipSuccess) e = dfss::launch_spmm_split(dS, meta, K, D.BH, D.Lq, D.Lk, D.d, dQ, st);       // dQ = dS' K
         if (e == hipSuccess) e = dfss::launch_spmm_t_split(P, meta, dO, D.BH, D.Lq, D.Lk, D.d, dV, st);     // dV = P^T dO
         if (e == hipSuccess) e = dfss::launch_spmm_t_split(dS, meta, Q, D.BH, D.Lq, D.Lk, D.d, dK, st);     // dK = dS'^T Q
         return hip_status(e);
     }
-    hipError_t e;
-    if (D.d == 64) {   // dS' and dQ = dS' K in one pass over the compressed rows
-        e = dfss::launch_masked_sddmm_ds(dO, V, O, P, meta, K, D.BH, D.Lq, D.Lk, D.LqR, D.LkR, D.d, scale, dS, dQ, st);
-    } else {
-        e = dfss::launch_masked_sddmm_ds(dO, V, O, P, meta, nullptr, D.BH, D.Lq, D.Lk, D.LqR, D.LkR, D.d, scale, dS,
-                                         nullptr, st);
-        if (e == hipSuccess) e = dfss::launch_spmm(dS, meta, K, D.BH, D.Lq, D.Lk, D.LqR, D.LkR, D.d, dQ, st);   // dQ = dS' K
-    }
-    if (e == hipSuccess) e = dfss::launch_spmm_t(P, meta, dO, D.BH, D.Lq, D.Lk, D.LqR, D.LkR, D.d, dV, st);    // dV = P^T dO
-    if (e == hipSuccess) e = dfss::launch_spmm_t(dS, meta, Q, D.BH, D.Lq, D.Lk, D.LqR, D.LkR, D.d, dK, st);    // dK = dS'^T Q
-    return hip_status(e);
+    return hip_status(dfss::launch_backward(dO, Q, K, V, O, P, meta, D.BH, D.Lq, D.Lk, D.LqR, D.LkR, D.d, scale, (float *)ws,
+                                            dQ, dK, dV, st));
 }
 
 size_t dfss_backward_workspace_bytes(const dfss_shape *s) {

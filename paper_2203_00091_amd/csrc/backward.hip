@@ -5,18 +5,14 @@
 // kept entries (Sec. 3.1) and dO the upstream gradient:
 //     dV = P^T dO,   dP = (dO V^T) at the kept positions,   delta_i = dO_i . O_i,
 //     dS = P .* (dP - delta),   dQ = scale dS K,   dK = scale dS^T Q.
-// Two kernels live here; dQ comes out of the first one at d = 64 and reuses the forward SpMM (stage 3) with K in the
-// place of V at d = 128.
 //
-//   k_masked_sddmm_ds  dS' = scale * P .* (dO V^T - delta) at the kept positions, written in the
-//                      compressed layout of the forward pass.  It is the stage-1 mainloop with V in
-//                      the place of K and dO in the place of Q; the epilogue picks the kept entries
-//                      with the stored position codes instead of selecting them.
-//   k_spmm_t           out = A^T X for a compressed A (dV = P^T dO, dK = dS'^T Q).  The contraction
+//   k_backward_dq      dQ, and -delta for the other one; walks the keys, layout of the one-kernel forward pass
+//   k_backward_dkv     dV and dK in one pass over the queries
+//   k_spmm_t           out = A^T X for a compressed A (the public transposed product).  The contraction
 //                      runs over queries, across which the N:M structure does not run, so the tile
 //                      of A is expanded to dense bfloat16 in LDS and both operands are read with the
 //                      transposing LDS read.
-#include <cstdlib>
+#include <type_traits>
 
 #include "dfss_device.hpp"
 #include "dfss_kernels.hpp"
@@ -203,249 +199,425 @@ __global__ __launch_bounds__(NT, 2) void k_spmm_t(const uint32_t *__restrict__ A
 }
 
 // ------------------------------------------------------------------------------------------------
-// dS'[q][c] = scale * P[q][c] * (dO[q] . V[key(q, c)] - delta_q),  delta_q = dO[q] . O[q]
-// for the kept entries c of every row, in the compressed layout (same addresses as the weights P).
-// Mainloop and data layout of the 16-query stage-1 kernel: keys on the MFMA rows, so lane
-// (column li, row group kb) of a 128-key block holds, per half, the 16 consecutive keys
-// 32 kb + 16 half .. +15 of query li: four runs of four, of which the position codes name the two
-// kept ones.
+// The gradients.  dS is formed twice, once per direction of the sums it enters, and never written: the kept weights and
+// the metadata are read twice (2 x 1.125 B per score) instead of P twice, dS' written and read once, the metadata three
+// times (4.4 B), and the product that dS' costs a second time runs on the matrix unit.  Together, before (dS' written,
+// one transposed product each for dV and dK) and now, 4096 x 4096 with 24 heads: 505 -> 312 us; 512 x 512 with 192 heads:
+// 76 -> 59 us; d = 128, 2048 x 2048 with 64 heads: 485 -> 382 us.
 // ------------------------------------------------------------------------------------------------
-// DQ: the same pass also forms dQ = dS' K (the dS' values a lane has just computed ARE the compressed operand of the
-// structured-sparse matrix instruction for its query, and the stored position codes its index operand, exactly as
-// in the forward SpMM), so dS' is not read back for it.  Needs the whole key range in one workgroup (ksplit = 1) and
-// a second LDS tile per block (K in row order for the transposing read): d = 64 only.
-// UNP: dO, O, dQ hold LqR <= Lq rows per head and V, K LkR <= Lk keys, while P, meta and dS have the layout of the
-// padded lengths.  Rows past LqR are computed on a copy of the last row (their dS' is meaningless and the transposed
-// products skip it), the places of absent keys in a partial last block take the block's last key (their weights are
-// 0, so their dS' is 0), and rows of dQ past LqR are not stored.
-template <int D, int NQ, bool DQ, bool UNP>
-__global__ __launch_bounds__(NT, 2) void k_masked_sddmm_ds(const __bf16 *__restrict__ dO, const __bf16 *__restrict__ V,
-                                                           const __bf16 *__restrict__ O,
-                                                           const uint32_t *__restrict__ P,
-                                                           const uint32_t *__restrict__ meta,
-                                                           const __bf16 *__restrict__ K, int Lq, int Lk, int LqR,
-                                                           int LkR, float scale, int ksplit, int blocks_per_wg,
-                                                           uint32_t *__restrict__ dS, uint16_t *__restrict__ dQ) {
-    constexpr int CPR = D / 8;           // 16-byte chunks per row
-    constexpr int TILE = KB * CPR;       // chunks per V block
-    constexpr int LPT = TILE / NT;       // asynchronous copies per thread per block
-    constexpr int STEPS = D / 32;        // MFMA k-steps
-    constexpr int DS = D / 16;           // 16-column tiles of dQ
-    constexpr int TQ = 64 * NQ;          // queries per workgroup
-    static_assert(!DQ || D == 64, "the fused dQ needs two LDS tiles per block");
-    __shared__ u32x4 Vs[2][TILE];
-    __shared__ u32x4 Kr[DQ ? 2 : 1][DQ ? TILE : 1];   // K block, row = key, chunk c at row * CPR + (c ^ tr_row_swizzle(row))
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// Bit `pos` of w in every bit, and x where the bits of such a mask are set, else y: one instruction each.  (The empty
+// statement hides where the mask comes from: the pair otherwise becomes a mask, a comparison and a select.  The values
+// themselves stay out of assembly: the compiler has to see who reads the result of a matrix instruction.)
+__device__ __forceinline__ uint32_t spread_bit(uint32_t w, int pos) {
+    uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)w, pos, 1);
+    asm("" : "+v"(m));
+    return m;
+}
+__device__ __forceinline__ float choose(uint32_t m, float x, float y) {
+    return __uint_as_float((m & __float_as_uint(x)) | (~m & __float_as_uint(y)));
+}
+
+// dQ = scale * dS K with dS = P .* (dO V^T - delta) at the kept positions, delta_q = dO_q . O_q; and -delta, fp32
+// [BH][Lq], for the kernel below.
+// The layout is that of the one-kernel forward pass (fused_attention32.hip) with dO in the place of Q, V in the place of
+// K and K in the place of V: a wave owns 32 queries, keys sit on the rows of the first product, so that a lane ends up
+// with dP of 16 consecutive keys of one query and finds its 8 kept weights in 16 consecutive bytes of P, their position
+// codes in 16 bits of the metadata; the 8 dS values ARE the compressed operand of the sparse instruction, the codes its
+// index.  The first product starts from -delta (delta belongs to the lane's query), so dP - delta needs no instruction.
+// UNP: dO, O, dQ hold LqR <= Lq rows per head and V, K LkR <= Lk keys, while P and meta have the layout of the padded
+// lengths Lq (a multiple of 64) and Lk (of 128).  Rows past LqR are computed on a copy of the last one and not stored; the
+// places of absent keys in a partial last block take the block's last key (their weights are 0).  Blocks that hold no real
+// key are not visited.
+template <int D, int NW, bool UNP>
+__global__ __launch_bounds__(64 * NW, D == 64 ? 12 / NW : 8 / NW) void k_backward_dq(
+    const __bf16 *__restrict__ dO, const __bf16 *__restrict__ V, const __bf16 *__restrict__ O,
+    const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta, const __bf16 *__restrict__ K, int Lq, int Lk,
+    int LqR, int LkR, float scale, uint16_t *__restrict__ dQ, float *__restrict__ neg_delta) {
+    constexpr int THREADS = 64 * NW;
+    constexpr int KEYS = 64;                 // keys per block: two 32-key tiles
+    constexpr int CPR = D / 8;               // 16-byte chunks per row
+    constexpr int TILE = KEYS * CPR;         // chunks per V (or K) block
+    constexpr int LPT = TILE / THREADS;      // asynchronous copies per thread, block and operand
+    constexpr int STEPS = D / 16;
+    constexpr int DT = D / 32;
+    constexpr int TQ = 32 * NW;
+    __shared__ u32x4 Vs[2][TILE], Kr[2][TILE];
 
     const int tid = threadIdx.x;
-    const int w = tid >> 6, l = tid & 63, li = l & 15, kb = l >> 4;
-
-    const unsigned qtiles = Lq / TQ;
+    const int w = tid >> 6, l = tid & 63, lj = l & 31, h = l >> 5;
+    const unsigned qtiles = (Lq + TQ - 1) / TQ;
     const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int ks_id = item % ksplit;
-    const int qt = (item / ksplit) % qtiles;
-    const int bh = item / (ksplit * qtiles);
-    const int jb0 = ks_id * blocks_per_wg;
-    const int q0 = qt * TQ + w * 16 * NQ;
+    const int qt = item % qtiles, bh = item / qtiles;
+    const int q0 = qt * TQ + w * 32;
+    const int nblocks = (LkR + KEYS - 1) / KEYS;
 
-    // LDS position p (16-byte units) = slot * CPR + (c ^ operand_row_swizzle(slot)) holds chunk c of the key stored in row
-    // slot `slot`; slot 16 t' + i (MFMA tile t', row i) holds key 32 (i/4) + 4 t' + i%4 ... in the order that
-    // gives a lane 16 consecutive keys per half
-    const __bf16 *Vh = V + (size_t)bh * LkR * D;
-    int src_off[LPT];
+    // V block: row slot 32 t + 8 g + 4 h' + x holds key 32 t + 16 h' + 4 g + x, chunk c at slot * CPR + (c ^ operand_row_swizzle)
+    // K block: row = key, chunk c at row * CPR + (c ^ tr32_swizzle(row))
+    int v_key[LPT], v_chunk[LPT], k_key[LPT], k_chunk[LPT];
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
-        const int p = i * NT + tid;
-        const int slot = p / CPR, c = (p % CPR) ^ operand_row_swizzle<CPR, 16>(slot);
-        const int key = (slot & 3) | (((slot >> 4) & 7) << 2) | (((slot >> 2) & 3) << 5);
-        src_off[i] = key * D + c * 8;
+        const int p = i * THREADS + tid, slot = p / CPR;
+        v_key[i] = (slot & 32) | (((slot >> 2) & 1) << 4) | (((slot >> 3) & 3) << 2) | (slot & 3);
+        v_chunk[i] = ((p % CPR) ^ operand_row_swizzle<CPR, 32>(slot)) * 8;
+        k_key[i] = slot;
+        k_chunk[i] = ((p % CPR) ^ tr32_swizzle<CPR>(slot)) * 8;
     }
-    const uint32_t lds_v = lds_address(&Vs[0][w * 64]);
-    int k_off[LPT];
-#pragma unroll
-    for (int i = 0; i < LPT; ++i) {
-        const int p = i * NT + tid;
-        const int row = p / CPR, c = (p % CPR) ^ tr_row_swizzle<CPR>(row);
-        k_off[i] = row * D + c * 8;
-    }
-    const uint32_t lds_k = lds_address(&Kr[0][DQ ? w * 64 : 0]);
-    const __bf16 *Kh = DQ ? K + (size_t)bh * LkR * D : nullptr;
+    const uint32_t lds_v = lds_address(&Vs[0][w * 64]), lds_k = lds_address(&Kr[0][w * 64]);
+    const uint64_t v_base = uniform_address(V + (size_t)bh * LkR * D), k_base = uniform_address(K + (size_t)bh * LkR * D);
     auto issue_block = [&](int jb, int buf) {
-        const __bf16 *src = Vh + (size_t)jb * KB * D;
-        const int real = LkR - jb * KB;   // real keys from this block's first one on
-        if (UNP && real < KB) {
+        const uint64_t vs = v_base + (uint64_t)jb * (KEYS * D * 2), ks = k_base + (uint64_t)jb * (KEYS * D * 2);
+        const int last = UNP ? LkR - jb * KEYS - 1 : KEYS - 1;   // the block's last real key
 #pragma unroll
-            for (int i = 0; i < LPT; ++i) {
-                const int p = i * NT + tid;
-                const int slot = p / CPR, c = (p % CPR) ^ operand_row_swizzle<CPR, 16>(slot);
-                const int key = (slot & 3) | (((slot >> 4) & 7) << 2) | (((slot >> 2) & 3) << 5);
-                async_copy16(src, 2u * ((key < real ? key : real - 1) * D + c * 8), lds_v + 16u * (buf * TILE + i * NT));
-            }
-            if constexpr (DQ) {
-                const __bf16 *ksrc = Kh + (size_t)jb * KB * D;
+        for (int i = 0; i < LPT; ++i)
+            async_copy16(vs, 2u * ((UNP && v_key[i] > last ? last : v_key[i]) * D + v_chunk[i]), lds_v + 16u * (buf * TILE + i * THREADS));
 #pragma unroll
-                for (int i = 0; i < LPT; ++i) {
-                    const int p = i * NT + tid;
-                    const int row = p / CPR, c = (p % CPR) ^ tr_row_swizzle<CPR>(row);
-                    async_copy16(ksrc, 2u * ((row < real ? row : real - 1) * D + c * 8), lds_k + 16u * (buf * TILE + i * NT));
-                }
-            }
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < LPT; ++i) async_copy16(src, 2u * src_off[i], lds_v + 16u * (buf * TILE + i * NT));
-        if constexpr (DQ) {
-            const __bf16 *ksrc = Kh + (size_t)jb * KB * D;
-#pragma unroll
-            for (int i = 0; i < LPT; ++i) async_copy16(ksrc, 2u * k_off[i], lds_k + 16u * (buf * TILE + i * NT));
-        }
+        for (int i = 0; i < LPT; ++i)
+            async_copy16(ks, 2u * ((UNP && k_key[i] > last ? last : k_key[i]) * D + k_chunk[i]), lds_k + 16u * (buf * TILE + i * THREADS));
     };
+    // Blocks go in pairs (the last pair may be a single block).  Workgroup g starts at pair g mod npairs and wraps around
+    // (rows of P are a power of two apart for the usual lengths; workgroups in step would read the same few memory channels).
+    const int npairs = (nblocks + 1) / 2;
+    const int rot = __builtin_amdgcn_readfirstlane((int)(item % (unsigned)npairs));
+    issue_block(2 * rot, 0);
 
-    issue_block(jb0, 0);
+    // weights and codes of this lane's query for a pair of blocks (128 keys: a whole line of P per row), loaded one pair
+    // ahead: v[2 i + t] = keys 64 i + 32 t + 16 h .. +15 of the pair, slot 2 t + i of the codes their 32-key word
+    const int prow = q0 + lj < Lq ? q0 + lj : Lq - 1;
+    const u32x4 *const p_row = reinterpret_cast<const u32x4 *>(P + ((size_t)bh * Lq + prow) * (size_t)(Lk / 4)) + h;
+    const u32x4 *const m_row = reinterpret_cast<const u32x4 *>(meta) + ((size_t)bh * (Lq / 16) + (prow >> 4)) * (Lk / KB) * 16 + (prow & 15);
+    struct Kept {
+        u32x4 v[4], codes;
+    };
+    constexpr int KEPT_LOADS = 5;
+    auto load_kept = [&](int pair) {
+        Kept r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r.v[i] = p_row[8 * pair + 2 * i];
+        r.codes = m_row[(size_t)pair * 16];
+        return r;
+    };
+    Kept next = load_kept(rot);
 
-    // dO operand: lane (column li, chunk kb) of MFMA step s holds dO[q][32 s + 8 kb .. +7]; the same
-    // elements of O give this lane's share of delta_q
-    bf16x8 bq[NQ][STEPS];
-    float delta[NQ];
+    bf16x8 bq[STEPS];
+    float nd = 0.f;   // -delta of query lj
+    const int qrow = q0 + lj < LqR ? q0 + lj : LqR - 1;
 #pragma unroll
-    for (int qs = 0; qs < NQ; ++qs) {
-        float part = 0.f;
+    for (int s = 0; s < STEPS; ++s) {
+        const size_t off = ((size_t)bh * LqR + qrow) * D + 16 * s + 8 * h;
+        const u32x4 g = *reinterpret_cast<const u32x4 *>(dO + off), o = *reinterpret_cast<const u32x4 *>(O + off);
+        bq[s] = __builtin_bit_cast(bf16x8, g);
 #pragma unroll
-        for (int s = 0; s < STEPS; ++s) {
-            const int qrow = UNP && q0 + 16 * qs + li >= LqR ? LqR - 1 : q0 + 16 * qs + li;
-            const size_t off = ((size_t)bh * LqR + qrow) * D + 32 * s + 8 * kb;
-            const u32x4 g = *reinterpret_cast<const u32x4 *>(dO + off);
-            const u32x4 o = *reinterpret_cast<const u32x4 *>(O + off);
-            bq[qs][s] = __builtin_bit_cast(bf16x8, g);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                part += bf16_lo_to_f32(g[e]) * bf16_lo_to_f32(o[e]) + bf16_hi_to_f32(g[e]) * bf16_hi_to_f32(o[e]);
-        }
-        part += __shfl_xor(part, 16, 64);
-        part += __shfl_xor(part, 32, 64);
-        delta[qs] = part;
+        for (int e = 0; e < 4; ++e)
+            nd -= bf16_lo_to_f32(g[e]) * bf16_lo_to_f32(o[e]) + bf16_hi_to_f32(g[e]) * bf16_hi_to_f32(o[e]);
     }
+    nd += __shfl_xor(nd, 32, kWave);
+    if (h == 0 && q0 + lj < Lq) neg_delta[(size_t)bh * Lq + q0 + lj] = nd;
+    f32x16 start;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) start[r] = nd;
 
-    const int rb0 = q0 >> 4;                 // first 16-row block of this wave
-    const int meta_slot = ((kb & 1) << 1) | (kb >> 1);
+    f32x16 acc_q[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc_q[dt][r] = 0.f;
 
-    // DQ: accumulators of dQ (rows 4 kb + r of the 16-query tile, column 16 ds + li) and the lane's role in the
-    // transposing read of K (as in the forward SpMM)
-    f32x4 acc_dq[NQ][DS];
-#pragma unroll
-    for (int qs = 0; qs < NQ; ++qs)
-#pragma unroll
-        for (int ds = 0; ds < DS; ++ds) acc_dq[qs][ds] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int tr_row = li >> 2, tr_sub = (li >> 1) & 1, tr_byte = 8 * (li & 1);
+    const int s16 = l & 15;
+    const int tr_row = s16 >> 2, tr_sub = (s16 >> 1) & 1, tr_byte = 8 * (s16 & 1), tr_xor = tr32_swizzle<CPR>(tr_row);
+    const int tr_colgrp = (l >> 4) & 1;
 
-    for (int it = 0; it < blocks_per_wg; ++it) {
-        const int jb = jb0 + it;
-        const int buf = it & 1;
-        // this block's copy has landed; the 2 NQ stores of the previous iteration may stay in flight
-        if (it == 0) wait_async_copies();
-        else wait_async_copies_keep<2 * NQ>();
-        __syncthreads();
-        if (it + 1 < blocks_per_wg) issue_block(jb + 1, buf ^ 1);
-
-        uint32_t mword[NQ];
+    // one block; buf: its LDS buffer and its place in the pair
+    auto block = [&](auto parity, const Kept &cur) {
+        constexpr int buf = decltype(parity)::value;
+        const char *kbase = reinterpret_cast<const char *>(&Kr[buf][0]);
+        auto tr = [&](int key0, int dt) {
+            return lds_read_tr16(kbase + ((key0 + tr_row) * CPR + ((4 * dt + 2 * tr_colgrp + tr_sub) ^ tr_xor)) * 16 + tr_byte);
+        };
 #pragma unroll
-        for (int qs = 0; qs < NQ; ++qs)
-            mword[qs] = meta[((((size_t)bh * (Lq / 16) + rb0 + qs) * (Lk / KB) + jb) * 16 + li) * 4 + meta_slot];
-
-        u32x4 ds_out[2][NQ];   // dS' of both halves: a lane's 32 contiguous bytes, stored together
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const int kbase = KB * jb + 32 * kb + 16 * half;
-            u32x4 pw[NQ];   // the weights of this lane's 8 kept entries
-#pragma unroll
-            for (int qs = 0; qs < NQ; ++qs) {
-                const size_t row = (size_t)bh * Lq + q0 + 16 * qs + li;
-                pw[qs] = *reinterpret_cast<const u32x4 *>(P + (row * (size_t)(Lk / 2) + kbase / 2) / 2);
-            }
-            f32x4 acc[NQ][4];
-#pragma unroll
-            for (int qs = 0; qs < NQ; ++qs)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) acc[qs][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < 2; ++t) {
+            // acc[4 g + x] = dO[q] . V[key] - delta_q, key 64 jb + 32 t + 16 h + 4 g + x
+            f32x16 acc;
 #pragma unroll
             for (int s = 0; s < STEPS; ++s) {
-                bf16x8 av[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int slot = 16 * (4 * half + t) + li;
-                    av[t] = __builtin_bit_cast(bf16x8, Vs[buf][slot * CPR + ((4 * s + kb) ^ operand_row_swizzle<CPR, 16>(li))]);
-                }
-#pragma unroll
-                for (int qs = 0; qs < NQ; ++qs)
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) acc[qs][t] = mfma16(av[t], bq[qs][s], acc[qs][t]);
+                const bf16x8 av = __builtin_bit_cast(
+                    bf16x8, Vs[buf][(32 * t + lj) * CPR + ((2 * s + h) ^ operand_row_swizzle<CPR, 32>(lj))]);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bq[s], s == 0 ? start : acc, 0, 0, 0);
             }
-            // acc[qs][t][r] = dO[q] . V[key], key = 128 jb + 32 kb + 16 half + 4 t + r
+            const uint32_t codes = cur.codes[2 * t + buf] >> (16 * h);
+            const u32x4 kept = cur.v[2 * buf + t];
+            u32x4 ds;
 #pragma unroll
-            for (int qs = 0; qs < NQ; ++qs) {
-                const size_t row = (size_t)bh * Lq + q0 + 16 * qs + li;
-                u32x4 o;
+            for (int g = 0; g < 4; ++g) {
+                // codes p_lo | p_hi << 2 with p_lo in 0 .. 2, p_hi in 1 .. 3
+                const uint32_t b0 = spread_bit(codes, 4 * g), b1 = spread_bit(codes, 4 * g + 1);
+                const uint32_t b2 = spread_bit(codes, 4 * g + 2), b3 = spread_bit(codes, 4 * g + 3);
+                const float lo = choose(b1, acc[4 * g + 2], choose(b0, acc[4 * g + 1], acc[4 * g]));
+                const float hi = choose(b3, choose(b2, acc[4 * g + 3], acc[4 * g + 2]), acc[4 * g + 1]);
+                ds[g] = pack_bf16x2(bf16_lo_to_f32(kept[g]) * lo, bf16_hi_to_f32(kept[g]) * hi);
+            }
+            const bf16x8 a = __builtin_bit_cast(bf16x8, ds);
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const uint32_t code = (mword[qs] >> (16 * half + 4 * t)) & 0xFu;
-                    const uint32_t plo = code & 3u, phi = code >> 2;     // plo in {0,1,2}, phi in {1,2,3}
-                    const f32x4 a = acc[qs][t];
-                    const float dp_lo = plo == 0 ? a[0] : (plo == 1 ? a[1] : a[2]);
-                    const float dp_hi = phi == 3 ? a[3] : (phi == 2 ? a[2] : a[1]);
-                    const float ds_lo = bf16_lo_to_f32(pw[qs][t]) * (dp_lo - delta[qs]) * scale;
-                    const float ds_hi = bf16_hi_to_f32(pw[qs][t]) * (dp_hi - delta[qs]) * scale;
-                    o[t] = pack_bf16x2(ds_lo, ds_hi);
-                }
-                ds_out[half][qs] = o;
-                if constexpr (DQ) {
-                    // dQ += dS' K over the block's keys 32 c + 16 half .. +15 (c = lane group): instruction `half`
-                    const char *kbase_lds = reinterpret_cast<const char *>(&Kr[buf][0]);
-                    auto tr = [&](int key0, int ds) {
-                        const int krow = key0 + tr_row;
-                        const int chunk = (2 * ds + tr_sub) ^ tr_row_swizzle<CPR>(krow);
-                        return lds_read_tr16(kbase_lds + (krow * CPR + chunk) * 16 + tr_byte);
-                    };
-                    const int k0 = 32 * (kb >> 1) + 16 * half + 8 * (kb & 1);
-                    const bf16x8 a = __builtin_bit_cast(bf16x8, o);
-#pragma unroll
-                    for (int ds = 0; ds < DS; ++ds) {
-                        const s16x4 t0 = tr(k0, ds), t1 = tr(k0 + 4, ds), t2 = tr(64 + k0, ds), t3 = tr(64 + k0 + 4, ds);
-                        const s16x8 lo = __builtin_shufflevector(t0, t1, 0, 1, 2, 3, 4, 5, 6, 7);
-                        const s16x8 hi = __builtin_shufflevector(t2, t3, 0, 1, 2, 3, 4, 5, 6, 7);
-                        const bf16x16 b = __builtin_bit_cast(
-                            bf16x16, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15));
-                        if (half == 0)
-                            acc_dq[qs][ds] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(a, b, acc_dq[qs][ds],
-                                                                                       (int)mword[qs], 0, 0);
-                        else
-                            acc_dq[qs][ds] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(a, b, acc_dq[qs][ds],
-                                                                                       (int)mword[qs], 0, 1);
-                    }
-                }
+            for (int dt = 0; dt < DT; ++dt) {
+                const int k0 = 32 * t + 8 * h;
+                const s16x4 t0 = tr(k0, dt), t1 = tr(k0 + 4, dt), t2 = tr(k0 + 16, dt), t3 = tr(k0 + 20, dt);
+                const s16x8 lo = __builtin_shufflevector(t0, t1, 0, 1, 2, 3, 4, 5, 6, 7);
+                const s16x8 hi = __builtin_shufflevector(t2, t3, 0, 1, 2, 3, 4, 5, 6, 7);
+                const bf16x16 b = __builtin_bit_cast(
+                    bf16x16, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15));
+                acc_q[dt] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(a, b, acc_q[dt], (int)codes, 0, 0);
             }
         }
-        // the two halves of a lane are adjacent in memory (keys 32 kb .. +31 of the row): issued back to back, the
-        // four lanes of a row complete a whole 128-byte line
+    };
+    int pair = rot;
+    for (int it = 0; it < npairs; ++it) {
+        const bool single = 2 * pair + 1 >= nblocks, last = it + 1 == npairs;
+        const int after = pair + 1 == npairs ? 0 : pair + 1;
+        wait_async_copies();   // the pair's first block and its weights are in
+        __syncthreads();
+        const Kept cur = next;
+        if (!single) issue_block(2 * pair + 1, 1);
+        if (!last) next = load_kept(after);
+        block(std::integral_constant<int, 0>{}, cur);
+        if (single) {   // (the other buffer is free: everybody is past its use)
+            __syncthreads();
+            if (!last) issue_block(2 * after, 0);
+        } else {
+            // the second block is in; the weights of the next pair, issued after it, stay in flight
+            if (!last) wait_async_copies_keep<KEPT_LOADS>();
+            else wait_async_copies();
+            __syncthreads();
+            if (!last) issue_block(2 * after, 0);
+            block(std::integral_constant<int, 1>{}, cur);
+        }
+        pair = after;
+    }
+
+    // acc_q[dt][r] = dQ[q][32 dt + lj] / scale, q = q0 + 8 (r / 4) + 4 h + r % 4
 #pragma unroll
-        for (int qs = 0; qs < NQ; ++qs) {
-            const size_t row = (size_t)bh * Lq + q0 + 16 * qs + li;
-            u32x4 *dst = reinterpret_cast<u32x4 *>(dS + (row * (size_t)(Lk / 2) + (KB * jb + 32 * kb) / 2) / 2);
-            __builtin_nontemporal_store(ds_out[0][qs], dst);
-            __builtin_nontemporal_store(ds_out[1][qs], dst + 1);
+    for (int r = 0; r < 16; ++r) {
+        const int q = q0 + 8 * (r >> 2) + 4 * h + (r & 3);
+        if (q >= LqR) continue;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+            dQ[((size_t)bh * LqR + q) * D + 32 * dt + lj] = (uint16_t)(pack_bf16x2(acc_q[dt][r] * scale, 0.f) & 0xFFFFu);
+    }
+}
+
+// Sixteen zeros made on the spot (as a constant they are kept in sixteen registers of their own and copied from there)
+__device__ __forceinline__ f32x16 fresh_zeros() {
+    f32x16 z;
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {
+        uint64_t p = 0;
+        asm volatile("" : "+v"(p));
+        z[r] = __uint_as_float((uint32_t)p), z[r + 1] = __uint_as_float((uint32_t)(p >> 32));
+    }
+    return z;
+}
+
+// dV = P^T dO and dK = scale * dS^T Q in one pass over the queries; a workgroup owns 128 keys of a head, a wave 32 of them.
+// Both sums contract over the queries, across which the N:M structure does not run, so a wave needs P (and dP) with a KEY
+// in every lane and the queries along the registers.  The matrix unit does that transposition: the compressed weights
+// of 32 queries x 32 keys times the identity (one sparse instruction, operand and index as stored) is the dense tile in
+// the accumulator layout -- column = key, registers = queries, exact in fp32 -- with no vector instruction per element.
+// dP - delta arrives in the same layout from the dense product of dO (rows) with V (columns, in registers for the whole
+// kernel), started from -delta of the rows; dS is one multiplication per element.  Rounded to bfloat16 both tiles are the A
+// operands (row = key) of the two products, contraction index 8 m' + 4 h + x of step m = register order, against dO
+// and Q from the transposing LDS read in the same order.
+// Bound by the matrix unit: 13 instructions of 32 cycles per 32 x 32 tile at d = 64 (25 at d = 128).
+// UNP as above; the rows LqR .. Lq - 1 of P, whatever they hold, count as zeros.
+template <int D, bool UNP>
+__global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void k_backward_dkv(
+    const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta, const __bf16 *__restrict__ dO,
+    const __bf16 *__restrict__ Q, const __bf16 *__restrict__ V, const float *__restrict__ neg_delta, int Lq, int Lk,
+    int LqR, int LkR, float scale, uint16_t *__restrict__ dK, uint16_t *__restrict__ dV) {
+    constexpr int QB = D == 64 ? 64 : 32;    // queries per block (d = 128: so that two workgroups share a compute unit)
+    constexpr int CPR = D / 8;
+    constexpr int XT = QB * CPR;             // chunks per dO (or Q) block
+    constexpr int LPT = XT / NT;
+    constexpr int PT = QB * 8;               // chunks per block of kept weights (128 keys = 128 bytes per row)
+    constexpr int STEPS = D / 16;
+    constexpr int DT = D / 32;
+    static_assert(XT % NT == 0 && PT % NT == 0, "every thread copies the same number of chunks");
+    constexpr bool V_LDS = D == 128;         // the V operand: in LDS where registers are short (read back for every tile)
+    // LDS in 16-byte units; every place but the V operand twice, `BUF` apart.  One array: an access is one of a few lane
+    // offsets plus a constant.
+    constexpr int AT_G = 0, AT_Q = XT, AT_P = 2 * XT, AT_M = AT_P + PT, AT_D = AT_M + QB, BUF = AT_D + QB / 4, AT_V = 2 * BUF;
+    __shared__ u32x4 Smem[AT_V + (V_LDS ? KB * CPR : 0)];
+
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, lj = l & 31, h = l >> 5;
+    const unsigned kblocks = Lk / KB;
+    const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int jblk = item % kblocks, bh = item / kblocks;
+    const int nq = (LqR + QB - 1) / QB;
+
+    // dO and Q blocks: row = query, chunk c at row * CPR + (c ^ both_ways_swizzle(row)); kept weights: row = query, chunk c
+    // at row * 8 + (c ^ operand_row_swizzle(row)); metadata: 16 bytes per row
+    int x_row[LPT], x_chunk[LPT];
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) {
+        const int p = i * NT + tid;
+        x_row[i] = p / CPR;
+        x_chunk[i] = ((p % CPR) ^ both_ways_swizzle<CPR>(x_row[i])) * 8;
+    }
+    const uint32_t lds = lds_address(Smem), lds_w = lds + 16u * 64 * w;
+    const uint64_t g_base = uniform_address(dO + (size_t)bh * LqR * D), q_base = uniform_address(Q + (size_t)bh * LqR * D);
+    const uint64_t p_base = uniform_address(P + ((size_t)bh * Lq * (size_t)(Lk / 4) + (size_t)jblk * 32));
+    const uint64_t m_base = uniform_address(meta + ((size_t)bh * (Lq / 16) * kblocks + jblk) * 64);
+    const uint64_t d_base = uniform_address(neg_delta + (size_t)bh * Lq);
+    const uint32_t p_off = (uint32_t)(tid >> 3) * (uint32_t)Lk + 16u * ((tid & 7) ^ operand_row_swizzle<8, 32>(tid >> 3));
+    auto issue_block = [&](int qb, int buf) {
+        const uint64_t gs = g_base + (uint64_t)qb * (QB * D * 2), qs = q_base + (uint64_t)qb * (QB * D * 2);
+        const int last = UNP ? LqR - qb * QB - 1 : QB - 1;   // the block's last real row
+#pragma unroll
+        for (int i = 0; i < LPT; ++i) {
+            const uint32_t off = 2u * ((UNP && x_row[i] > last ? last : x_row[i]) * D + x_chunk[i]);
+            async_copy16(gs, off, lds_w + 16u * (buf * BUF + AT_G + i * NT));
+            async_copy16(qs, off, lds_w + 16u * (buf * BUF + AT_Q + i * NT));
+        }
+        // (32 rows further: the swizzle takes row bits 1 .. 3, which do not move)
+#pragma unroll
+        for (int i = 0; i < PT / NT; ++i)
+            async_copy16(p_base + ((uint64_t)qb * QB + 32 * i) * (uint64_t)Lk, p_off, lds_w + 16u * (buf * BUF + AT_P + i * NT));
+        if (w == 0) {
+            if (l < QB)
+                async_copy16(m_base + (uint64_t)qb * (QB / 16) * kblocks * 256u, (uint32_t)(l >> 4) * kblocks * 256u + 16u * (l & 15),
+                             lds + 16u * (buf * BUF + AT_M));
+        } else if (w == 1) {
+            if (l < QB / 4) async_copy16(d_base + (uint64_t)qb * (QB * 4), 16u * l, lds + 16u * (buf * BUF + AT_D));
+        }
+    };
+    issue_block(0, 0);
+
+    // V operand: column = key lj of this wave, k = 16 s + 8 h .. +7
+    bf16x8 bv[V_LDS ? 1 : STEPS];
+    {
+        const int real = UNP ? LkR - jblk * KB : KB;   // real keys of this workgroup
+        const __bf16 *const v_rows = V + ((size_t)bh * LkR + (size_t)jblk * KB) * D;
+        if constexpr (V_LDS) {   // row = key, chunk c at row * CPR + (c ^ operand_row_swizzle(row))
+#pragma unroll
+            for (int i = 0; i < KB * CPR / NT; ++i) {
+                const int p = i * NT + tid, row = p / CPR;
+                async_copy16(v_rows, 2u * ((UNP && row >= real ? real - 1 : row) * D + ((p % CPR) ^ operand_row_swizzle<CPR, 32>(row)) * 8),
+                             lds_w + 16u * (AT_V + i * NT));
+            }
+        } else {
+            const int row = UNP && 32 * w + lj >= real ? real - 1 : 32 * w + lj;
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s)
+                bv[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(v_rows + row * D + 16 * s + 8 * h));
         }
     }
-    if constexpr (DQ) {
-        // acc_dq[qs][ds][r] = dQ[q][16 ds + li], q = q0 + 16 qs + 4 kb + r
+    // the identity as B operand of the sparse instruction: lane (column lj, h) holds keys 8 h .. +7 and 16 + 8 h .. +7
+    bf16x16 eye;
+    {
+        s16x16 e16;
 #pragma unroll
-        for (int qs = 0; qs < NQ; ++qs)
+        for (int e = 0; e < 16; ++e) e16[e] = (e < 8 ? 8 * h + e : 8 + 8 * h + e) == lj ? (short)0x3F80 : (short)0;
+        eye = __builtin_bit_cast(bf16x16, e16);
+    }
+
+    f32x16 acc_v[DT], acc_k[DT];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int qrow = q0 + 16 * qs + 4 * kb + r;
-                if (UNP && qrow >= LqR) continue;
-                const size_t q = (size_t)bh * LqR + qrow;
+    for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-                for (int ds = 0; ds < DS; ++ds)
-                    dQ[q * D + 16 * ds + li] = (uint16_t)(pack_bf16x2(acc_dq[qs][ds][r], 0.f) & 0xFFFFu);
+        for (int r = 0; r < 16; ++r) acc_v[dt][r] = 0.f, acc_k[dt][r] = 0.f;
+
+    // Lane offsets (bytes).  Operand read of dO (and of V): row lj, chunk 2 s + h.  Transposing read of dO and Q: rows
+    // row0 + 4 h + 8 j + tr_row (j = 0, 1; row0 a multiple of 16: it does not move the swizzle), columns 32 dt .. +31.
+    const int s16 = l & 15;
+    const int tr_row = s16 >> 2, tr_chunk = 2 * ((l >> 4) & 1) + ((s16 >> 1) & 1), tr_byte = 8 * (s16 & 1);
+    int op_off[STEPS], v_off[V_LDS ? STEPS : 1], tr_off[2][DT];
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+        op_off[s] = 16 * (lj * CPR + ((2 * s + h) ^ both_ways_swizzle<CPR>(lj)));
+        if constexpr (V_LDS) v_off[s] = 16 * (AT_V + (32 * w + lj) * CPR + ((2 * s + h) ^ operand_row_swizzle<CPR, 32>(lj)));
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+            const int row = 4 * h + 8 * j + tr_row;
+            tr_off[j][dt] = 16 * (row * CPR + ((4 * dt + tr_chunk) ^ both_ways_swizzle<CPR>(row))) + tr_byte;
+        }
+    const int p_lane = 16 * (lj * 8 + ((2 * w + h) ^ operand_row_swizzle<8, 32>(lj)));
+    const int m_lane = 16 * lj + 4 * (((w & 1) << 1) | (w >> 1));   // the word of 32-key chunk w in a row's 16 bytes
+    const int d_lane = 16 * h;
+    const char *const smem = reinterpret_cast<const char *>(Smem);
+    auto read16 = [&](int lane_off, int at) { return *reinterpret_cast<const u32x4 *>(smem + lane_off + 16 * at); };
+
+    auto block = [&](auto parity, int qb) {
+        constexpr int buf = decltype(parity)::value;
+        wait_async_copies();
+        __syncthreads();
+        if (qb + 1 < nq) issue_block(qb + 1, buf ^ 1);
+#pragma unroll
+        for (int qt = 0; qt < QB / 32; ++qt) {
+            constexpr int B0 = buf * BUF;
+            u32x4 kept = read16(p_lane, B0 + AT_P + 32 * 8 * qt);
+            if (UNP && qb * QB + 32 * qt + lj >= LqR) kept = u32x4{0u, 0u, 0u, 0u};
+            const uint32_t codes = *reinterpret_cast<const uint32_t *>(smem + m_lane + 16 * (B0 + AT_M + 32 * qt)) >> (16 * h);
+            f32x16 dp, pd;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const f32x4 nd = __builtin_bit_cast(f32x4, read16(d_lane, B0 + AT_D + 8 * qt + 2 * g));   // rows 32 qt + 8 g + 4 h .. +3
+#pragma unroll
+                for (int x = 0; x < 4; ++x) dp[4 * g + x] = nd[x];
             }
+            pd = fresh_zeros();
+            pd = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(__builtin_bit_cast(bf16x8, kept), eye, pd, (int)codes, 0, 0);
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s) {
+                const bf16x8 ag = __builtin_bit_cast(bf16x8, read16(op_off[s], B0 + AT_G + 32 * CPR * qt));
+                bf16x8 b;
+                if constexpr (V_LDS) b = __builtin_bit_cast(bf16x8, read16(v_off[s], 0));
+                else b = bv[s];
+                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag, b, dp, 0, 0, 0);
+            }
+            // register r: query 32 qt + 8 (r / 4) + 4 h + r % 4, key lj
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                u32x4 pw, sw;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = 8 * m + 2 * e;
+                    pw[e] = pack_bf16x2(pd[r], pd[r + 1]);
+                    sw[e] = pack_bf16x2(pd[r] * dp[r], pd[r + 1] * dp[r + 1]);
+                }
+                const bf16x8 ap = __builtin_bit_cast(bf16x8, pw), as = __builtin_bit_cast(bf16x8, sw);
+                auto tr = [&](int at, int dt) {
+                    const int rows = 16 * (B0 + at + CPR * (32 * qt + 16 * m));
+                    const s16x4 t0 = lds_read_tr16(smem + tr_off[0][dt] + rows), t1 = lds_read_tr16(smem + tr_off[1][dt] + rows);
+                    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(t0, t1, 0, 1, 2, 3, 4, 5, 6, 7));
+                };
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+                    acc_v[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ap, tr(AT_G, dt), acc_v[dt], 0, 0, 0);
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+                    acc_k[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as, tr(AT_Q, dt), acc_k[dt], 0, 0, 0);
+            }
+        }
+    };
+    for (int qb = 0; qb < nq; qb += 2) {
+        block(std::integral_constant<int, 0>{}, qb);
+        if (qb + 1 < nq) block(std::integral_constant<int, 1>{}, qb + 1);
+    }
+
+    // acc[dt][r]: key 8 (r / 4) + 4 h + r % 4 of the wave's 32, column 32 dt + lj
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int key = jblk * KB + 32 * w + 8 * (r >> 2) + 4 * h + (r & 3);
+        if (UNP && key >= LkR) continue;
+        const size_t at = ((size_t)bh * LkR + key) * D + lj;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+            dV[at + 32 * dt] = (uint16_t)(pack_bf16x2(acc_v[dt][r], 0.f) & 0xFFFFu);
+            dK[at + 32 * dt] = (uint16_t)(pack_bf16x2(acc_k[dt][r] * scale, 0.f) & 0xFFFFu);
+        }
     }
 }
 
@@ -467,53 +639,37 @@ hipError_t launch_spmm_t(const void *vals, const void *meta, const void *X, int 
     return hipGetLastError();
 }
 
-}  // namespace dfss
-
-namespace dfss {
-
-namespace {
-template <int NQ, bool UNP>
-hipError_t launch_ds_nq(const void *dO, const void *V, const void *O, const void *P, const void *meta, const void *K,
-                        int BH, int Lq, int Lk, int LqR, int LkR, int d, float scale, void *dS, void *dQ,
-                        hipStream_t st) {
-    const int qtiles = Lq / (64 * NQ);
-    const int kblocks = Lk / KB;
-    const bool with_dq = dQ != nullptr;   // (d = 64: checked by the caller)
-    // split the key range until the grid has a few workgroups per compute unit (not with the fused dQ, whose sums
-    // run over all keys of a query)
-    int ksplit = 1;
-    if (!with_dq) {
-        while ((long)BH * qtiles * ksplit < 1024 && kblocks % (ksplit * 2) == 0) ksplit *= 2;
-        if ((long)BH * qtiles * ksplit < 1024 && kblocks % 3 == 0 && ksplit == 1) ksplit = 3;
-    }
-    const int per_wg = kblocks / ksplit;
-    const unsigned grid = (unsigned)((long)BH * qtiles * ksplit);
-#define DFSS_LAUNCH(DD, WITH)                                                                                      \
-    hipLaunchKernelGGL((k_masked_sddmm_ds<DD, NQ, WITH, UNP>), dim3(grid), dim3(NT), 0, st, (const __bf16 *)dO,    \
-                       (const __bf16 *)V, (const __bf16 *)O, (const uint32_t *)P, (const uint32_t *)meta,         \
-                       (const __bf16 *)K, Lq, Lk, LqR, LkR, scale, ksplit, per_wg, (uint32_t *)dS, (uint16_t *)dQ)
+// P, meta: as kept from the forward pass.  scratch: fp32 [BH][Lq] (-delta, passed from the first kernel to the second).
+hipError_t launch_backward(const void *dO, const void *Q, const void *K, const void *V, const void *O, const void *P,
+                           const void *meta, int BH, int Lq, int Lk, int LqR, int LkR, int d, float scale, float *scratch,
+                           void *dQ, void *dK, void *dV, hipStream_t st) {
+    const bool unp = LqR != Lq || LkR != Lk;
+    // 128-query workgroups where they fill the chip (three per compute unit at d = 64, two at d = 128), else 64-query ones
+    const bool four = (long)BH * ((Lq + 127) / 128) >= 512;
+    const unsigned grid_q = (unsigned)((long)BH * (four ? (Lq + 127) / 128 : Lq / 64));
+    const unsigned grid_k = (unsigned)((long)BH * (Lk / KB));
+#define DFSS_DQ(DD, NW, UU)                                                                                              \
+    hipLaunchKernelGGL((k_backward_dq<DD, NW, UU>), dim3(grid_q), dim3(64 * NW), 0, st, (const __bf16 *)dO,              \
+                       (const __bf16 *)V, (const __bf16 *)O, (const uint32_t *)P, (const uint32_t *)meta,               \
+                       (const __bf16 *)K, Lq, Lk, LqR, LkR, scale, (uint16_t *)dQ, scratch)
+#define DFSS_DKV(DD, UU)                                                                                                 \
+    hipLaunchKernelGGL((k_backward_dkv<DD, UU>), dim3(grid_k), dim3(NT), 0, st, (const uint32_t *)P,                     \
+                       (const uint32_t *)meta, (const __bf16 *)dO, (const __bf16 *)Q, (const __bf16 *)V, scratch, Lq, Lk, \
+                       LqR, LkR, scale, (uint16_t *)dK, (uint16_t *)dV)
+#define DFSS_BOTH(DD, UU)                                         \
+    do {                                                          \
+        if (four) DFSS_DQ(DD, 4, UU); else DFSS_DQ(DD, 2, UU);    \
+        DFSS_DKV(DD, UU);                                         \
+    } while (0)
     if (d == 64) {
-        if (with_dq) DFSS_LAUNCH(64, true); else DFSS_LAUNCH(64, false);
+        if (unp) DFSS_BOTH(64, true); else DFSS_BOTH(64, false);
     } else {
-        DFSS_LAUNCH(128, false);
+        if (unp) DFSS_BOTH(128, true); else DFSS_BOTH(128, false);
     }
-#undef DFSS_LAUNCH
+#undef DFSS_BOTH
+#undef DFSS_DKV
+#undef DFSS_DQ
     return hipGetLastError();
-}
-}  // namespace
-
-// K, dQ: both null, or (d = 64 only) the keys and the output of dQ = dS' K, formed in the same pass.
-hipError_t launch_masked_sddmm_ds(const void *dO, const void *V, const void *O, const void *P, const void *meta,
-                                  const void *K, int BH, int Lq, int Lk, int LqR, int LkR, int d, float scale, void *dS,
-                                  void *dQ, hipStream_t st) {
-    if (dQ && d != 64) return hipErrorInvalidValue;
-    if (LqR != Lq || LkR != Lk) {
-        if (Lq % 128 == 0)
-            return launch_ds_nq<2, true>(dO, V, O, P, meta, K, BH, Lq, Lk, LqR, LkR, d, scale, dS, dQ, st);
-        return launch_ds_nq<1, true>(dO, V, O, P, meta, K, BH, Lq, Lk, LqR, LkR, d, scale, dS, dQ, st);
-    }
-    if (Lq % 128 == 0) return launch_ds_nq<2, false>(dO, V, O, P, meta, K, BH, Lq, Lk, Lq, Lk, d, scale, dS, dQ, st);
-    return launch_ds_nq<1, false>(dO, V, O, P, meta, K, BH, Lq, Lk, Lq, Lk, d, scale, dS, dQ, st);
 }
 
 }  // namespace dfss

@@ -119,6 +119,20 @@ __device__ __forceinline__ int tr_row_swizzle(int row) {
     return CPR == 8 ? (((row >> 1) & 1) << 1) | (g << 2) : ((row & 3) << 1) | (g << 3);
 }
 
+// XOR pattern for the 16-byte chunks of V row `row` (transposing read of a 32-column tile: the 32 lanes served together
+// read 64 bytes of each of four consecutive rows, which have to fall into different quarters of the 64 banks)
+template <int CPR>
+__device__ __forceinline__ int tr32_swizzle(int row) {
+    return CPR == 8 ? (row & 3) << 1 : (row & 3) << 2;
+}
+// The same for a tile that is read both ways: 32 rows as operand (operand_row_swizzle<CPR, 32>: 16 consecutive rows in 16
+// groups of banks) and with the transposing read of a 32-column tile (the two rows of four that share banks, or all
+// four of them, differ in the chunk bits from bit 2 up).
+template <int CPR>
+__device__ __forceinline__ int both_ways_swizzle(int row) {
+    return CPR == 8 ? (((row >> 1) & 1) << 2) | ((row >> 2) & 3) : ((row & 3) << 2) | ((row >> 2) & 3);
+}
+
 // Orders this wave's own LDS traffic: writes issued before the call are visible to reads of any
 // lane of the same wave issued after it.  The hardware executes a wave's LDS operations in order;
 // the fences (wavefront scope, no instructions) only keep the compiler from moving them across.

@@ -65,13 +65,6 @@ __device__ __forceinline__ uint32_t push_position(uint32_t idx, float v) {
     return __builtin_amdgcn_alignbit(__float_as_uint(v), idx, 2);
 }
 
-// XOR pattern for the 16-byte chunks of V row `row` (transposing read of a 32-column tile: the 32 lanes served together
-// read 64 bytes of each of four consecutive rows, which have to fall into different quarters of the 64 banks)
-template <int CPR>
-__device__ __forceinline__ int tr32_swizzle(int row) {
-    return CPR == 8 ? (row & 3) << 1 : (row & 3) << 2;
-}
-
 // NW waves per workgroup = NW / KS query tiles of 32 queries x KS waves per tile.  With KS = 2 the two
 // waves of a query tile share its keys: of every 64-key block, wave ks takes the 32-key tile ks (its own
 // reference value, row sums and partial O, merged at the end through LDS).  Smaller work items, more

@@ -128,6 +128,39 @@ def test_forward_stages_then_backward_on_exact_scores():
             assert np.max(np.abs(got - ref)) <= tol, (name, h)
 
 
+@pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
+    (192, 320, 384, 64, 1, 2),     # 128-query workgroups, the last one of a head half empty
+    (96, 704, 704, 64, 2, 4),      # 11 blocks of 64 keys: a single one in the last pair
+    (140, 512, 256, 128, 2, 4),    # d = 128, 128-query workgroups
+])
+def test_backward_on_grids_that_fill_the_chip(BH, Lq, Lk, d, N, M):
+    """Waves that compete for the matrix unit see its results later than a lone wave does; sampled heads against the
+    oracle, differentiating through the GPU's own forward results."""
+    scale = 1.0 / math.sqrt(d)
+    Q, K, V = synth.gaussian_qkv(BH, Lq, Lk, d, 1.0, seed=9800 + Lq + d)
+    g = torch.Generator().manual_seed(9801 + d)
+    dO = torch.randn(BH, Lq, d, generator=g).to(torch.bfloat16)
+    s = Shape(1, BH, Lq, Lk, d, N, M)
+    Qd, Kd, Vd, dOd = _dev(Q), _dev(K), _dev(V), _dev(dO)
+    P, meta = dfss.dfss_sddmm_prune(Qd, Kd, s, scale)
+    dfss.dfss_sparse_softmax(P, s)
+    O = dfss.dfss_spmm(P, meta, Vd, s)
+    dQ, dK, dV = dfss.dfss_attention_backward(dOd, Qd, Kd, Vd, O, P, meta, s, scale)
+    canon = dfss.dfss_meta_to_canonical(meta, s)
+    torch.cuda.synchronize()
+    for h in (0, BH // 3, BH // 2 + 1, BH - 1):
+        kidx = oracle.decode_meta(canon[h].cpu().numpy().view(np.uint16), s.LkP)[:Lq]
+        Ph = _np(P[h])[:Lq]
+        real = kidx < Lk
+        assert np.all(Ph[~real] == 0.0)
+        ki, Pr = np.where(real, kidx, 0).astype(np.int32), np.where(real, Ph, 0.0).astype(np.float32)
+        Qn, Kn, Vn, dOn = (synth.to_numpy_f32(t[h]) for t in (Q, K, V, dO))
+        rQ, rK, rV = oracle.attention_backward(Qn, Kn, Vn, dOn, Pr, ki, scale)
+        for name, got, ref in (("dQ", _np(dQ[h]), rQ), ("dK", _np(dK[h]), rK), ("dV", _np(dV[h]), rV)):
+            tol = 2.0 ** -7 * np.max(np.abs(ref)) + 1e-4      # as above
+            assert np.max(np.abs(got - ref)) <= tol, (name, h)
+
+
 # ----------------------------------------------------------------------------------
 # lengths that are not tile multiples: P, meta and dS' keep the layout of the padded lengths
 # ----------------------------------------------------------------------------------
