@@ -35,7 +35,7 @@ EXPORTS = (
 )
 # exported for the library's own tests only (csrc/dfss_internal.h)
 INTERNAL_EXPORTS = ("dfss_internal_attention_variant",)
-VARIANT_AUTO, VARIANT_Q16, VARIANT_Q16X2, VARIANT_Q32W2, VARIANT_Q32W4, VARIANT_Q32K2 = range(6)
+VARIANT_AUTO, VARIANT_Q16, VARIANT_Q16X2, VARIANT_Q32W2, VARIANT_Q32W4, VARIANT_Q32K2, VARIANT_FEW = range(7)
 
 
 DFSS_BF16, DFSS_F32, DFSS_F32_BF16X3 = 0, 1, 2

@@ -198,7 +198,9 @@ static dfss_status attention_forward(const void *Q, const void *K, const void *V
     Dims D;
     if (!Q || !K || !V || !O) return DFSS_ERR_NULL;
     // (unpadded lengths: the staged calls only; the one-kernel calls for them are the *_ragged ones)
-    if (dfss_status st = staged ? check_shape_stage(s, true, &D) : check_shape(s, true, &D)) return st;
+    if (dfss_status st = staged ? check_shape_stage(s, true, &D)
+                         : variant == DFSS_VARIANT_FEW ? check_shape_ragged(s, true, &D) : check_shape(s, true, &D))
+        return st;
     if (bad_scale(scale)) return DFSS_ERR_UNSUPPORTED;
     if (misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(O) || misaligned(key_bias))
         return DFSS_ERR_SHAPE;

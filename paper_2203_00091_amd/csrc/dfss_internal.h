@@ -21,7 +21,8 @@ enum {
     DFSS_VARIANT_Q32W2 = 3,  /* 32 queries per wave, 32x32x16 matrix instruction, 2 waves              */
     DFSS_VARIANT_Q32W4 = 4,  /* ... 4 waves, 128-query workgroups (Lq % 128 == 0)                       */
     DFSS_VARIANT_Q32K2 = 5,  /* 32 queries per pair of waves that split the keys, 4 waves, 64 queries  */
-    DFSS_VARIANT_LAST = 5
+    DFSS_VARIANT_FEW = 6,    /* 16-query workgroups whose waves share the keys (any lengths; no block pattern)  */
+    DFSS_VARIANT_LAST = 6
 };
 
 /* dfss_attention_bias (dense == 0) or dense_attention_fused_bias (dense != 0) on bfloat16 data with the

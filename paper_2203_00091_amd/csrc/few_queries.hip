@@ -1,0 +1,304 @@
+// Whole DFSS forward pass in one kernel for calls with few query tiles (see fused_attention.hip for the method and the
+// operand layouts: arXiv 2203.00091, Sec. 3.1 stages, Sec. 3.4 pruning on the accumulators, App. A.1.3 softmax).
+//
+// One new query against a cache of keys, a short prompt, a single short sequence: K and V are read for at most a few query
+// tiles, and the kernels that give a workgroup 64 or 128 queries leave most compute units idle while each of their
+// workgroups walks over the keys alone.  Here a workgroup owns 16 queries and its waves share the KEYS: wave w takes every
+// NW-th 64-key block, on its own, and the partial results are merged through LDS at the end.  What bounds it is the rate at
+// which a compute unit can pull K and V, so all of the design goes into bytes in flight:
+//   K     16 bytes per lane straight from global memory in the layout of the matrix operand (nobody shares it: no LDS),
+//         one block ahead, in registers
+//   V     by asynchronous copies, one block ahead, into LDS that belongs to the wave (the transposing read needs LDS)
+// No barrier before the merge: a wave waits for its own copies only.
+// Measured: a round of one block per wave (128 KiB per workgroup) takes 2.3 us whether 12 or 96 workgroups run, 57 GB/s per
+// compute unit; 1024 heads x 1 query x 4096 keys 179 us (6 TB/s).  96 heads x 1 x 4096: 47.9 us with 64-query workgroups,
+// 21.1 us here.
+#include <math.h>
+
+#include <type_traits>
+
+#include "block_list.hpp"
+#include "dfss_device.hpp"
+#include "dfss_kernels.hpp"
+
+namespace dfss {
+
+namespace {
+
+constexpr int KB = 64;    // keys per block
+constexpr float kTau = 8.0f;
+constexpr float kLog2e = 1.4426950408889634f;
+
+enum { MODE_2TO4 = 0, MODE_1TO2 = 1 };
+
+// Any Lq; Lk a multiple of 4 (the absent keys of a partial last block are copies of the last key whose scores become -inf;
+// absent queries are computed on a copy of the last one and not stored).
+// BIAS: key_bias fp32 [BH / H][Lk], as in k_fused; blocks whose keys are all masked are skipped.
+template <int D, int MODE, int NW, bool PRESCALE, bool BIAS>
+__global__ __launch_bounds__(64 * NW) void k_few(const __bf16 *__restrict__ Q, const __bf16 *__restrict__ K,
+                                                 const __bf16 *__restrict__ V, const float *__restrict__ key_bias, int H,
+                                                 int Lq, int Lk, float scale, uint16_t *__restrict__ O) {
+    constexpr int CPR = D / 8;          // 16-byte chunks per row
+    constexpr int TILE = KB * CPR;      // chunks per V block
+    constexpr int LPT = TILE / 64;      // asynchronous copies per lane and V block
+    constexpr int STEPS = D / 32;       // MFMA k-steps of Q K^T
+    constexpr int DS = D / 16;          // 16-column tiles of O
+    constexpr int NF = 4 * DS + 5;      // floats per lane of a partial result
+    __shared__ u32x4 Vs[NW * 2 * TILE];
+    static_assert(NW * NF * 64 * 4 <= NW * 2 * TILE * 16, "the partial results fit into the V buffers");
+
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), l = threadIdx.x & 63, li = l & 15, kb = l >> 4;
+    const unsigned qtiles = (Lq + 15) / 16;
+    const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int q0 = (item % qtiles) * 16, bh = item / qtiles;
+    const int nblocks = (Lk + KB - 1) / KB;
+
+    // V block: row = key, chunk c at row * CPR + (c ^ tr_row_swizzle(row))
+    int v_row[LPT], v_chunk[LPT];
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) {
+        const int p = i * 64 + l;
+        v_row[i] = p / CPR;
+        v_chunk[i] = ((p % CPR) ^ tr_row_swizzle<CPR>(v_row[i])) * 8;
+    }
+    const uint32_t lds_v = lds_address(&Vs[w * 2 * TILE]);
+    const uint64_t v_base = uniform_address(V + (size_t)bh * Lk * D);
+    const __bf16 *const Kh = K + (size_t)bh * Lk * D;
+    const float *const brow = BIAS ? key_bias + (size_t)(bh / H) * Lk : nullptr;
+
+    // What a wave holds of a block in registers.  MFMA row i of tile t is key 16 (i / 4) + 4 t + i % 4 (as in k_fused), so
+    // that lane (query li, kb) ends up with the scores of keys 16 kb .. +15.
+    struct Block {
+        u32x4 k[STEPS][4];
+        f32x4 bias[BIAS ? 4 : 1];
+    };
+    auto load_block = [&](int jb, auto parity, Block &b) {
+        const int last = Lk - 1 - jb * KB;   // the block's last real key (KB - 1 or more: all are)
+        const uint64_t vs = v_base + (uint64_t)jb * (KB * D * 2);
+#pragma unroll
+        for (int i = 0; i < LPT; ++i)
+            async_copy16(vs, 2u * ((v_row[i] < last ? v_row[i] : last) * D + v_chunk[i]), lds_v + 16u * (decltype(parity)::value * TILE + i * 64));
+        const __bf16 *const ks = Kh + (size_t)jb * (KB * D);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int key = 16 * (li >> 2) + 4 * t + (li & 3);
+            const __bf16 *const row = ks + (key < last ? key : last) * D + 8 * kb;
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s) b.k[s][t] = *reinterpret_cast<const u32x4 *>(row + 32 * s);
+            if constexpr (BIAS) {   // (Lk is a multiple of 4: four keys exist together)
+                const int k4 = 16 * kb + 4 * t;
+                b.bias[t] = *reinterpret_cast<const f32x4 *>(brow + jb * KB + (k4 < last ? k4 : last - 3));
+            }
+        }
+    };
+
+    BlockList<BIAS, true> blocks;
+    if constexpr (BIAS) {
+        blocks.init(true, brow, false, nullptr, 0, 0, 16, 0, Lq, Lk, nblocks, l);
+        for (int i = 0; i < w; ++i) blocks.take();
+    }
+    int next_plain = w;
+    auto take = [&]() -> int {
+        if constexpr (BIAS) {
+            const int j = blocks.take();
+            for (int i = 1; i < NW; ++i) blocks.take();
+            return __builtin_amdgcn_readfirstlane(j);
+        } else {
+            const int j = next_plain;
+            next_plain += NW;
+            return j;
+        }
+    };
+
+    Block b0, b1;
+    int jb = take(), jn = take();
+    if (jb < nblocks) load_block(jb, std::integral_constant<int, 0>{}, b0);
+
+    // Q operand: lane (column li, chunk kb) of step s holds Q[q][32 s + 8 kb .. +7]
+    bf16x8 bq[STEPS];
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+        const int qrow = q0 + li < Lq ? q0 + li : Lq - 1;
+        const u32x4 raw = *reinterpret_cast<const u32x4 *>(Q + ((size_t)bh * Lq + qrow) * D + 32 * s + 8 * kb);
+        if constexpr (PRESCALE) {
+            u32x4 sc;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sc[e] = pack_bf16x2(bf16_lo_to_f32(raw[e]) * scale, bf16_hi_to_f32(raw[e]) * scale);
+            bq[s] = __builtin_bit_cast(bf16x8, sc);
+        } else {
+            bq[s] = __builtin_bit_cast(bf16x8, raw);
+        }
+    }
+
+    float m_ref = -1.0e30f;   // reference of the query in column li (the same in its four lanes)
+    f32x4 acc_o[DS], acc_l = {0.f, 0.f, 0.f, 0.f};   // O and row sums, rows 4 kb + r
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds) acc_o[ds] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const uint32_t one2 = 0x3F803F80u;  // two bfloat16 ones
+    const bf16x8 ones8 = __builtin_bit_cast(bf16x8, u32x4{one2, one2, one2, one2});
+    const int tr_row = li >> 2, tr_sub = (li >> 1) & 1, tr_byte = 8 * (li & 1);
+
+    auto block = [&](auto parity, const Block &b, Block &after) {
+        constexpr int buf = decltype(parity)::value;
+        // This block is in, and the LDS reads of the block before it (whose buffer the next copies overwrite) are done.
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
+        asm volatile("" ::: "memory");
+        if (jn < nblocks) load_block(jn, std::integral_constant<int, buf ^ 1>{}, after);
+
+        // acc[t][r] = s(query li, key 64 jb + 16 kb + 4 t + r)
+        f32x4 acc[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (BIAS && PRESCALE) acc[t] = b.bias[t];
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s) acc[t] = mfma16(__builtin_bit_cast(bf16x8, b.k[s][t]), bq[s], acc[t]);
+            if constexpr (!PRESCALE) {
+                acc[t] = acc[t] * scale;
+                if constexpr (BIAS) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[t][r] = add_unfused(acc[t][r], b.bias[t][r]);
+                }
+            }
+        }
+        if (jb * KB + KB > Lk) {   // the block that the keys end in
+            const int left = Lk - jb * KB - 16 * kb;   // real keys from this lane's first one on (a multiple of 4)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (4 * t >= left) acc[t] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        }
+
+        float kept[8];
+        uint32_t idx = 0;
+        float m_blk = -3.0e38f;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            float lo, hi;
+            uint32_t code;
+            if constexpr (MODE == MODE_2TO4) select_2of4(acc[t][0], acc[t][1], acc[t][2], acc[t][3], 4 * t, lo, hi, code);
+            else select_1of2(acc[t][0], acc[t][1], acc[t][2], acc[t][3], 4 * t, lo, hi, code);
+            kept[2 * t] = lo;
+            kept[2 * t + 1] = hi;
+            idx |= code;
+            m_blk = fmaxf(fmaxf(m_blk, lo), hi);
+        }
+        if (__any(m_blk > m_ref + kTau)) {   // raise the reference where the block outgrew it (rare after the first one)
+            m_blk = fmaxf(m_blk, __shfl_xor(m_blk, 16, 64));
+            m_blk = fmaxf(m_blk, __shfl_xor(m_blk, 32, 64));
+            const float m_new = m_blk > m_ref + kTau ? m_blk : m_ref;
+            const float alpha = __builtin_amdgcn_exp2f((m_ref - m_new) * kLog2e);
+            m_ref = m_new;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float a_r = __shfl(alpha, 4 * kb + r, 64);
+                acc_l[r] *= a_r;
+#pragma unroll
+                for (int ds = 0; ds < DS; ++ds) acc_o[ds][r] *= a_r;
+            }
+        }
+        const float mb = m_ref * kLog2e;
+        u32x4 pk;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            pk[e] = pack_bf16x2(__builtin_amdgcn_exp2f(__builtin_fmaf(kept[2 * e], kLog2e, -mb)),
+                                __builtin_amdgcn_exp2f(__builtin_fmaf(kept[2 * e + 1], kLog2e, -mb)));
+        const bf16x8 a = __builtin_bit_cast(bf16x8, pk);
+        const char *vbase = reinterpret_cast<const char *>(&Vs[(2 * w + buf) * TILE]);
+        auto tr = [&](int key0, int ds) {
+            const int row = key0 + tr_row;
+            const int chunk = (2 * ds + tr_sub) ^ tr_row_swizzle<CPR>(row);
+            return lds_read_tr16(vbase + (row * CPR + chunk) * 16 + tr_byte);
+        };
+#pragma unroll
+        for (int ds = 0; ds < DS; ++ds) {
+            const s16x4 t0 = tr(8 * kb, ds), t1 = tr(8 * kb + 4, ds), t2 = tr(32 + 8 * kb, ds), t3 = tr(36 + 8 * kb, ds);
+            const s16x8 lo = __builtin_shufflevector(t0, t1, 0, 1, 2, 3, 4, 5, 6, 7);
+            const s16x8 hi = __builtin_shufflevector(t2, t3, 0, 1, 2, 3, 4, 5, 6, 7);
+            const bf16x16 bv = __builtin_bit_cast(
+                bf16x16, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15));
+            acc_o[ds] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(a, bv, acc_o[ds], (int)idx, 0, 0);
+        }
+        acc_l = mfma16(a, ones8, acc_l);   // (against ones the positions do not matter: dense instruction)
+        jb = jn;
+        jn = take();
+    };
+    while (jb < nblocks) {
+        block(std::integral_constant<int, 0>{}, b0, b1);
+        if (jb >= nblocks) break;
+        block(std::integral_constant<int, 1>{}, b1, b0);
+    }
+
+    // Merge: value f of lane l of wave g at float f * 64 + l of the wave's slot; wave w forms the 16-column tiles w,
+    // w + NW, ... of O.  (No copy is in flight: a wave waits for its last block.)
+    __syncthreads();   // every wave is done with its V buffers
+    float *const slots = reinterpret_cast<float *>(Vs);
+    {
+        float *const mine = slots + w * (NF * 64) + l;
+        mine[0] = m_ref;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mine[(1 + r) * 64] = acc_l[r];
+#pragma unroll
+        for (int ds = 0; ds < DS; ++ds)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) mine[(5 + 4 * ds + r) * 64] = acc_o[ds][r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int d0 = 0; d0 < DS; d0 += NW) {
+        const int ds = d0 + w;
+        if (ds >= DS) break;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = 4 * kb + r;
+            if (q0 + row >= Lq) continue;
+            float m = -1.0e30f;
+#pragma unroll
+            for (int g = 0; g < NW; ++g) m = fmaxf(m, slots[g * (NF * 64) + row]);
+            float sum = 0.f, o = 0.f;
+#pragma unroll
+            for (int g = 0; g < NW; ++g) {
+                const float f = __builtin_amdgcn_exp2f((slots[g * (NF * 64) + row] - m) * kLog2e);
+                sum += f * slots[g * (NF * 64) + (1 + r) * 64 + l];
+                o += f * slots[g * (NF * 64) + (5 + 4 * ds + r) * 64 + l];
+            }
+            O[((size_t)bh * Lq + q0 + row) * D + 16 * ds + li] = (uint16_t)(pack_bf16x2(o * __builtin_amdgcn_rcpf(sum), 0.f) & 0xFFFFu);
+        }
+    }
+}
+
+inline bool is_pow2(float x) {
+    int e;
+    return frexpf(x, &e) == 0.5f;
+}
+
+template <int D, int MODE, int NW>
+hipError_t launch_few(const void *Q, const void *K, const void *V, const float *key_bias, int H, int BH, int Lq, int Lk,
+                      float scale, void *O, hipStream_t st) {
+    const unsigned grid = (unsigned)((long)BH * ((Lq + 15) / 16));
+#define DFSS_LAUNCH(PRE, BB)                                                                                        \
+    hipLaunchKernelGGL((k_few<D, MODE, NW, PRE, BB>), dim3(grid), dim3(64 * NW), 0, st, (const __bf16 *)Q,          \
+                       (const __bf16 *)K, (const __bf16 *)V, key_bias, H, Lq, Lk, scale, (uint16_t *)O)
+    if (is_pow2(scale)) {
+        if (key_bias) DFSS_LAUNCH(true, true); else DFSS_LAUNCH(true, false);
+    } else {
+        if (key_bias) DFSS_LAUNCH(false, true); else DFSS_LAUNCH(false, false);
+    }
+#undef DFSS_LAUNCH
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// mode 0 or 1; any Lq, Lk a multiple of 4; key_bias may be null.
+hipError_t launch_fused_attention_few(const void *Q, const void *K, const void *V, const float *key_bias, int H, int BH,
+                                      int Lq, int Lk, int d, int mode, float scale, void *O, hipStream_t st) {
+    if (d == 64) {
+        if (mode == 0) return launch_few<64, MODE_2TO4, 8>(Q, K, V, key_bias, H, BH, Lq, Lk, scale, O, st);
+        return launch_few<64, MODE_1TO2, 8>(Q, K, V, key_bias, H, BH, Lq, Lk, scale, O, st);
+    }
+    if (mode == 0) return launch_few<128, MODE_2TO4, 4>(Q, K, V, key_bias, H, BH, Lq, Lk, scale, O, st);
+    return launch_few<128, MODE_1TO2, 4>(Q, K, V, key_bias, H, BH, Lq, Lk, scale, O, st);
+}
+
+}  // namespace dfss

@@ -837,6 +837,8 @@ hipError_t launch_fused_attention32(const void *Q, const void *K, const void *V,
                                     int nw, int ks, float scale, void *O, hipStream_t st);
 hipError_t launch_fused_attention32_ragged(const void *Q, const void *K, const void *V, int BH, int Lq, int Lk, int d,
                                            int mode, float scale, void *O, hipStream_t st);
+hipError_t launch_fused_attention_few(const void *Q, const void *K, const void *V, const float *key_bias, int H, int BH,
+                                      int Lq, int Lk, int d, int mode, float scale, void *O, hipStream_t st);
 
 namespace {
 
@@ -908,12 +910,23 @@ hipError_t launch_fused_attention(const void *Q, const void *K, const void *V, c
     // two key halves costs more than it gains there).  Full attention
     // (the baseline) runs the 16-query kernel below: the faster of the two at every shape measured (96 heads x 384,
     // 24 heads x 1024 .. 4096, 192 heads x 512, d = 128), the 32-query form being reachable through the test hook.
+    // Few query tiles: the kernel whose waves share the keys (few_queries.hip), as long as its 16-query workgroups fit the
+    // chip at once (one per compute unit).  Measured against the kernels below, d = 64 / 128: one query and 4096 keys,
+    // 96 heads 47.9 -> 21.1 / 73 -> 41 us; 16 heads x 256 queries, 1024 keys 10.9 -> 9.1 / 21.2 -> 14.3 us; one head x 512
+    // x 512 8.6 -> 6.8 us.  With two rounds of workgroups it loses (96 heads x 64 queries, 4096 keys: 42 against 32 us)
+    // unless the kernels below would spend their tiles on absent queries (1024 heads x 1 query, 4096 keys: 212 -> 179 us),
+    // and so it does on two key blocks (one head x 128 x 128: 4.8 against 4.3 us).  Two identities keep a call out: a key
+    // bias on whole tiles gives bit for bit what a block pattern that keeps every block gives (the masked kernel below),
+    // and unpadded rows of fewer than 256 keys what the same call gives on masked padding (likewise).
+    const bool tiles = Lq % 64 == 0 && Lk % 64 == 0;
+    const bool few = Lq <= 16 ? Lk > 128 : Lk >= 256 && (long)BH * ((Lq + 15) / 16) <= 256 && !(key_bias && tiles);
+    if (((variant == DFSS_VARIANT_AUTO && few) || variant == DFSS_VARIANT_FEW) && mode != 2 && !block_mask && !causal)
+        return launch_fused_attention_few(Q, K, V, key_bias, H, BH, Lq, Lk, d, mode, scale, O, st);
     const bool masked = key_bias || block_mask || causal;
     // masked calls: the 32-query kernel where it measured faster -- the causal mask on 128-query workgroups (alone: its
     // form without the masking machinery, d = 64 and 128; with a key bias: the masked form, d = 64); a key bias alone
     // and block patterns stay with the kernel above
     const bool masked32 = causal && !block_mask && (d == 64 || !key_bias) && Lq % 128 == 0 && mode != 2;
-    const bool tiles = Lq % 64 == 0 && Lk % 64 == 0;
     if (tiles && (!masked || masked32) && variant != DFSS_VARIANT_Q16 && variant != DFSS_VARIANT_Q16X2) {
         const long wg128 = (long)BH * (Lq / 128);
         int nw = Lq % 128 == 0 ? 4 : 2, ks = 1;

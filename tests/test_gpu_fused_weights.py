@@ -87,7 +87,7 @@ def _int_qk(BH, Lq, Lk, d, seed, tdtype=torch.bfloat16):
 
 
 VARIANTS = [binding.VARIANT_Q16, binding.VARIANT_Q16X2, binding.VARIANT_Q32W2, binding.VARIANT_Q32W4,
-            binding.VARIANT_Q32K2]
+            binding.VARIANT_Q32K2, binding.VARIANT_FEW]
 
 
 @pytest.mark.parametrize("variant", VARIANTS)
@@ -106,6 +106,29 @@ def test_every_tiling_selects_and_weighs_like_the_oracle(variant, BH, Lq, Lk, d,
         lambda V: binding.internal_attention_variant(Qd, Kd, V, None, s, scale, variant), BH, Lq, Lk, d, torch.bfloat16)
     ties = _compare(W, Qn, Kn, N, M, scale)
     assert ties > 100          # the tie rule was exercised
+
+
+@pytest.mark.parametrize("BH,Lq,Lk,d,N,M,scale,bias", [
+    (3, 1, 132, 64, 2, 4, 0.125, False),       # one query; one run of keys in the last block, most waves without a block
+    (2, 16, 576, 64, 1, 2, 1.0 / 3.0, False),  # a whole query tile; nine blocks: one wave takes two
+    (2, 17, 1092, 64, 2, 4, 0.125, True),      # a tile with one query; 18 blocks, list of live blocks
+    (2, 33, 324, 128, 2, 4, 1.0 / 3.0, True),
+    (1, 5, 260, 128, 1, 2, 0.125, False),
+])
+def test_few_queries(BH, Lq, Lk, d, N, M, scale, bias):
+    """The kernel whose waves share the keys: the weights of every key, through the public call that takes it."""
+    scale = float(np.float32(scale))
+    Q, K, Qn, Kn = _int_qk(BH, Lq, Lk, d, seed=8700 + Lk + d + N)
+    kb = None
+    if bias:   # finite integers, and padding that ends in a block and leaves whole blocks masked
+        kb = torch.randint(-2, 3, (BH, Lk), generator=torch.Generator().manual_seed(8701)).float()
+        kb[0, Lk // 3 + 2:] = -math.inf
+        kb[1, 64:128] = -math.inf
+    s = Shape(BH, 1, Lq, Lk, d, N, M)
+    Qd, Kd, kbd = Q.to(DEV), K.to(DEV), None if kb is None else kb.to(DEV)
+    W = _weights_through_identity_v(
+        lambda V: dfss.dfss_attention_ragged(Qd, Kd, V, kbd, s, scale), BH, Lq, Lk, d, torch.bfloat16)
+    _compare(W, Qn, Kn, N, M, scale, key_bias=None if kb is None else kb.numpy())
 
 
 @pytest.mark.parametrize("variant", VARIANTS)
