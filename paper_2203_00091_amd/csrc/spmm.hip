@@ -7,7 +7,9 @@
 // through the same kernel.  The dense variant (P V of Eq. 1, for the baseline) shares the
 // V staging and uses v_mfma_f32_16x16x32_bf16.
 //
-// The SOFTMAX variant takes the kept SCORES of stage 1 instead of weights and applies the softmax
+// Three products: k_spmm on compressed weights; k_av on compressed SCORES (SPARSE: two-kernel forward pass) or on dense weights.
+//
+// The product on scores takes the kept SCORES of stage 1 instead of weights and applies the softmax
 // on the way (Sec. 3.1; the max-subtracted form of App. A.1.3 with a running reference m in the place of the
 // maximum): the scores of a block become exp(s - m) in registers before they enter the matrix instruction,
 // the accumulators are rescaled when a block exceeds m by more than a threshold, the row sums come from the
@@ -23,6 +25,8 @@
 // 32c + 16h .. +15 of the block -- the 16 keys whose kept weights lane group c holds in
 // half h of its 32 bytes.
 #include <cstdlib>
+#include <type_traits>
+
 #include "dfss_device.hpp"
 #include "dfss_kernels.hpp"
 
@@ -36,7 +40,7 @@ constexpr int KB = 128;   // keys per block
 // UNPADDED: V holds LkR <= Lk keys per head and O LqR <= Lq rows, while P and meta have the layout of the padded
 // lengths Lq (a multiple of 64) and Lk (of 128).  The weights of the absent keys are 0 (their scores were -inf); their
 // places in a partial last block of V are filled with the block's last real key, and rows past LqR are not stored.
-template <int D, bool SPARSE, int RB, bool SOFTMAX, bool UNPADDED = false>
+template <int D, bool SPARSE, int RB, bool UNPADDED = false>
 __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta,
                                               const __bf16 *__restrict__ V, int Lq, int Lk, int LqR, int LkR,
                                               uint16_t *__restrict__ O) {
@@ -45,6 +49,7 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
     constexpr int LPT = TILE / NT;      // direct-to-LDS loads per thread per block
     constexpr int DS = D / 16;          // 16-column output tiles
     constexpr int TQ = 64 * RB;         // queries per workgroup
+    constexpr bool SOFTMAX = SPARSE;    // (weights, on which there is nothing to do: k_spmm)
     __shared__ u32x4 Vs[2][TILE];
 
     const int tid = threadIdx.x;
@@ -121,7 +126,6 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
     const int tr_byte = 8 * (li & 1);
 
     // SOFTMAX: reference value of row li of each row block (the same in the four lane groups kb of a row)
-    static_assert(!SOFTMAX || SPARSE, "the softmax is folded into the sparse product only");
     constexpr float kLog2e = 1.4426950408889634f;
     constexpr float kTau = 8.0f;   // the running reference of a row is raised when a score exceeds it by more than this
     float m_run[RB];
@@ -270,13 +274,185 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
     }
 }
 
-template <bool SPARSE, bool SOFTMAX = false>
+// O = A_sparse V from compressed weights.  Bound by the stream of kept weights (1.125 bytes per score, read once): little
+// arithmetic per byte, so what counts is that enough of it is in flight.  A wave takes the weights of TWO 128-key blocks at
+// a time -- 256 contiguous bytes of every row -- and the loads of the next pair are issued before the first of the two is
+// multiplied and waited for after the second; the wait for the second block's V leaves them in flight.  4096 x 4096 with 24
+// heads (453 MB of weights and codes): 126 us with one block at a time, 113 us so; d = 128, 64 heads x 2048 (302 MB): 106 and
+// 97 us.  V comes out of the L2 for every workgroup: with 64 queries per workgroup (twice the V) 136 and 124 us.
+// Blocks go in pairs (the last pair may be a single block).  The workgroups start at different pairs and wrap around: the
+// rows of P are a power of two apart for the usual lengths, and workgroups in step would read the same few memory
+// channels at a time.  At d = 64 four neighbours start together and share V blocks (119 -> 113 us); at d = 128, where only
+// two workgroups run on a compute unit, every one starts on its own (97 against 103 us).
+template <int D, int RB, bool UNPADDED>
+__global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void k_spmm(const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta,
+                                                              const __bf16 *__restrict__ V, int Lq, int Lk, int LqR, int LkR,
+                                                              uint16_t *__restrict__ O) {
+    constexpr int CPR = D / 8;          // 16-byte chunks per V row
+    constexpr int TILE = KB * CPR;      // chunks per V block
+    constexpr int LPT = TILE / NT;      // direct-to-LDS loads per thread per block
+    constexpr int DS = D / 16;          // 16-column output tiles
+    constexpr int TQ = 64 * RB;         // queries per workgroup
+    __shared__ u32x4 Vs[2][TILE];
+
+    const int tid = threadIdx.x;
+    const int w = tid >> 6, l = tid & 63, li = l & 15, kb = l >> 4;
+
+    const unsigned qtiles = Lq / TQ;
+    const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int qt = item % qtiles;
+    const int bh = item / qtiles;
+    const int rb0 = (qt * TQ >> 4) + w * RB;   // first 16-row block of this wave
+    const int nblocks = Lk / KB;
+    const int meta_slot = ((kb & 1) << 1) | (kb >> 1);   // where the word of 32-key chunk kb sits in a row's 16 bytes
+
+    // LDS position p (16-byte units) = row * CPR + (c ^ tr_row_swizzle(row)) holds chunk c of key `row`
+    int v_row[LPT], v_chunk[LPT];
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) {
+        const int p = i * NT + tid;
+        v_row[i] = p / CPR;
+        v_chunk[i] = ((p % CPR) ^ tr_row_swizzle<CPR>(v_row[i])) * 8;
+    }
+    const uint32_t lds_v = lds_address(&Vs[0][w * 64]);   // this wave's 1 KB slice of copy 0, buffer 0
+    const uint64_t v_base = uniform_address(V + (size_t)bh * LkR * D);
+    auto issue_block = [&](int jb, int buf) {
+        const uint64_t src = v_base + (uint64_t)jb * (KB * D * 2);
+        const int last = UNPADDED ? LkR - jb * KB - 1 : KB - 1;   // the block's last real key
+#pragma unroll
+        for (int i = 0; i < LPT; ++i)
+            async_copy16(src, 2u * ((UNPADDED && v_row[i] > last ? last : v_row[i]) * D + v_chunk[i]), lds_v + 16u * (buf * TILE + i * NT));
+    };
+
+    // A operand of a pair: kept weights of keys 128 jb + 32 kb .. +31 (32 bytes) and their codes, both blocks
+    struct Kept {
+        u32x4 v[RB][2][2];
+        uint32_t idx[RB][2];
+    };
+    constexpr int KEPT_LOADS = 6 * RB;
+    const u32x4 *const p_row = reinterpret_cast<const u32x4 *>(P + ((size_t)bh * Lq + (size_t)rb0 * 16 + li) * (size_t)(Lk / 4)) + 2 * kb;
+    const uint32_t *const m_row = meta + (((size_t)bh * (Lq / 16) + rb0) * nblocks * 16 + li) * 4 + meta_slot;
+    auto load_kept = [&](int pair) {
+        Kept r;
+        // (a single last block is loaded twice: the number of loads is fixed)
+        const int second = 2 * pair + 1 < nblocks ? 1 : 0;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int jb = 2 * pair + (i ? second : 0);
+                const u32x4 *const pr = p_row + (size_t)rb * 16 * (Lk / 16) + 8 * jb;
+                r.v[rb][i][0] = pr[0];
+                r.v[rb][i][1] = pr[1];
+                r.idx[rb][i] = m_row[((size_t)rb * nblocks + jb) * 64];
+            }
+        return r;
+    };
+
+    const int npairs = (nblocks + 1) / 2;
+    const int rot = __builtin_amdgcn_readfirstlane((int)((D == 64 ? item / 4 : item) % (unsigned)npairs));
+    issue_block(2 * rot, 0);
+    Kept next = load_kept(rot);
+
+    f32x4 acc[RB][DS];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int ds = 0; ds < DS; ++ds) acc[rb][ds] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // transposing read: lane li of a 16-lane group addresses V[key0 + li/4][col0 + 4*(li%4)]
+    const int tr_row = li >> 2, tr_sub = (li >> 1) & 1, tr_byte = 8 * (li & 1);
+
+    // one block; buf: its LDS buffer and its place in the pair
+    auto block = [&](auto parity, const Kept &cur) {
+        constexpr int buf = decltype(parity)::value;
+        const char *vbase = reinterpret_cast<const char *>(&Vs[buf][0]);
+        auto tr = [&](int key0, int ds) {
+            const int row = key0 + tr_row;
+            return lds_read_tr16(vbase + (row * CPR + ((2 * ds + tr_sub) ^ tr_row_swizzle<CPR>(row))) * 16 + tr_byte);
+        };
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k0 = 32 * (kb >> 1) + 16 * h + 8 * (kb & 1);
+#pragma unroll
+            for (int ds = 0; ds < DS; ++ds) {
+                const s16x4 t0 = tr(k0, ds), t1 = tr(k0 + 4, ds), t2 = tr(64 + k0, ds), t3 = tr(64 + k0 + 4, ds);
+                const s16x8 lo = __builtin_shufflevector(t0, t1, 0, 1, 2, 3, 4, 5, 6, 7);
+                const s16x8 hi = __builtin_shufflevector(t2, t3, 0, 1, 2, 3, 4, 5, 6, 7);
+                const bf16x16 b = __builtin_bit_cast(
+                    bf16x16, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15));
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    const bf16x8 a = __builtin_bit_cast(bf16x8, cur.v[rb][buf][h]);
+                    if (h == 0) acc[rb][ds] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(a, b, acc[rb][ds], (int)cur.idx[rb][buf], 0, 0);
+                    else acc[rb][ds] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(a, b, acc[rb][ds], (int)cur.idx[rb][buf], 0, 1);
+                }
+            }
+        }
+    };
+    int pair = rot;
+    for (int it = 0; it < npairs; ++it) {
+        const bool single = 2 * pair + 1 >= nblocks, last = it + 1 == npairs;
+        const int after = pair + 1 == npairs ? 0 : pair + 1;
+        wait_async_copies();   // the pair's first block and its weights are in
+        __syncthreads();
+        const Kept cur = next;
+        if (!single) issue_block(2 * pair + 1, 1);
+        if (!last) next = load_kept(after);
+        block(std::integral_constant<int, 0>{}, cur);
+        if (single) {   // (everybody has to be past the buffer's use)
+            __syncthreads();
+            if (!last) issue_block(2 * after, 0);
+        } else {
+            // the second block is in; the weights of the next pair, issued after it, stay in flight
+            if (!last) wait_async_copies_keep<KEPT_LOADS>();
+            else wait_async_copies();
+            __syncthreads();
+            if (!last) issue_block(2 * after, 0);
+            block(std::integral_constant<int, 1>{}, cur);
+        }
+        pair = after;
+    }
+
+    // acc[rb][ds][r] = O[q][16 ds + li], q = 16 (rb0 + rb) + 4 kb + r
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int qrow = (rb0 + rb) * 16 + 4 * kb + r;
+            if (UNPADDED && qrow >= LqR) continue;
+            const size_t q = (size_t)bh * LqR + qrow;
+#pragma unroll
+            for (int ds = 0; ds < DS; ++ds)
+                O[q * D + 16 * ds + li] = (uint16_t)(pack_bf16x2(acc[rb][ds][r], 0.f) & 0xFFFFu);
+        }
+}
+
+hipError_t launch_sparse(const void *P, const void *meta, const void *V, int BH, int Lq, int Lk, int LqR, int LkR, int d,
+                         void *O, hipStream_t st) {
+    const bool unp = LqR != Lq || LkR != Lk;
+    // two row blocks per wave when that still leaves two workgroups per compute unit (as below)
+    const bool rb2 = !unp && Lq % 128 == 0 && (long)BH * (Lq / 128) >= 512;
+    const unsigned grid = (unsigned)((long)BH * (Lq / (rb2 ? 128 : 64)));
+#define DFSS_LAUNCH(DD, RR, UU)                                                                                      \
+    hipLaunchKernelGGL((k_spmm<DD, RR, UU>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P, (const uint32_t *)meta, \
+                       (const __bf16 *)V, Lq, Lk, LqR, LkR, (uint16_t *)O)
+    if (d == 64) {
+        if (unp) DFSS_LAUNCH(64, 1, true); else if (rb2) DFSS_LAUNCH(64, 2, false); else DFSS_LAUNCH(64, 1, false);
+    } else {
+        if (unp) DFSS_LAUNCH(128, 1, true); else if (rb2) DFSS_LAUNCH(128, 2, false); else DFSS_LAUNCH(128, 1, false);
+    }
+#undef DFSS_LAUNCH
+    return hipGetLastError();
+}
+
+template <bool SPARSE>
 hipError_t launch(const void *P, const void *meta, const void *V, int BH, int Lq, int Lk, int LqR, int LkR, int d,
                   void *O, hipStream_t st) {
     if (LqR != Lq || LkR != Lk) {   // unpadded lengths: 64-query workgroups (Lq is a multiple of 64)
         const unsigned grid = (unsigned)((long)BH * (Lq / 64));
 #define DFSS_LAUNCH(DD)                                                                                             \
-    hipLaunchKernelGGL((k_av<DD, SPARSE, 1, SOFTMAX, true>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P,     \
+    hipLaunchKernelGGL((k_av<DD, SPARSE, 1, true>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P,     \
                        (const uint32_t *)meta, (const __bf16 *)V, Lq, Lk, LqR, LkR, (uint16_t *)O)
         if (d == 64) DFSS_LAUNCH(64); else DFSS_LAUNCH(128);
 #undef DFSS_LAUNCH
@@ -287,7 +463,7 @@ hipError_t launch(const void *P, const void *meta, const void *V, int BH, int Lq
     bool rb2 = (Lq % 128 == 0) && ((long)BH * (Lq / 128) >= 512);
     const unsigned grid = (unsigned)((long)BH * (Lq / (rb2 ? 128 : 64)));
 #define DFSS_LAUNCH(DD, RR)                                                                                   \
-    hipLaunchKernelGGL((k_av<DD, SPARSE, RR, SOFTMAX>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P,              \
+    hipLaunchKernelGGL((k_av<DD, SPARSE, RR>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P,              \
                        (const uint32_t *)meta, (const __bf16 *)V, Lq, Lk, Lq, Lk, (uint16_t *)O)
     if (d == 64) {
         if (rb2) DFSS_LAUNCH(64, 2); else DFSS_LAUNCH(64, 1);
@@ -302,12 +478,12 @@ hipError_t launch(const void *P, const void *meta, const void *V, int BH, int Lq
 
 hipError_t launch_spmm(const void *vals, const void *meta, const void *V, int BH, int Lq, int Lk, int LqR, int LkR, int d,
                        void *O, hipStream_t st) {
-    return launch<true>(vals, meta, V, BH, Lq, Lk, LqR, LkR, d, O, st);
+    return launch_sparse(vals, meta, V, BH, Lq, Lk, LqR, LkR, d, O, st);
 }
 
 hipError_t launch_softmax_spmm(const void *scores, const void *meta, const void *V, int BH, int Lq, int Lk, int LqR,
                                int LkR, int d, void *O, hipStream_t st) {
-    return launch<true, true>(scores, meta, V, BH, Lq, Lk, LqR, LkR, d, O, st);
+    return launch<true>(scores, meta, V, BH, Lq, Lk, LqR, LkR, d, O, st);
 }
 
 hipError_t launch_dense_av(const void *P, const void *V, int BH, int Lq, int Lk, int LqR, int LkR, int d, void *O,

@@ -194,6 +194,35 @@ def test_stage3_spmm(BH, Lq, Lk, d, N, M):
     assert np.all(err <= 2.0 ** -8 * np.abs(ref) + 1e-4), err.max()
 
 
+@pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
+    (512, 128, 384, 64, 2, 4),    # two row blocks per wave; a pair of key blocks and a single one
+    (520, 128, 128, 128, 1, 2),   # ... a single block only
+    (5, 64, 640, 64, 1, 2),       # one row block per wave; every starting pair, the single block in the middle too
+    (7, 192, 768, 128, 2, 4),
+])
+def test_stage3_spmm_pairs_of_key_blocks(BH, Lq, Lk, d, N, M):
+    """The product on kept weights of random values at random positions, against the dense product in 64 bits."""
+    g = torch.Generator().manual_seed(7600 + Lk + d)
+    W = torch.rand(BH, Lq, Lk // 2, generator=g).to(torch.bfloat16)
+    V = torch.randn(BH, Lk, d, generator=g).to(torch.bfloat16)
+    pairs = torch.tensor([(0, 1), (0, 2), (0, 3), (1, 2), (1, 3), (2, 3)] if (N, M) == (2, 4) else
+                         [(0, 2), (0, 3), (1, 2), (1, 3)])
+    pos = pairs[torch.randint(len(pairs), (BH, Lq, Lk // 4), generator=g)]            # [BH, Lq, runs, 2]
+    code = (pos[..., 0] | pos[..., 1] << 2).view(BH, Lq, Lk // 16, 4)
+    words = (code << torch.tensor([0, 4, 8, 12])).sum(-1)
+    meta_c = words.numpy().astype(np.uint16).view(np.int16)
+    s = Shape(1, BH, Lq, Lk, d, N, M)
+    meta = dfss.dfss_meta_from_canonical(_dev(torch.from_numpy(meta_c)), s)
+    O = dfss.dfss_spmm(_dev(W), meta, _dev(V), s)
+    torch.cuda.synchronize()
+    kidx = (torch.arange(Lk // 4).view(1, 1, -1, 1) * 4 + pos).reshape(BH, Lq, Lk // 2)
+    for h in {0, 1, BH // 2, BH - 1}:
+        P = torch.zeros(Lq, Lk, dtype=torch.float64).scatter_(1, kidx[h], W[h].double())
+        ref = (P @ V[h].double()).numpy()
+        # bfloat16 output (2^-9 relative) and fp32 sums of Lk / 2 terms
+        assert np.max(np.abs(_np(O)[h] - ref)) <= 2.0 ** -8 * np.max(np.abs(ref)) + 1e-4
+
+
 def test_meta_order_round_trip():
     s = Shape(1, 3, 128, 256, 64, 2, 4)
     canon = torch.randint(-32768, 32767, (3, 128, 16), dtype=torch.int16)
