@@ -9,7 +9,8 @@ from __future__ import annotations
 
 import ctypes
 import os
-from dataclasses import dataclass
+from dataclasses import dataclass, fields
+from functools import cached_property
 
 import torch
 
@@ -51,6 +52,20 @@ class _CShape(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int32) for n in ("B", "H", "Lq", "Lk", "d", "N", "M", "dtype")]
 
 
+class _Call:
+    """Element types, sizes and the C structure of a shape, as the calls use them.  (Deriving them on every call took 4 of
+    the 11 us of host time of a small one, as much as the kernel launch itself.)"""
+    __slots__ = ("c", "ref", "torch_dtype", "O_shape", "q_numel", "kv_numel")
+
+    def __init__(self, s: Shape):
+        self.c = s.c()
+        self.ref = ctypes.byref(self.c)     # read by the C side only
+        self.torch_dtype = s.torch_dtype
+        self.O_shape = (s.BH, s.Lq, s.d)
+        self.q_numel = s.BH * s.Lq * s.d
+        self.kv_numel = s.BH * s.Lk * s.d
+
+
 @dataclass(frozen=True)
 class Shape:
     """Mirror of ``dfss_shape``: B*H heads, Lq queries, Lk keys, head size d, keep N of M."""
@@ -86,6 +101,14 @@ class Shape:
 
     def c(self) -> _CShape:
         return _CShape(self.B, self.H, self.Lq, self.Lk, self.d, self.N, self.M, self.dtype)
+
+    @cached_property
+    def _call(self) -> _Call:
+        """What every call with this shape needs, derived once (a function of the fields, which do not change)."""
+        return _Call(self)
+
+    def __getstate__(self):   # copies and pickles carry the fields only
+        return {f.name: getattr(self, f.name) for f in fields(self)}
 
     @property
     def BH(self) -> int:
@@ -181,7 +204,9 @@ def _check(fn: str, status: int):
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """Handle of the current stream of the current device (without the Stream object around it: 2.7 us a call).  Called
+    after the tensors' checks, so that the runtime is up."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t: torch.Tensor | None) -> int | None:
@@ -208,10 +233,16 @@ def _data(t: torch.Tensor | None, s: Shape, *shape) -> int | None:
 
 
 def _q(t, s: Shape):      # Q, O and their gradients: [BH, Lq, d]
+    c = s._call
+    if t is not None and t.dtype is c.torch_dtype and t.numel() == c.q_numel and t.is_cuda and t.is_contiguous():
+        return t.data_ptr()
     return _data(t, s, s.BH, s.Lq, s.d)
 
 
 def _kv(t, s: Shape):     # K, V and their gradients: [BH, Lk, d]
+    c = s._call
+    if t is not None and t.dtype is c.torch_dtype and t.numel() == c.kv_numel and t.is_cuda and t.is_contiguous():
+        return t.data_ptr()
     return _data(t, s, s.BH, s.Lk, s.d)
 
 
@@ -226,19 +257,19 @@ def _meta(t: torch.Tensor, s: Shape) -> int:
 
 
 def dfss_vals_bytes(s: Shape) -> int:
-    return int(load_library().dfss_vals_bytes(ctypes.byref(s.c())))
+    return int(load_library().dfss_vals_bytes(s._call.ref))
 
 
 def dfss_meta_bytes(s: Shape) -> int:
-    return int(load_library().dfss_meta_bytes(ctypes.byref(s.c())))
+    return int(load_library().dfss_meta_bytes(s._call.ref))
 
 
 def dfss_workspace_bytes(s: Shape) -> int:
-    return int(load_library().dfss_workspace_bytes(ctypes.byref(s.c())))
+    return int(load_library().dfss_workspace_bytes(s._call.ref))
 
 
 def dense_workspace_bytes(s: Shape) -> int:
-    return int(load_library().dense_workspace_bytes(ctypes.byref(s.c())))
+    return int(load_library().dense_workspace_bytes(s._call.ref))
 
 
 def _alloc_bytes(n: int, device) -> torch.Tensor:
@@ -251,7 +282,7 @@ def dfss_sddmm_prune(Q, K, s: Shape, scale: float, vals=None, meta=None):
         vals = torch.empty((s.BH, s.LqP, s.Lc), dtype=s.torch_dtype, device=Q.device)
     if meta is None:
         meta = torch.empty((s.BH * s.LqP * s.meta_words,), dtype=torch.int16, device=Q.device)
-    st = load_library().dfss_sddmm_prune(_q(Q, s), _kv(K, s), ctypes.byref(s.c()), scale,
+    st = load_library().dfss_sddmm_prune(_q(Q, s), _kv(K, s), s._call.ref, scale,
                                          _kept(vals, s), _meta(meta, s), _stream())
     _check("dfss_sddmm_prune", st)
     return vals, meta
@@ -259,16 +290,16 @@ def dfss_sddmm_prune(Q, K, s: Shape, scale: float, vals=None, meta=None):
 
 def dfss_sparse_softmax(vals, s: Shape):
     """Stage 2, in place on vals."""
-    _check("dfss_sparse_softmax", load_library().dfss_sparse_softmax(_kept(vals, s), ctypes.byref(s.c()), _stream()))
+    _check("dfss_sparse_softmax", load_library().dfss_sparse_softmax(_kept(vals, s), s._call.ref, _stream()))
     return vals
 
 
 def dfss_spmm(vals, meta, V, s: Shape, O=None):
     """Stage 3.  Returns O [BH, Lq, d]."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=V.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=V.device)
     st = load_library().dfss_spmm(_kept(vals, s), _meta(meta, s), _kv(V, s),
-                                  ctypes.byref(s.c()), _q(O, s), _stream())
+                                  s._call.ref, _q(O, s), _stream())
     _check("dfss_spmm", st)
     return O
 
@@ -282,11 +313,11 @@ def dfss_attention(Q, K, V, s: Shape, scale: float, O=None, ws=None):
     """Whole DFSS forward in one kernel.  ``ws`` is passed on if given (the library uses it with DFSS_F32 only,
     where it is allocated here if absent)."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     if ws is None and _needs_workspace(s):
         ws = _alloc_bytes(dfss_workspace_bytes(s), Q.device)
     st = load_library().dfss_attention(_q(Q, s), _kv(K, s), _kv(V, s),
-                                       ctypes.byref(s.c()), scale, _q(O, s), _ptr(ws),
+                                       s._call.ref, scale, _q(O, s), _ptr(ws),
                                        0 if ws is None else ws.numel() * ws.element_size(), _stream())
     _check("dfss_attention", st)
     return O
@@ -296,11 +327,11 @@ def dfss_attention_staged(Q, K, V, s: Shape, scale: float, O=None, ws=None):
     """Whole DFSS forward through ``ws`` (allocated if not given): stage 1, then the product that applies the
     softmax as it reads the kept scores (4-byte dtypes: the three stage kernels)."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     if ws is None:
         ws = _alloc_bytes(dfss_workspace_bytes(s), Q.device)
     st = load_library().dfss_attention_staged(_q(Q, s), _kv(K, s), _kv(V, s),
-                                              ctypes.byref(s.c()), scale, _q(O, s), _ptr(ws),
+                                              s._call.ref, scale, _q(O, s), _ptr(ws),
                                               ws.numel() * ws.element_size(), _stream())
     _check("dfss_attention_staged", st)
     return O
@@ -309,11 +340,11 @@ def dfss_attention_staged(Q, K, V, s: Shape, scale: float, O=None, ws=None):
 def dfss_attention_staged_bias(Q, K, V, key_bias, s: Shape, scale: float, O=None, ws=None):
     """dfss_attention_staged with an additive key bias (may be None)."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     if ws is None:
         ws = _alloc_bytes(dfss_workspace_bytes(s), Q.device)
     st = load_library().dfss_attention_staged_bias(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                                   ctypes.byref(s.c()), scale, _q(O, s), _ptr(ws),
+                                                   s._call.ref, scale, _q(O, s), _ptr(ws),
                                                    ws.numel() * ws.element_size(), _stream())
     _check("dfss_attention_staged_bias", st)
     return O
@@ -326,7 +357,7 @@ def dfss_static_scratch_bytes() -> int:
 def dfss_attention_staged_static(Q, K, V, key_bias, s: Shape, scale: float, O):
     """The staged forward pass with the library's own fixed scratch array; allocates nothing (O is the caller's)."""
     st = load_library().dfss_attention_staged_static(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                                     ctypes.byref(s.c()), scale, _q(O, s), _stream())
+                                                     s._call.ref, scale, _q(O, s), _stream())
     _check("dfss_attention_staged_static", st)
     return O
 
@@ -334,9 +365,9 @@ def dfss_attention_staged_static(Q, K, V, key_bias, s: Shape, scale: float, O):
 def internal_attention_variant(Q, K, V, key_bias, s: Shape, scale: float, variant: int, dense: bool = False, O=None):
     """Test hook: the one-kernel forward pass (DFSS, or full attention if ``dense``) with a named tiling."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     st = load_library().dfss_internal_attention_variant(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                                        ctypes.byref(s.c()), scale, _q(O, s), int(variant),
+                                                        s._call.ref, scale, _q(O, s), int(variant),
                                                         int(bool(dense)), _stream())
     _check("dfss_internal_attention_variant", st)
     return O
@@ -345,11 +376,11 @@ def internal_attention_variant(Q, K, V, key_bias, s: Shape, scale: float, varian
 def dense_attention(Q, K, V, s: Shape, scale: float, O=None, ws=None):
     """Full attention baseline on the same GPU."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     if ws is None:
         ws = _alloc_bytes(dense_workspace_bytes(s), Q.device)
     st = load_library().dense_attention(_q(Q, s), _kv(K, s), _kv(V, s),
-                                        ctypes.byref(s.c()), scale, _q(O, s), _ptr(ws),
+                                        s._call.ref, scale, _q(O, s), _ptr(ws),
                                         ws.numel() * ws.element_size(), _stream())
     _check("dense_attention", st)
     return O
@@ -358,9 +389,9 @@ def dense_attention(Q, K, V, s: Shape, scale: float, O=None, ws=None):
 def dense_attention_fused(Q, K, V, s: Shape, scale: float, O=None):
     """Full attention in one kernel (the stronger baseline)."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     st = load_library().dense_attention_fused(_q(Q, s), _kv(K, s), _kv(V, s),
-                                              ctypes.byref(s.c()), scale, _q(O, s),
+                                              s._call.ref, scale, _q(O, s),
                                               _stream())
     _check("dense_attention_fused", st)
     return O
@@ -381,7 +412,7 @@ def dfss_sddmm_prune_bias(Q, K, key_bias, s: Shape, scale: float, vals=None, met
     if meta is None:
         meta = torch.empty((s.BH * s.LqP * s.meta_words,), dtype=torch.int16, device=Q.device)
     st = load_library().dfss_sddmm_prune_bias(_q(Q, s), _kv(K, s), _bias_ptr(key_bias, s),
-                                              ctypes.byref(s.c()), scale, _kept(vals, s), _meta(meta, s), _stream())
+                                              s._call.ref, scale, _kept(vals, s), _meta(meta, s), _stream())
     _check("dfss_sddmm_prune_bias", st)
     return vals, meta
 
@@ -389,11 +420,11 @@ def dfss_sddmm_prune_bias(Q, K, key_bias, s: Shape, scale: float, vals=None, met
 def dfss_attention_bias(Q, K, V, key_bias, s: Shape, scale: float, O=None, ws=None):
     """Whole DFSS forward (one kernel) with an additive key bias."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     if ws is None and _needs_workspace(s):
         ws = _alloc_bytes(dfss_workspace_bytes(s), Q.device)
     st = load_library().dfss_attention_bias(_q(Q, s), _kv(K, s), _kv(V, s),
-                                            _bias_ptr(key_bias, s), ctypes.byref(s.c()), scale, _q(O, s), _ptr(ws),
+                                            _bias_ptr(key_bias, s), s._call.ref, scale, _q(O, s), _ptr(ws),
                                             0 if ws is None else ws.numel() * ws.element_size(), _stream())
     _check("dfss_attention_bias", st)
     return O
@@ -402,11 +433,11 @@ def dfss_attention_bias(Q, K, V, key_bias, s: Shape, scale: float, O=None, ws=No
 def dense_attention_bias(Q, K, V, key_bias, s: Shape, scale: float, O=None, ws=None):
     """Full attention (three stages) with an additive key bias."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     if ws is None:
         ws = _alloc_bytes(dense_workspace_bytes(s), Q.device)
     st = load_library().dense_attention_bias(_q(Q, s), _kv(K, s), _kv(V, s),
-                                             _bias_ptr(key_bias, s), ctypes.byref(s.c()), scale, _q(O, s), _ptr(ws),
+                                             _bias_ptr(key_bias, s), s._call.ref, scale, _q(O, s), _ptr(ws),
                                             ws.numel() * ws.element_size(), _stream())
     _check("dense_attention_bias", st)
     return O
@@ -415,9 +446,9 @@ def dense_attention_bias(Q, K, V, key_bias, s: Shape, scale: float, O=None, ws=N
 def dense_attention_fused_bias(Q, K, V, key_bias, s: Shape, scale: float, O=None):
     """Full attention in one kernel with an additive key bias."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     st = load_library().dense_attention_fused_bias(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                                   ctypes.byref(s.c()), scale, _q(O, s), _stream())
+                                                   s._call.ref, scale, _q(O, s), _stream())
     _check("dense_attention_fused_bias", st)
     return O
 
@@ -429,7 +460,7 @@ def dfss_sddmm_prune_causal(Q, K, key_bias, s: Shape, scale: float, vals=None, m
     if meta is None:
         meta = torch.empty((s.BH * s.LqP * s.meta_words,), dtype=torch.int16, device=Q.device)
     st = load_library().dfss_sddmm_prune_causal(_q(Q, s), _kv(K, s), _bias_ptr(key_bias, s),
-                                                ctypes.byref(s.c()), scale, _kept(vals, s), _meta(meta, s), _stream())
+                                                s._call.ref, scale, _kept(vals, s), _meta(meta, s), _stream())
     _check("dfss_sddmm_prune_causal", st)
     return vals, meta
 
@@ -437,9 +468,9 @@ def dfss_sddmm_prune_causal(Q, K, key_bias, s: Shape, scale: float, vals=None, m
 def dfss_attention_causal(Q, K, V, key_bias, s: Shape, scale: float, O=None):
     """Whole DFSS forward in one kernel under the causal mask; key_bias may be None."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     st = load_library().dfss_attention_causal(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                              ctypes.byref(s.c()), scale, _q(O, s), _stream())
+                                              s._call.ref, scale, _q(O, s), _stream())
     _check("dfss_attention_causal", st)
     return O
 
@@ -447,11 +478,11 @@ def dfss_attention_causal(Q, K, V, key_bias, s: Shape, scale: float, O=None):
 def dfss_attention_staged_causal(Q, K, V, key_bias, s: Shape, scale: float, O=None, ws=None):
     """dfss_attention_staged under the causal mask; key_bias may be None."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     if ws is None:
         ws = _alloc_bytes(dfss_workspace_bytes(s), Q.device)
     st = load_library().dfss_attention_staged_causal(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                                     ctypes.byref(s.c()), scale, _q(O, s), _ptr(ws),
+                                                     s._call.ref, scale, _q(O, s), _ptr(ws),
                                                      ws.numel() * ws.element_size(), _stream())
     _check("dfss_attention_staged_causal", st)
     return O
@@ -460,11 +491,11 @@ def dfss_attention_staged_causal(Q, K, V, key_bias, s: Shape, scale: float, O=No
 def dense_attention_causal(Q, K, V, key_bias, s: Shape, scale: float, O=None, ws=None):
     """Full attention (three stages) under the causal mask; key_bias may be None."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     if ws is None:
         ws = _alloc_bytes(dense_workspace_bytes(s), Q.device)
     st = load_library().dense_attention_causal(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                               ctypes.byref(s.c()), scale, _q(O, s), _ptr(ws),
+                                               s._call.ref, scale, _q(O, s), _ptr(ws),
                                                ws.numel() * ws.element_size(), _stream())
     _check("dense_attention_causal", st)
     return O
@@ -473,9 +504,9 @@ def dense_attention_causal(Q, K, V, key_bias, s: Shape, scale: float, O=None, ws
 def dense_attention_fused_causal(Q, K, V, key_bias, s: Shape, scale: float, O=None):
     """Full attention in one kernel under the causal mask; key_bias may be None."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     st = load_library().dense_attention_fused_causal(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                                     ctypes.byref(s.c()), scale, _q(O, s), _stream())
+                                                     s._call.ref, scale, _q(O, s), _stream())
     _check("dense_attention_fused_causal", st)
     return O
 
@@ -483,9 +514,9 @@ def dense_attention_fused_causal(Q, K, V, key_bias, s: Shape, scale: float, O=No
 def dfss_attention_ragged(Q, K, V, key_bias, s: Shape, scale: float, O=None):
     """DFSS forward in one kernel on unpadded arrays: any Lq, Lk a multiple of 4; key_bias may be None."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     st = load_library().dfss_attention_ragged(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                              ctypes.byref(s.c()), scale, _q(O, s), _stream())
+                                              s._call.ref, scale, _q(O, s), _stream())
     _check("dfss_attention_ragged", st)
     return O
 
@@ -493,9 +524,9 @@ def dfss_attention_ragged(Q, K, V, key_bias, s: Shape, scale: float, O=None):
 def dense_attention_fused_ragged(Q, K, V, key_bias, s: Shape, scale: float, O=None):
     """Full attention in one kernel on unpadded arrays (the baseline of dfss_attention_ragged)."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     st = load_library().dense_attention_fused_ragged(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                                     ctypes.byref(s.c()), scale, _q(O, s), _stream())
+                                                     s._call.ref, scale, _q(O, s), _stream())
     _check("dense_attention_fused_ragged", st)
     return O
 
@@ -509,9 +540,9 @@ def _block_mask_ptr(block_mask, s: Shape):
 def dfss_attention_blocked(Q, K, V, key_bias, block_mask, s: Shape, scale: float, O=None):
     """DFSS forward restricted to the 64 x 64 score blocks with a non-zero entry in block_mask."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     st = load_library().dfss_attention_blocked(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                               _block_mask_ptr(block_mask, s), ctypes.byref(s.c()), scale, _q(O, s),
+                                               _block_mask_ptr(block_mask, s), s._call.ref, scale, _q(O, s),
                                                _stream())
     _check("dfss_attention_blocked", st)
     return O
@@ -520,9 +551,9 @@ def dfss_attention_blocked(Q, K, V, key_bias, block_mask, s: Shape, scale: float
 def dense_attention_fused_blocked(Q, K, V, key_bias, block_mask, s: Shape, scale: float, O=None):
     """Block-sparse full attention (same block pattern, no N:M pruning)."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     st = load_library().dense_attention_fused_blocked(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                                      _block_mask_ptr(block_mask, s), ctypes.byref(s.c()), scale,
+                                                      _block_mask_ptr(block_mask, s), s._call.ref, scale,
                                                       _q(O, s), _stream())
     _check("dense_attention_fused_blocked", st)
     return O
@@ -540,7 +571,7 @@ def dfss_sddmm_prune_mask(Q, K, mask, s: Shape, scale: float, vals=None, meta=No
         vals = torch.empty((s.BH, s.LqP, s.Lc), dtype=s.torch_dtype, device=Q.device)
     if meta is None:
         meta = torch.empty((s.BH * s.LqP * s.meta_words,), dtype=torch.int16, device=Q.device)
-    st = load_library().dfss_sddmm_prune_mask(_q(Q, s), _kv(K, s), _mask_ptr(mask, s), ctypes.byref(s.c()), scale,
+    st = load_library().dfss_sddmm_prune_mask(_q(Q, s), _kv(K, s), _mask_ptr(mask, s), s._call.ref, scale,
                                               _kept(vals, s), _meta(meta, s), _stream())
     _check("dfss_sddmm_prune_mask", st)
     return vals, meta
@@ -549,11 +580,11 @@ def dfss_sddmm_prune_mask(Q, K, mask, s: Shape, scale: float, vals=None, meta=No
 def dfss_attention_staged_mask(Q, K, V, mask, s: Shape, scale: float, O=None, ws=None):
     """dfss_attention_staged with an additive mask [Lq, Lk] shared by all heads."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     if ws is None:
         ws = _alloc_bytes(dfss_workspace_bytes(s), Q.device)
     st = load_library().dfss_attention_staged_mask(_q(Q, s), _kv(K, s), _kv(V, s), _mask_ptr(mask, s),
-                                                   ctypes.byref(s.c()), scale, _q(O, s), _ptr(ws),
+                                                   s._call.ref, scale, _q(O, s), _ptr(ws),
                                                    ws.numel() * ws.element_size(), _stream())
     _check("dfss_attention_staged_mask", st)
     return O
@@ -562,10 +593,10 @@ def dfss_attention_staged_mask(Q, K, V, mask, s: Shape, scale: float, O=None, ws
 def dense_attention_mask(Q, K, V, mask, s: Shape, scale: float, O=None, ws=None):
     """Full attention (three kernels) with the same mask."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     if ws is None:
         ws = _alloc_bytes(dense_workspace_bytes(s), Q.device)
-    st = load_library().dense_attention_mask(_q(Q, s), _kv(K, s), _kv(V, s), _mask_ptr(mask, s), ctypes.byref(s.c()),
+    st = load_library().dense_attention_mask(_q(Q, s), _kv(K, s), _kv(V, s), _mask_ptr(mask, s), s._call.ref,
                                              scale, _q(O, s), _ptr(ws), ws.numel() * ws.element_size(), _stream())
     _check("dense_attention_mask", st)
     return O
@@ -580,8 +611,8 @@ def _len_ptr(key_len: torch.Tensor, s: Shape) -> int:
 def dfss_attention_varlen(Q, K, V, key_len, s: Shape, scale: float, O=None):
     """DFSS forward in one kernel on a padded batch: keys key_len[b] .. Lk - 1 of batch element b are padding."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
-    st = load_library().dfss_attention_varlen(_q(Q, s), _kv(K, s), _kv(V, s), _len_ptr(key_len, s), ctypes.byref(s.c()),
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
+    st = load_library().dfss_attention_varlen(_q(Q, s), _kv(K, s), _kv(V, s), _len_ptr(key_len, s), s._call.ref,
                                               scale, _q(O, s), _stream())
     _check("dfss_attention_varlen", st)
     return O
@@ -590,8 +621,8 @@ def dfss_attention_varlen(Q, K, V, key_len, s: Shape, scale: float, O=None):
 def dfss_attention_mask(Q, K, V, mask, s: Shape, scale: float, O=None):
     """DFSS forward in one kernel with an additive mask fp32 [Lq, Lk] (any Lq, Lk a multiple of 4; arrays unpadded)."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
-    st = load_library().dfss_attention_mask(_q(Q, s), _kv(K, s), _kv(V, s), _mask_ptr(mask, s), ctypes.byref(s.c()),
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
+    st = load_library().dfss_attention_mask(_q(Q, s), _kv(K, s), _kv(V, s), _mask_ptr(mask, s), s._call.ref,
                                             scale, _q(O, s), _stream())
     _check("dfss_attention_mask", st)
     return O
@@ -600,25 +631,25 @@ def dfss_attention_mask(Q, K, V, mask, s: Shape, scale: float, O=None):
 def dense_attention_fused_mask(Q, K, V, mask, s: Shape, scale: float, O=None):
     """Full attention in one kernel with the same mask (the baseline of dfss_attention_mask)."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     st = load_library().dense_attention_fused_mask(_q(Q, s), _kv(K, s), _kv(V, s), _mask_ptr(mask, s),
-                                                   ctypes.byref(s.c()), scale, _q(O, s), _stream())
+                                                   s._call.ref, scale, _q(O, s), _stream())
     _check("dense_attention_fused_mask", st)
     return O
 
 
 def dfss_blocked_split_workspace_bytes(s: Shape) -> int:
-    return int(load_library().dfss_blocked_split_workspace_bytes(ctypes.byref(s.c())))
+    return int(load_library().dfss_blocked_split_workspace_bytes(s._call.ref))
 
 
 def dfss_attention_blocked_split(Q, K, V, key_bias, block_mask, s: Shape, scale: float, O=None, ws=None):
     """dfss_attention_blocked with a workspace: long row blocks are shared between several workgroups."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     if ws is None:
         ws = _alloc_bytes(dfss_blocked_split_workspace_bytes(s), Q.device)
     st = load_library().dfss_attention_blocked_split(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                                     _block_mask_ptr(block_mask, s), ctypes.byref(s.c()), scale,
+                                                     _block_mask_ptr(block_mask, s), s._call.ref, scale,
                                                      _q(O, s), ws.data_ptr(), ws.numel() * ws.element_size(), _stream())
     _check("dfss_attention_blocked_split", st)
     return O
@@ -627,11 +658,11 @@ def dfss_attention_blocked_split(Q, K, V, key_bias, block_mask, s: Shape, scale:
 def dense_attention_fused_blocked_split(Q, K, V, key_bias, block_mask, s: Shape, scale: float, O=None, ws=None):
     """Block-sparse full attention with the same workspace (the baseline of dfss_attention_blocked_split)."""
     if O is None:
-        O = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     if ws is None:
         ws = _alloc_bytes(dfss_blocked_split_workspace_bytes(s), Q.device)
     st = load_library().dense_attention_fused_blocked_split(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                                            _block_mask_ptr(block_mask, s), ctypes.byref(s.c()), scale,
+                                                            _block_mask_ptr(block_mask, s), s._call.ref, scale,
                                                             _q(O, s), ws.data_ptr(), ws.numel() * ws.element_size(),
                                                             _stream())
     _check("dense_attention_fused_blocked_split", st)
@@ -643,19 +674,19 @@ def dfss_spmm_t(vals, meta, X, s: Shape, out=None):
     if out is None:
         out = torch.empty((s.BH, s.Lk, s.d), dtype=s.torch_dtype, device=X.device)
     st = load_library().dfss_spmm_t(_kept(vals, s), _meta(meta, s), _q(X, s),
-                                    ctypes.byref(s.c()), _kv(out, s), _stream())
+                                    s._call.ref, _kv(out, s), _stream())
     _check("dfss_spmm_t", st)
     return out
 
 
 def dfss_backward_workspace_bytes(s: Shape) -> int:
-    return int(load_library().dfss_backward_workspace_bytes(ctypes.byref(s.c())))
+    return int(load_library().dfss_backward_workspace_bytes(s._call.ref))
 
 
 def dfss_attention_backward(dO, Q, K, V, O, P, meta, s: Shape, scale: float, dQ=None, dK=None, dV=None, ws=None):
     """Gradients through the fixed selection.  P, meta: weights and metadata kept from the forward stages."""
     if dQ is None:
-        dQ = torch.empty((s.BH, s.Lq, s.d), dtype=s.torch_dtype, device=Q.device)
+        dQ = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
     if dK is None:
         dK = torch.empty((s.BH, s.Lk, s.d), dtype=s.torch_dtype, device=Q.device)
     if dV is None:
@@ -663,7 +694,7 @@ def dfss_attention_backward(dO, Q, K, V, O, P, meta, s: Shape, scale: float, dQ=
     if ws is None:
         ws = _alloc_bytes(dfss_backward_workspace_bytes(s), Q.device)
     st = load_library().dfss_attention_backward(_q(dO, s), _q(Q, s), _kv(K, s), _kv(V, s), _q(O, s),
-                                                _kept(P, s), _meta(meta, s), ctypes.byref(s.c()), scale,
+                                                _kept(P, s), _meta(meta, s), s._call.ref, scale,
                                                 _q(dQ, s), _kv(dK, s),
                                                 _kv(dV, s), _ptr(ws),
                                                 ws.numel() * ws.element_size(), _stream())
@@ -675,7 +706,7 @@ def dfss_meta_to_canonical(meta, s: Shape, canon=None):
     """Library word order -> canonical uint16 [BH, Lq, Lk/16] (held as int16 bits)."""
     if canon is None:
         canon = torch.empty((s.BH, s.LqP, s.meta_words), dtype=torch.int16, device=meta.device)
-    st = load_library().dfss_meta_to_canonical(_meta(meta, s), ctypes.byref(s.c()), _meta(canon, s), _stream())
+    st = load_library().dfss_meta_to_canonical(_meta(meta, s), s._call.ref, _meta(canon, s), _stream())
     _check("dfss_meta_to_canonical", st)
     return canon
 
@@ -683,6 +714,6 @@ def dfss_meta_to_canonical(meta, s: Shape, canon=None):
 def dfss_meta_from_canonical(canon, s: Shape, meta=None):
     if meta is None:
         meta = torch.empty((s.BH * s.LqP * s.meta_words,), dtype=torch.int16, device=canon.device)
-    st = load_library().dfss_meta_from_canonical(_meta(canon, s), ctypes.byref(s.c()), _meta(meta, s), _stream())
+    st = load_library().dfss_meta_from_canonical(_meta(canon, s), s._call.ref, _meta(meta, s), _stream())
     _check("dfss_meta_from_canonical", st)
     return meta

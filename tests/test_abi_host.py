@@ -229,3 +229,16 @@ def test_binding_refuses_host_tensors():
         dfss.dfss_sddmm_prune(q.float(), q.float(), s, 0.125, vals=q, meta=q)
     with pytest.raises(ValueError):   # key bias of the wrong shape or type
         dfss.dfss_attention_bias(q, q, q, torch.zeros(2, 128), s, 0.125, O=q, ws=q)
+
+
+def test_shape_carries_its_fields_only():
+    """What a shape derives for its calls stays out of copies, pickles and comparisons."""
+    import copy
+    import dataclasses
+    import pickle
+
+    s = dfss.Shape(2, 3, 64, 128, 64, 1, 2)
+    assert s._call.q_numel == 6 * 64 * 64 and s._call.kv_numel == 6 * 128 * 64 and s._call.c.N == 1
+    for t in (copy.copy(s), copy.deepcopy(s), pickle.loads(pickle.dumps(s))):
+        assert t == s and hash(t) == hash(s) and "_call" not in vars(t)
+    assert dataclasses.replace(s, B=4)._call.q_numel == 12 * 64 * 64
