@@ -320,6 +320,14 @@ dfss_status dense_attention_fused_blocked_split(const void *Q, const void *K, co
  * above bit for bit. */
 dfss_status dfss_attention_ragged(const void *Q, const void *K, const void *V, const void *key_bias,
                                   const dfss_shape *s, float scale, void *O, void *stream);
+/* dfss_attention_ragged with a workspace: with at most 16 queries, many keys and no key bias several workgroups share the keys
+ * of a query tile (partial results in ws, fp32, merged by a second kernel in a fixed order); every other call is that of
+ * dfss_attention_ragged, and ws is not touched.  ws: device, 256-byte aligned, at least
+ * dfss_ragged_split_workspace_bytes(s) bytes (0: nothing to share, or unsupported; ws may then be NULL). */
+size_t dfss_ragged_split_workspace_bytes(const dfss_shape *s);
+dfss_status dfss_attention_ragged_split(const void *Q, const void *K, const void *V, const void *key_bias,
+                                        const dfss_shape *s, float scale, void *O, void *ws, size_t ws_bytes,
+                                        void *stream);
 dfss_status dense_attention_fused_ragged(const void *Q, const void *K, const void *V, const void *key_bias,
                                          const dfss_shape *s, float scale, void *O, void *stream);
 

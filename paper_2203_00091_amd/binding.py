@@ -33,6 +33,7 @@ EXPORTS = (
     "dfss_sddmm_prune_mask", "dfss_attention_staged_mask", "dense_attention_mask",
     "dfss_attention_mask", "dense_attention_fused_mask",
     "dfss_attention_varlen",
+    "dfss_ragged_split_workspace_bytes", "dfss_attention_ragged_split",
 )
 # exported for the library's own tests only (csrc/dfss_internal.h)
 INTERNAL_EXPORTS = ("dfss_internal_attention_variant",)
@@ -55,7 +56,7 @@ class _CShape(ctypes.Structure):
 class _Call:
     """Element types, sizes and the C structure of a shape, as the calls use them.  (Deriving them on every call took 4 of
     the 11 us of host time of a small one, as much as the kernel launch itself.)"""
-    __slots__ = ("c", "ref", "torch_dtype", "O_shape", "q_numel", "kv_numel")
+    __slots__ = ("c", "ref", "torch_dtype", "O_shape", "q_numel", "kv_numel", "ragged_ws")
 
     def __init__(self, s: Shape):
         self.c = s.c()
@@ -64,6 +65,7 @@ class _Call:
         self.O_shape = (s.BH, s.Lq, s.d)
         self.q_numel = s.BH * s.Lq * s.d
         self.kv_numel = s.BH * s.Lk * s.d
+        self.ragged_ws = None               # workspace bytes of dfss_attention_ragged, asked for once
 
 
 @dataclass(frozen=True)
@@ -138,7 +140,8 @@ def load_library():
         sp = ctypes.POINTER(_CShape)
         vp, sz, f32 = ctypes.c_void_p, ctypes.c_size_t, ctypes.c_float
         for name in ("dfss_vals_bytes", "dfss_meta_bytes", "dfss_workspace_bytes", "dense_workspace_bytes",
-                     "dfss_backward_workspace_bytes", "dfss_blocked_split_workspace_bytes"):
+                     "dfss_backward_workspace_bytes", "dfss_blocked_split_workspace_bytes",
+                     "dfss_ragged_split_workspace_bytes"):
             getattr(L, name).argtypes = [sp]
             getattr(L, name).restype = sz
         L.dfss_sddmm_prune.argtypes = [vp, vp, sp, f32, vp, vp, vp]
@@ -162,6 +165,7 @@ def load_library():
         L.dfss_attention_varlen.argtypes = [vp, vp, vp, vp, sp, f32, vp, vp]
         L.dense_attention_fused_mask.argtypes = [vp, vp, vp, vp, sp, f32, vp, vp]
         L.dfss_attention_ragged.argtypes = [vp, vp, vp, vp, sp, f32, vp, vp]
+        L.dfss_attention_ragged_split.argtypes = [vp, vp, vp, vp, sp, f32, vp, vp, sz, vp]
         L.dfss_attention_staged.argtypes = [vp, vp, vp, sp, f32, vp, vp, sz, vp]
         L.dfss_attention_staged_bias.argtypes = [vp, vp, vp, vp, sp, f32, vp, vp, sz, vp]
         L.dfss_attention_staged_static.argtypes = [vp, vp, vp, vp, sp, f32, vp, vp]
@@ -190,7 +194,7 @@ def load_library():
                      "dfss_attention_blocked_split", "dense_attention_fused_blocked_split",
                      "dfss_sddmm_prune_mask", "dfss_attention_staged_mask", "dense_attention_mask",
                      "dfss_attention_mask", "dense_attention_fused_mask",
-                     "dfss_attention_varlen"):
+                     "dfss_attention_varlen", "dfss_attention_ragged_split"):
             getattr(L, name).restype = ctypes.c_int
         L.dfss_status_string.argtypes = [ctypes.c_int]
         L.dfss_status_string.restype = ctypes.c_char_p
@@ -515,10 +519,22 @@ def dfss_attention_ragged(Q, K, V, key_bias, s: Shape, scale: float, O=None):
     """DFSS forward in one kernel on unpadded arrays: any Lq, Lk a multiple of 4; key_bias may be None."""
     if O is None:
         O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
-    st = load_library().dfss_attention_ragged(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                              s._call.ref, scale, _q(O, s), _stream())
+    n = s._call.ragged_ws
+    if n is None:
+        n = s._call.ragged_ws = dfss_ragged_split_workspace_bytes(s)
+    if n and key_bias is None:   # few queries, many keys: several workgroups share the keys of a query tile through a workspace
+        ws = _alloc_bytes(n, Q.device)
+        st = load_library().dfss_attention_ragged_split(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
+                                                        s._call.ref, scale, _q(O, s), _ptr(ws), n, _stream())
+    else:
+        st = load_library().dfss_attention_ragged(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
+                                                  s._call.ref, scale, _q(O, s), _stream())
     _check("dfss_attention_ragged", st)
     return O
+
+
+def dfss_ragged_split_workspace_bytes(s: Shape) -> int:
+    return int(load_library().dfss_ragged_split_workspace_bytes(s._call.ref))
 
 
 def dense_attention_fused_ragged(Q, K, V, key_bias, s: Shape, scale: float, O=None):

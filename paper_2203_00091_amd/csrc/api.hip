@@ -574,6 +574,27 @@ dfss_status dfss_attention_ragged(const void *Q, const void *K, const void *V, c
     return attention_ragged(Q, K, V, key_bias, s, false, scale, O, stream);
 }
 
+size_t dfss_ragged_split_workspace_bytes(const dfss_shape *s) {
+    Dims D;
+    if (check_shape_ragged(s, true, &D) != DFSS_OK || D.f32 || D.Lq > 16) return 0;
+    return dfss::few_queries_workspace_bytes(D.BH, D.Lq, D.Lk, D.d);
+}
+
+dfss_status dfss_attention_ragged_split(const void *Q, const void *K, const void *V, const void *key_bias,
+                                        const dfss_shape *s, float scale, void *O, void *ws, size_t ws_bytes, void *stream) {
+    const size_t need = dfss_ragged_split_workspace_bytes(s);
+    if (need == 0 || key_bias) return attention_ragged(Q, K, V, key_bias, s, false, scale, O, stream);
+    Dims D;
+    if (!Q || !K || !V || !O || !ws) return DFSS_ERR_NULL;
+    if (dfss_status st = check_shape_ragged(s, true, &D)) return st;
+    if (bad_scale(scale)) return DFSS_ERR_UNSUPPORTED;
+    if (misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(O)) return DFSS_ERR_SHAPE;
+    if ((reinterpret_cast<uintptr_t>(ws) & (kAlign - 1)) != 0) return DFSS_ERR_SHAPE;
+    if (ws_bytes < need) return DFSS_ERR_WORKSPACE;
+    return hip_status(dfss::launch_fused_attention_few_split(Q, K, V, D.BH, D.Lq, D.Lk, D.d, D.mode, scale, O, ws,
+                                                             (hipStream_t)stream));
+}
+
 dfss_status dense_attention_fused_ragged(const void *Q, const void *K, const void *V, const void *key_bias,
                                          const dfss_shape *s, float scale, void *O, void *stream) {
     return attention_ragged(Q, K, V, key_bias, s, true, scale, O, stream);

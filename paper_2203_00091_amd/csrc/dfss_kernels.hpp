@@ -46,6 +46,11 @@ hipError_t launch_fused_attention_mask(const void *Q, const void *K, const void 
 hipError_t launch_fused_attention(const void *Q, const void *K, const void *V, const float *key_bias, int H,
                                   const uint8_t *block_mask, int causal, int BH, int Lq, int Lk, int d, int mode, float scale,
                                   void *O, int variant, hipStream_t st);
+// Calls whose few query tiles take the kernel of few_queries.hip, shared between several workgroups each: bytes of the
+// workspace (0: not such a call, or nothing to gain), and the call with it (no key bias).
+size_t few_queries_workspace_bytes(int BH, int Lq, int Lk, int d);
+hipError_t launch_fused_attention_few_split(const void *Q, const void *K, const void *V, int BH, int Lq, int Lk, int d, int mode,
+                                            float scale, void *O, void *part, hipStream_t st);
 // The same with a block pattern (block_mask not null) and a workspace of fused_attention_split_workspace_bytes: row
 // blocks that visit many blocks are shared between several workgroups and merged by a second kernel.
 size_t fused_attention_split_workspace_bytes(int BH, int Lq, int d);

@@ -34,10 +34,13 @@ enum { MODE_2TO4 = 0, MODE_1TO2 = 1 };
 // Any Lq; Lk a multiple of 4 (the absent keys of a partial last block are copies of the last key whose scores become -inf;
 // absent queries are computed on a copy of the last one and not stored).
 // BIAS: key_bias fp32 [BH / H][Lk], as in k_fused; blocks whose keys are all masked are skipped.
-template <int D, int MODE, int NW, bool PRESCALE, bool BIAS>
+// SPLIT (no key bias): `splits` workgroups share the keys of a query tile; each writes its partial result (reference, row sums,
+// unnormalised O, fp32) to `part` [item][split][16 x (D + 2)] and k_few_merge forms O.
+template <int D, int MODE, int NW, bool PRESCALE, bool BIAS, bool SPLIT>
 __global__ __launch_bounds__(64 * NW) void k_few(const __bf16 *__restrict__ Q, const __bf16 *__restrict__ K,
                                                  const __bf16 *__restrict__ V, const float *__restrict__ key_bias, int H,
-                                                 int Lq, int Lk, float scale, uint16_t *__restrict__ O) {
+                                                 int Lq, int Lk, float scale, uint16_t *__restrict__ O,
+                                                 int splits, float *__restrict__ part) {
     constexpr int CPR = D / 8;          // 16-byte chunks per row
     constexpr int TILE = KB * CPR;      // chunks per V block
     constexpr int LPT = TILE / 64;      // asynchronous copies per lane and V block
@@ -49,8 +52,12 @@ __global__ __launch_bounds__(64 * NW) void k_few(const __bf16 *__restrict__ Q, c
 
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), l = threadIdx.x & 63, li = l & 15, kb = l >> 4;
     const unsigned qtiles = (Lq + 15) / 16;
-    const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);
+    const unsigned share = xcd_contiguous(blockIdx.x, gridDim.x);
+    const unsigned item = SPLIT ? share / (unsigned)splits : share;
+    const int sp = SPLIT ? share % (unsigned)splits : 0;
     const int q0 = (item % qtiles) * 16, bh = item / qtiles;
+    static_assert(!SPLIT || !BIAS, "shared keys: no key bias");
+    const int first = __builtin_amdgcn_readfirstlane(sp * NW + w), stride = SPLIT ? NW * splits : NW;   // this wave's blocks
     const int nblocks = (Lk + KB - 1) / KB;
 
     // V block: row = key, chunk c at row * CPR + (c ^ tr_row_swizzle(row))
@@ -95,17 +102,17 @@ __global__ __launch_bounds__(64 * NW) void k_few(const __bf16 *__restrict__ Q, c
     BlockList<BIAS, true> blocks;
     if constexpr (BIAS) {
         blocks.init(true, brow, false, nullptr, 0, 0, 16, 0, Lq, Lk, nblocks, l);
-        for (int i = 0; i < w; ++i) blocks.take();
+        for (int i = 0; i < first; ++i) blocks.take();
     }
-    int next_plain = w;
+    int next_plain = first;
     auto take = [&]() -> int {
         if constexpr (BIAS) {
             const int j = blocks.take();
-            for (int i = 1; i < NW; ++i) blocks.take();
+            for (int i = 1; i < stride; ++i) blocks.take();
             return __builtin_amdgcn_readfirstlane(j);
         } else {
             const int j = next_plain;
-            next_plain += NW;
+            next_plain += stride;
             return j;
         }
     };
@@ -262,9 +269,42 @@ __global__ __launch_bounds__(64 * NW) void k_few(const __bf16 *__restrict__ Q, c
                 sum += f * slots[g * (NF * 64) + (1 + r) * 64 + l];
                 o += f * slots[g * (NF * 64) + (5 + 4 * ds + r) * 64 + l];
             }
+            if constexpr (SPLIT) {
+                float *const P = part + ((size_t)item * splits + sp) * (16 * (D + 2));
+                if (ds == 0 && li == 0) P[row] = m, P[16 + row] = sum;
+                P[32 + row * D + 16 * ds + li] = o;
+                continue;
+            }
             O[((size_t)bh * Lq + q0 + row) * D + 16 * ds + li] = (uint16_t)(pack_bf16x2(o * __builtin_amdgcn_rcpf(sum), 0.f) & 0xFFFFu);
         }
     }
+}
+
+// O of the query tiles whose keys `splits` workgroups shared, in a fixed order.  One workgroup per tile; a thread forms 8
+// columns of a row.
+template <int D>
+__global__ __launch_bounds__(2 * D) void k_few_merge(const float *__restrict__ part, int splits, int Lq, uint16_t *__restrict__ O) {
+    const unsigned qtiles = (Lq + 15) / 16;
+    const int q0 = (blockIdx.x % qtiles) * 16, bh = blockIdx.x / qtiles;
+    const int row = threadIdx.x / (D / 8), c = (threadIdx.x % (D / 8)) * 8;
+    if (q0 + row >= Lq) return;
+    const float *const P = part + (size_t)blockIdx.x * splits * (16 * (D + 2));
+    float m = -1.0e30f;
+    for (int sp = 0; sp < splits; ++sp) m = fmaxf(m, P[sp * (16 * (D + 2)) + row]);
+    float sum = 0.f;
+    f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = {0.f, 0.f, 0.f, 0.f};
+    for (int sp = 0; sp < splits; ++sp) {
+        const float *const S = P + sp * (16 * (D + 2));
+        const float f = __builtin_amdgcn_exp2f((S[row] - m) * kLog2e);
+        const f32x4 *const src = reinterpret_cast<const f32x4 *>(S + 32 + row * D + c);
+        sum += f * S[16 + row];
+        a0 += src[0] * f;
+        a1 += src[1] * f;
+    }
+    const float inv = __builtin_amdgcn_rcpf(sum);
+    a0 *= inv, a1 *= inv;
+    *reinterpret_cast<u32x4 *>(O + ((size_t)bh * Lq + q0 + row) * D + c) = u32x4{
+        pack_bf16x2(a0[0], a0[1]), pack_bf16x2(a0[2], a0[3]), pack_bf16x2(a1[0], a1[1]), pack_bf16x2(a1[2], a1[3])};
 }
 
 inline bool is_pow2(float x) {
@@ -272,20 +312,37 @@ inline bool is_pow2(float x) {
     return frexpf(x, &e) == 0.5f;
 }
 
-template <int D, int MODE, int NW>
+constexpr int waves_of(int d) { return d == 64 ? 8 : 4; }
+
+template <int D, int MODE, bool SPLIT>
 hipError_t launch_few(const void *Q, const void *K, const void *V, const float *key_bias, int H, int BH, int Lq, int Lk,
-                      float scale, void *O, hipStream_t st) {
-    const unsigned grid = (unsigned)((long)BH * ((Lq + 15) / 16));
-#define DFSS_LAUNCH(PRE, BB)                                                                                        \
-    hipLaunchKernelGGL((k_few<D, MODE, NW, PRE, BB>), dim3(grid), dim3(64 * NW), 0, st, (const __bf16 *)Q,          \
-                       (const __bf16 *)K, (const __bf16 *)V, key_bias, H, Lq, Lk, scale, (uint16_t *)O)
-    if (is_pow2(scale)) {
+                      float scale, void *O, int splits, float *part, hipStream_t st) {
+    constexpr int NW = waves_of(D);
+    const unsigned tiles = (unsigned)((long)BH * ((Lq + 15) / 16));
+#define DFSS_LAUNCH(PRE, BB)                                                                                             \
+    hipLaunchKernelGGL((k_few<D, MODE, NW, PRE, BB, SPLIT>), dim3(tiles * splits), dim3(64 * NW), 0, st,                 \
+                       (const __bf16 *)Q, (const __bf16 *)K, (const __bf16 *)V, key_bias, H, Lq, Lk, scale, (uint16_t *)O, \
+                       splits, part)
+    const bool pre = is_pow2(scale);
+    if constexpr (SPLIT) {   // (no key bias: see few_queries_splits)
+        if (pre) DFSS_LAUNCH(true, false); else DFSS_LAUNCH(false, false);
+    } else if (pre) {
         if (key_bias) DFSS_LAUNCH(true, true); else DFSS_LAUNCH(true, false);
     } else {
         if (key_bias) DFSS_LAUNCH(false, true); else DFSS_LAUNCH(false, false);
     }
 #undef DFSS_LAUNCH
+    if (SPLIT) hipLaunchKernelGGL(k_few_merge<D>, dim3(tiles), dim3(2 * D), 0, st, part, splits, Lq, (uint16_t *)O);
     return hipGetLastError();
+}
+
+template <bool SPLIT>
+hipError_t launch_any(const void *Q, const void *K, const void *V, const float *key_bias, int H, int BH, int Lq, int Lk, int d,
+                      int mode, float scale, void *O, int splits, float *part, hipStream_t st) {
+#define DFSS_FEW(DD, MM) launch_few<DD, MM, SPLIT>(Q, K, V, key_bias, H, BH, Lq, Lk, scale, O, splits, part, st)
+    if (d == 64) return mode == 0 ? DFSS_FEW(64, MODE_2TO4) : DFSS_FEW(64, MODE_1TO2);
+    return mode == 0 ? DFSS_FEW(128, MODE_2TO4) : DFSS_FEW(128, MODE_1TO2);
+#undef DFSS_FEW
 }
 
 }  // namespace
@@ -293,12 +350,32 @@ hipError_t launch_few(const void *Q, const void *K, const void *V, const float *
 // mode 0 or 1; any Lq, Lk a multiple of 4; key_bias may be null.
 hipError_t launch_fused_attention_few(const void *Q, const void *K, const void *V, const float *key_bias, int H, int BH,
                                       int Lq, int Lk, int d, int mode, float scale, void *O, hipStream_t st) {
-    if (d == 64) {
-        if (mode == 0) return launch_few<64, MODE_2TO4, 8>(Q, K, V, key_bias, H, BH, Lq, Lk, scale, O, st);
-        return launch_few<64, MODE_1TO2, 8>(Q, K, V, key_bias, H, BH, Lq, Lk, scale, O, st);
-    }
-    if (mode == 0) return launch_few<128, MODE_2TO4, 4>(Q, K, V, key_bias, H, BH, Lq, Lk, scale, O, st);
-    return launch_few<128, MODE_1TO2, 4>(Q, K, V, key_bias, H, BH, Lq, Lk, scale, O, st);
+    return launch_any<false>(Q, K, V, key_bias, H, BH, Lq, Lk, d, mode, scale, O, 1, nullptr, st);
+}
+
+// Workgroups per query tile where a workspace lets several share its keys (1 query, d = 64, in us, alone and shared, the
+// merge kernel included): 12 heads x 4096 keys 20.5 and 11.6, 12 x 3072 16.3 and 11.2, 72 x 3072 16.6 and 14.7, 96 x 4096 21.1
+// and 19.5; d = 128: 12 x 1536 16.8 and 11.5, 96 x 4096 41.2 and 34.0.  With 120 heads the chip pulls its keys as fast alone
+// (21.6 and 23.1; d = 128, 1536 keys 18.7 and 19.6).  Not with a key bias: each workgroup would scan the whole bias row
+// first (half of 4096 keys masked, 12 heads: 16.5 and 18.1).
+int few_queries_splits(int BH, int Lq, int Lk, int d) {
+    const long tiles = (long)BH * ((Lq + 15) / 16);
+    const int nblocks = (Lk + KB - 1) / KB, nw = waves_of(d);
+    long n = 256 / tiles;                        // all workgroups on the chip at once, one per compute unit
+    if (n > nblocks / (2 * nw)) n = nblocks / (2 * nw);   // at least two blocks per wave
+    return tiles > 96 || nblocks < 6 * nw || n < 2 ? 1 : (int)n;
+}
+
+size_t few_queries_workspace_bytes(int BH, int Lq, int Lk, int d) {
+    const int n = few_queries_splits(BH, Lq, Lk, d);
+    return n == 1 ? 0 : (size_t)BH * ((Lq + 15) / 16) * n * 16 * (d + 2) * sizeof(float);
+}
+
+// The same with a workspace of few_queries_workspace_bytes (not 0).
+hipError_t launch_fused_attention_few_split(const void *Q, const void *K, const void *V, int BH, int Lq, int Lk, int d, int mode,
+                                            float scale, void *O, void *part, hipStream_t st) {
+    return launch_any<true>(Q, K, V, nullptr, 1, BH, Lq, Lk, d, mode, scale, O, few_queries_splits(BH, Lq, Lk, d),
+                            (float *)part, st);
 }
 
 }  // namespace dfss
