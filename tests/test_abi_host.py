@@ -106,6 +106,14 @@ def test_errors_are_reported_before_any_launch():
     assert lib.dfss_attention(aligned, aligned, aligned, ctypes.byref(unp), 0.125, aligned, None, 0, None) == E_SHAPE
     bad = Shape(1, 1, 128, 128, 64, 4, 8).c()
     assert lib.dfss_sddmm_prune(aligned, aligned, ctypes.byref(bad), 0.125, aligned, aligned, None) == E_UNSUP
+    few = Shape(1, 12, 1, 4096, 64)        # shared keys: a workspace, its size and its alignment
+    need, fc = dfss.dfss_ragged_split_workspace_bytes(few), few.c()
+    call = lambda ws, n: lib.dfss_attention_ragged_split(aligned, aligned, aligned, None, ctypes.byref(fc), 0.125, aligned, ws, n, None)
+    ws = ctypes.c_void_p((p.value + 255) // 256 * 256)
+    assert need > 0 and call(None, need) == E_NULL and call(ws, need - 1) == E_WS
+    assert call(ctypes.c_void_p(ws.value + 16), need) == E_SHAPE
+    assert all(dfss.dfss_ragged_split_workspace_bytes(x) == 0 for x in (
+        Shape(1, 12, 17, 4096, 64), Shape(1, 97, 1, 4096, 64), Shape(1, 12, 1, 2048, 64), Shape(1, 12, 1, 4096, 64, 1, 2, 2)))
     for scale in (0.0, -1.0, float("inf"), float("nan")):
         assert lib.dfss_sddmm_prune(aligned, aligned, ctypes.byref(ok), scale, aligned, aligned, None) == E_UNSUP
     odd = ctypes.c_void_p(aligned.value + 2)
