@@ -11,7 +11,7 @@
 //   V     by asynchronous copies, one block ahead, into LDS that belongs to the wave (the transposing read needs LDS)
 // No barrier before the merge: a wave waits for its own copies only.
 // Measured: a round of one block per wave (128 KiB per workgroup) takes 2.3 us whether 12 or 96 workgroups run, 57 GB/s per
-// compute unit; 1024 heads x 1 query x 4096 keys 179 us (6 TB/s).  96 heads x 1 x 4096: 47.9 us with 64-query workgroups,
+// compute unit; 1024 heads x 1 query x 4096 keys 177 us (6 TB/s).  96 heads x 1 x 4096: 47.9 us with 64-query workgroups,
 // 21.1 us here.
 #include <math.h>
 
@@ -314,10 +314,9 @@ inline bool is_pow2(float x) {
 
 constexpr int waves_of(int d) { return d == 64 ? 8 : 4; }
 
-template <int D, int MODE, bool SPLIT>
+template <int D, int MODE, int NW, bool SPLIT>
 hipError_t launch_few(const void *Q, const void *K, const void *V, const float *key_bias, int H, int BH, int Lq, int Lk,
                       float scale, void *O, int splits, float *part, hipStream_t st) {
-    constexpr int NW = waves_of(D);
     const unsigned tiles = (unsigned)((long)BH * ((Lq + 15) / 16));
 #define DFSS_LAUNCH(PRE, BB)                                                                                             \
     hipLaunchKernelGGL((k_few<D, MODE, NW, PRE, BB, SPLIT>), dim3(tiles * splits), dim3(64 * NW), 0, st,                 \
@@ -339,7 +338,13 @@ hipError_t launch_few(const void *Q, const void *K, const void *V, const float *
 template <bool SPLIT>
 hipError_t launch_any(const void *Q, const void *K, const void *V, const float *key_bias, int H, int BH, int Lq, int Lk, int d,
                       int mode, float scale, void *O, int splits, float *part, hipStream_t st) {
-#define DFSS_FEW(DD, MM) launch_few<DD, MM, SPLIT>(Q, K, V, key_bias, H, BH, Lq, Lk, scale, O, splits, part, st)
+    // Tiles that do not fit the chip at once: two waves per workgroup, so that several workgroups share a compute unit and one
+    // starts while another merges (1 query, 2 against 8 waves, d = 64: 768 heads x 592 keys 19.0 and 27.0 us -- the 64-query
+    // kernel 24.7 --, 384 x 260 6.3 and 8.3, 1024 x 4096 177 and 179).
+    const bool many = !SPLIT && (long)BH * ((Lq + 15) / 16) > 256;
+#define DFSS_FEW(DD, MM)                                                                                                     \
+    (many ? launch_few<DD, MM, 2, false>(Q, K, V, key_bias, H, BH, Lq, Lk, scale, O, 1, nullptr, st)                          \
+          : launch_few<DD, MM, waves_of(DD), SPLIT>(Q, K, V, key_bias, H, BH, Lq, Lk, scale, O, splits, part, st))
     if (d == 64) return mode == 0 ? DFSS_FEW(64, MODE_2TO4) : DFSS_FEW(64, MODE_1TO2);
     return mode == 0 ? DFSS_FEW(128, MODE_2TO4) : DFSS_FEW(128, MODE_1TO2);
 #undef DFSS_FEW
