@@ -419,6 +419,40 @@ __device__ __forceinline__ f32x16 fresh_zeros() {
     return z;
 }
 
+// Expands the kept weights of 32 queries x 32 keys (see k_backward_dkv) where some are infinite or NaN: times the identity
+// such a weight would spread over its whole row (0 x infinity).  They are taken out, marked (1: NaN, 2: infinity, 3: -infinity),
+// expanded on their own and put back where they belong.
+__device__ __forceinline__ f32x16 expand_non_finite(u32x4 kept, bf16x16 eye, uint32_t codes) {
+    u32x4 marks;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        uint32_t clean = 0u, mark = 0u;
+#pragma unroll
+        for (int h = 0; h < 32; h += 16) {
+            const uint32_t w = (kept[e] >> h) & 0xFFFFu;
+            const bool bad = (w & 0x7F80u) == 0x7F80u;
+            clean |= bad ? 0u : w << h;
+            mark |= (!bad ? 0u : (w & 0x7Fu) ? 0x3F80u : (w & 0x8000u) ? 0x4040u : 0x4000u) << h;   // bfloat16 1, 3, 2
+        }
+        kept[e] = clean;
+        marks[e] = mark;
+    }
+    f32x16 x = fresh_zeros();
+    x = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(__builtin_bit_cast(bf16x8, marks), eye, x, (int)codes, 0, 0);
+    uint32_t kinds = 0u;   // two bits per register
+#pragma unroll
+    for (int r = 0; r < 16; ++r) kinds |= (uint32_t)(int)x[r] << (2 * r);
+    x = fresh_zeros();
+    x = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(__builtin_bit_cast(bf16x8, kept), eye, x, (int)codes, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const uint32_t k = (kinds >> (2 * r)) & 3u;
+        const uint32_t v = k == 1u ? 0x7FC00000u : k == 2u ? 0x7F800000u : 0xFF800000u;
+        x[r] = __uint_as_float(k ? v : __float_as_uint(x[r]));
+    }
+    return x;
+}
+
 // dV = P^T dO and dK = scale * dS^T Q in one pass over the queries; a workgroup owns 128 keys of a head, a wave 32 of them.
 // Both sums contract over the queries, across which the N:M structure does not run, so a wave needs P (and dP) with a KEY
 // in every lane and the queries along the registers.  The matrix unit does that transposition: the compressed weights
@@ -430,27 +464,44 @@ __device__ __forceinline__ f32x16 fresh_zeros() {
 // and Q from the transposing LDS read in the same order.
 // Bound by the matrix unit: 13 instructions of 32 cycles per 32 x 32 tile at d = 64 (25 at d = 128).
 // UNP as above; the rows LqR .. Lq - 1 of P, whatever they hold, count as zeros.
-template <int D, bool UNP>
-__global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void k_backward_dkv(
-    const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta, const __bf16 *__restrict__ dO,
+// What is infinite or NaN has to stay at the kept places, but the two products are formed at every place: a row of V that no
+// query kept, a row of dO, a weight that is infinite or NaN meets zeros there, and 0 times it is NaN.  Such a NaN always
+// reaches the sums.  A workgroup whose sums are all finite stores them; another one starts again, CAREFUL: non-finite
+// weights are expanded apart, and dS is formed by the multiplication in which 0 times anything is 0.
+// w: the wave.  Result, the same in every thread of the workgroup: nothing was stored, start again.
+template <int D>
+struct DkvPlace {   // the kernel's LDS in 16-byte units (an access is one of a few lane offsets plus a constant);
+                    // every place but the V operand twice, BUF apart
+    static constexpr int QB = D == 64 ? 64 : 32;    // queries per block (d = 128: so that two workgroups share a compute unit)
+    static constexpr int XT = QB * (D / 8);         // chunks per dO (or Q) block
+    static constexpr int PT = QB * 8;               // chunks per block of kept weights (128 keys = 128 bytes per row)
+    static constexpr bool V_LDS = D == 128;         // the V operand: in LDS where registers are short (read back for every tile)
+    static constexpr int AT_G = 0, AT_Q = XT, AT_P = 2 * XT, AT_M = AT_P + PT, AT_D = AT_M + QB, BUF = AT_D + QB / 4, AT_V = 2 * BUF;
+    static constexpr int SIZE = AT_V + (V_LDS ? KB * (D / 8) : 0);
+};
+template <int D, bool UNP, bool CAREFUL>
+__device__ __forceinline__ bool dkv_pass(
+    u32x4 *Smem, const int w, const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta, const __bf16 *__restrict__ dO,
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ V, const float *__restrict__ neg_delta, int Lq, int Lk,
     int LqR, int LkR, float scale, uint16_t *__restrict__ dK, uint16_t *__restrict__ dV) {
-    constexpr int QB = D == 64 ? 64 : 32;    // queries per block (d = 128: so that two workgroups share a compute unit)
+    using L = DkvPlace<D>;
+    constexpr int QB = L::QB, XT = L::XT, PT = L::PT, AT_G = L::AT_G, AT_Q = L::AT_Q, AT_P = L::AT_P, AT_M = L::AT_M, AT_D = L::AT_D;
+    constexpr int BUF = L::BUF, AT_V = L::AT_V;
+    constexpr bool V_LDS = L::V_LDS;
     constexpr int CPR = D / 8;
-    constexpr int XT = QB * CPR;             // chunks per dO (or Q) block
     constexpr int LPT = XT / NT;
-    constexpr int PT = QB * 8;               // chunks per block of kept weights (128 keys = 128 bytes per row)
     constexpr int STEPS = D / 16;
     constexpr int DT = D / 32;
     static_assert(XT % NT == 0 && PT % NT == 0, "every thread copies the same number of chunks");
-    constexpr bool V_LDS = D == 128;         // the V operand: in LDS where registers are short (read back for every tile)
-    // LDS in 16-byte units; every place but the V operand twice, `BUF` apart.  One array: an access is one of a few lane
-    // offsets plus a constant.
-    constexpr int AT_G = 0, AT_Q = XT, AT_P = 2 * XT, AT_M = AT_P + PT, AT_D = AT_M + QB, BUF = AT_D + QB / 4, AT_V = 2 * BUF;
-    __shared__ u32x4 Smem[AT_V + (V_LDS ? KB * CPR : 0)];
 
-    const int tid = threadIdx.x;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, lj = l & 31, h = l >> 5;
+    // (the lane number is asked for again in a second pass, so that nothing derived from it is kept through the first one)
+    int tid = threadIdx.x;
+    if constexpr (CAREFUL) {
+        tid = __lane_id();
+        asm volatile("" : "+v"(tid));
+        tid += 64 * w;
+    }
+    const int l = tid & 63, lj = l & 31, h = l >> 5;
     const unsigned kblocks = Lk / KB;
     const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);
     const int jblk = item % kblocks, bh = item / kblocks;
@@ -569,8 +620,12 @@ __global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void k_backward_dkv(
 #pragma unroll
                 for (int x = 0; x < 4; ++x) dp[4 * g + x] = nd[x];
             }
-            pd = fresh_zeros();
-            pd = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(__builtin_bit_cast(bf16x8, kept), eye, pd, (int)codes, 0, 0);
+            if constexpr (CAREFUL) {
+                pd = expand_non_finite(kept, eye, codes);
+            } else {
+                pd = fresh_zeros();
+                pd = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(__builtin_bit_cast(bf16x8, kept), eye, pd, (int)codes, 0, 0);
+            }
 #pragma unroll
             for (int s = 0; s < STEPS; ++s) {
                 const bf16x8 ag = __builtin_bit_cast(bf16x8, read16(op_off[s], B0 + AT_G + 32 * CPR * qt));
@@ -587,7 +642,8 @@ __global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void k_backward_dkv(
                 for (int e = 0; e < 4; ++e) {
                     const int r = 8 * m + 2 * e;
                     pw[e] = pack_bf16x2(pd[r], pd[r + 1]);
-                    sw[e] = pack_bf16x2(pd[r] * dp[r], pd[r + 1] * dp[r + 1]);
+                    if constexpr (CAREFUL) sw[e] = pack_bf16x2(mul_or_zero(pd[r], dp[r]), mul_or_zero(pd[r + 1], dp[r + 1]));
+                    else sw[e] = pack_bf16x2(pd[r] * dp[r], pd[r + 1] * dp[r + 1]);
                 }
                 const bf16x8 ap = __builtin_bit_cast(bf16x8, pw), as = __builtin_bit_cast(bf16x8, sw);
                 auto tr = [&](int at, int dt) {
@@ -609,18 +665,54 @@ __global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void k_backward_dkv(
         if (qb + 1 < nq) block(std::integral_constant<int, 1>{}, qb + 1);
     }
 
-    // acc[dt][r]: key 8 (r / 4) + 4 h + r % 4 of the wave's 32, column 32 dt + lj
+    // Is some sum infinite or NaN?  (The same care in every pass: 5 - 18 % on small grids; this test: 0.35 us a call.)  The waves
+    // agree through LDS, at a place of the buffer that the last block did not use.
+    if constexpr (!CAREFUL) {
+        uint32_t largest = 0u;   // magnitude, as bits
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const uint32_t v = __float_as_uint(acc_v[dt][r]) & 0x7FFFFFFFu, k = __float_as_uint(acc_k[dt][r]) & 0x7FFFFFFFu;
+                largest = largest > v ? largest : v;
+                largest = largest > k ? largest : k;
+            }
+        uint32_t *const flags = reinterpret_cast<uint32_t *>(Smem + (((nq - 1) & 1) ? 0 : BUF));
+        const bool mine = __any(largest >= 0x7F800000u);
+        if (__lane_id() == 0) flags[w] = mine ? 1u : 0u;
+        __syncthreads();
+        const uint32_t any = flags[0] | flags[1] | flags[2] | flags[3];
+        if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)any) != 0, 0)) {
+            __syncthreads();   // everybody has read the flags; the buffers are free
+            return true;
+        }
+    }
+
+    // acc[dt][r]: key 8 (r / 4) + 4 (lane / 32) + r % 4 of the wave's 32, column 32 dt + lane % 32
+    const int lane = __lane_id();   // (asked for again: a register less through the loop)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        const int key = jblk * KB + 32 * w + 8 * (r >> 2) + 4 * h + (r & 3);
+        const int key = jblk * KB + 32 * w + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
         if (UNP && key >= LkR) continue;
-        const size_t at = ((size_t)bh * LkR + key) * D + lj;
+        const size_t at = ((size_t)bh * LkR + key) * D + (lane & 31);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) {
             dV[at + 32 * dt] = (uint16_t)(pack_bf16x2(acc_v[dt][r], 0.f) & 0xFFFFu);
             dK[at + 32 * dt] = (uint16_t)(pack_bf16x2(acc_k[dt][r] * scale, 0.f) & 0xFFFFu);
         }
     }
+    return false;
+}
+
+template <int D, bool UNP>
+__global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void k_backward_dkv(
+    const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta, const __bf16 *__restrict__ dO,
+    const __bf16 *__restrict__ Q, const __bf16 *__restrict__ V, const float *__restrict__ neg_delta, int Lq, int Lk,
+    int LqR, int LkR, float scale, uint16_t *__restrict__ dK, uint16_t *__restrict__ dV) {
+    __shared__ u32x4 Smem[DkvPlace<D>::SIZE];
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (dkv_pass<D, UNP, false>(Smem, w, P, meta, dO, Q, V, neg_delta, Lq, Lk, LqR, LkR, scale, dK, dV))
+        dkv_pass<D, UNP, true>(Smem, w, P, meta, dO, Q, V, neg_delta, Lq, Lk, LqR, LkR, scale, dK, dV);
 }
 
 }  // namespace

@@ -46,6 +46,10 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// x y, and 0 where x or y is 0, whatever the other one is (v_mul_legacy_f32).  The compiler has no builtin for it, so its
+// intrinsic is named; an assembly statement would hide from the compiler that it reads a matrix instruction's result.
+__device__ float mul_or_zero(float x, float y) __asm("llvm.amdgcn.fmul.legacy");
+
 // Transposing LDS read: within each group of 16 lanes, lane s supplies the address of
 // four consecutive 16-bit elements; lane t receives element t%4 of source lanes
 // t/4, 4 + t/4, 8 + t/4, 12 + t/4.

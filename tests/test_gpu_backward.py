@@ -161,6 +161,69 @@ def test_backward_on_grids_that_fill_the_chip(BH, Lq, Lk, d, N, M):
             assert np.max(np.abs(got - ref)) <= tol, (name, h)
 
 
+@pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
+    (2, 128, 256, 64, 2, 4), (2, 192, 128, 64, 1, 2), (2, 64, 384, 128, 2, 4),
+    (2, 100, 132, 64, 2, 4), (2, 70, 260, 128, 1, 2),       # no tile multiples
+])
+@pytest.mark.parametrize("what", ["V", "dO", "P", "one weight"])
+def test_what_is_not_finite_reaches_the_kept_places_only(what, BH, Lq, Lk, d, N, M):
+    """Infinities and NaN in a row of V that no query kept, in a row of dO, in a row of weights, in a single weight: every
+    gradient that they do not enter through a kept place is, bit for bit, what it is with zeros instead."""
+    scale = 1.0 / math.sqrt(d)
+    Q, K, V = synth.gaussian_qkv(BH, Lq, Lk, d, 1.0, seed=9600 + Lq + d)
+    dO = torch.randn(BH, Lq, d, generator=torch.Generator().manual_seed(9601 + Lq)).to(torch.bfloat16)
+    Qn, Kn, Vn = (synth.to_numpy_f32(t) for t in (Q, K, V))
+    s = Shape(1, BH, Lq, Lk, d, N, M)
+    never = [5, 70, 99, Lk - 2]            # one key of a run each: masked, so that no query keeps it
+    kidx, O = [], []
+    P = np.full((BH, s.LqP, s.Lc), 0.25, dtype=np.float32)
+    meta_c = np.full((BH, s.LqP, s.meta_words), 0x4444, dtype=np.uint16)
+    for h in range(BH):
+        S = np.full((Lq, s.LkP), -np.inf, dtype=np.float32)
+        S[:, :Lk] = oracle.scores(Qn[h], Kn[h], scale)
+        S[:, never] = -np.inf
+        _, vals, ki = oracle.prune(S, N, M)
+        assert not np.isin(never, ki).any()
+        kidx.append(ki)
+        P[h, :Lq] = oracle.round_bf16(oracle.softmax_kept(oracle.round_bf16(vals)))
+        meta_c[h, :Lq] = oracle.encode_meta(ki, s.LkP)
+        Pd = np.zeros((Lq, s.LkP))
+        np.put_along_axis(Pd, ki.astype(np.int64), P[h, :Lq].astype(np.float64), axis=1)
+        O.append((Pd[:, :Lk] @ Vn[h].astype(np.float64)).astype(np.float32))
+    meta = dfss.dfss_meta_from_canonical(_dev(torch.from_numpy(meta_c.view(np.int16))), s)
+    Qd, Kd, Od = _dev(Q), _dev(K), _dev(_bf16(np.stack(O)))
+    q0, e0 = 37, 21                        # the row; the kept entry of the single weight
+    for bad in (math.nan, math.inf, -math.inf):
+        got = []
+        for x in (0.0, bad):
+            V_, dO_, P_ = V.clone(), dO.clone(), _bf16(P)
+            if what == "V":
+                V_[0, never] = x
+            elif what == "dO":
+                dO_[0, q0] = x
+            elif what == "P":
+                P_[0, q0] = x
+            else:
+                P_[0, q0, e0] = x
+            grads = dfss.dfss_attention_backward(_dev(dO_), Qd, Kd, _dev(V_), Od, _dev(P_), meta, s, scale)
+            torch.cuda.synchronize()
+            got.append([_np(t) for t in grads])
+        rows = np.ones((BH, Lq), bool)     # rows of dQ, and of dK and dV, that have to agree
+        keys = {"dK": np.ones((BH, Lk), bool), "dV": np.ones((BH, Lk), bool)}
+        if what != "V":
+            rows[0, q0] = False
+            hit = kidx[0][q0] if what != "one weight" else kidx[0][q0, e0:e0 + 1]
+            for k in keys.values():
+                k[0, hit[hit < Lk]] = False
+            if what == "dO":               # dO itself is a factor of dV: every key of the head
+                keys["dV"][0] = False
+        (zQ, zK, zV), (bQ, bK, bV) = got
+        for name, z, b, sel in (("dQ", zQ, bQ, rows), ("dK", zK, bK, keys["dK"]), ("dV", zV, bV, keys["dV"])):
+            assert np.isfinite(z).all() and np.array_equal(z[sel], b[sel]), (name, bad)
+            if name != "dQ" and what != "V":
+                assert not np.isfinite(b[~sel]).any(), (name, bad)
+
+
 # ----------------------------------------------------------------------------------
 # lengths that are not tile multiples: P, meta and dS' keep the layout of the padded lengths
 # ----------------------------------------------------------------------------------
