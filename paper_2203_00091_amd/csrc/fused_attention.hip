@@ -915,12 +915,11 @@ hipError_t launch_fused_attention(const void *Q, const void *K, const void *V, c
     // 96 heads 47.9 -> 21.1 / 73 -> 41 us; 16 heads x 256 queries, 1024 keys 10.9 -> 9.1 / 21.2 -> 14.3 us; one head x 512
     // x 512 8.6 -> 6.8 us.  With two rounds of workgroups it loses (96 heads x 64 queries, 4096 keys: 42 against 32 us)
     // unless the kernels below would spend their tiles on absent queries (1024 heads x 1 query, 4096 keys: 216 -> 177 us; 768 x 1
-    // x 592 24.7 -> 19.0),
-    // and so it does on two key blocks (one head x 128 x 128: 4.8 against 4.3 us).  Two identities keep a call out: a key
-    // bias on whole tiles gives bit for bit what a block pattern that keeps every block gives (the masked kernel below),
-    // and unpadded rows of fewer than 256 keys what the same call gives on masked padding (likewise).
+    // x 592 24.7 -> 19.0).  Two identities keep a call out: a key bias on whole tiles gives bit for bit what a block pattern
+    // that keeps every block gives (the masked kernel below), and unpadded rows of fewer than 256 keys, however few the
+    // queries, what the same call gives on masked padding (likewise; 1 query x 132 .. 252 keys would gain 4 - 70 % here).
     const bool tiles = Lq % 64 == 0 && Lk % 64 == 0;
-    const bool few = Lq <= 16 ? Lk > 128 : Lk >= 256 && (long)BH * ((Lq + 15) / 16) <= 256 && !(key_bias && tiles);
+    const bool few = Lk >= 256 && (Lq <= 16 || ((long)BH * ((Lq + 15) / 16) <= 256 && !(key_bias && tiles)));
     if (((variant == DFSS_VARIANT_AUTO && few) || variant == DFSS_VARIANT_FEW) && mode != 2 && !block_mask && !causal)
         return launch_fused_attention_few(Q, K, V, key_bias, H, BH, Lq, Lk, d, mode, scale, O, st);
     const bool masked = key_bias || block_mask || causal;

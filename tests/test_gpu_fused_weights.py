@@ -109,13 +109,15 @@ def test_every_tiling_selects_and_weighs_like_the_oracle(variant, BH, Lq, Lk, d,
 
 
 @pytest.mark.parametrize("BH,Lq,Lk,d,N,M,scale,bias", [
-    (3, 1, 132, 64, 2, 4, 0.125, False),       # one query; one run of keys in the last block, most waves without a block
+    (3, 1, 132, 64, 2, 4, 0.125, False),       # (fewer than 256 keys: the kernel of the masked calls)
+    (3, 1, 260, 64, 2, 4, 0.125, False),       # one query; one run of keys in the last block, most waves without a block
     (2, 16, 576, 64, 1, 2, 1.0 / 3.0, False),  # a whole query tile; nine blocks: one wave takes two
     (2, 17, 1092, 64, 2, 4, 0.125, True),      # a tile with one query; 18 blocks, list of live blocks
     (2, 33, 324, 128, 2, 4, 1.0 / 3.0, True),
     (1, 5, 260, 128, 1, 2, 0.125, False),
     (260, 1, 324, 64, 2, 4, 0.125, True),      # more tiles than compute units: two waves per workgroup
-    (257, 2, 196, 128, 1, 2, 0.125, False),
+    (257, 2, 196, 128, 1, 2, 0.125, False),    # (fewer than 256 keys)
+    (257, 1, 260, 128, 1, 2, 0.125, False),    # more tiles than compute units, d = 128
     (3, 3, 3076, 64, 2, 4, 0.125, False),      # 49 blocks shared between workgroups (d = 64: from 48 on)
     (2, 16, 1540, 128, 1, 2, 1.0 / 3.0, False),   # ... d = 128: from 24 on
     (70, 1, 1536, 128, 2, 4, 0.125, False),    # ... three workgroups per tile

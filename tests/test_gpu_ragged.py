@@ -139,6 +139,26 @@ def test_ragged_equals_padded_and_masked(dtype, N, M):
     assert np.array_equal(O, _np(Op)[:, :Lq])
 
 
+@pytest.mark.parametrize("Lq,Lk,d,N,M,scale", [
+    (1, 132, 64, 2, 4, 0.125), (1, 252, 64, 1, 2, 0.125), (16, 192, 64, 2, 4, 0.11), (7, 200, 64, 2, 4, 0.125),
+    (16, 252, 128, 2, 4, 0.0884), (1, 140, 128, 1, 2, 0.0884),
+])
+def test_few_queries_against_few_keys_equal_padded_and_masked(Lq, Lk, d, N, M, scale):
+    """The same, bit for bit, for few queries against fewer than 256 keys."""
+    B, H = 2, 3
+    Lqp, Lkp = 64, (Lk + 127) // 128 * 128
+    Q, K, V, _ = _inputs(B * H, Lq, Lk, d, DFSS_BF16, 8310 + Lk)
+    Qp, Kp, Vp, _ = _inputs(B * H, Lqp, Lkp, d, DFSS_BF16, 8311)
+    Qp[:, :Lq], Kp[:, :Lk], Vp[:, :Lk] = Q, K, V
+    bias = torch.zeros((B, Lkp), dtype=torch.float32)
+    bias[:, Lk:] = float("-inf")
+    s, sp = Shape(B, H, Lq, Lk, d, N, M), Shape(B, H, Lqp, Lkp, d, N, M)
+    O = _run(dfss.dfss_attention_ragged, Q, K, V, None, s, scale)
+    Op = dfss.dfss_attention_bias(_dev(Qp), _dev(Kp), _dev(Vp), _dev(bias), sp, scale)
+    torch.cuda.synchronize()
+    assert np.array_equal(O, _np(Op)[:, :Lq])
+
+
 @pytest.mark.parametrize("dtype,N,M", [(DFSS_BF16, 2, 4), (DFSS_F32_BF16X3, 1, 2)])
 def test_ragged_call_on_tile_multiples_equals_the_plain_call(dtype, N, M):
     B, H, L, d = 2, 2, 256, 64
