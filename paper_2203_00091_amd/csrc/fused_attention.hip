@@ -911,15 +911,31 @@ hipError_t launch_fused_attention(const void *Q, const void *K, const void *V, c
     // (the baseline) runs the 16-query kernel below: the faster of the two at every shape measured (96 heads x 384,
     // 24 heads x 1024 .. 4096, 192 heads x 512, d = 128), the 32-query form being reachable through the test hook.
     // Few query tiles: the kernel whose waves share the keys (few_queries.hip), as long as its 16-query workgroups fit the
-    // chip at once (one per compute unit).  Measured against the kernels below, d = 64 / 128: one query and 4096 keys,
-    // 96 heads 47.9 -> 21.1 / 73 -> 41 us; 16 heads x 256 queries, 1024 keys 10.9 -> 9.1 / 21.2 -> 14.3 us; one head x 512
-    // x 512 8.6 -> 6.8 us.  With two rounds of workgroups it loses (96 heads x 64 queries, 4096 keys: 42 against 32 us)
-    // unless the kernels below would spend their tiles on absent queries (1024 heads x 1 query, 4096 keys: 216 -> 177 us; 768 x 1
-    // x 592 24.7 -> 19.0).  Two identities keep a call out: a key bias on whole tiles gives bit for bit what a block pattern
-    // that keeps every block gives (the masked kernel below), and unpadded rows of fewer than 256 keys, however few the
-    // queries, what the same call gives on masked padding (likewise; 1 query x 132 .. 252 keys would gain 4 - 70 % here).
+    // chip at once (one per compute unit).  Warm, against the kernels below, d = 64 / 128: one query and 4096 keys, 96 heads
+    // 47.9 -> 21.1 / 73 -> 41 us; 16 heads x 256 queries, 1024 keys 10.9 -> 9.1 / 21.2 -> 14.3 us; one head x 512 x 512
+    // 8.6 -> 6.8 us.  With two rounds of workgroups it loses (96 heads x 64 queries, 4096 keys: 42 against 32 us) unless the
+    // kernels below would spend their tiles on absent queries (1024 heads x 1 query, 4096 keys: 216 -> 177 us; 768 x 1 x 592
+    // 24.7 -> 19.0).  Where it gains nothing or loses, the kernels below run:
+    //   d = 128, 2 .. 16 queries, more than 224 heads: level below 1024 keys (256 x 16: 384 keys 11.2 against 11.9 us, 1024
+    //     22.9 against 22.6)
+    //   a key bias, up to 16 queries, more heads than fit at once: from there on every workgroup scans its bias row first (d =
+    //     128, one query: 288 x 2048 38.0 against 42.8 us, 576 x 4092 179.7 against 188; d = 64 gains up to 512 heads, 480 x
+    //     1024 2 %, and breaks even at 576) -- until, at 768 heads, the kernel below takes two tiles of absent queries per
+    //     wave (864 x 512: 1.5 / 1.3 times as long as here)
+    //   a key bias, more queries: below 384 keys (one head x 33 x 260 5.6 against 6.1 us; 388 keys level, 1028 12.9 -> 10)
+    //   d = 128, an odd number of 64-query tiles, 256 keys: 7.0 against 7.3 us (384 keys 9.0 -> 8.5)
+    // Two identities keep a call out: a key bias on whole tiles gives bit for bit what a block pattern that keeps every
+    // block gives (the masked kernel below), and unpadded rows of fewer than 256 keys, however few the queries, what the
+    // same call gives on masked padding (likewise; 1 query x 132 .. 252 keys would gain 4 - 70 % here).
     const bool tiles = Lq % 64 == 0 && Lk % 64 == 0;
-    const bool few = Lk >= 256 && (Lq <= 16 || ((long)BH * ((Lq + 15) / 16) <= 256 && !(key_bias && tiles)));
+    const long tiles16 = (long)BH * ((Lq + 15) / 16);
+    bool few = Lk >= 256;
+    if (Lq <= 16) {
+        if (key_bias) few = few && (tiles16 <= (d == 64 ? 512 : 256) || tiles16 >= 768);
+        else if (d == 128 && Lq > 1 && tiles16 > 224) few = Lk >= 1024;
+    } else {
+        few = few && tiles16 <= 256 && !(key_bias && (tiles || Lk < 384)) && !(d == 128 && tiles && Lq % 128 != 0 && Lk == 256);
+    }
     if (((variant == DFSS_VARIANT_AUTO && few) || variant == DFSS_VARIANT_FEW) && mode != 2 && !block_mask && !causal)
         return launch_fused_attention_few(Q, K, V, key_bias, H, BH, Lq, Lk, d, mode, scale, O, st);
     const bool masked = key_bias || block_mask || causal;

@@ -118,6 +118,8 @@ def test_every_tiling_selects_and_weighs_like_the_oracle(variant, BH, Lq, Lk, d,
     (260, 1, 324, 64, 2, 4, 0.125, True),      # more tiles than compute units: two waves per workgroup
     (257, 2, 196, 128, 1, 2, 0.125, False),    # (fewer than 256 keys)
     (257, 1, 260, 128, 1, 2, 0.125, False),    # more tiles than compute units, d = 128
+    (768, 1, 260, 128, 2, 4, 0.125, True),     # ... with a key bias (d = 128: from 768 heads on again)
+    (320, 1, 260, 128, 2, 4, 0.125, True),     # (... the kernel below)
     (3, 3, 3076, 64, 2, 4, 0.125, False),      # 49 blocks shared between workgroups (d = 64: from 48 on)
     (2, 16, 1540, 128, 1, 2, 1.0 / 3.0, False),   # ... d = 128: from 24 on
     (70, 1, 1536, 128, 2, 4, 0.125, False),    # ... three workgroups per tile
