@@ -7,7 +7,8 @@
 // through the same kernel.  The dense variant (P V of Eq. 1, for the baseline) shares the
 // V staging and uses v_mfma_f32_16x16x32_bf16.
 //
-// Three products: k_spmm on compressed weights; k_av on compressed SCORES (SPARSE: two-kernel forward pass) or on dense weights.
+// k_av: compressed weights, compressed SCORES (SOFTMAX: two-kernel forward pass) or dense weights; k_spmm: compressed weights
+// again, where their stream is what bounds the product (see pairs_pay).
 //
 // The product on scores takes the kept SCORES of stage 1 instead of weights and applies the softmax
 // on the way (Sec. 3.1; the max-subtracted form of App. A.1.3 with a running reference m in the place of the
@@ -40,7 +41,7 @@ constexpr int KB = 128;   // keys per block
 // UNPADDED: V holds LkR <= Lk keys per head and O LqR <= Lq rows, while P and meta have the layout of the padded
 // lengths Lq (a multiple of 64) and Lk (of 128).  The weights of the absent keys are 0 (their scores were -inf); their
 // places in a partial last block of V are filled with the block's last real key, and rows past LqR are not stored.
-template <int D, bool SPARSE, int RB, bool UNPADDED = false>
+template <int D, bool SPARSE, int RB, bool SOFTMAX, bool UNPADDED = false>
 __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta,
                                               const __bf16 *__restrict__ V, int Lq, int Lk, int LqR, int LkR,
                                               uint16_t *__restrict__ O) {
@@ -49,7 +50,7 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
     constexpr int LPT = TILE / NT;      // direct-to-LDS loads per thread per block
     constexpr int DS = D / 16;          // 16-column output tiles
     constexpr int TQ = 64 * RB;         // queries per workgroup
-    constexpr bool SOFTMAX = SPARSE;    // (weights, on which there is nothing to do: k_spmm)
+    static_assert(!SOFTMAX || SPARSE, "the softmax is folded into the sparse product only");
     __shared__ u32x4 Vs[2][TILE];
 
     const int tid = threadIdx.x;
@@ -428,31 +429,13 @@ __global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void k_spmm(const uint32_t *__
         }
 }
 
-hipError_t launch_sparse(const void *P, const void *meta, const void *V, int BH, int Lq, int Lk, int LqR, int LkR, int d,
-                         void *O, hipStream_t st) {
-    const bool unp = LqR != Lq || LkR != Lk;
-    // two row blocks per wave when that still leaves two workgroups per compute unit (as below)
-    const bool rb2 = !unp && Lq % 128 == 0 && (long)BH * (Lq / 128) >= 512;
-    const unsigned grid = (unsigned)((long)BH * (Lq / (rb2 ? 128 : 64)));
-#define DFSS_LAUNCH(DD, RR, UU)                                                                                      \
-    hipLaunchKernelGGL((k_spmm<DD, RR, UU>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P, (const uint32_t *)meta, \
-                       (const __bf16 *)V, Lq, Lk, LqR, LkR, (uint16_t *)O)
-    if (d == 64) {
-        if (unp) DFSS_LAUNCH(64, 1, true); else if (rb2) DFSS_LAUNCH(64, 2, false); else DFSS_LAUNCH(64, 1, false);
-    } else {
-        if (unp) DFSS_LAUNCH(128, 1, true); else if (rb2) DFSS_LAUNCH(128, 2, false); else DFSS_LAUNCH(128, 1, false);
-    }
-#undef DFSS_LAUNCH
-    return hipGetLastError();
-}
-
-template <bool SPARSE>
-hipError_t launch(const void *P, const void *meta, const void *V, int BH, int Lq, int Lk, int LqR, int LkR, int d,
+template <bool SPARSE, bool SOFTMAX = false>
+hipError_t launch_av(const void *P, const void *meta, const void *V, int BH, int Lq, int Lk, int LqR, int LkR, int d,
                   void *O, hipStream_t st) {
     if (LqR != Lq || LkR != Lk) {   // unpadded lengths: 64-query workgroups (Lq is a multiple of 64)
         const unsigned grid = (unsigned)((long)BH * (Lq / 64));
 #define DFSS_LAUNCH(DD)                                                                                             \
-    hipLaunchKernelGGL((k_av<DD, SPARSE, 1, true>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P,     \
+    hipLaunchKernelGGL((k_av<DD, SPARSE, 1, SOFTMAX, true>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P,     \
                        (const uint32_t *)meta, (const __bf16 *)V, Lq, Lk, LqR, LkR, (uint16_t *)O)
         if (d == 64) DFSS_LAUNCH(64); else DFSS_LAUNCH(128);
 #undef DFSS_LAUNCH
@@ -463,12 +446,47 @@ hipError_t launch(const void *P, const void *meta, const void *V, int BH, int Lq
     bool rb2 = (Lq % 128 == 0) && ((long)BH * (Lq / 128) >= 512);
     const unsigned grid = (unsigned)((long)BH * (Lq / (rb2 ? 128 : 64)));
 #define DFSS_LAUNCH(DD, RR)                                                                                   \
-    hipLaunchKernelGGL((k_av<DD, SPARSE, RR>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P,              \
+    hipLaunchKernelGGL((k_av<DD, SPARSE, RR, SOFTMAX>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P,              \
                        (const uint32_t *)meta, (const __bf16 *)V, Lq, Lk, Lq, Lk, (uint16_t *)O)
     if (d == 64) {
         if (rb2) DFSS_LAUNCH(64, 2); else DFSS_LAUNCH(64, 1);
     } else {
         if (rb2) DFSS_LAUNCH(128, 2); else DFSS_LAUNCH(128, 1);
+    }
+#undef DFSS_LAUNCH
+    return hipGetLastError();
+}
+
+// Which kernel takes compressed weights.  wg: tiles of 64 queries; nblocks: 128-key blocks; rb2: 128 queries per workgroup.
+// k_spmm against k_av, warm (the weights as the softmax left them), over 900 shapes:
+//   the weights and codes exceed the last-level cache (256 MB): 1.0 - 1.3 times as fast (24 heads x 4096 x 4096 126 -> 113 us;
+//     d = 128, 12 x 4096 x 6144 1.3) -- at d = 128 only where many workgroups share a head's V (with 256 queries per head,
+//     768 .. 1024 tiles, it takes 1.2 times as long: V comes from the caches for every workgroup, twice as many bytes as at
+//     d = 64, and the workgroups of a head are not at the same block)
+//   d = 64, a workgroup per compute unit at most: 1.04 - 1.3 (one head x 4096 x 4096 20.3 -> 18.8 us); an odd number of
+//     blocks costs a barrier with nothing in flight: level at 9 blocks, 0.93 - 0.97 at 3
+//   d = 64, nearly four 64-query workgroups per compute unit: 1.0 - 1.1
+//   elsewhere, out of the caches: 0.66 - 1.05 (d = 64, 12 heads x 2048 x 2048 16.0 -> 17.2 us, 192 x 384 x 384 11.8 -> 13.5)
+inline bool pairs_pay(int d, long wg, int nblocks, int LqR, bool rb2) {
+    const bool streams = wg * nblocks * (64 * KB * 9 / 8) >= 256l << 20;
+    if (d == 128) return streams && LqR >= 2048;
+    return streams || (wg <= 256 ? nblocks >= 8 || (nblocks >= 4 && nblocks % 2 == 0) : !rb2 && wg >= 880 && nblocks >= 12);
+}
+
+hipError_t launch_sparse(const void *P, const void *meta, const void *V, int BH, int Lq, int Lk, int LqR, int LkR, int d,
+                         void *O, hipStream_t st) {
+    const bool unp = LqR != Lq || LkR != Lk;
+    // two row blocks per wave when that still leaves two workgroups per compute unit (as below)
+    const bool rb2 = !unp && Lq % 128 == 0 && (long)BH * (Lq / 128) >= 512;
+    if (!pairs_pay(d, (long)BH * (Lq / 64), Lk / KB, LqR, rb2)) return launch_av<true>(P, meta, V, BH, Lq, Lk, LqR, LkR, d, O, st);
+    const unsigned grid = (unsigned)((long)BH * (Lq / (rb2 ? 128 : 64)));
+#define DFSS_LAUNCH(DD, RR, UU)                                                                                      \
+    hipLaunchKernelGGL((k_spmm<DD, RR, UU>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P, (const uint32_t *)meta, \
+                       (const __bf16 *)V, Lq, Lk, LqR, LkR, (uint16_t *)O)
+    if (d == 64) {
+        if (unp) DFSS_LAUNCH(64, 1, true); else if (rb2) DFSS_LAUNCH(64, 2, false); else DFSS_LAUNCH(64, 1, false);
+    } else {
+        if (unp) DFSS_LAUNCH(128, 1, true); else if (rb2) DFSS_LAUNCH(128, 2, false); else DFSS_LAUNCH(128, 1, false);
     }
 #undef DFSS_LAUNCH
     return hipGetLastError();
@@ -483,12 +501,12 @@ hipError_t launch_spmm(const void *vals, const void *meta, const void *V, int BH
 
 hipError_t launch_softmax_spmm(const void *scores, const void *meta, const void *V, int BH, int Lq, int Lk, int LqR,
                                int LkR, int d, void *O, hipStream_t st) {
-    return launch<true>(scores, meta, V, BH, Lq, Lk, LqR, LkR, d, O, st);
+    return launch_av<true, true>(scores, meta, V, BH, Lq, Lk, LqR, LkR, d, O, st);
 }
 
 hipError_t launch_dense_av(const void *P, const void *V, int BH, int Lq, int Lk, int LqR, int LkR, int d, void *O,
                            hipStream_t st) {
-    return launch<false>(P, nullptr, V, BH, Lq, Lk, LqR, LkR, d, O, st);
+    return launch_av<false>(P, nullptr, V, BH, Lq, Lk, LqR, LkR, d, O, st);
 }
 
 }  // namespace dfss

@@ -199,6 +199,8 @@ def test_stage3_spmm(BH, Lq, Lk, d, N, M):
     (520, 128, 128, 128, 1, 2),   # ... a single block only
     (5, 64, 640, 64, 1, 2),       # one row block per wave; every starting pair, the single block in the middle too
     (7, 192, 768, 128, 2, 4),
+    (5, 64, 1152, 64, 1, 2),      # few workgroups, 9 blocks: taken in pairs from every place, the single one in the middle too
+    (9, 64, 512, 64, 2, 4),       # ... an even number of blocks: from four on
 ])
 def test_stage3_spmm_pairs_of_key_blocks(BH, Lq, Lk, d, N, M):
     """The product on kept weights of random values at random positions, against the dense product in 64 bits."""
@@ -221,6 +223,38 @@ def test_stage3_spmm_pairs_of_key_blocks(BH, Lq, Lk, d, N, M):
         ref = (P @ V[h].double()).numpy()
         # bfloat16 output (2^-9 relative) and fp32 sums of Lk / 2 terms
         assert np.max(np.abs(_np(O)[h] - ref)) <= 2.0 ** -8 * np.max(np.abs(ref)) + 1e-4
+
+
+@pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
+    (512, 128, 3712, 64, 2, 4),   # d = 64: two row blocks per wave, 29 key blocks (an odd number)
+    (220, 256, 1536, 64, 1, 2),   # ... one, nearly four workgroups per compute unit
+    (32, 2048, 3712, 128, 1, 2),  # d = 128: two row blocks, an odd number of key blocks
+    (16, 2048, 8192, 128, 2, 4),  # ... one
+    (16, 2050, 8100, 128, 2, 4),  # ... no tile multiples
+    (16, 1000, 8100, 128, 2, 4),  # (fewer queries: the kernel that keeps to one block)
+])
+def test_stage3_spmm_on_weights_that_exceed_the_cache(BH, Lq, Lk, d, N, M):
+    """The kernel that streams pairs of key blocks and the sizes it is taken for: the weights that stages 1 and 2 leave,
+    sampled rows of sampled heads against the product in 64 bits."""
+    g = torch.Generator(device=DEV).manual_seed(7700 + Lk + d)
+    Q, K, V = (torch.randn((BH, L, d), generator=g, device=DEV).to(torch.bfloat16) for L in (Lq, Lk, Lk))
+    s = Shape(1, BH, Lq, Lk, d, N, M)
+    P, meta = dfss.dfss_sddmm_prune(Q, K, s, 0.25 / math.sqrt(d))
+    dfss.dfss_sparse_softmax(P, s)
+    buf = torch.full((BH * Lq * d + 4096,), 777.0, dtype=torch.bfloat16, device=DEV)
+    O = dfss.dfss_spmm(P, meta, V, s, O=buf[:BH * Lq * d].view(BH, Lq, d))
+    canon = dfss.dfss_meta_to_canonical(meta, s)
+    torch.cuda.synchronize()
+    assert bool((buf[BH * Lq * d:] == 777.0).all()), "wrote behind O"
+    rows = np.r_[0:8, Lq // 2:Lq // 2 + 8, Lq - 8:Lq]
+    for h in (0, BH // 2 + 1, BH - 1):
+        kidx = oracle.decode_meta(canon[h].cpu().numpy().view(np.uint16), s.LkP)[rows].astype(np.int64)
+        Pd = np.zeros((len(rows), s.LkP))
+        np.put_along_axis(Pd, kidx, _np(P[h])[rows].astype(np.float64), axis=1)
+        assert not Pd[:, Lk:].any()
+        ref = Pd[:, :Lk] @ _np(V[h]).astype(np.float64)
+        # bfloat16 output (2^-9 relative) and fp32 sums of Lk / 2 terms
+        assert np.max(np.abs(_np(O[h])[rows] - ref)) <= 2.0 ** -8 * np.max(np.abs(ref)) + 1e-4, h
 
 
 def test_meta_order_round_trip():
