@@ -64,13 +64,17 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
     const int nblocks = Lk / KB;
     const int meta_slot = ((kb & 1) << 1) | (kb >> 1);   // where the word of 32-key chunk kb sits in a row's 16 bytes
 
-    // LDS position p (16-byte units) = row * CPR + (c ^ tr_row_swizzle(row)) holds chunk c of key `row`
+    // LDS position p (16-byte units) = row * CPR + (c ^ v_swizzle(row)) holds chunk c of key `row`.  With rows of 256 bytes
+    // two lanes meet in a pair of banks this way; tr_row_swizzle avoids that, but its patterns differ between the four reads
+    // of an operand and between h = 0 and 1, and the addresses cost more (4 heads x 64 x 8192: 53.8 against 60.2 us, 4 x
+    // 512 x 512 6.1 and 6.6; on dense weights no difference).
+    auto v_swizzle = [](int row) { return CPR == 16 ? (row & 3) << 1 : tr_row_swizzle<CPR>(row); };
     const __bf16 *Vh = V + (size_t)bh * LkR * D;
     int src_off[LPT];
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
         const int p = i * NT + tid;
-        const int row = p / CPR, c = (p % CPR) ^ tr_row_swizzle<CPR>(row);
+        const int row = p / CPR, c = (p % CPR) ^ v_swizzle(row);
         src_off[i] = row * D + c * 8;
     }
     const uint32_t lds_v = lds_address(&Vs[0][w * 64]);   // this wave's 1 KB slice of copy 0, buffer 0
@@ -81,7 +85,7 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
 #pragma unroll
             for (int i = 0; i < LPT; ++i) {
                 const int p = i * NT + tid;
-                const int row = p / CPR, c = (p % CPR) ^ tr_row_swizzle<CPR>(row);
+                const int row = p / CPR, c = (p % CPR) ^ v_swizzle(row);
                 async_copy16(src, 2u * ((row < real ? row : real - 1) * D + c * 8), lds_v + 16u * (buf * TILE + i * NT));
             }
             return;
@@ -204,7 +208,7 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
         const char *vbase = reinterpret_cast<const char *>(&Vs[buf][0]);
         auto tr = [&](int key0, int ds) {
             const int row = key0 + tr_row;
-            const int chunk = (2 * ds + tr_sub) ^ tr_row_swizzle<CPR>(row);
+            const int chunk = (2 * ds + tr_sub) ^ v_swizzle(row);
             return lds_read_tr16(vbase + (row * CPR + chunk) * 16 + tr_byte);
         };
         if constexpr (SPARSE) {
