@@ -154,16 +154,21 @@ __global__ __launch_bounds__(64 * NW, OCC * 4 / NW) void k_fused32(const __bf16 
     [[maybe_unused]] const int tail_keys = Lk - (nblocks - 1) * KB;   // RAGGED: keys of the last block
 
     // K block in LDS: row slot 32 kt + i (key tile kt, MFMA row i = 8g + 4h' + x) holds key
-    // 32 kt + 16 h' + 4 g + x; chunk c sits at slot * CPR + (c ^ operand_row_swizzle(slot)).
+    // 32 kt + 16 h' + 4 g + x; chunk c sits at slot * CPR + (c ^ k_swizzle(slot)).
     // V block: row = key, chunk c at row * CPR + (c ^ tr32_swizzle(row)).
     // Copy i of a thread handles LDS position p = i * NT + tid: NT / CPR row slots further on, which does not
     // move the low key bits nor, unless the step is 8 slots of 256 bytes, the swizzle: source = that of copy 0 + a
     // constant; with the step of 8 every second copy takes the other half of the row (chunk bit 3).
+    // (k_swizzle at d = 64: without bank conflicts, except where the low bits measured faster all the same -- with the masking
+    // machinery 24 heads x 512 x 2048 24.6 against 25.8 us, 2 x 4096 x 4096 45.3 and 47.6; 1:2 with the keys split over two
+    // waves or with key lengths 1 - 2 %.)
+    constexpr bool LOW_BITS = CPR == 8 && (MASKED || (MODE == MODE_1TO2 && (KS == 2 || VARLEN)));
+    auto k_swizzle = [](int slot) { return LOW_BITS ? slot & 7 : operand_row_swizzle<CPR, 32>(slot); };
     constexpr int SPC = NT / CPR;       // row slots between consecutive copies of a thread
     static_assert(SPC % 8 == 0, "the slot bits that a thread's copies differ in are bits 3, 4 and 5");
     const int slot0 = tid / CPR;
     const int key0 = (slot0 & 32) | (((slot0 >> 2) & 1) << 4) | (((slot0 >> 3) & 3) << 2) | (slot0 & 3);
-    const int k_chunk = ((tid % CPR) ^ operand_row_swizzle<CPR, 32>(slot0)) * 8;
+    const int k_chunk = ((tid % CPR) ^ k_swizzle(slot0)) * 8;
     const int v_chunk = ((tid % CPR) ^ tr32_swizzle<CPR>(slot0)) * 8;
     constexpr bool FLIP = CPR == 16 && SPC % 16 != 0;
     auto k_flip = [](int i) { return FLIP && ((i * SPC) & 8) ? 64 : 0; };   // what copy i adds to the chunk by XOR (elements)
@@ -260,7 +265,7 @@ __global__ __launch_bounds__(64 * NW, OCC * 4 / NW) void k_fused32(const __bf16 
 #pragma unroll
                 for (int s = 0; s < STEPS; ++s) {
                     const bf16x8 ak =
-                        __builtin_bit_cast(bf16x8, Ks[buf][(32 * t + lj) * CPR + ((2 * s + h) ^ operand_row_swizzle<CPR, 32>(lj))]);
+                        __builtin_bit_cast(bf16x8, Ks[buf][(32 * t + lj) * CPR + ((2 * s + h) ^ k_swizzle(lj))]);
                     acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak, bq[s], s == 0 ? cb : acc[t], 0, 0, 0);
                 }
             }
@@ -270,7 +275,7 @@ __global__ __launch_bounds__(64 * NW, OCC * 4 / NW) void k_fused32(const __bf16 
 #pragma unroll
                 for (int s = 0; s < STEPS; ++s) {
                     const bf16x8 ak =
-                        __builtin_bit_cast(bf16x8, Ks[buf][(32 * (kt0 + t) + lj) * CPR + ((2 * s + h) ^ operand_row_swizzle<CPR, 32>(lj))]);
+                        __builtin_bit_cast(bf16x8, Ks[buf][(32 * (kt0 + t) + lj) * CPR + ((2 * s + h) ^ k_swizzle(lj))]);
                     acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak, bq[s], s == 0 ? cneg : acc[t], 0, 0, 0);
                 }
             }
