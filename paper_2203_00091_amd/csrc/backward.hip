@@ -733,11 +733,18 @@ hipError_t launch_spmm_t(const void *vals, const void *meta, const void *X, int 
     return hipGetLastError();
 }
 
-// P, meta: as kept from the forward pass.  scratch: fp32 [BH][Lq] (-delta, passed from the first kernel to the second).
+// The row terms -delta, fp32 [BH][Lq], passed from the first kernel to the second.
+size_t backward_workspace_bytes(int BH, int Lq, int LqR, int LkR, int d) {
+    (void)LqR, (void)LkR, (void)d;
+    return ((size_t)BH * Lq * sizeof(float) + 255) / 256 * 256;
+}
+
+// P, meta: as kept from the forward pass.  ws: backward_workspace_bytes.
 hipError_t launch_backward(const void *dO, const void *Q, const void *K, const void *V, const void *O, const void *P,
-                           const void *meta, int BH, int Lq, int Lk, int LqR, int LkR, int d, float scale, float *scratch,
+                           const void *meta, int BH, int Lq, int Lk, int LqR, int LkR, int d, float scale, void *ws,
                            void *dQ, void *dK, void *dV, hipStream_t st) {
     const bool unp = LqR != Lq || LkR != Lk;
+    float *const scratch = (float *)ws;
     // 128-query workgroups where they fill the chip (three per compute unit at d = 64, two at d = 128), else 64-query ones
     const bool four = (long)BH * ((Lq + 127) / 128) >= 512;
     const unsigned grid_q = (unsigned)((long)BH * (four ? (Lq + 127) / 128 : Lq / 64));

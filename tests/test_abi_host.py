@@ -38,7 +38,8 @@ def test_sizes_follow_the_compressed_footprint():
     assert dfss.dfss_meta_bytes(s) == dense // 16          # 1/16 of the dense bits (Sec. 2.3)
     assert dfss.dense_workspace_bytes(s) >= dense
     assert dfss.dfss_workspace_bytes(s) >= dense // 2 + dense // 16
-    assert dfss.dfss_backward_workspace_bytes(s) >= dense // 2      # dS in the layout of the kept values
+    assert dfss.dfss_backward_workspace_bytes(s) == 96 * 384 * 4    # a row term per query (a multiple of 256 bytes here)
+    assert dfss.dfss_backward_workspace_bytes(Shape(1, 3, 100, 132, 64)) == 3 * 128 * 4        # ... of the padded length
     s12 = Shape(16, 12, 512, 512, 64, 1, 2)
     assert dfss.dfss_vals_bytes(s12) == 192 * 512 * 512
     assert dfss.dfss_meta_bytes(s12) == 192 * 512 * 512 // 8

@@ -162,6 +162,46 @@ def test_backward_on_grids_that_fill_the_chip(BH, Lq, Lk, d, N, M):
 
 
 @pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
+    (2, 70, 580, 128, 2, 4),       # no tile multiples
+    (9, 60, 4096, 64, 2, 4),
+    (2, 128, 256, 64, 2, 4),
+])
+def test_backward_with_a_workspace_of_exactly_the_size_it_asks_for(BH, Lq, Lk, d, N, M):
+    """Against the oracle, with poisoned scratch of exactly dfss_backward_workspace_bytes and guards behind it and behind
+    every gradient."""
+    scale = 1.0 / math.sqrt(d)
+    Q, K, V = synth.gaussian_qkv(BH, Lq, Lk, d, 1.0, seed=9900 + Lq + Lk + d)
+    dO = torch.randn(BH, Lq, d, generator=torch.Generator().manual_seed(9901 + Lk)).to(torch.bfloat16)
+    Qn, Kn, Vn, dOn = (synth.to_numpy_f32(t) for t in (Q, K, V, dO))
+    s = Shape(1, BH, Lq, Lk, d, N, M)
+    kidx, P, Pp, mp = _padded_forward(Qn, Kn, N, M, scale, s)
+    O = []
+    for h in range(BH):
+        Pd = np.zeros((Lq, s.LkP))
+        np.put_along_axis(Pd, kidx[h].astype(np.int64), P[h].astype(np.float64), axis=1)
+        O.append((Pd[:, :Lk] @ Vn[h].astype(np.float64)).astype(np.float32))
+    meta = dfss.dfss_meta_from_canonical(_dev(torch.from_numpy(mp.view(np.int16))), s)
+    guard, need = 4096, dfss.dfss_backward_workspace_bytes(s)
+    ws = torch.full((need + guard,), 0xFF, dtype=torch.uint8, device=DEV)
+    bufs = [torch.full((BH * L * d + guard,), 777.0, dtype=torch.bfloat16, device=DEV) for L in (Lq, Lk, Lk)]
+    dQ, dK, dV = (b[:b.numel() - guard].view(BH, L, d) for b, L in zip(bufs, (Lq, Lk, Lk)))
+    dfss.dfss_attention_backward(_dev(dO), _dev(Q), _dev(K), _dev(V), _dev(_bf16(np.stack(O))), _dev(_bf16(Pp)), meta, s,
+                                 scale, dQ=dQ, dK=dK, dV=dV, ws=ws[:need])
+    torch.cuda.synchronize()
+    assert bool((ws[need:] == 0xFF).all()), "wrote behind the workspace"
+    for b in bufs:
+        assert bool((b[b.numel() - guard:] == 777.0).all()), "wrote behind a gradient"
+    dQ, dK, dV = _np(dQ), _np(dK), _np(dV)
+    for h in range(BH):
+        real = kidx[h] < Lk
+        ki, Pr = np.where(real, kidx[h], 0).astype(np.int32), np.where(real, P[h], 0.0).astype(np.float32)
+        rQ, rK, rV = oracle.attention_backward(Qn[h], Kn[h], Vn[h], dOn[h], Pr, ki, scale)
+        for name, got, ref in (("dQ", dQ[h], rQ), ("dK", dK[h], rK), ("dV", dV[h], rV)):
+            tol = 2.0 ** -7 * np.max(np.abs(ref)) + 1e-4      # as above
+            assert np.max(np.abs(got - ref)) <= tol, (name, h)
+
+
+@pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
     (2, 128, 256, 64, 2, 4), (2, 192, 128, 64, 1, 2), (2, 64, 384, 128, 2, 4),
     (2, 100, 132, 64, 2, 4), (2, 70, 260, 128, 1, 2),       # no tile multiples
 ])
