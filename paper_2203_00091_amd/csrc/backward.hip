@@ -230,11 +230,14 @@ __device__ __forceinline__ float choose(uint32_t m, float x, float y) {
 // lengths Lq (a multiple of 64) and Lk (of 128).  Rows past LqR are computed on a copy of the last one and not stored; the
 // places of absent keys in a partial last block take the block's last key (their weights are 0).  Blocks that hold no real
 // key are not visited.
-template <int D, int NW, bool UNP>
+// SPLIT: `splits` workgroups share the keys of a query tile, each a run of pairs of blocks; their sums, unscaled fp32, go to
+// `part` [split][head and query][D], and k_backward_dq_merge forms dQ.
+template <int D, int NW, bool UNP, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 12 / NW : 8 / NW) void k_backward_dq(
     const __bf16 *__restrict__ dO, const __bf16 *__restrict__ V, const __bf16 *__restrict__ O,
     const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta, const __bf16 *__restrict__ K, int Lq, int Lk,
-    int LqR, int LkR, float scale, uint16_t *__restrict__ dQ, float *__restrict__ neg_delta) {
+    int LqR, int LkR, float scale, uint16_t *__restrict__ dQ, float *__restrict__ neg_delta, int splits,
+    float *__restrict__ part) {
     constexpr int THREADS = 64 * NW;
     constexpr int KEYS = 64;                 // keys per block: two 32-key tiles
     constexpr int CPR = D / 8;               // 16-byte chunks per row
@@ -248,7 +251,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 12 / NW : 8 / NW) void k_backwar
     const int tid = threadIdx.x;
     const int w = tid >> 6, l = tid & 63, lj = l & 31, h = l >> 5;
     const unsigned qtiles = (Lq + TQ - 1) / TQ;
-    const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);
+    const unsigned share = xcd_contiguous(blockIdx.x, gridDim.x);
+    const unsigned item = SPLIT ? share / (unsigned)splits : share;
+    const int sp = SPLIT ? share % (unsigned)splits : 0;
     const int qt = item % qtiles, bh = item / qtiles;
     const int q0 = qt * TQ + w * 32;
     const int nblocks = (LkR + KEYS - 1) / KEYS;
@@ -281,7 +286,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 12 / NW : 8 / NW) void k_backwar
     // four neighbours at the same one: they share K and V blocks in the L2 (512 x 512, 192 heads 28.1 -> 26.5 us against
     // one by one; 4096 x 4096, 24 heads 140 -> 137 us; d = 128, 64 heads x 2048 152.6 -> 150 us).
     const int npairs = (nblocks + 1) / 2;
-    const int rot = __builtin_amdgcn_readfirstlane((int)((item / 4) % (unsigned)npairs));
+    const int rot = __builtin_amdgcn_readfirstlane(SPLIT ? npairs * sp / splits : (int)((item / 4) % (unsigned)npairs));
+    const int visits = SPLIT ? __builtin_amdgcn_readfirstlane(npairs * (sp + 1) / splits) - rot : npairs;   // (splits <= npairs)
     issue_block(2 * rot, 0);
 
     // weights and codes of this lane's query for a pair of blocks (128 keys: a whole line of P per row), loaded one pair
@@ -315,7 +321,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 12 / NW : 8 / NW) void k_backwar
             nd -= bf16_lo_to_f32(g[e]) * bf16_lo_to_f32(o[e]) + bf16_hi_to_f32(g[e]) * bf16_hi_to_f32(o[e]);
     }
     nd += __shfl_xor(nd, 32, kWave);
-    if (h == 0 && q0 + lj < Lq) neg_delta[(size_t)bh * Lq + q0 + lj] = nd;
+    if (h == 0 && q0 + lj < Lq && (!SPLIT || sp == 0)) neg_delta[(size_t)bh * Lq + q0 + lj] = nd;
     f32x16 start;
 #pragma unroll
     for (int r = 0; r < 16; ++r) start[r] = nd;
@@ -373,8 +379,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 12 / NW : 8 / NW) void k_backwar
         }
     };
     int pair = rot;
-    for (int it = 0; it < npairs; ++it) {
-        const bool single = 2 * pair + 1 >= nblocks, last = it + 1 == npairs;
+    for (int it = 0; it < visits; ++it) {
+        const bool single = 2 * pair + 1 >= nblocks, last = it + 1 == visits;
         const int after = pair + 1 == npairs ? 0 : pair + 1;
         wait_async_copies();   // the pair's first block and its weights are in
         __syncthreads();
@@ -401,10 +407,29 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 12 / NW : 8 / NW) void k_backwar
     for (int r = 0; r < 16; ++r) {
         const int q = q0 + 8 * (r >> 2) + 4 * h + (r & 3);
         if (q >= LqR) continue;
+        const size_t row = (size_t)bh * LqR + q;
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-            dQ[((size_t)bh * LqR + q) * D + 32 * dt + lj] = (uint16_t)(pack_bf16x2(acc_q[dt][r] * scale, 0.f) & 0xFFFFu);
+        for (int dt = 0; dt < DT; ++dt) {
+            if constexpr (SPLIT) part[((size_t)sp * (gridDim.x / splits / qtiles * LqR) + row) * D + 32 * dt + lj] = acc_q[dt][r];
+            else dQ[row * D + 32 * dt + lj] = (uint16_t)(pack_bf16x2(acc_q[dt][r] * scale, 0.f) & 0xFFFFu);
+        }
     }
+}
+
+// dQ from the sums of `splits` workgroups, in a fixed order; a thread forms 8 consecutive values of the n.
+__global__ __launch_bounds__(NT) void k_backward_dq_merge(const float *__restrict__ part, int splits, size_t n, float scale,
+                                                          uint16_t *__restrict__ dQ) {
+    const size_t i = 8 * ((size_t)blockIdx.x * NT + threadIdx.x);
+    if (i >= n) return;
+    f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+#pragma unroll 4
+    for (int sp = 0; sp < splits; ++sp) {
+        const f32x4 *const src = reinterpret_cast<const f32x4 *>(part + sp * n + i);
+        a += src[0];
+        b += src[1];
+    }
+    a *= scale, b *= scale;
+    *reinterpret_cast<u32x4 *>(dQ + i) = u32x4{pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(b[0], b[1]), pack_bf16x2(b[2], b[3])};
 }
 
 // Sixteen zeros made on the spot (as a constant they are kept in sixteen registers of their own and copied from there)
@@ -733,10 +758,33 @@ hipError_t launch_spmm_t(const void *vals, const void *meta, const void *X, int 
     return hipGetLastError();
 }
 
-// The row terms -delta, fp32 [BH][Lq], passed from the first kernel to the second.
+namespace {
+
+// Workgroups that share the keys of a query tile in dQ (1: none).  A tile of 64 queries walks over the keys at the pace of
+// two waves; where a grid of such workgroups leaves half of the chip idle and the keys are many, several take a run of
+// them each.  The whole backward pass, alone and shared, us: d = 128, one head x 64 x 8192 145.6 and 21.7, 12 x 64 x 2048
+// 46.6 and 22.0, 32 x 128 x 1024 32.3 and 27.4, 12 x 512 x 4096 100 and 72; level with more than 128 tiles, and at 512 keys
+// with more than 16 (64 heads x 64 x 512 22.0 and 23.1).  At d = 64 a block takes half the time; there it is the few tiles
+// against the most keys that sharing is for (one head x 64 x 8192 90.6 and 17.4).
+int dq_splits(int BH, int Lq, int LkR, int d) {
+    const long wg = (long)BH * (Lq / 64);
+    const int npairs = (LkR + KB - 1) / KB;
+    if (d == 128 ? wg > 128 || npairs < (wg <= 16 ? 4 : 8) : wg > 8 || npairs < 32) return 1;
+    long n = 256 / wg;
+    if (n > npairs / 2) n = npairs / 2;   // two pairs of blocks each, or more
+    if (n > 32) n = 32;
+    return (int)n;
+}
+
+size_t align256(size_t x) { return (x + 255) / 256 * 256; }
+size_t delta_bytes(int BH, int Lq) { return align256((size_t)BH * Lq * sizeof(float)); }
+
+}  // namespace
+
+// The row terms -delta, fp32 [BH][Lq], then (dq_splits) the sums of the workgroups that share keys.
 size_t backward_workspace_bytes(int BH, int Lq, int LqR, int LkR, int d) {
-    (void)LqR, (void)LkR, (void)d;
-    return ((size_t)BH * Lq * sizeof(float) + 255) / 256 * 256;
+    const int n = dq_splits(BH, Lq, LkR, d);
+    return delta_bytes(BH, Lq) + (n == 1 ? 0 : align256((size_t)n * BH * LqR * d * sizeof(float)));
 }
 
 // P, meta: as kept from the forward pass.  ws: backward_workspace_bytes.
@@ -744,23 +792,26 @@ hipError_t launch_backward(const void *dO, const void *Q, const void *K, const v
                            const void *meta, int BH, int Lq, int Lk, int LqR, int LkR, int d, float scale, void *ws,
                            void *dQ, void *dK, void *dV, hipStream_t st) {
     const bool unp = LqR != Lq || LkR != Lk;
-    float *const scratch = (float *)ws;
+    float *const neg_delta = (float *)ws, *const part = (float *)((char *)ws + delta_bytes(BH, Lq));
+    const int splits = dq_splits(BH, Lq, LkR, d);
     // 128-query workgroups where they fill the chip (three per compute unit at d = 64, two at d = 128), else 64-query ones
     const bool four = (long)BH * ((Lq + 127) / 128) >= 512;
-    const unsigned grid_q = (unsigned)((long)BH * (four ? (Lq + 127) / 128 : Lq / 64));
+    const unsigned grid_q = (unsigned)((long)BH * (four ? (Lq + 127) / 128 : Lq / 64)) * splits;
     const unsigned grid_k = (unsigned)((long)BH * (Lk / KB));
-#define DFSS_DQ(DD, NW, UU)                                                                                              \
-    hipLaunchKernelGGL((k_backward_dq<DD, NW, UU>), dim3(grid_q), dim3(64 * NW), 0, st, (const __bf16 *)dO,              \
+#define DFSS_DQ(DD, NW, UU, SS)                                                                                          \
+    hipLaunchKernelGGL((k_backward_dq<DD, NW, UU, SS>), dim3(grid_q), dim3(64 * NW), 0, st, (const __bf16 *)dO,          \
                        (const __bf16 *)V, (const __bf16 *)O, (const uint32_t *)P, (const uint32_t *)meta,               \
-                       (const __bf16 *)K, Lq, Lk, LqR, LkR, scale, (uint16_t *)dQ, scratch)
+                       (const __bf16 *)K, Lq, Lk, LqR, LkR, scale, (uint16_t *)dQ, neg_delta, splits, part)
 #define DFSS_DKV(DD, UU)                                                                                                 \
     hipLaunchKernelGGL((k_backward_dkv<DD, UU>), dim3(grid_k), dim3(NT), 0, st, (const uint32_t *)P,                     \
-                       (const uint32_t *)meta, (const __bf16 *)dO, (const __bf16 *)Q, (const __bf16 *)V, scratch, Lq, Lk, \
+                       (const uint32_t *)meta, (const __bf16 *)dO, (const __bf16 *)Q, (const __bf16 *)V, neg_delta, Lq, Lk, \
                        LqR, LkR, scale, (uint16_t *)dK, (uint16_t *)dV)
-#define DFSS_BOTH(DD, UU)                                         \
-    do {                                                          \
-        if (four) DFSS_DQ(DD, 4, UU); else DFSS_DQ(DD, 2, UU);    \
-        DFSS_DKV(DD, UU);                                         \
+#define DFSS_BOTH(DD, UU)                                                \
+    do {                                                                 \
+        if (four) DFSS_DQ(DD, 4, UU, false);                             \
+        else if (splits == 1) DFSS_DQ(DD, 2, UU, false);                 \
+        else DFSS_DQ(DD, 2, UU, true);                                   \
+        DFSS_DKV(DD, UU);                                                \
     } while (0)
     if (d == 64) {
         if (unp) DFSS_BOTH(64, true); else DFSS_BOTH(64, false);
@@ -770,6 +821,10 @@ hipError_t launch_backward(const void *dO, const void *Q, const void *K, const v
 #undef DFSS_BOTH
 #undef DFSS_DKV
 #undef DFSS_DQ
+    if (splits > 1) {
+        const size_t n = (size_t)BH * LqR * d;
+        hipLaunchKernelGGL(k_backward_dq_merge, dim3((unsigned)((n / 8 + NT - 1) / NT)), dim3(NT), 0, st, part, splits, n, scale, (uint16_t *)dQ);
+    }
     return hipGetLastError();
 }
 

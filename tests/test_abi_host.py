@@ -40,6 +40,7 @@ def test_sizes_follow_the_compressed_footprint():
     assert dfss.dfss_workspace_bytes(s) >= dense // 2 + dense // 16
     assert dfss.dfss_backward_workspace_bytes(s) == 96 * 384 * 4    # a row term per query (a multiple of 256 bytes here)
     assert dfss.dfss_backward_workspace_bytes(Shape(1, 3, 100, 132, 64)) == 3 * 128 * 4        # ... of the padded length
+    assert dfss.dfss_backward_workspace_bytes(Shape(1, 1, 64, 1024, 128)) == 256 + 4 * 64 * 128 * 4   # shared keys: four sums
     s12 = Shape(16, 12, 512, 512, 64, 1, 2)
     assert dfss.dfss_vals_bytes(s12) == 192 * 512 * 512
     assert dfss.dfss_meta_bytes(s12) == 192 * 512 * 512 // 8

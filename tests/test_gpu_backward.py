@@ -162,13 +162,18 @@ def test_backward_on_grids_that_fill_the_chip(BH, Lq, Lk, d, N, M):
 
 
 @pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
-    (2, 70, 580, 128, 2, 4),       # no tile multiples
-    (9, 60, 4096, 64, 2, 4),
+    (1, 64, 512, 128, 2, 4),       # dQ: two workgroups share the keys of a query tile (d = 128: from 512 keys on)
+    (2, 128, 640, 128, 1, 2),      # ... five pairs of key blocks for two
+    (1, 1, 8192, 128, 2, 4),       # ... 32 workgroups; one query
+    (2, 70, 580, 128, 2, 4),       # ... no tile multiples; a single block in the last pair
+    (1, 64, 4096, 64, 1, 2),       # ... d = 64: from 32 pairs on
+    (3, 100, 4100, 64, 2, 4),
+    (9, 60, 4096, 64, 2, 4),       # (more than 8 tiles: one workgroup each)
     (2, 128, 256, 64, 2, 4),
 ])
 def test_backward_with_a_workspace_of_exactly_the_size_it_asks_for(BH, Lq, Lk, d, N, M):
-    """Against the oracle, with poisoned scratch of exactly dfss_backward_workspace_bytes and guards behind it and behind
-    every gradient."""
+    """Few queries against many keys, against the oracle; poisoned scratch of exactly dfss_backward_workspace_bytes and
+    guards behind it and behind every gradient."""
     scale = 1.0 / math.sqrt(d)
     Q, K, V = synth.gaussian_qkv(BH, Lq, Lk, d, 1.0, seed=9900 + Lq + Lk + d)
     dO = torch.randn(BH, Lq, d, generator=torch.Generator().manual_seed(9901 + Lk)).to(torch.bfloat16)
