@@ -232,8 +232,12 @@ __device__ __forceinline__ float choose(uint32_t m, float x, float y) {
 // key are not visited.
 // SPLIT: `splits` workgroups share the keys of a query tile, each a run of pairs of blocks; their sums, unscaled fp32, go to
 // `part` [split][head and query][D], and k_backward_dq_merge forms dQ.
+// (Second number of the bounds: waves per SIMD.  At d = 128 it is what registers (four waves) and LDS (two) allow.  At d = 64
+// that would be three; the two-wave form asks for six, which the compiler reports as out of reach, because the order of
+// instructions that it arrives at on the way is the faster one: 1 - 2 % on small grids, 4 - 6 % on unpadded lengths against
+// three (12 heads x 100 x 1000 20.9 and 22.0 us; 24 x 1024 x 1024 level).)
 template <int D, int NW, bool UNP, bool SPLIT>
-__global__ __launch_bounds__(64 * NW, D == 64 ? 12 / NW : 8 / NW) void k_backward_dq(
+__global__ __launch_bounds__(64 * NW, D == 128 ? NW / 2 : NW == 4 ? 3 : 6) void k_backward_dq(
     const __bf16 *__restrict__ dO, const __bf16 *__restrict__ V, const __bf16 *__restrict__ O,
     const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta, const __bf16 *__restrict__ K, int Lq, int Lk,
     int LqR, int LkR, float scale, uint16_t *__restrict__ dQ, float *__restrict__ neg_delta, int splits,
