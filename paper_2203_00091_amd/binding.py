@@ -1,8 +1,9 @@
 """ctypes binding of the C ABI declared in include/dfss.h.
 
-Each function has the name of the C entry point it calls and only marshals
-arguments: tensors are passed as raw device pointers, the current PyTorch HIP
-stream as the stream handle.  There is no fallback: if ``libdfss.so`` is
+Each function has the name of the C entry point it calls (dfss_attention_ragged
+calls its _split form where that is the faster one) and only marshals arguments:
+tensors are passed as raw device pointers, the current PyTorch HIP stream as the
+stream handle, and arrays that are not given are allocated.  There is no fallback: if ``libdfss.so`` is
 missing or a call reports an error, an exception is raised.
 """
 from __future__ import annotations
@@ -515,21 +516,36 @@ def dense_attention_fused_causal(Q, K, V, key_bias, s: Shape, scale: float, O=No
     return O
 
 
-def dfss_attention_ragged(Q, K, V, key_bias, s: Shape, scale: float, O=None):
-    """DFSS forward in one kernel on unpadded arrays: any Lq, Lk a multiple of 4; key_bias may be None."""
-    if O is None:
-        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
+def dfss_attention_ragged(Q, K, V, key_bias, s: Shape, scale: float, O=None, ws=None):
+    """DFSS forward on unpadded arrays: any Lq, Lk a multiple of 4; key_bias may be None.  One kernel, except for few queries
+    against many keys without a key bias (dfss_ragged_split_workspace_bytes is not 0): those calls are
+    dfss_attention_ragged_split, with ``ws`` as described there.  Elsewhere ``ws`` is not touched."""
     n = s._call.ragged_ws
     if n is None:
         n = s._call.ragged_ws = dfss_ragged_split_workspace_bytes(s)
-    if n and key_bias is None:   # few queries, many keys: several workgroups share the keys of a query tile through a workspace
-        ws = _alloc_bytes(n, Q.device)
-        st = load_library().dfss_attention_ragged_split(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                                        s._call.ref, scale, _q(O, s), _ptr(ws), n, _stream())
-    else:
-        st = load_library().dfss_attention_ragged(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
-                                                  s._call.ref, scale, _q(O, s), _stream())
+    if n and key_bias is None:
+        return dfss_attention_ragged_split(Q, K, V, None, s, scale, O, ws)
+    if O is None:
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
+    st = load_library().dfss_attention_ragged(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
+                                              s._call.ref, scale, _q(O, s), _stream())
     _check("dfss_attention_ragged", st)
+    return O
+
+
+def dfss_attention_ragged_split(Q, K, V, key_bias, s: Shape, scale: float, O=None, ws=None):
+    """dfss_attention_ragged with a workspace of dfss_ragged_split_workspace_bytes (allocated if not given), through which
+    several workgroups share the keys of a query tile: two kernels."""
+    if O is None:
+        O = torch.empty(s._call.O_shape, dtype=s._call.torch_dtype, device=Q.device)
+    if ws is None:
+        n = dfss_ragged_split_workspace_bytes(s) if key_bias is None else 0
+        if n:
+            ws = _alloc_bytes(n, Q.device)
+    st = load_library().dfss_attention_ragged_split(_q(Q, s), _kv(K, s), _kv(V, s), _bias_ptr(key_bias, s),
+                                                    s._call.ref, scale, _q(O, s), _ptr(ws),
+                                                    0 if ws is None else ws.numel() * ws.element_size(), _stream())
+    _check("dfss_attention_ragged_split", st)
     return O
 
 

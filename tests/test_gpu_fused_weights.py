@@ -12,6 +12,7 @@ whole weight matrix, which is compared with the oracle entry by entry:
 Q and K hold small integers, so every score is exact in fp32 on both sides and equal scores (ties) abound:
 the selection must then agree with the oracle's rank rule exactly, ties included.
 """
+import ctypes
 import math
 
 import numpy as np
@@ -108,6 +109,16 @@ def test_every_tiling_selects_and_weighs_like_the_oracle(variant, BH, Lq, Lk, d,
     assert ties > 100          # the tie rule was exercised
 
 
+def _ragged_without_workspace(Q, K, V, key_bias, s, scale):
+    """The C entry dfss_attention_ragged itself, at shapes whose Python call goes through a workspace."""
+    assert key_bias is None
+    O = torch.empty_like(Q)
+    st = dfss.load_library().dfss_attention_ragged(Q.data_ptr(), K.data_ptr(), V.data_ptr(), None, ctypes.byref(s.c()), scale,
+                                                   O.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    return O
+
+
 @pytest.mark.parametrize("BH,Lq,Lk,d,N,M,scale,bias", [
     (3, 1, 132, 64, 2, 4, 0.125, False),       # (fewer than 256 keys: the kernel of the masked calls)
     (3, 1, 260, 64, 2, 4, 0.125, False),       # one query; one run of keys in the last block, most waves without a block
@@ -125,7 +136,8 @@ def test_every_tiling_selects_and_weighs_like_the_oracle(variant, BH, Lq, Lk, d,
     (70, 1, 1536, 128, 2, 4, 0.125, False),    # ... three workgroups per tile
 ])
 def test_few_queries(BH, Lq, Lk, d, N, M, scale, bias):
-    """The kernel whose waves share the keys: the weights of every key, through the public call that takes it."""
+    """The kernel whose waves share the keys: the weights of every key, through the public calls that take it (where
+    several workgroups share keys, the call with a workspace and the one without)."""
     scale = float(np.float32(scale))
     Q, K, Qn, Kn = _int_qk(BH, Lq, Lk, d, seed=8700 + Lk + d + N)
     kb = None
@@ -135,9 +147,48 @@ def test_few_queries(BH, Lq, Lk, d, N, M, scale, bias):
         kb[1, 64:128] = -math.inf
     s = Shape(BH, 1, Lq, Lk, d, N, M)
     Qd, Kd, kbd = Q.to(DEV), K.to(DEV), None if kb is None else kb.to(DEV)
-    W = _weights_through_identity_v(
-        lambda V: dfss.dfss_attention_ragged(Qd, Kd, V, kbd, s, scale), BH, Lq, Lk, d, torch.bfloat16)
-    _compare(W, Qn, Kn, N, M, scale, key_bias=None if kb is None else kb.numpy())
+    calls = [dfss.dfss_attention_ragged]
+    if dfss.dfss_ragged_split_workspace_bytes(s) and not bias:
+        calls.append(_ragged_without_workspace)
+    for call in calls:
+        W = _weights_through_identity_v(lambda V: call(Qd, Kd, V, kbd, s, scale), BH, Lq, Lk, d, torch.bfloat16)
+        _compare(W, Qn, Kn, N, M, scale, key_bias=None if kb is None else kb.numpy())
+
+
+def test_shared_keys_and_their_workspace():
+    """dfss_attention_ragged_split: workspace given or allocated, poisoned, of exactly the size, guarded; shapes that share
+    nothing and calls with a key bias are dfss_attention_ragged and take no workspace."""
+    def case(BH, Lq, Lk, d):
+        g = torch.Generator().manual_seed(8800 + Lk + d)
+        s = Shape(BH, 1, Lq, Lk, d)
+        return s, [torch.randn(BH, L, d, generator=g).to(DEV, torch.bfloat16) for L in (Lq, Lk, Lk)]
+
+    for BH, Lq, Lk, d in ((12, 1, 3072, 64), (2, 16, 1540, 128), (96, 3, 4096, 64)):
+        s, (Q, K, V) = case(BH, Lq, Lk, d)
+        need = dfss.dfss_ragged_split_workspace_bytes(s)
+        assert need > 0
+        ref = dfss.dfss_attention_ragged(Q, K, V, None, s, 0.125)
+        for fill in (0x00, 0xFF):
+            ws = torch.full((need + 4096,), fill, dtype=torch.uint8, device=DEV)
+            for call in (dfss.dfss_attention_ragged, dfss.dfss_attention_ragged_split):
+                O = torch.full_like(Q, math.nan)
+                assert call(Q, K, V, None, s, 0.125, O=O, ws=ws[:need]) is O
+                torch.cuda.synchronize()
+                assert torch.equal(O, ref) and bool((ws[need:] == fill).all())
+        assert torch.equal(dfss.dfss_attention_ragged_split(Q, K, V, None, s, 0.125), ref)
+        plain = _ragged_without_workspace(Q, K, V, None, s, 0.125)
+        # the same weights, rounded to bfloat16 relative to another reference (2^-8), and one rounding of O
+        assert (plain.float() - ref.float()).abs().max() <= 2.0 ** -7 * V.float().abs().max()
+        with pytest.raises(dfss.DfssError, match="dfss_attention_ragged_split"):
+            dfss.dfss_attention_ragged(Q, K, V, None, s, 0.125, ws=ws[:need - 256])
+        bias = torch.zeros((BH, Lk), device=DEV)
+        assert torch.equal(dfss.dfss_attention_ragged_split(Q, K, V, bias, s, 0.125),
+                           dfss.dfss_attention_ragged(Q, K, V, bias, s, 0.125))
+    for BH, Lq, Lk, d in ((12, 17, 4096, 64), (12, 1, 2048, 64), (3, 100, 332, 64)):
+        s, (Q, K, V) = case(BH, Lq, Lk, d)
+        assert dfss.dfss_ragged_split_workspace_bytes(s) == 0
+        assert torch.equal(dfss.dfss_attention_ragged_split(Q, K, V, None, s, 0.125),
+                           dfss.dfss_attention_ragged(Q, K, V, None, s, 0.125))
 
 
 @pytest.mark.parametrize("variant", VARIANTS)
