@@ -823,3 +823,60 @@ def test_calls_replay_correctly_from_a_hip_graph():
         torch.cuda.synchronize()
         for k in outs:
             assert torch.equal(outs[k], eager[k]), (rep, k)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_calls_with_partial_results_replay_correctly_from_a_hip_graph(d):
+    """The calls whose workgroups hand partial results on through a workspace -- shared keys of few queries, and the
+    backward pass (row terms; sums of dQ) --, workspaces given and allocated, on poisoned scratch and outputs."""
+    s = Shape(2, 2, 3, 4100, d)                  # forward: shared keys; backward: sums of dQ
+    sb = Shape(1, 3, 192, 256, d)                # backward: the row terms only
+    scale = 1.0 / math.sqrt(d)
+    g = torch.Generator().manual_seed(9300 + d)
+
+    def randn(*shape):
+        return torch.randn(shape, generator=g).to(DEV, torch.bfloat16)
+
+    n, nb = dfss.dfss_ragged_split_workspace_bytes(s), dfss.dfss_backward_workspace_bytes(s)
+    assert n > 0 and nb > 4 * 64 * s.BH * 4
+    Q, K, V, dO = randn(4, 3, d), randn(4, 4100, d), randn(4, 4100, d), randn(4, 3, d)
+    Qb, Kb, Vb, dOb = randn(3, 192, d), randn(3, 256, d), randn(3, 256, d), randn(3, 192, d)
+    ws, wsb = torch.empty(n, dtype=torch.uint8, device=DEV), torch.empty(nb, dtype=torch.uint8, device=DEV)
+    outs = {"few": torch.empty_like(Q), "few, allocated": torch.empty_like(Q)}
+    for k, (q, kv) in {"few": (Q, K), "rows": (Qb, Kb)}.items():
+        outs |= {k + " dQ": torch.empty_like(q), k + " dK": torch.empty_like(kv), k + " dV": torch.empty_like(kv)}
+    kept = {}
+    for k, sh in (("few", s), ("rows", sb)):
+        kept[k] = (torch.empty((sh.BH, sh.LqP, sh.Lc), dtype=torch.bfloat16, device=DEV),
+                   torch.empty((sh.BH * sh.LqP * sh.meta_words,), dtype=torch.int16, device=DEV),
+                   torch.empty((sh.BH, sh.Lq, d), dtype=torch.bfloat16, device=DEV))
+
+    def run_all():
+        dfss.dfss_attention_ragged(Q, K, V, None, s, scale, O=outs["few"], ws=ws)
+        dfss.dfss_attention_ragged(Q, K, V, None, s, scale, O=outs["few, allocated"])
+        for k, sh, q, kk, v, do, w in (("few", s, Q, K, V, dO, wsb), ("rows", sb, Qb, Kb, Vb, dOb, None)):
+            vals, meta, O = kept[k]
+            dfss.dfss_sddmm_prune(q, kk, sh, scale, vals=vals, meta=meta)
+            dfss.dfss_sparse_softmax(vals, sh)
+            dfss.dfss_spmm(vals, meta, v, sh, O=O)
+            dfss.dfss_attention_backward(do, q, kk, v, O, vals, meta, sh, scale, dQ=outs[k + " dQ"], dK=outs[k + " dK"],
+                                         dV=outs[k + " dV"], ws=w)
+
+    run_all()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run_all()
+    for rep in range(3):
+        for t in (Q, dO, Qb, dOb):
+            t.copy_(randn(*t.shape))
+        run_all()                                   # eager reference on the new inputs
+        torch.cuda.synchronize()
+        eager = {k: v.clone() for k, v in outs.items()}
+        assert torch.equal(eager["few"], eager["few, allocated"])
+        for t in (*outs.values(), ws.view(torch.int16), wsb.view(torch.int16)):
+            t.view(torch.int16).fill_(-1 if rep % 2 else 0)      # 0xFF bytes, or zeros
+        graph.replay()
+        torch.cuda.synchronize()
+        for k in outs:
+            assert torch.isfinite(eager[k].float()).all() and torch.equal(outs[k], eager[k]), (rep, k)
