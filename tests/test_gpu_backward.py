@@ -79,8 +79,8 @@ def _oracle_backward_case(BH, Lq, Lk, d, N, M, seed, scale):
 
 
 @pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
-    (2, 128, 256, 64, 2, 4),       # 32 queries per wave in the dS kernel
-    (2, 192, 384, 64, 1, 2),       # 16 queries per wave, key range split three ways
+    (2, 128, 256, 64, 2, 4),
+    (2, 192, 384, 64, 1, 2),       # three tiles of 64 queries, three pairs of key blocks
     (2, 128, 128, 128, 2, 4),      # d = 128
 ])
 def test_backward_against_oracle_through_the_same_selection(BH, Lq, Lk, d, N, M):
@@ -132,10 +132,13 @@ def test_forward_stages_then_backward_on_exact_scores():
     (192, 320, 384, 64, 1, 2),     # 128-query workgroups, the last one of a head half empty
     (96, 704, 704, 64, 2, 4),      # 11 blocks of 64 keys: a single one in the last pair
     (140, 512, 256, 128, 2, 4),    # d = 128, 128-query workgroups
+    (192, 300, 388, 64, 2, 4),     # no tile multiples: the last workgroup of a head half empty, and absent rows and keys
+    (180, 330, 260, 128, 1, 2),
 ])
 def test_backward_on_grids_that_fill_the_chip(BH, Lq, Lk, d, N, M):
     """Waves that compete for the matrix unit see its results later than a lone wave does; sampled heads against the
-    oracle, differentiating through the GPU's own forward results."""
+    oracle, differentiating through the GPU's own forward results.  What the rows of the weights past Lq hold must not
+    matter (NaN here); nothing is written behind a gradient."""
     scale = 1.0 / math.sqrt(d)
     Q, K, V = synth.gaussian_qkv(BH, Lq, Lk, d, 1.0, seed=9800 + Lq + d)
     g = torch.Generator().manual_seed(9801 + d)
@@ -145,9 +148,14 @@ def test_backward_on_grids_that_fill_the_chip(BH, Lq, Lk, d, N, M):
     P, meta = dfss.dfss_sddmm_prune(Qd, Kd, s, scale)
     dfss.dfss_sparse_softmax(P, s)
     O = dfss.dfss_spmm(P, meta, Vd, s)
-    dQ, dK, dV = dfss.dfss_attention_backward(dOd, Qd, Kd, Vd, O, P, meta, s, scale)
+    P[:, Lq:] = math.nan
+    bufs = [torch.full((BH * L * d + 4096,), 777.0, dtype=torch.bfloat16, device=DEV) for L in (Lq, Lk, Lk)]
+    dQ, dK, dV = (x[:BH * L * d].view(BH, L, d) for x, L in zip(bufs, (Lq, Lk, Lk)))
+    dfss.dfss_attention_backward(dOd, Qd, Kd, Vd, O, P, meta, s, scale, dQ=dQ, dK=dK, dV=dV)
     canon = dfss.dfss_meta_to_canonical(meta, s)
     torch.cuda.synchronize()
+    for x in bufs:
+        assert bool((x[-4096:] == 777.0).all()), "wrote behind a gradient"
     for h in (0, BH // 3, BH // 2 + 1, BH - 1):
         kidx = oracle.decode_meta(canon[h].cpu().numpy().view(np.uint16), s.LkP)[:Lq]
         Ph = _np(P[h])[:Lq]
@@ -270,7 +278,7 @@ def test_what_is_not_finite_reaches_the_kept_places_only(what, BH, Lq, Lk, d, N,
 
 
 # ----------------------------------------------------------------------------------
-# lengths that are not tile multiples: P, meta and dS' keep the layout of the padded lengths
+# lengths that are not tile multiples: P and meta keep the layout of the padded lengths
 # ----------------------------------------------------------------------------------
 def _padded_forward(Qn, Kn, N, M, scale, s):
     """The oracle's forward results in the padded layout: absent keys count as -inf; the rows past Lq hold finite
@@ -293,9 +301,9 @@ def _padded_forward(Qn, Kn, N, M, scale, s):
 
 
 @pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
-    (2, 100, 132, 64, 2, 4),       # fused dQ; one partial query tile, a partial second key block
-    (2, 250, 516, 64, 1, 2),       # 32 queries per wave in the dS kernel (LqP = 256), 4 real keys in the last block
-    (2, 70, 260, 128, 2, 4),       # d = 128: dQ through the forward product kernel
+    (2, 100, 132, 64, 2, 4),       # one partial query tile, a partial second key block
+    (2, 250, 516, 64, 1, 2),       # 4 real keys in the last block
+    (2, 70, 260, 128, 2, 4),       # d = 128
 ])
 def test_backward_on_unpadded_lengths(BH, Lq, Lk, d, N, M):
     scale = 1.0 / math.sqrt(d)
