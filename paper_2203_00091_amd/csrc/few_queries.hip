@@ -11,8 +11,8 @@
 //   V     by asynchronous copies, one block ahead, into LDS that belongs to the wave (the transposing read needs LDS)
 // No barrier before the merge: a wave waits for its own copies only.
 // Measured: a round of one block per wave (128 KiB per workgroup) takes 2.3 us whether 12 or 96 workgroups run, 57 GB/s per
-// compute unit; 1024 heads x 1 query x 4096 keys 177 us (6 TB/s).  96 heads x 1 x 4096: 47.9 us with 64-query workgroups,
-// 21.1 us here.
+// compute unit; 1024 heads x 1 query x 4096 keys 177 us (6 TB/s).  96 heads x 1 x 4096, warm: 47.9 us with 64-query
+// workgroups, 21.1 us here (from memory 28.4; shared between two workgroups each, below, 19.6 and 24.1).
 #include <math.h>
 
 #include <type_traits>
@@ -358,17 +358,20 @@ hipError_t launch_fused_attention_few(const void *Q, const void *K, const void *
     return launch_any<false>(Q, K, V, key_bias, H, BH, Lq, Lk, d, mode, scale, O, 1, nullptr, st);
 }
 
-// Workgroups per query tile where a workspace lets several share its keys (1 query, d = 64, in us, alone and shared, the
-// merge kernel included): 12 heads x 4096 keys 20.5 and 11.6, 12 x 3072 16.3 and 11.2, 72 x 3072 16.6 and 14.7, 96 x 4096 21.1
-// and 19.5; d = 128: 12 x 1536 16.8 and 11.5, 96 x 4096 41.2 and 34.0.  With 120 heads the chip pulls its keys as fast alone
-// (21.6 and 23.1; d = 128, 1536 keys 18.7 and 19.6).  Not with a key bias: each workgroup would scan the whole bias row
-// first (half of 4096 keys masked, 12 heads: 16.5 and 18.1).
+// Workgroups per query tile where a workspace lets several share its keys.  1 query, d = 64, us, alone and shared, the merge
+// kernel included, K and V warm: 12 heads x 4096 keys 20.5 and 11.6, 12 x 3072 16.3 and 11.2, 64 x 3072 16.5 and 14.0, 96 x
+// 4096 21.2 and 19.6; d = 128: 12 x 1536 16.8 and 11.5, 96 x 4096 41.1 and 34.4.  The line at 104 tiles (which share in
+// twos): with the fewest keys that share, warm, it breaks even at 98 .. 104 (d = 64, 3072 keys: 98 heads 16.8 and 16.7, 104
+// 16.9 and 17.3, 112 17.0 and 18.1; d = 128, 1536 keys: 104 18.3 and 18.0, 112 18.5 and 18.7), with 8192 at 112 and beyond.
+// Cold, as in a model of many layers, it pays up to 128 tiles (4096 keys: 96 heads 28.4 and 24.1, 104 28.7 and 25.7, 128
+// 29.6 and 29.2).  Not with a key bias: each workgroup would scan the whole bias row first (half of 4096 keys masked, 12
+// heads: 16.5 and 18.1).
 int few_queries_splits(int BH, int Lq, int Lk, int d) {
     const long tiles = (long)BH * ((Lq + 15) / 16);
     const int nblocks = (Lk + KB - 1) / KB, nw = waves_of(d);
     long n = 256 / tiles;                        // all workgroups on the chip at once, one per compute unit
     if (n > nblocks / (2 * nw)) n = nblocks / (2 * nw);   // at least two blocks per wave
-    return tiles > 96 || nblocks < 6 * nw || n < 2 ? 1 : (int)n;
+    return tiles > 104 || nblocks < 6 * nw || n < 2 ? 1 : (int)n;
 }
 
 size_t few_queries_workspace_bytes(int BH, int Lq, int Lk, int d) {

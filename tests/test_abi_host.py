@@ -114,8 +114,9 @@ def test_errors_are_reported_before_any_launch():
     ws = ctypes.c_void_p((p.value + 255) // 256 * 256)
     assert need > 0 and call(None, need) == E_NULL and call(ws, need - 1) == E_WS
     assert call(ctypes.c_void_p(ws.value + 16), need) == E_SHAPE
+    assert dfss.dfss_ragged_split_workspace_bytes(Shape(1, 104, 1, 4096, 64)) == 104 * 2 * 16 * (64 + 2) * 4
     assert all(dfss.dfss_ragged_split_workspace_bytes(x) == 0 for x in (
-        Shape(1, 12, 17, 4096, 64), Shape(1, 97, 1, 4096, 64), Shape(1, 12, 1, 2048, 64), Shape(1, 12, 1, 4096, 64, 1, 2, 2)))
+        Shape(1, 12, 17, 4096, 64), Shape(1, 105, 1, 4096, 64), Shape(1, 12, 1, 2048, 64), Shape(1, 12, 1, 4096, 64, 1, 2, 2)))
     for scale in (0.0, -1.0, float("inf"), float("nan")):
         assert lib.dfss_sddmm_prune(aligned, aligned, ctypes.byref(ok), scale, aligned, aligned, None) == E_UNSUP
     odd = ctypes.c_void_p(aligned.value + 2)
