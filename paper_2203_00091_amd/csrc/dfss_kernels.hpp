@@ -2,9 +2,16 @@
 // interface is include/dfss.h).  Every launcher assumes validated arguments.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace dfss {
+
+// A scale that is a power of two can be folded into Q without a rounding.
+inline bool is_pow2(float x) {
+    int e;
+    return frexpf(x, &e) == 0.5f;
+}
 
 // key_bias (where present): fp32 [BH / H][Lk] added to the scaled scores before the selection, or
 // nullptr for none (then H is ignored).

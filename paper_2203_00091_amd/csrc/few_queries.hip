@@ -307,11 +307,6 @@ __global__ __launch_bounds__(2 * D) void k_few_merge(const float *__restrict__ p
         pack_bf16x2(a0[0], a0[1]), pack_bf16x2(a0[2], a0[3]), pack_bf16x2(a1[0], a1[1]), pack_bf16x2(a1[2], a1[3])};
 }
 
-inline bool is_pow2(float x) {
-    int e;
-    return frexpf(x, &e) == 0.5f;
-}
-
 constexpr int waves_of(int d) { return d == 64 ? 8 : 4; }
 
 template <int D, int MODE, int NW, bool SPLIT>

@@ -745,11 +745,6 @@ __global__ __launch_bounds__(NT) void k_merge_split(const float *__restrict__ pa
     }
 }
 
-inline bool is_pow2(float x) {
-    int e;
-    return frexpf(x, &e) == 0.5f;
-}
-
 template <int MODE, int NQ, bool MASKED, bool RAGGED = false>
 hipError_t launch_nq(const void *Q, const void *K, const void *V, const float *key_bias, int H,
                      const uint8_t *block_mask, int causal, int BH, int Lq, int Lk, int d, float scale, void *O,

@@ -521,11 +521,6 @@ __global__ __launch_bounds__(NT, 2) void k_sddmm32(const __bf16 *__restrict__ Q,
     }
 }
 
-inline bool is_pow2(float x) {
-    int e;
-    return frexpf(x, &e) == 0.5f;
-}
-
 template <int MODE, int NQ, bool BIAS, bool CAUSAL>
 hipError_t launch_nq(const void *Q, const void *K, const float *key_bias, int H, int BH, int Lq, int Lk,
                      int d, float scale, void *out, void *meta, hipStream_t st) {
