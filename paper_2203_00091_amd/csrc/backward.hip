@@ -495,9 +495,9 @@ __device__ __forceinline__ f32x16 expand_non_finite(u32x4 kept, bf16x16 eye, uin
 // UNP as above; the rows LqR .. Lq - 1 of P, whatever they hold, count as zeros.
 // What is infinite or NaN has to stay at the kept places, but the two products are formed at every place: a row of V that no
 // query kept, a row of dO, a weight that is infinite or NaN meets zeros there, and 0 times it is NaN.  Such a NaN always
-// reaches the sums.  A workgroup whose sums are all finite stores them; another one starts again, CAREFUL: non-finite
-// weights are expanded apart, and dS is formed by the multiplication in which 0 times anything is 0.
-// w: the wave.  Result, the same in every thread of the workgroup: nothing was stored, start again.
+// reaches the sums.  A workgroup without a NaN in its sums is done; another one starts again, CAREFUL: non-finite weights are
+// expanded apart, and dS is formed by the multiplication in which 0 times anything is 0.
+// w: the wave.  Result, the same in every thread of the workgroup: start again.
 template <int D>
 struct DkvPlace {   // the kernel's LDS in 16-byte units (an access is one of a few lane offsets plus a constant);
                     // every place but the V operand twice, BUF apart
@@ -694,43 +694,43 @@ __device__ __forceinline__ bool dkv_pass(
         if (qb + 1 < nq) block(std::integral_constant<int, 1>{}, qb + 1);
     }
 
-    // Is some sum infinite or NaN?  (The same care in every pass: 5 - 18 % on small grids; this test: 0.35 us a call.)  The waves
-    // agree through LDS, at a place of the buffer that the last block did not use.
-    if constexpr (!CAREFUL) {
-        uint32_t largest = 0u;   // magnitude, as bits
+    // acc[dt][r]: key 8 (r / 4) + 4 (lane / 32) + r % 4 of the wave's 32, column 32 dt + lane % 32
+    auto store = [&]() {
+        const int lane = __lane_id();   // (asked for again: a register less through the loop)
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
+        for (int r = 0; r < 16; ++r) {
+            const int key = jblk * KB + 32 * w + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+            if (UNP && key >= LkR) continue;
+            const size_t at = ((size_t)bh * LkR + key) * D + (lane & 31);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const uint32_t v = __float_as_uint(acc_v[dt][r]) & 0x7FFFFFFFu, k = __float_as_uint(acc_k[dt][r]) & 0x7FFFFFFFu;
-                largest = largest > v ? largest : v;
-                largest = largest > k ? largest : k;
+            for (int dt = 0; dt < DT; ++dt) {
+                dV[at + 32 * dt] = (uint16_t)(pack_bf16x2(acc_v[dt][r], 0.f) & 0xFFFFu);
+                dK[at + 32 * dt] = (uint16_t)(pack_bf16x2(acc_k[dt][r] * scale, 0.f) & 0xFFFFu);
             }
+        }
+    };
+    if constexpr (CAREFUL) {
+        store();
+        return false;
+    } else {
+        // Did some sum become NaN?  A NaN in the row of a key fills the whole row, so one column of each tile tells; their total
+        // is NaN with it (or infinite).  The care in every pass would cost 5 - 18 % on small grids.  The waves agree through LDS,
+        // at a place of the buffer that the last block did not use, while the stores of the ones without a NaN are on their way.
+        f32x4 total = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < 16; ++r) total[r & 3] += acc_v[0][r], total[r & 3] += acc_k[0][r];
+        uint32_t t = __float_as_uint((total[0] + total[1]) + (total[2] + total[3]));
+        asm("" : "+v"(t));   // (as a number, under the flags of this library, it could not be NaN)
         uint32_t *const flags = reinterpret_cast<uint32_t *>(Smem + (((nq - 1) & 1) ? 0 : BUF));
-        const bool mine = __any(largest >= 0x7F800000u);
+        const bool mine = __any((t & 0x7F800000u) == 0x7F800000u);
         if (__lane_id() == 0) flags[w] = mine ? 1u : 0u;
+        if (__builtin_expect(!mine, 1)) store();
         __syncthreads();
         const uint32_t any = flags[0] | flags[1] | flags[2] | flags[3];
-        if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)any) != 0, 0)) {
-            __syncthreads();   // everybody has read the flags; the buffers are free
-            return true;
-        }
+        if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)any) == 0, 1)) return false;
+        __syncthreads();   // everybody has read the flags; the buffers are free
+        return true;
     }
-
-    // acc[dt][r]: key 8 (r / 4) + 4 (lane / 32) + r % 4 of the wave's 32, column 32 dt + lane % 32
-    const int lane = __lane_id();   // (asked for again: a register less through the loop)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int key = jblk * KB + 32 * w + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (UNP && key >= LkR) continue;
-        const size_t at = ((size_t)bh * LkR + key) * D + (lane & 31);
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-            dV[at + 32 * dt] = (uint16_t)(pack_bf16x2(acc_v[dt][r], 0.f) & 0xFFFFu);
-            dK[at + 32 * dt] = (uint16_t)(pack_bf16x2(acc_k[dt][r] * scale, 0.f) & 0xFFFFu);
-        }
-    }
-    return false;
 }
 
 template <int D, bool UNP>
