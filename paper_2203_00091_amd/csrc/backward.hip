@@ -201,9 +201,9 @@ __global__ __launch_bounds__(NT, 2) void k_spmm_t(const uint32_t *__restrict__ A
 // ------------------------------------------------------------------------------------------------
 // The gradients.  dS is formed twice, once per direction of the sums it enters, and never written: the kept weights and
 // the metadata are read twice (2 x 1.125 B per score) instead of P twice, dS' written and read once, the metadata three
-// times (4.4 B), and the product that dS' costs a second time runs on the matrix unit.  Together, before (dS' written,
-// one transposed product each for dV and dK) and now, 4096 x 4096 with 24 heads: 505 -> 312 us; 512 x 512 with 192 heads:
-// 76 -> 59 us; d = 128, 2048 x 2048 with 64 heads: 485 -> 382 us.
+// times (4.4 B), and the product that dS' costs a second time runs on the matrix unit.  The whole call, warm, before (dS'
+// written, one transposed product each for dV and dK) and now, 4096 x 4096 with 24 heads: 518 -> 298 us; 512 x 512 with 192
+// heads: 71 -> 51 us; d = 128, 2048 x 2048 with 64 heads: 500 -> 354 us.
 // ------------------------------------------------------------------------------------------------
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -491,7 +491,9 @@ __device__ __forceinline__ f32x16 expand_non_finite(u32x4 kept, bf16x16 eye, uin
 // kernel), started from -delta of the rows; dS is one multiplication per element.  Rounded to bfloat16 both tiles are the A
 // operands (row = key) of the two products, contraction index 8 m' + 4 h + x of step m = register order, against dO
 // and Q from the transposing LDS read in the same order.
-// Bound by the matrix unit: 13 instructions of 32 cycles per 32 x 32 tile at d = 64 (25 at d = 128).
+// 13 matrix instructions of 32 cycles per 32 x 32 tile at d = 64 (25 at d = 128) keep the matrix unit busy 56 % of the time
+// (4096 x 4096, 24 heads; the vector unit 31 %; d = 128, 64 heads x 2048: 53 and 21 %).  The rest is waiting: one wait for the
+// copies and one barrier per block, with P, which comes from memory, asked for one block ahead.
 // UNP as above; the rows LqR .. Lq - 1 of P, whatever they hold, count as zeros.
 // What is infinite or NaN has to stay at the kept places, but the two products are formed at every place: a row of V that no
 // query kept, a row of dO, a weight that is infinite or NaN meets zeros there, and 0 times it is NaN.  Such a NaN always

@@ -282,9 +282,10 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
 // O = A_sparse V from compressed weights.  Bound by the stream of kept weights (1.125 bytes per score, read once): little
 // arithmetic per byte, so what counts is that enough of it is in flight.  A wave takes the weights of TWO 128-key blocks at
 // a time -- 256 contiguous bytes of every row -- and the loads of the next pair are issued before the first of the two is
-// multiplied and waited for after the second; the wait for the second block's V leaves them in flight.  4096 x 4096 with 24
-// heads (453 MB of weights and codes): 126 us with one block at a time, 113 us so; d = 128, 64 heads x 2048 (302 MB): 106 and
-// 97 us.  V comes out of the L2 for every workgroup: with 64 queries per workgroup (twice the V) 136 and 124 us.
+// multiplied and waited for after the second; the wait for the second block's V leaves them in flight.  In a training step,
+// 4096 x 4096 with 24 heads (453 MB of weights and codes): 126 us with one block at a time, 113 us so; d = 128, 64 heads x 2048
+// (302 MB): 106 and 97 us (the call by itself, over and over: 108 -> 100 and 93 -> 88).  V comes out of the L2 for every
+// workgroup: with 64 queries per workgroup (twice the V) 136 and 124 us.
 // Blocks go in pairs (the last pair may be a single block).  The workgroups start at different pairs and wrap around: the
 // rows of P are a power of two apart for the usual lengths, and workgroups in step would read the same few memory
 // channels at a time.  At d = 64 four neighbours start together and share V blocks (119 -> 113 us); at d = 128, where only
@@ -463,7 +464,7 @@ hipError_t launch_av(const void *P, const void *meta, const void *V, int BH, int
 
 // Which kernel takes compressed weights.  wg: tiles of 64 queries; nblocks: 128-key blocks; rb2: 128 queries per workgroup.
 // k_spmm against k_av, warm (the weights as the softmax left them), over 900 shapes:
-//   the weights and codes exceed the last-level cache (256 MB): 1.0 - 1.3 times as fast (24 heads x 4096 x 4096 126 -> 113 us;
+//   the weights and codes exceed the last-level cache (256 MB): 1.0 - 1.3 times as fast (24 heads x 4096 x 4096 108 -> 100 us;
 //     d = 128, 12 x 4096 x 6144 1.3) -- at d = 128 only where many workgroups share a head's V (with 256 queries per head,
 //     768 .. 1024 tiles, it takes 1.2 times as long: V comes from the caches for every workgroup, twice as many bytes as at
 //     d = 64, and the workgroups of a head are not at the same block)
