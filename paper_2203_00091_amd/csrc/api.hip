@@ -625,7 +625,7 @@ dfss_status dfss_attention_backward(const void *dO, const void *Q, const void *K
         return DFSS_ERR_SHAPE;
     if ((reinterpret_cast<uintptr_t>(ws) & (kAlign - 1)) != 0) return DFSS_ERR_SHAPE;
     if (D.f32 && !D.split) return DFSS_ERR_UNSUPPORTED;
-    if (ws_bytes < dfss_backward_workspace_bytes(s)) return DFSS_ERR_WORKSPACE;
+    if (ws_bytes < (D.f32 ? align_up(dfss_vals_bytes(s)) : dfss::backward_workspace_least(D.BH, D.Lq))) return DFSS_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     if (D.f32) {
         void *dS = ws;   // scale * dS in the compressed layout of P
@@ -635,8 +635,8 @@ dfss_status dfss_attention_backward(const void *dO, const void *Q, const void *K
         if (e == hipSuccess) e = dfss::launch_spmm_t_split(dS, meta, Q, D.BH, D.Lq, D.Lk, D.d, dK, st);     // dK = dS'^T Q
         return hip_status(e);
     }
-    return hip_status(dfss::launch_backward(dO, Q, K, V, O, P, meta, D.BH, D.Lq, D.Lk, D.LqR, D.LkR, D.d, scale, ws, dQ,
-                                            dK, dV, st));
+    return hip_status(dfss::launch_backward(dO, Q, K, V, O, P, meta, D.BH, D.Lq, D.Lk, D.LqR, D.LkR, D.d, scale, ws,
+                                            ws_bytes, dQ, dK, dV, st));
 }
 
 size_t dfss_backward_workspace_bytes(const dfss_shape *s) {

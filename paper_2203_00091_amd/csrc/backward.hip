@@ -787,19 +787,22 @@ size_t delta_bytes(int BH, int Lq) { return align256((size_t)BH * Lq * sizeof(fl
 
 }  // namespace
 
-// The row terms -delta, fp32 [BH][Lq], then (dq_splits) the sums of the workgroups that share keys.
+// The row terms -delta, fp32 [BH][Lq] (the least that the pass needs), then (dq_splits) the sums of the workgroups that share
+// keys.
+size_t backward_workspace_least(int BH, int Lq) { return delta_bytes(BH, Lq); }
 size_t backward_workspace_bytes(int BH, int Lq, int LqR, int LkR, int d) {
     const int n = dq_splits(BH, Lq, LkR, d);
     return delta_bytes(BH, Lq) + (n == 1 ? 0 : align256((size_t)n * BH * LqR * d * sizeof(float)));
 }
 
-// P, meta: as kept from the forward pass.  ws: backward_workspace_bytes.
+// P, meta: as kept from the forward pass.  ws: backward_workspace_least or more; keys are shared if the sums fit (the whole is
+// less for a large grid than for a small one, and a workspace made for the largest shape has to do for all).
 hipError_t launch_backward(const void *dO, const void *Q, const void *K, const void *V, const void *O, const void *P,
                            const void *meta, int BH, int Lq, int Lk, int LqR, int LkR, int d, float scale, void *ws,
-                           void *dQ, void *dK, void *dV, hipStream_t st) {
+                           size_t ws_bytes, void *dQ, void *dK, void *dV, hipStream_t st) {
     const bool unp = LqR != Lq || LkR != Lk;
     float *const neg_delta = (float *)ws, *const part = (float *)((char *)ws + delta_bytes(BH, Lq));
-    const int splits = dq_splits(BH, Lq, LkR, d);
+    const int splits = ws_bytes < backward_workspace_bytes(BH, Lq, LqR, LkR, d) ? 1 : dq_splits(BH, Lq, LkR, d);
     // 128-query workgroups where they fill the chip (three per compute unit at d = 64, two at d = 128), else 64-query ones
     const bool four = (long)BH * ((Lq + 127) / 128) >= 512;
     const unsigned grid_q = (unsigned)((long)BH * (four ? (Lq + 127) / 128 : Lq / 64)) * splits;

@@ -68,12 +68,13 @@ hipError_t launch_fused_attention_split_rows(const void *Q, const void *K, const
 // dV = P^T dO and dK = dS^T Q of the backward pass.
 hipError_t launch_spmm_t(const void *vals, const void *meta, const void *X, int BH, int Lq, int Lk, int LqR, int LkR,
                          int d, void *out, hipStream_t st);
-// Backward pass through the fixed selection (P, meta as kept from the forward pass).  ws: backward_workspace_bytes, 256-byte
-// aligned.
+// Backward pass through the fixed selection (P, meta as kept from the forward pass).  ws: backward_workspace_least or more,
+// 256-byte aligned; with backward_workspace_bytes workgroups may share keys.
+size_t backward_workspace_least(int BH, int Lq);
 size_t backward_workspace_bytes(int BH, int Lq, int LqR, int LkR, int d);
 hipError_t launch_backward(const void *dO, const void *Q, const void *K, const void *V, const void *O, const void *P,
                            const void *meta, int BH, int Lq, int Lk, int LqR, int LkR, int d, float scale, void *ws,
-                           void *dQ, void *dK, void *dV, hipStream_t st);
+                           size_t ws_bytes, void *dQ, void *dK, void *dV, hipStream_t st);
 // The 4-byte mode (Sec. 2.3: float data, 1:2): fp32 Q, K, V, kept scores, weights and O; metadata = one
 // 4-bit code per kept float, 32-bit words in the blocked order [BH, Lq/16, Lk/64, 16, 4].
 hipError_t launch_sddmm_prune_f32(const void *Q, const void *K, const float *key_bias, int H, int BH, int Lq, int Lk,

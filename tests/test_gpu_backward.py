@@ -214,6 +214,36 @@ def test_backward_with_a_workspace_of_exactly_the_size_it_asks_for(BH, Lq, Lk, d
             assert np.max(np.abs(got - ref)) <= tol, (name, h)
 
 
+def test_backward_with_a_workspace_that_holds_the_row_terms_only():
+    """A workspace of a larger shape's size serves a smaller shape whose workgroups would share keys: the same gradients
+    but for the order of the sums in dQ; one that does not hold the row terms is refused."""
+    large, s = Shape(1, 64, 512, 512, 128), Shape(1, 2, 64, 2048, 128)
+    least, need = 4 * s.BH * s.LqP, dfss.dfss_backward_workspace_bytes(s)
+    assert least <= dfss.dfss_backward_workspace_bytes(large) < need
+    g = torch.Generator().manual_seed(9950)
+    Q, K, V, dO = (torch.randn(s.BH, L, s.d, generator=g).to(DEV, torch.bfloat16) for L in (s.Lq, s.Lk, s.Lk, s.Lq))
+    scale = 1.0 / math.sqrt(s.d)
+    P, meta = dfss.dfss_sddmm_prune(Q, K, s, scale)
+    dfss.dfss_sparse_softmax(P, s)
+    O = dfss.dfss_spmm(P, meta, V, s)
+
+    def run(n):
+        ws = torch.full((n + 4096,), 0xFF, dtype=torch.uint8, device=DEV)
+        out = dfss.dfss_attention_backward(dO, Q, K, V, O, P, meta, s, scale, ws=ws[:n])
+        torch.cuda.synchronize()
+        assert bool((ws[n:] == 0xFF).all())
+        return out
+
+    shared, alone, alone2 = run(need), run(dfss.dfss_backward_workspace_bytes(large)), run(least)
+    for a, b, c in zip(shared, alone, alone2):
+        assert torch.equal(b, c)
+        # fp32 sums in another order, rounded to bfloat16: half a unit in the last place apart at most, and rarely
+        assert (a.float() - b.float()).abs().max() <= 2.0 ** -8 * b.float().abs().max()
+    assert torch.equal(shared[1], alone[1]) and torch.equal(shared[2], alone[2])      # dK, dV
+    with pytest.raises(dfss.DfssError):
+        run(least - 256)
+
+
 @pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
     (2, 128, 256, 64, 2, 4), (2, 192, 128, 64, 1, 2), (2, 64, 384, 128, 2, 4),
     (2, 100, 132, 64, 2, 4), (2, 70, 260, 128, 1, 2),       # no tile multiples
