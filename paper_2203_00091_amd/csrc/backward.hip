@@ -383,7 +383,9 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? NW / 2 : NW == 4 ? 3 : 6) void 
         }
     };
     int pair = rot;
+    Pace<> pace(visits);
     for (int it = 0; it < visits; ++it) {
+        pace.at(visits - it);
         const bool single = 2 * pair + 1 >= nblocks, last = it + 1 == visits;
         const int after = pair + 1 == npairs ? 0 : pair + 1;
         wait_async_copies();   // the pair's first block and its weights are in
@@ -691,7 +693,9 @@ __device__ __forceinline__ bool dkv_pass(
             }
         }
     };
+    Pace<> pace(nq);
     for (int qb = 0; qb < nq; qb += 2) {
+        pace.at(nq - qb);
         block(std::integral_constant<int, 0>{}, qb);
         if (qb + 1 < nq) block(std::integral_constant<int, 1>{}, qb + 1);
     }

@@ -383,7 +383,9 @@ __global__ __launch_bounds__(NT, 2) void k_sddmm32(const __bf16 *__restrict__ Q,
     u32x4 *const meta_row4 = reinterpret_cast<u32x4 *>(
         meta + (((size_t)bh * (Lq / 16) + ((q0 + lj) >> 4)) * (Lk / KB) * 16 + (lj & 15)) * 4);
 
+    Pace<> pace(blocks_per_wg);
     for (int it = 0; it < blocks_per_wg; ++it) {
+        pace.at(blocks_per_wg - it);
         const int jb = blk(it);
         const int buf = it & 1;
         // Block `it` must have landed.  The stores of the previous iteration were issued after its

@@ -199,7 +199,9 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
     if (nblocks > 1) load_a(blk(1), a_nxt);
     if constexpr (SOFTMAX) softmax_block(a_cur);
 
+    Pace<> pace(nblocks);
     for (int jb = 0; jb < nblocks; ++jb) {   // jb: place in the order
+        pace.at(nblocks - jb);
         const int buf = jb & 1;
         wait_async_copies();  // vmcnt(0): this block's V copies and the A loads of the next block are in
         __syncthreads();
@@ -397,7 +399,9 @@ __global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void k_spmm(const uint32_t *__
         }
     };
     int pair = rot;
+    Pace<> pace(npairs);
     for (int it = 0; it < npairs; ++it) {
+        pace.at(npairs - it);
         const bool single = 2 * pair + 1 >= nblocks, last = it + 1 == npairs;
         const int after = pair + 1 == npairs ? 0 : pair + 1;
         wait_async_copies();   // the pair's first block and its weights are in

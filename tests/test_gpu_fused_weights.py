@@ -343,6 +343,32 @@ def test_default_call_with_half_a_workgroup_left_over_on_a_large_grid(BH, Lq, Lk
     assert ties > 100
 
 
+@pytest.mark.parametrize("path,BH,Lq,Lk,d,N,M,scale", [
+    ("attention", 288, 128, 128, 64, 2, 4, 0.125),     # two blocks: every mark but the first is missed
+    ("attention", 136, 256, 384, 64, 1, 2, 0.125),     # six blocks
+    ("attention", 160, 128, 1152, 64, 2, 4, 0.125),    # keys of a block split over two waves, 18 blocks
+    ("attention", 264, 128, 256, 128, 2, 4, 0.0625),
+    ("causal", 136, 256, 256, 128, 2, 4, 0.0625),      # workgroups of two and of four blocks
+    ("lengths", 272, 128, 256, 64, 2, 4, 0.125),       # one block to four
+])
+def test_workgroups_that_keep_level_on_their_compute_unit(path, BH, Lq, Lk, d, N, M, scale):
+    """More workgroups than compute units: the one-kernel path gives up wave priority at marks along the keys.  Weight by weight
+    against the oracle, every sixteenth head."""
+    Q, K, Qn, Kn = _int_qk(BH, Lq, Lk, d, seed=8900 + Lk + d)
+    s = Shape(BH, 1, Lq, Lk, d, N, M)
+    Qd, Kd = Q.to(DEV), K.to(DEV)
+    lens = torch.arange(BH, dtype=torch.int32) * 37 % Lk + 1
+    call, mask, bias = {
+        "attention": (lambda V: dfss.dfss_attention(Qd, Kd, V, s, scale), None, None),
+        "causal": (lambda V: dfss.dfss_attention_causal(Qd, Kd, V, None, s, scale),
+                   np.triu(np.full((Lq, Lk), -np.inf, np.float32), 1), None),
+        "lengths": (lambda V: dfss.dfss_attention_varlen(Qd, Kd, V, lens.to(DEV), s, scale), None,
+                    synth.key_padding_bias(lens, Lk).numpy()[::16]),
+    }[path]
+    W = _weights_through_identity_v(call, BH, Lq, Lk, d, torch.bfloat16)
+    _compare(W[::16], Qn[::16], Kn[::16], N, M, scale, key_bias=bias, mask=mask)
+
+
 def test_float_one_kernel_path():
     """The 4-byte mode's one-kernel path (split products; integer inputs are exact in its bfloat16 pieces)."""
     BH, Lq, Lk, d = 2, 128, 256, 64
