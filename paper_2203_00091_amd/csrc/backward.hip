@@ -250,10 +250,10 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? NW / 2 : NW == 4 ? 3 : 6) void 
     constexpr int STEPS = D / 16;
     constexpr int DT = D / 32;
     constexpr int TQ = 32 * NW;
-    __shared__ u32x4 Vs[2][TILE], Kr[2][TILE];
+    __shared__ u32x4 Vs[2][TILE], Kr[2][TILE], Ps[NW][32 * 8];
 
     const int tid = threadIdx.x;
-    const int w = tid >> 6, l = tid & 63, lj = l & 31, h = l >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, lj = l & 31, h = l >> 5;
     const unsigned qtiles = (Lq + TQ - 1) / TQ;
     const unsigned share = xcd_contiguous(blockIdx.x, gridDim.x);
     const unsigned item = SPLIT ? share / (unsigned)splits : share;
@@ -294,23 +294,28 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? NW / 2 : NW == 4 ? 3 : 6) void 
     const int visits = SPLIT ? __builtin_amdgcn_readfirstlane(npairs * (sp + 1) / splits) - rot : npairs;   // (splits <= npairs)
     issue_block(2 * rot, 0);
 
-    // weights and codes of this lane's query for a pair of blocks (128 keys: a whole line of P per row), loaded one pair
-    // ahead: v[2 i + t] = keys 64 i + 32 t + 16 h .. +15 of the pair, slot 2 t + i of the codes their 32-key word
-    const int prow = q0 + lj < Lq ? q0 + lj : Lq - 1;
-    const u32x4 *const p_row = reinterpret_cast<const u32x4 *>(P + ((size_t)bh * Lq + prow) * (size_t)(Lk / 4)) + h;
-    const u32x4 *const m_row = reinterpret_cast<const u32x4 *>(meta) + ((size_t)bh * (Lq / 16) + (prow >> 4)) * (Lk / KB) * 16 + (prow & 15);
-    struct Kept {
+    // Weights and codes of the wave's queries for a pair of blocks (128 keys: a whole line of P per row), asked for one pair
+    // ahead.  The weights go through LDS, whole lines at a time: loaded by the lane that needs them, one row per lane, an instruction
+    // takes 64 address cycles instead of 16, and the address unit was busy 70 % of the time (4096 x 4096, 24 heads: whole
+    // backward pass 296 -> 284 us; d = 128, 64 heads x 2048 362 -> 351; 512 x 512, 192 heads 53.1 -> 50.7; small grids level).
+    // Row r, chunk c (keys 16 c .. +15) at r * 8 + (c ^ operand_row_swizzle(r)); copy i brings rows 8 i .. +7, for which the
+    // pattern is that of copy i % 2.  (Waves past the last query read the last 32 rows.)
+    const int pq0 = q0 < Lq ? q0 : Lq - 32;
+    const uint64_t p_base = uniform_address(P + ((size_t)bh * Lq + pq0) * (size_t)(Lk / 4));
+    const uint32_t p_off = (uint32_t)(l >> 3) * (uint32_t)Lk + 16u * ((l & 7) ^ operand_row_swizzle<8, 32>(l >> 3));
+    const uint32_t lds_p = lds_address(&Ps[w][0]);
+    const u32x4 *const m_row = reinterpret_cast<const u32x4 *>(meta) + ((size_t)bh * (Lq / 16) + ((pq0 + lj) >> 4)) * (Lk / KB) * 16 + (lj & 15);
+    constexpr int KEPT_LOADS = 5;
+    auto load_kept = [&](int pair) {   // returns the codes: slot 2 t + i the word of 32 keys 64 i + 32 t .. +31 of the pair
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            async_copy16(p_base + (uint64_t)pair * 128u + (uint64_t)(8 * i) * (uint64_t)Lk, i & 1 ? p_off ^ 64u : p_off, lds_p + 16u * 64 * i);
+        return m_row[(size_t)pair * 16];
+    };
+    struct Kept {   // v[2 i + t] = keys 64 i + 32 t + 16 h .. +15 of the pair
         u32x4 v[4], codes;
     };
-    constexpr int KEPT_LOADS = 5;
-    auto load_kept = [&](int pair) {
-        Kept r;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) r.v[i] = p_row[8 * pair + 2 * i];
-        r.codes = m_row[(size_t)pair * 16];
-        return r;
-    };
-    Kept next = load_kept(rot);
+    u32x4 next_codes = load_kept(rot);
 
     bf16x8 bq[STEPS];
     float nd = 0.f;   // -delta of query lj
@@ -390,9 +395,14 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? NW / 2 : NW == 4 ? 3 : 6) void 
         const int after = pair + 1 == npairs ? 0 : pair + 1;
         wait_async_copies();   // the pair's first block and its weights are in
         __syncthreads();
-        const Kept cur = next;
         if (!single) issue_block(2 * pair + 1, 1);
-        if (!last) next = load_kept(after);
+        Kept cur;
+        cur.codes = next_codes;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) cur.v[i] = Ps[w][lj * 8 + ((2 * i + h) ^ operand_row_swizzle<8, 32>(lj))];
+        // (the weights have to be in registers before their place is given to the next ones)
+        asm volatile("" : "+v"(cur.v[0]), "+v"(cur.v[1]), "+v"(cur.v[2]), "+v"(cur.v[3]) : : "memory");
+        if (!last) next_codes = load_kept(after);
         block(std::integral_constant<int, 0>{}, cur);
         if (single) {   // (the other buffer is free: everybody is past its use)
             __syncthreads();
