@@ -7,8 +7,7 @@
 // through the same kernel.  The dense variant (P V of Eq. 1, for the baseline) shares the
 // V staging and uses v_mfma_f32_16x16x32_bf16.
 //
-// k_av: compressed weights, compressed SCORES (SOFTMAX: two-kernel forward pass) or dense weights; k_spmm: compressed weights
-// again, where their stream is what bounds the product (see pairs_pay).
+// k_spmm: compressed weights; k_av: compressed SCORES (SOFTMAX: two-kernel forward pass) or dense weights.
 //
 // The product on scores takes the kept SCORES of stage 1 instead of weights and applies the softmax
 // on the way (Sec. 3.1; the max-subtracted form of App. A.1.3 with a running reference m in the place of the
@@ -41,7 +40,8 @@ constexpr int KB = 128;   // keys per block
 // UNPADDED: V holds LkR <= Lk keys per head and O LqR <= Lq rows, while P and meta have the layout of the padded
 // lengths Lq (a multiple of 64) and Lk (of 128).  The weights of the absent keys are 0 (their scores were -inf); their
 // places in a partial last block of V are filled with the block's last real key, and rows past LqR are not stored.
-template <int D, bool SPARSE, int RB, bool SOFTMAX, bool UNPADDED = false>
+// SPARSE: compressed scores, turned into weights on the way; else dense weights.
+template <int D, bool SPARSE, int RB, bool UNPADDED = false>
 __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta,
                                               const __bf16 *__restrict__ V, int Lq, int Lk, int LqR, int LkR,
                                               uint16_t *__restrict__ O) {
@@ -50,7 +50,7 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
     constexpr int LPT = TILE / NT;      // direct-to-LDS loads per thread per block
     constexpr int DS = D / 16;          // 16-column output tiles
     constexpr int TQ = 64 * RB;         // queries per workgroup
-    static_assert(!SOFTMAX || SPARSE, "the softmax is folded into the sparse product only");
+    constexpr bool SOFTMAX = SPARSE;
     __shared__ u32x4 Vs[2][TILE];
 
     const int tid = threadIdx.x;
@@ -282,85 +282,94 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
 }
 
 // O = A_sparse V from compressed weights.  Bound by the stream of kept weights (1.125 bytes per score, read once): little
-// arithmetic per byte, so what counts is that enough of it is in flight.  A wave takes the weights of TWO 128-key blocks at
-// a time -- 256 contiguous bytes of every row -- and the loads of the next pair are issued before the first of the two is
-// multiplied and waited for after the second; the wait for the second block's V leaves them in flight.  In a training step,
-// 4096 x 4096 with 24 heads (453 MB of weights and codes): 126 us with one block at a time, 113 us so; d = 128, 64 heads x 2048
-// (302 MB): 106 and 97 us (the call by itself, over and over: 108 -> 100 and 93 -> 88).  V comes out of the L2 for every
-// workgroup: with 64 queries per workgroup (twice the V) 136 and 124 us.
-// Blocks go in pairs (the last pair may be a single block).  The workgroups start at different pairs and wrap around: the
+// arithmetic per byte, so what counts is that the loads cost few cycles and that enough of them are in flight.
+// The weights of a wave's rows come by asynchronous copies, whole 128-byte lines, into LDS of the wave's own; there every lane
+// picks up its row.  Loaded by the lane that needs them, one row per lane, an instruction takes 64 address cycles instead
+// of 16, and the address unit was busy 75 % of the time (4096 x 4096, 24 heads).  As soon as a block's weights are in registers the
+// copies of the block PD further on are issued into their place.  Before (register loads; pairs of blocks where the weights
+// exceed the cache) and now, us, the call over and over: d = 64, 24 heads x 4096 x 4096 100 -> 89 (403 MB of weights, 5.1 TB/s with
+// the codes), 24 x 4000 x 4000 118 -> 89, 24 x 1024 x 1024 9.4 -> 7.5, 192 x 512 x 512 15.6 -> 13.7; d = 128, 64 x 2048 x 2048 87.6 ->
+// 83.3, 24 x 2048 x 2048 39.0 -> 27.1, 64 x 512 x 512 9.9 -> 8.5.
+// V comes out of the L2 for every workgroup, one block ahead.  The workgroups start at different blocks and wrap around: the
 // rows of P are a power of two apart for the usual lengths, and workgroups in step would read the same few memory
-// channels at a time.  At d = 64 four neighbours start together and share V blocks (119 -> 113 us); at d = 128, where only
-// two workgroups run on a compute unit, every one starts on its own (97 against 103 us).
-template <int D, int RB, bool UNPADDED>
-__global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void k_spmm(const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta,
-                                                              const __bf16 *__restrict__ V, int Lq, int Lk, int LqR, int LkR,
-                                                              uint16_t *__restrict__ O) {
-    constexpr int CPR = D / 8;          // 16-byte chunks per V row
-    constexpr int TILE = KB * CPR;      // chunks per V block
-    constexpr int LPT = TILE / NT;      // direct-to-LDS loads per thread per block
-    constexpr int DS = D / 16;          // 16-column output tiles
-    constexpr int TQ = 64 * RB;         // queries per workgroup
-    __shared__ u32x4 Vs[2][TILE];
+// channels at a time.  At d = 64 four neighbours start together and share V blocks; at d = 128 every one starts on its own.
+// (Two blocks of weights ahead at d = 64: 102 us instead of 89, as two workgroups per compute unit are left of three; a wave of
+// its own for V, 64 keys at a time, in front of two blocks of weights: 111.)
+// VB: V buffers, one if there is one block of keys.
+template <int D, int RB, int NW, int PD, bool UNPADDED, int VB = 2>
+__global__ __launch_bounds__(64 * NW, D == 128 ? 2 : VB == 1 ? 5 : NW == 8 ? 4 : 3) void k_spmm(
+    const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta, const __bf16 *__restrict__ V, int Lq, int Lk, int LqR, int LkR,
+    uint16_t *__restrict__ O) {
+    constexpr int THREADS = 64 * NW;
+    constexpr int CPR = D / 8;              // 16-byte chunks per V row
+    constexpr int TILE = KB * CPR;          // chunks per V block
+    constexpr int LPT = TILE / THREADS;     // copies per thread and V block
+    constexpr int DS = D / 16;              // 16-column output tiles
+    constexpr int TQ = 16 * RB * NW;        // queries per workgroup
+    constexpr int PT = 16 * RB * 8;         // chunks of a wave's kept weights of one block (128 bytes per row)
+    constexpr int PL = PT / 64;             // copies per thread for them
+    constexpr bool CODES_LDS = PD > 1;      // (with one block in flight every wait is for everything, and the codes come in registers)
+    constexpr int CT = CODES_LDS ? 16 * RB : 0;   // chunks of their codes
+    __shared__ u32x4 Vs[VB][TILE], Ps[NW][PD][PT + CT];
 
     const int tid = threadIdx.x;
-    const int w = tid >> 6, l = tid & 63, li = l & 15, kb = l >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, li = l & 15, kb = l >> 4;
 
-    const unsigned qtiles = Lq / TQ;
+    const unsigned qtiles = (Lq + TQ - 1) / TQ;
     const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);
     const int qt = item % qtiles;
     const int bh = item / qtiles;
     const int rb0 = (qt * TQ >> 4) + w * RB;   // first 16-row block of this wave
+    const int rbp = rb0 * 16 < Lq ? rb0 : Lq / 16 - RB;   // (a wave past the last query reads the last rows and stores nothing)
     const int nblocks = Lk / KB;
     const int meta_slot = ((kb & 1) << 1) | (kb >> 1);   // where the word of 32-key chunk kb sits in a row's 16 bytes
 
-    // LDS position p (16-byte units) = row * CPR + (c ^ tr_row_swizzle(row)) holds chunk c of key `row`
+    // LDS position p (16-byte units) = row * CPR + (c ^ v_swizzle(row)) holds chunk c of key `row` (the pattern of k_av)
+    auto v_swizzle = [](int row) { return CPR == 16 ? (row & 3) << 1 : tr_row_swizzle<CPR>(row); };
     int v_row[LPT], v_chunk[LPT];
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
-        const int p = i * NT + tid;
+        const int p = i * THREADS + tid;
         v_row[i] = p / CPR;
-        v_chunk[i] = ((p % CPR) ^ tr_row_swizzle<CPR>(v_row[i])) * 8;
+        v_chunk[i] = ((p % CPR) ^ v_swizzle(v_row[i])) * 8;
     }
     const uint32_t lds_v = lds_address(&Vs[0][w * 64]);   // this wave's 1 KB slice of copy 0, buffer 0
+    const uint32_t lds_p = lds_address(&Ps[w][0][0]);
     const uint64_t v_base = uniform_address(V + (size_t)bh * LkR * D);
-    auto issue_block = [&](int jb, int buf) {
+    auto issue_v = [&](int jb, int buf) {
         const uint64_t src = v_base + (uint64_t)jb * (KB * D * 2);
         const int last = UNPADDED ? LkR - jb * KB - 1 : KB - 1;   // the block's last real key
 #pragma unroll
         for (int i = 0; i < LPT; ++i)
-            async_copy16(src, 2u * ((UNPADDED && v_row[i] > last ? last : v_row[i]) * D + v_chunk[i]), lds_v + 16u * (buf * TILE + i * NT));
+            async_copy16(src, 2u * ((UNPADDED && v_row[i] > last ? last : v_row[i]) * D + v_chunk[i]), lds_v + 16u * (buf * TILE + i * THREADS));
+    };
+    // The wave's kept weights of a block: row r, chunk c (keys 16 c .. +15) at r * 8 + (c ^ ((r >> 1) & 7)); copy i brings rows
+    // 8 i .. +7, for which the pattern is that of copy i % 2.
+    const uint64_t p_base = uniform_address(P + ((size_t)bh * Lq + (size_t)rbp * 16) * (size_t)(Lk / 4));
+    const uint32_t p_off = (uint32_t)(l >> 3) * (uint32_t)Lk + 16u * ((l & 7) ^ (l >> 4));
+    const uint32_t *const m_row = meta + (((size_t)bh * (Lq / 16) + rbp) * nblocks * 16 + li) * 4 + meta_slot;
+    const uint64_t c_base = uniform_address(meta + (((size_t)bh * (Lq / 16) + rbp) * nblocks * 16) * 4);
+    constexpr int P_LOADS = PL + 1;         // (CODES_LDS)
+    uint32_t codes[RB];
+    auto issue_p = [&](int jb, int buf) {
+        const uint64_t src = p_base + (uint64_t)jb * 128u;
+#pragma unroll
+        for (int i = 0; i < PL; ++i)
+            async_copy16(src + (uint64_t)(8 * i) * (uint64_t)Lk, i & 1 ? p_off ^ 64u : p_off, lds_p + 16u * (buf * (PT + CT) + i * 64));
+        if constexpr (CODES_LDS) {
+            if (l < 16 * RB)
+                async_copy16(c_base + (uint64_t)jb * 256u, (uint32_t)(l >> 4) * nblocks * 256u + 16u * (l & 15), lds_p + 16u * (buf * (PT + CT) + PT));
+        } else {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) codes[rb] = m_row[((size_t)rb * nblocks + jb) * 64];
+        }
     };
 
-    // A operand of a pair: kept weights of keys 128 jb + 32 kb .. +31 (32 bytes) and their codes, both blocks
-    struct Kept {
-        u32x4 v[RB][2][2];
-        uint32_t idx[RB][2];
-    };
-    constexpr int KEPT_LOADS = 6 * RB;
-    const u32x4 *const p_row = reinterpret_cast<const u32x4 *>(P + ((size_t)bh * Lq + (size_t)rb0 * 16 + li) * (size_t)(Lk / 4)) + 2 * kb;
-    const uint32_t *const m_row = meta + (((size_t)bh * (Lq / 16) + rb0) * nblocks * 16 + li) * 4 + meta_slot;
-    auto load_kept = [&](int pair) {
-        Kept r;
-        // (a single last block is loaded twice: the number of loads is fixed)
-        const int second = 2 * pair + 1 < nblocks ? 1 : 0;
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int jb = 2 * pair + (i ? second : 0);
-                const u32x4 *const pr = p_row + (size_t)rb * 16 * (Lk / 16) + 8 * jb;
-                r.v[rb][i][0] = pr[0];
-                r.v[rb][i][1] = pr[1];
-                r.idx[rb][i] = m_row[((size_t)rb * nblocks + jb) * 64];
-            }
-        return r;
-    };
-
-    const int npairs = (nblocks + 1) / 2;
-    const int rot = __builtin_amdgcn_readfirstlane((int)((D == 64 ? item / 4 : item) % (unsigned)npairs));
-    issue_block(2 * rot, 0);
-    Kept next = load_kept(rot);
+    const int rot = __builtin_amdgcn_readfirstlane((int)((D == 64 ? item / 4 : item) % (unsigned)nblocks));
+    auto blk = [&](int it) { return it + rot < nblocks ? it + rot : it + rot - nblocks; };
+    issue_v(blk(0), 0);
+    issue_p(blk(0), 0);
+    if (PD == 2 && nblocks > 1) issue_p(blk(1), 1);
 
     f32x4 acc[RB][DS];
 #pragma unroll
@@ -371,13 +380,32 @@ __global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void k_spmm(const uint32_t *__
     // transposing read: lane li of a 16-lane group addresses V[key0 + li/4][col0 + 4*(li%4)]
     const int tr_row = li >> 2, tr_sub = (li >> 1) & 1, tr_byte = 8 * (li & 1);
 
-    // one block; buf: its LDS buffer and its place in the pair
-    auto block = [&](auto parity, const Kept &cur) {
+    // block `it` in the order of visits; buf: its V buffer
+    auto block = [&](auto parity, int it) {
         constexpr int buf = decltype(parity)::value;
+        constexpr int pb = PD == 2 ? buf : 0;
+        // V and the weights of this block are in (PD = 2: the weights of the next one, issued after this V, stay in flight)
+        if (PD == 2 && it + 1 < nblocks) wait_async_copies_keep<P_LOADS>();
+        else wait_async_copies();
+        __syncthreads();
+        u32x4 a[RB][2];
+        uint32_t idx[RB];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            if constexpr (CODES_LDS) idx[rb] = reinterpret_cast<const uint32_t *>(&Ps[w][pb][PT + 16 * rb + li])[meta_slot];
+            else idx[rb] = codes[rb];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) a[rb][h] = Ps[w][pb][(16 * rb + li) * 8 + ((2 * kb + h) ^ ((li >> 1) & 7))];
+        }
+        if (VB == 2 && it + 1 < nblocks) issue_v(blk(it + 1), buf ^ 1);
+        // (the weights have to be in registers before their place is given to the next ones)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) asm volatile("" : "+v"(a[rb][0]), "+v"(a[rb][1]), "+v"(idx[rb]) : : "memory");
+        if (it + PD < nblocks) issue_p(blk(it + PD), pb);
         const char *vbase = reinterpret_cast<const char *>(&Vs[buf][0]);
         auto tr = [&](int key0, int ds) {
             const int row = key0 + tr_row;
-            return lds_read_tr16(vbase + (row * CPR + ((2 * ds + tr_sub) ^ tr_row_swizzle<CPR>(row))) * 16 + tr_byte);
+            return lds_read_tr16(vbase + (row * CPR + ((2 * ds + tr_sub) ^ v_swizzle(row))) * 16 + tr_byte);
         };
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -391,37 +419,19 @@ __global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void k_spmm(const uint32_t *__
                     bf16x16, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15));
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) {
-                    const bf16x8 a = __builtin_bit_cast(bf16x8, cur.v[rb][buf][h]);
-                    if (h == 0) acc[rb][ds] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(a, b, acc[rb][ds], (int)cur.idx[rb][buf], 0, 0);
-                    else acc[rb][ds] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(a, b, acc[rb][ds], (int)cur.idx[rb][buf], 0, 1);
+                    const bf16x8 x = __builtin_bit_cast(bf16x8, a[rb][h]);
+                    if (h == 0) acc[rb][ds] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(x, b, acc[rb][ds], (int)idx[rb], 0, 0);
+                    else acc[rb][ds] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(x, b, acc[rb][ds], (int)idx[rb], 0, 1);
                 }
             }
         }
     };
-    int pair = rot;
-    Pace<> pace(npairs);
-    for (int it = 0; it < npairs; ++it) {
-        pace.at(npairs - it);
-        const bool single = 2 * pair + 1 >= nblocks, last = it + 1 == npairs;
-        const int after = pair + 1 == npairs ? 0 : pair + 1;
-        wait_async_copies();   // the pair's first block and its weights are in
-        __syncthreads();
-        const Kept cur = next;
-        if (!single) issue_block(2 * pair + 1, 1);
-        if (!last) next = load_kept(after);
-        block(std::integral_constant<int, 0>{}, cur);
-        if (single) {   // (everybody has to be past the buffer's use)
-            __syncthreads();
-            if (!last) issue_block(2 * after, 0);
-        } else {
-            // the second block is in; the weights of the next pair, issued after it, stay in flight
-            if (!last) wait_async_copies_keep<KEPT_LOADS>();
-            else wait_async_copies();
-            __syncthreads();
-            if (!last) issue_block(2 * after, 0);
-            block(std::integral_constant<int, 1>{}, cur);
-        }
-        pair = after;
+    Pace<> pace(nblocks);
+    for (int it = 0; it < nblocks; it += 2) {
+        pace.at(nblocks - it);
+        block(std::integral_constant<int, 0>{}, it);
+        if constexpr (VB == 1) break;
+        else if (it + 1 < nblocks) block(std::integral_constant<int, 1>{}, it + 1);
     }
 
     // acc[rb][ds][r] = O[q][16 ds + li], q = 16 (rb0 + rb) + 4 kb + r
@@ -430,7 +440,7 @@ __global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void k_spmm(const uint32_t *__
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int qrow = (rb0 + rb) * 16 + 4 * kb + r;
-            if (UNPADDED && qrow >= LqR) continue;
+            if (qrow >= LqR) continue;
             const size_t q = (size_t)bh * LqR + qrow;
 #pragma unroll
             for (int ds = 0; ds < DS; ++ds)
@@ -438,13 +448,13 @@ __global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void k_spmm(const uint32_t *__
         }
 }
 
-template <bool SPARSE, bool SOFTMAX = false>
+template <bool SPARSE>
 hipError_t launch_av(const void *P, const void *meta, const void *V, int BH, int Lq, int Lk, int LqR, int LkR, int d,
                   void *O, hipStream_t st) {
     if (LqR != Lq || LkR != Lk) {   // unpadded lengths: 64-query workgroups (Lq is a multiple of 64)
         const unsigned grid = (unsigned)((long)BH * (Lq / 64));
 #define DFSS_LAUNCH(DD)                                                                                             \
-    hipLaunchKernelGGL((k_av<DD, SPARSE, 1, SOFTMAX, true>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P,     \
+    hipLaunchKernelGGL((k_av<DD, SPARSE, 1, true>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P,     \
                        (const uint32_t *)meta, (const __bf16 *)V, Lq, Lk, LqR, LkR, (uint16_t *)O)
         if (d == 64) DFSS_LAUNCH(64); else DFSS_LAUNCH(128);
 #undef DFSS_LAUNCH
@@ -455,7 +465,7 @@ hipError_t launch_av(const void *P, const void *meta, const void *V, int BH, int
     bool rb2 = (Lq % 128 == 0) && ((long)BH * (Lq / 128) >= 512);
     const unsigned grid = (unsigned)((long)BH * (Lq / (rb2 ? 128 : 64)));
 #define DFSS_LAUNCH(DD, RR)                                                                                   \
-    hipLaunchKernelGGL((k_av<DD, SPARSE, RR, SOFTMAX>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P,              \
+    hipLaunchKernelGGL((k_av<DD, SPARSE, RR>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P,              \
                        (const uint32_t *)meta, (const __bf16 *)V, Lq, Lk, Lq, Lk, (uint16_t *)O)
     if (d == 64) {
         if (rb2) DFSS_LAUNCH(64, 2); else DFSS_LAUNCH(64, 1);
@@ -466,36 +476,46 @@ hipError_t launch_av(const void *P, const void *meta, const void *V, int BH, int
     return hipGetLastError();
 }
 
-// Which kernel takes compressed weights.  wg: tiles of 64 queries; nblocks: 128-key blocks; rb2: 128 queries per workgroup.
-// k_spmm against k_av, warm (the weights as the softmax left them), over 900 shapes:
-//   the weights and codes exceed the last-level cache (256 MB): 1.0 - 1.3 times as fast (24 heads x 4096 x 4096 108 -> 100 us;
-//     d = 128, 12 x 4096 x 6144 1.3) -- at d = 128 only where many workgroups share a head's V (with 256 queries per head,
-//     768 .. 1024 tiles, it takes 1.2 times as long: V comes from the caches for every workgroup, twice as many bytes as at
-//     d = 64, and the workgroups of a head are not at the same block)
-//   d = 64, a workgroup per compute unit at most: 1.04 - 1.3 (one head x 4096 x 4096 20.3 -> 18.8 us); an odd number of
-//     blocks costs a barrier with nothing in flight: level at 9 blocks, 0.93 - 0.97 at 3
-//   d = 64, nearly four 64-query workgroups per compute unit: 1.0 - 1.1
-//   elsewhere, out of the caches: 0.66 - 1.05 (d = 64, 12 heads x 2048 x 2048 16.0 -> 17.2 us, 192 x 384 x 384 11.8 -> 13.5)
-inline bool pairs_pay(int d, long wg, int nblocks, int LqR, bool rb2) {
-    const bool streams = wg * nblocks * (64 * KB * 9 / 8) >= 256l << 20;
-    if (d == 128) return streams && LqR >= 2048;
-    return streams || (wg <= 256 ? nblocks >= 8 || (nblocks >= 4 && nblocks % 2 == 0) : !rb2 && wg >= 880 && nblocks >= 12);
-}
-
+// The product on kept weights.  Queries per workgroup, measured over 40 shapes (us):
+//   64 where 128-query workgroups would not fill the chip.  d = 64, three of those per compute unit at most: up to 511 of them
+//     (384 of them, 24 heads x 2048 x 2048: 19.8 against 19.9; 256, 32 x 1024 x 1024: 9.2 against 10.3; 768 of them, 24 x
+//     4096 x 4096: 120 against 89).  d = 128: up to 256 workgroups of 64 queries (12 x 1024 x 1024 9.7 against 11.2; with 384, 48 x
+//     512 x 512 8.2 against 7.9)
+//   256, eight waves, at d = 64 where 128-query workgroups would be more than the three per compute unit that fit and the larger
+//     ones all fit at once (64 x 2048 x 2048 59.5 against 76.1, 224 x 512 x 512 16.1 against 16.9, 80 x 2048 x 2048, too many, 96.7
+//     against 88.7, 512 x 256 x 256 13.6 against 13.1)
+//   256 at d = 128 on long sequences: V is read half as often and there is room for two blocks of weights in
+//     flight; from a workgroup per compute unit on (32 x 2048 x 2048 31.0 against 33.5, 64 x 2048 x 2048 83.3 against 88.0; 24 x
+//     2048 x 2048 28.1 against 27.1) and 16 blocks of keys on (64 x 1024 x 1024 20.9 against 19.7)
+// A larger tile only if not more than an eighth is added to the queries.
 hipError_t launch_sparse(const void *P, const void *meta, const void *V, int BH, int Lq, int Lk, int LqR, int LkR, int d,
                          void *O, hipStream_t st) {
     const bool unp = LqR != Lq || LkR != Lk;
-    // two row blocks per wave when that still leaves two workgroups per compute unit (as below)
-    const bool rb2 = !unp && Lq % 128 == 0 && (long)BH * (Lq / 128) >= 512;
-    if (!pairs_pay(d, (long)BH * (Lq / 64), Lk / KB, LqR, rb2)) return launch_av<true>(P, meta, V, BH, Lq, Lk, LqR, LkR, d, O, st);
-    const unsigned grid = (unsigned)((long)BH * (Lq / (rb2 ? 128 : 64)));
-#define DFSS_LAUNCH(DD, RR, UU)                                                                                      \
-    hipLaunchKernelGGL((k_spmm<DD, RR, UU>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P, (const uint32_t *)meta, \
-                       (const __bf16 *)V, Lq, Lk, LqR, LkR, (uint16_t *)O)
+    auto tiles = [&](int tq) { return (Lq + tq - 1) / tq; };
+    auto fits = [&](int tq) { return 8 * (tiles(tq) * tq - Lq) <= Lq; };
+    int tq = 64;
+    if (fits(128) && (d == 64 ? (long)BH * tiles(128) >= 512 : (long)BH * tiles(64) > 256)) tq = 128;
+    if (fits(256) && (d == 64 ? Lk >= 512 && (long)BH * tiles(128) > 768 && (long)BH * tiles(256) <= 512 : Lk >= 2048 && (long)BH * tiles(256) >= 256))
+        tq = 256;
+    const unsigned grid = (unsigned)((long)BH * tiles(tq));
+#define DFSS_LAUNCH(DD, RR, WW, PP, VV)                                                                               \
+    do {                                                                                                              \
+        if (unp)                                                                                                      \
+            hipLaunchKernelGGL((k_spmm<DD, RR, WW, PP, true, VV>), dim3(grid), dim3(64 * WW), 0, st, (const uint32_t *)P, \
+                               (const uint32_t *)meta, (const __bf16 *)V, Lq, Lk, LqR, LkR, (uint16_t *)O);           \
+        else                                                                                                          \
+            hipLaunchKernelGGL((k_spmm<DD, RR, WW, PP, false, VV>), dim3(grid), dim3(64 * WW), 0, st, (const uint32_t *)P, \
+                               (const uint32_t *)meta, (const __bf16 *)V, Lq, Lk, LqR, LkR, (uint16_t *)O);           \
+    } while (0)
     if (d == 64) {
-        if (unp) DFSS_LAUNCH(64, 1, true); else if (rb2) DFSS_LAUNCH(64, 2, false); else DFSS_LAUNCH(64, 1, false);
+        if (tq == 64) DFSS_LAUNCH(64, 1, 4, 1, 2);
+        else if (tq == 256) DFSS_LAUNCH(64, 2, 8, 1, 2);
+        else if (Lk == KB) DFSS_LAUNCH(64, 2, 4, 1, 1);   // more workgroups at a time (1024 heads x 128 x 128 10.4 -> 9.7 us)
+        else DFSS_LAUNCH(64, 2, 4, 1, 2);
     } else {
-        if (unp) DFSS_LAUNCH(128, 1, true); else if (rb2) DFSS_LAUNCH(128, 2, false); else DFSS_LAUNCH(128, 1, false);
+        if (tq == 64) DFSS_LAUNCH(128, 1, 4, 1, 2);
+        else if (tq == 128) DFSS_LAUNCH(128, 2, 4, 1, 2);
+        else DFSS_LAUNCH(128, 2, 8, 2, 2);
     }
 #undef DFSS_LAUNCH
     return hipGetLastError();
@@ -510,7 +530,7 @@ hipError_t launch_spmm(const void *vals, const void *meta, const void *V, int BH
 
 hipError_t launch_softmax_spmm(const void *scores, const void *meta, const void *V, int BH, int Lq, int Lk, int LqR,
                                int LkR, int d, void *O, hipStream_t st) {
-    return launch_av<true, true>(scores, meta, V, BH, Lq, Lk, LqR, LkR, d, O, st);
+    return launch_av<true>(scores, meta, V, BH, Lq, Lk, LqR, LkR, d, O, st);
 }
 
 hipError_t launch_dense_av(const void *P, const void *V, int BH, int Lq, int Lk, int LqR, int LkR, int d, void *O,

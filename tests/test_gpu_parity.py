@@ -226,6 +226,41 @@ def test_stage3_spmm_pairs_of_key_blocks(BH, Lq, Lk, d, N, M):
 
 
 @pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
+    (512, 64, 128, 64, 2, 4),      # 64 queries per workgroup (the half-empty tile of 128 would add half)
+    (64, 1088, 256, 64, 1, 2),     # d = 64: 128 queries, the last workgroup of a head half empty
+    (32, 1088, 384, 128, 2, 4),    # ... d = 128
+    (64, 1000, 380, 64, 2, 4),     # ... no tile multiples
+    (520, 128, 128, 64, 1, 2),     # ... one block of keys, one V buffer
+    (600, 100, 100, 64, 2, 4),     # ... no tile multiples
+    (400, 256, 512, 64, 2, 4),     # d = 64: 256 queries, workgroups that all fit at once
+    (98, 1000, 516, 64, 1, 2),     # ... no tile multiples
+    (48, 2000, 2044, 128, 1, 2),   # d = 128: 256 queries, 16 blocks of keys; a workgroup with two waves past the last query
+    (260, 256, 2176, 128, 2, 4),   # ... 17 blocks
+    (230, 320, 2048, 128, 2, 4),   # (256 queries per workgroup would add a third: 128 add a fifth, 64 it is)
+])
+def test_stage3_spmm_every_tile(BH, Lq, Lk, d, N, M):
+    """Both sizes of a tile and the rule between them: the weights that stages 1 and 2 leave, some heads whole against the product in
+    64 bits; nothing behind O is touched."""
+    g = torch.Generator(device=DEV).manual_seed(7650 + Lk + d)
+    Q, K, V = (torch.randn((BH, L, d), generator=g, device=DEV).to(torch.bfloat16) for L in (Lq, Lk, Lk))
+    s = Shape(1, BH, Lq, Lk, d, N, M)
+    P, meta = dfss.dfss_sddmm_prune(Q, K, s, 0.25 / math.sqrt(d))
+    dfss.dfss_sparse_softmax(P, s)
+    buf = torch.full((BH * Lq * d + 65536,), 777.0, dtype=torch.bfloat16, device=DEV)
+    O = dfss.dfss_spmm(P, meta, V, s, O=buf[:BH * Lq * d].view(BH, Lq, d))
+    canon = dfss.dfss_meta_to_canonical(meta, s)
+    torch.cuda.synchronize()
+    assert bool((buf[BH * Lq * d:] == 777.0).all()), "wrote behind O"
+    for h in (0, BH // 2 + 1, BH - 1):
+        kidx = oracle.decode_meta(canon[h].cpu().numpy().view(np.uint16), s.LkP)[:Lq].astype(np.int64)
+        Pd = np.zeros((Lq, s.LkP))
+        np.put_along_axis(Pd, kidx, _np(P[h])[:Lq].astype(np.float64), axis=1)
+        ref = Pd[:, :Lk] @ _np(V[h]).astype(np.float64)
+        # bfloat16 output (2^-9 relative) and fp32 sums of Lk / 2 terms
+        assert np.max(np.abs(_np(O[h]) - ref)) <= 2.0 ** -8 * np.max(np.abs(ref)) + 1e-4, h
+
+
+@pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
     (512, 128, 3712, 64, 2, 4),   # d = 64: two row blocks per wave, 29 key blocks (an odd number)
     (220, 256, 1536, 64, 1, 2),   # ... one, nearly four workgroups per compute unit
     (32, 2048, 3712, 128, 1, 2),  # d = 128: two row blocks, an odd number of key blocks
