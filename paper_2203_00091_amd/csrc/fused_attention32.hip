@@ -43,6 +43,12 @@ namespace dfss {
 
 namespace {
 
+// Operands read from LDS ahead of the matrix instruction that needs them, in both products.  Without an order the eight (d = 64:
+// four) instructions of the product with V each waited for their own reads.  us, before and with 2: 4096 x 4096, 24 heads 94.7 ->
+// 93.4, 384 x 384, 96 heads 9.5 -> 9.1, 24 x 1024 x 1024 14.9 -> 13.2; d = 128, 64 heads x 2048 111.3 -> 108.2, causal 67.6 -> 65.0, 16
+// x 1024 x 1024 21.2 -> 18.8.  Measured also: 1 up to 3 % slower, 3 and (first product) 4 and 6 level.  The copies of the next
+// block issued behind the first product instead of in front of it: 1 % faster on full grids, 5 - 9 % slower with one wave per SIMD.
+constexpr int AHEAD = 2;
 constexpr int KB = 64;    // keys per block (two 32-key tiles)
 constexpr float kTau = 4.0f;    // distance of the reference above the row maximum it was set from (score units)
 constexpr float kLog2e = 1.4426950408889634f;
@@ -280,6 +286,7 @@ __global__ __launch_bounds__(64 * NW, OCC * 4 / NW) void k_fused32(const __bf16 
                     acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak, bq[s], s == 0 ? cneg : acc[t], 0, 0, 0);
                 }
             }
+            if constexpr (SPARSE) read_ahead<KT * STEPS, 1, AHEAD, 0>();
         }
         if constexpr (VARLEN || RAGGED) {
             if (KB * jb + KB > lk_eff) {   // the block the sequence ends in: keys from lk_eff on count as masked
@@ -443,6 +450,7 @@ __global__ __launch_bounds__(64 * NW, OCC * 4 / NW) void k_fused32(const __bf16 
                 }
             }
         }
+        if constexpr (SPARSE) read_ahead<KT * DT, 4, AHEAD, 1, KT>();
     };
     if constexpr (!MASKED) {
         Pace<PACED> pace(nblocks);
