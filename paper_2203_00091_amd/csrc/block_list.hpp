@@ -142,6 +142,12 @@ struct BlockList {
         }
     }
 
+    // how many there are
+    __device__ __forceinline__ int left() const {
+        static_assert(MASKED, "a list");
+        return __builtin_popcountll(live_lo) + __builtin_popcountll(live_hi);
+    }
+
     __device__ __forceinline__ bool has_bias(int jb) const {
         if constexpr (!MASKED) return false;
         return ((jb < 64 ? bias_lo >> jb : bias_hi >> (jb - 64)) & 1ull) != 0;

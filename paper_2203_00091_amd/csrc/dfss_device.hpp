@@ -146,20 +146,20 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Order for the scheduler: OPS matrix instructions, each of whose operands takes READS reads from LDS, with the reads
+// Order for the scheduler: OPS operands, READS reads from LDS each and good for EACH matrix instructions, with the reads
 // AHEAD operands in front (left to itself it reads an operand right before the instruction that needs it, and the wave waits
 // out the latency of LDS, four times that of the instruction).  To stand behind the instructions, in their basic block; ID
 // tells the groups of one block apart.  EXTRA: matrix instructions without reads, at the end.
-template <int OPS, int READS, int AHEAD, int ID, int EXTRA = 0>
+template <int OPS, int READS, int AHEAD, int ID, int EXTRA = 0, int EACH = 1>
 __device__ __forceinline__ void read_ahead() {
     constexpr int A = AHEAD < OPS ? AHEAD : OPS;
     __builtin_amdgcn_sched_group_barrier(0x100, A * READS, ID);
 #pragma unroll
     for (int i = 0; i < OPS - A; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, ID);
+        __builtin_amdgcn_sched_group_barrier(0x008, EACH, ID);
         __builtin_amdgcn_sched_group_barrier(0x100, READS, ID);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, A + EXTRA, ID);
+    __builtin_amdgcn_sched_group_barrier(0x008, EACH * A + EXTRA, ID);
 }
 
 // Keeps the workgroups that share a compute unit level.  Among waves of equal priority the hardware serves the oldest

@@ -34,6 +34,10 @@ namespace {
 
 constexpr int NT = 256;   // threads per workgroup (4 waves)
 constexpr int KB = 64;    // keys per block
+// Operands read from LDS ahead of the matrix instructions that need them, in both products (192 heads x 512 x 512 with a padding
+// bias 17.8 -> 17.4 us, d = 128, 96 heads 25.3 -> 23.4, unpadded 48 x 250 x 1000 14.7 -> 13.2; four in the first product cost
+// registers: 2:4, 768 heads x 128 x 128 12.6 -> 14.6).
+constexpr int AHEAD = 2;
 constexpr float kTau = 8.0f;
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -138,8 +142,9 @@ struct MaskTiling {
 //              the scaled score of query i and key j where the key bias would.  Every block is visited and every
 //              block takes the arithmetic with bias; a lane reads the 16 entries of its query and its keys one
 //              block ahead.  No block mask, no causal flag.
+//   PACED      (a key bias) the workgroups of a compute unit give up priority as their list of live blocks gets shorter (Pace).
 template <int D, int MODE, int NQ, bool PRESCALE, bool MASKED, bool RAGGED = false, int G = 1, int SPLIT = 1,
-          bool MASK2D = false>
+          bool MASK2D = false, bool PACED = false>
 __global__ __launch_bounds__(NT * G, 2) void k_fused(const __bf16 *__restrict__ Q, const __bf16 *__restrict__ K,
                                                  const __bf16 *__restrict__ V, const float *__restrict__ key_bias,
                                                  int H, const uint8_t *__restrict__ block_mask, int causal, int Lq,
@@ -155,6 +160,7 @@ __global__ __launch_bounds__(NT * G, 2) void k_fused(const __bf16 *__restrict__ 
     static_assert(!RAGGED || MASKED, "ragged lengths use the masking machinery");
     static_assert(G == 1 || (MASKED && !RAGGED && NQ == 1), "key groups: block patterns on 64-query workgroups");
     static_assert(SPLIT == 1 || (MASKED && !RAGGED && NQ == 1 && G == 1), "split rows: block patterns, 64-query workgroups");
+    static_assert(!PACED || (MASKED && G == 1 && SPLIT == 1 && !MASK2D), "the list of live blocks");
     static_assert(!MASK2D || (MASKED && NQ == 1 && G == 1 && SPLIT == 1), "general mask: 64-query workgroups, no groups");
     // per key group: two K buffers, then two V buffers; MASK_LDS: then 16 rows x 64 entries of the mask per wave
     constexpr bool MASK_LDS = MASK2D && D == 64;
@@ -385,8 +391,10 @@ __global__ __launch_bounds__(NT * G, 2) void k_fused(const __bf16 *__restrict__ 
         if (jb < nblocks) load_mask(jb);
     }
 
+    Pace<PACED> pace(nblocks);   // (of all blocks of the row: workgroups with more left go first)
     for (int it = 0; lead < nblocks; ++it) {
         const int buf = it & 1;
+        if constexpr (PACED) pace.at(blocks.left() + 1 + (jn < nblocks));
         wait_async_copies();  // vmcnt(0): this block's copies have landed
         __syncthreads();
         if (jn < nblocks) issue_block(jn, buf ^ 1);
@@ -417,6 +425,7 @@ __global__ __launch_bounds__(NT * G, 2) void k_fused(const __bf16 *__restrict__ 
                         acc[qs][t] = mfma16(ak[t], bq[qs][s], c);
                     }
             }
+            read_ahead<4 * STEPS, 1, AHEAD, 0, 0, NQ>();
         };
         if (MASKED && with_bias) {
 #pragma unroll
@@ -584,6 +593,7 @@ __global__ __launch_bounds__(NT * G, 2) void k_fused(const __bf16 *__restrict__ 
                 const bf16x8 a = __builtin_bit_cast(bf16x8, u32x4{pk[qs][0], pk[qs][1], pk[qs][2], pk[qs][3]});
                 acc_l[qs] = mfma16(a, ones8, acc_l[qs]);   // (against ones the positions do not matter: dense instruction)
             }
+            read_ahead<DS, 4, AHEAD, 1, NQ, NQ>();
         } else {
             // dense: MFMA m (0/1) contracts the lane's keys 16 kb + 8 m .. +7
 #pragma unroll
@@ -751,6 +761,19 @@ hipError_t launch_nq(const void *Q, const void *K, const void *V, const float *k
                      hipStream_t st) {
     const unsigned grid = (unsigned)((long)BH * ((Lq + 64 * NQ - 1) / (64 * NQ)));
     const bool pre = is_pow2(scale);
+    // More workgroups than compute units, a key bias: the ones with more blocks left go first (d = 64: 192 heads x 512 x 512 17.4 ->
+    // 16.5 us, 48 x 1024 x 1024 21.3 -> 20.0, 192 x 192 x 512 13.1 -> 12.3; d = 128 1 - 2 % slower; one to a compute unit 7 %).
+    if constexpr (MASKED && !RAGGED) {
+        if (d == 64 && key_bias && !block_mask && !causal && grid > 256) {
+#define DFSS_LAUNCH(PRE)                                                                                        \
+    hipLaunchKernelGGL((k_fused<64, MODE, NQ, PRE, true, false, 1, 1, false, true>), dim3(grid), dim3(NT), 0, st, \
+                       (const __bf16 *)Q, (const __bf16 *)K, (const __bf16 *)V, key_bias, H, block_mask, causal, \
+                       Lq, Lk, scale, (uint16_t *)O, (float *)nullptr)
+            if (pre) DFSS_LAUNCH(true); else DFSS_LAUNCH(false);
+#undef DFSS_LAUNCH
+            return hipGetLastError();
+        }
+    }
 #define DFSS_LAUNCH(DD, PRE)                                                                                    \
     hipLaunchKernelGGL((k_fused<DD, MODE, NQ, PRE, MASKED, RAGGED>), dim3(grid), dim3(NT), 0, st,               \
                        (const __bf16 *)Q, (const __bf16 *)K, (const __bf16 *)V, key_bias, H, block_mask, causal, \

@@ -453,7 +453,8 @@ __global__ __launch_bounds__(64 * NW, OCC * 4 / NW) void k_fused32(const __bf16 
         if constexpr (SPARSE) read_ahead<KT * DT, 4, AHEAD, 1, KT>();
     };
     if constexpr (!MASKED) {
-        Pace<PACED> pace(nblocks);
+        // (VARLEN: of the padded length, so that workgroups with more left go first: 16 x 12 x 512 x 512, 1:2 16.2 -> 15.8 us)
+        Pace<PACED> pace(VARLEN ? Lk / KB : nblocks);
         for (int jb = 0; jb < nblocks; jb += 2) {
             pace.at(nblocks - jb);
             block(std::integral_constant<int, 0>{}, jb, jb + 1, jb == 0);
