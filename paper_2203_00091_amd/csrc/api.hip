@@ -642,7 +642,7 @@ dfss_status dfss_attention_backward(const void *dO, const void *Q, const void *K
 size_t dfss_backward_workspace_bytes(const dfss_shape *s) {
     Dims D;
     if (check_shape_stage(s, true, &D) != DFSS_OK || (D.f32 && !D.split)) return 0;   // (float mode: split products only)
-    return D.f32 ? align_up(dfss_vals_bytes(s)) : dfss::backward_workspace_bytes(D.BH, D.Lq, D.LqR, D.LkR, D.d);
+    return D.f32 ? align_up(dfss_vals_bytes(s)) : dfss::backward_workspace_bytes(D.BH, D.Lq, D.Lk, D.LqR, D.LkR, D.d);
 }
 
 dfss_status dfss_meta_to_canonical(const void *meta, const dfss_shape *s, uint16_t *canon, void *stream) {

@@ -437,20 +437,39 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? NW / 2 : NW == 4 ? 3 : 6) void 
     }
 }
 
-// dQ from the sums of `splits` workgroups, in a fixed order; a thread forms 8 consecutive values of the n.
-__global__ __launch_bounds__(NT) void k_backward_dq_merge(const float *__restrict__ part, int splits, size_t n, float scale,
-                                                          uint16_t *__restrict__ dQ) {
-    const size_t i = 8 * ((size_t)blockIdx.x * NT + threadIdx.x);
-    if (i >= n) return;
+// Gradients from the sums of workgroups that shared them, added in a fixed order: out = scale (part[0] + part[1] + ...), n values
+// (a multiple of 8) each, consecutive parts `stride` apart.  A thread forms 8 consecutive values; the jobs follow one another.
+struct MergeJob {
+    const float *part;
+    uint16_t *out;
+    size_t n, stride;
+    int splits;
+    float scale;
+};
+struct MergeJobs {
+    MergeJob job[3];
+};
+__global__ __launch_bounds__(NT) void k_backward_merge(MergeJobs jobs) {
+    size_t i = 8 * ((size_t)blockIdx.x * NT + threadIdx.x);
+    MergeJob j = jobs.job[0];
+    if (i >= j.n) {
+        i -= j.n;
+        j = jobs.job[1];
+        if (i >= j.n) {
+            i -= j.n;
+            j = jobs.job[2];
+            if (i >= j.n) return;
+        }
+    }
     f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
 #pragma unroll 4
-    for (int sp = 0; sp < splits; ++sp) {
-        const f32x4 *const src = reinterpret_cast<const f32x4 *>(part + sp * n + i);
+    for (int sp = 0; sp < j.splits; ++sp) {
+        const f32x4 *const src = reinterpret_cast<const f32x4 *>(j.part + sp * j.stride + i);
         a += src[0];
         b += src[1];
     }
-    a *= scale, b *= scale;
-    *reinterpret_cast<u32x4 *>(dQ + i) = u32x4{pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(b[0], b[1]), pack_bf16x2(b[2], b[3])};
+    a *= j.scale, b *= j.scale;
+    *reinterpret_cast<u32x4 *>(j.out + i) = u32x4{pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(b[0], b[1]), pack_bf16x2(b[2], b[3])};
 }
 
 // Sixteen zeros made on the spot (as a constant they are kept in sixteen registers of their own and copied from there)
@@ -527,11 +546,11 @@ struct DkvPlace {   // the kernel's LDS in 16-byte units (an access is one of a 
     static constexpr int AT_G = 0, AT_Q = XT, AT_P = 2 * XT, AT_M = AT_P + PT, AT_D = AT_M + QB, BUF = AT_D + QB / 4, AT_V = 2 * BUF;
     static constexpr int SIZE = AT_V + (V_LDS ? KB * (D / 8) : 0);
 };
-template <int D, bool UNP, bool CAREFUL>
+template <int D, bool UNP, bool CAREFUL, bool SPLIT>
 __device__ __forceinline__ bool dkv_pass(
     u32x4 *Smem, const int w, const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta, const __bf16 *__restrict__ dO,
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ V, const float *__restrict__ neg_delta, int Lq, int Lk,
-    int LqR, int LkR, float scale, uint16_t *__restrict__ dK, uint16_t *__restrict__ dV) {
+    int LqR, int LkR, float scale, uint16_t *__restrict__ dK, uint16_t *__restrict__ dV, int splits, float *__restrict__ part) {
     using L = DkvPlace<D>;
     constexpr int QB = L::QB, XT = L::XT, PT = L::PT, AT_G = L::AT_G, AT_Q = L::AT_Q, AT_P = L::AT_P, AT_M = L::AT_M, AT_D = L::AT_D;
     constexpr int BUF = L::BUF, AT_V = L::AT_V;
@@ -551,9 +570,13 @@ __device__ __forceinline__ bool dkv_pass(
     }
     const int l = tid & 63, lj = l & 31, h = l >> 5;
     const unsigned kblocks = Lk / KB;
-    const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);
+    const unsigned share = xcd_contiguous(blockIdx.x, gridDim.x);
+    const unsigned item = SPLIT ? share / (unsigned)splits : share;
+    const int sp = SPLIT ? share % (unsigned)splits : 0;
     const int jblk = item % kblocks, bh = item / kblocks;
-    const int nq = (LqR + QB - 1) / QB;
+    const int all = (LqR + QB - 1) / QB;   // blocks of queries: this workgroup takes nq of them from qb0 on (splits <= all)
+    const int qb0 = SPLIT ? __builtin_amdgcn_readfirstlane(all * sp / splits) : 0;
+    const int nq = SPLIT ? __builtin_amdgcn_readfirstlane(all * (sp + 1) / splits) - qb0 : all;
 
     // dO and Q blocks: row = query, chunk c at row * CPR + (c ^ both_ways_swizzle(row)); kept weights: row = query, chunk c
     // at row * 8 + (c ^ operand_row_swizzle(row)); metadata: 16 bytes per row
@@ -591,7 +614,7 @@ __device__ __forceinline__ bool dkv_pass(
             if (l < QB / 4) async_copy16(d_base + (uint64_t)qb * (QB * 4), 16u * l, lds + 16u * (buf * BUF + AT_D));
         }
     };
-    issue_block(0, 0);
+    issue_block(qb0, 0);
 
     // V operand: column = key lj of this wave, k = 16 s + 8 h .. +7
     bf16x8 bv[V_LDS ? 1 : STEPS];
@@ -654,7 +677,7 @@ __device__ __forceinline__ bool dkv_pass(
         constexpr int buf = decltype(parity)::value;
         wait_async_copies();
         __syncthreads();
-        if (qb + 1 < nq) issue_block(qb + 1, buf ^ 1);
+        if (qb + 1 < qb0 + nq) issue_block(qb + 1, buf ^ 1);
 #pragma unroll
         for (int qt = 0; qt < QB / 32; ++qt) {
             constexpr int B0 = buf * BUF;
@@ -712,10 +735,10 @@ __device__ __forceinline__ bool dkv_pass(
         }
     };
     Pace<> pace(nq);
-    for (int qb = 0; qb < nq; qb += 2) {
-        pace.at(nq - qb);
-        block(std::integral_constant<int, 0>{}, qb);
-        if (qb + 1 < nq) block(std::integral_constant<int, 1>{}, qb + 1);
+    for (int i = 0; i < nq; i += 2) {
+        pace.at(nq - i);
+        block(std::integral_constant<int, 0>{}, qb0 + i);
+        if (i + 1 < nq) block(std::integral_constant<int, 1>{}, qb0 + i + 1);
     }
 
     // acc[dt][r]: key 8 (r / 4) + 4 (lane / 32) + r % 4 of the wave's 32, column 32 dt + lane % 32
@@ -728,6 +751,12 @@ __device__ __forceinline__ bool dkv_pass(
             const size_t at = ((size_t)bh * LkR + key) * D + (lane & 31);
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {
+                if constexpr (SPLIT) {   // [split][dV, dK][head and key][D]
+                    const size_t n = (size_t)(gridDim.x / splits / kblocks) * LkR * D;
+                    part[2 * sp * n + at + 32 * dt] = acc_v[dt][r];
+                    part[(2 * sp + 1) * n + at + 32 * dt] = acc_k[dt][r];
+                    continue;
+                }
                 dV[at + 32 * dt] = (uint16_t)(pack_bf16x2(acc_v[dt][r], 0.f) & 0xFFFFu);
                 dK[at + 32 * dt] = (uint16_t)(pack_bf16x2(acc_k[dt][r] * scale, 0.f) & 0xFFFFu);
             }
@@ -757,15 +786,15 @@ __device__ __forceinline__ bool dkv_pass(
     }
 }
 
-template <int D, bool UNP>
+template <int D, bool UNP, bool SPLIT>
 __global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void k_backward_dkv(
     const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta, const __bf16 *__restrict__ dO,
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ V, const float *__restrict__ neg_delta, int Lq, int Lk,
-    int LqR, int LkR, float scale, uint16_t *__restrict__ dK, uint16_t *__restrict__ dV) {
+    int LqR, int LkR, float scale, uint16_t *__restrict__ dK, uint16_t *__restrict__ dV, int splits, float *__restrict__ part) {
     __shared__ u32x4 Smem[DkvPlace<D>::SIZE];
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    if (dkv_pass<D, UNP, false>(Smem, w, P, meta, dO, Q, V, neg_delta, Lq, Lk, LqR, LkR, scale, dK, dV))
-        dkv_pass<D, UNP, true>(Smem, w, P, meta, dO, Q, V, neg_delta, Lq, Lk, LqR, LkR, scale, dK, dV);
+    if (dkv_pass<D, UNP, false, SPLIT>(Smem, w, P, meta, dO, Q, V, neg_delta, Lq, Lk, LqR, LkR, scale, dK, dV, splits, part))
+        dkv_pass<D, UNP, true, SPLIT>(Smem, w, P, meta, dO, Q, V, neg_delta, Lq, Lk, LqR, LkR, scale, dK, dV, splits, part);
 }
 
 }  // namespace
@@ -788,20 +817,45 @@ hipError_t launch_spmm_t(const void *vals, const void *meta, const void *X, int 
 
 namespace {
 
-// Workgroups that share the keys of a query tile in dQ (1: none).  A tile of 64 queries walks over the keys at the pace of
-// two waves; where a grid of such workgroups leaves half of the chip idle and the keys are many, several take a run of
-// them each.  The whole backward pass, alone and shared, us: d = 128, one head x 64 x 8192 145.6 and 21.7, 12 x 64 x 2048
-// 46.6 and 22.0, 32 x 128 x 1024 32.3 and 27.4, 12 x 512 x 4096 100 and 72; level with more than 128 tiles, and at 512 keys
-// with more than 16 (64 heads x 64 x 512 22.0 and 23.1).  At d = 64 a block takes half the time; there it is the few tiles
-// against the most keys that sharing is for (one head x 64 x 8192 90.6 and 17.4).
-int dq_splits(int BH, int Lq, int LkR, int d) {
-    const long wg = (long)BH * (Lq / 64);
-    const int npairs = (LkR + KB - 1) / KB;
-    if (d == 128 ? wg > 128 || npairs < (wg <= 16 ? 4 : 8) : wg > 8 || npairs < 32) return 1;
-    long n = 256 / wg;
-    if (n > npairs / 2) n = npairs / 2;   // two pairs of blocks each, or more
-    if (n > 32) n = 32;
-    return (int)n;
+// How many workgroups share the keys of a query tile (dQ) and the queries of a key tile (dV and dK); 1: none.  A tile is walked at
+// the pace of one workgroup, and a small grid leaves most of the chip idle; sharing costs the sums, written and read in fp32,
+// and the kernel that adds them.  The counts are the powers of two with the least of
+//     us per step x steps / count x (1 + slope (workgroups / chip - 1) beyond a full chip) + sums, at 5 TB/s + 4 us for that kernel
+// (a larger count has to save a tenth), where it gains 2 us or more and the two kernels take longer than their launches (one head x
+// 512 x 512, d = 64: 19.2 us, with a third launch 22.1).  Measured alone: a step of dQ, 128 keys, 1.4 us at d = 64 and 2.2 at d = 128, the
+// chip full with 512 workgroups of two waves; a step of dV and dK, 64 queries, 0.9 and 1.56 us, full with 256 of four.
+// The whole pass, before (keys shared at d = 128 up to 128 tiles) and now, us: d = 64, one head x 4096 x 4096 102 -> 37, 4 x 4096 103
+// -> 65, 4 x 2048 55 -> 33, 4 x 1024 31 -> 23, 4 x 4096 x 512 66 -> 26; d = 128, one head x 4096 122 -> 50, 4 x 4096 171 -> 114, 4 x
+// 2048 76 -> 47; left alone, rightly: 12 x 1024 (31.4; shared by two 32.0), 24 x 512 (19.4; 25.5), 48 x 512 at d = 128 (33.9; 46.3).
+struct Sharing {
+    int dq, dkv;
+};
+float shared_us(float step, int steps, int n, float fill, float slope, double sum_bytes) {
+    return step * (float)steps / (float)n * (fill * n > 1.f ? 1.f + slope * (fill * n - 1.f) : 1.f) + (n > 1 ? (float)(n * sum_bytes / 5.0e6) : 0.f);
+}
+Sharing sharing(int BH, int Lq, int Lk, int LqR, int LkR, int d) {
+    constexpr float kMerge = 4.f, kGain = 2.f, kHost = 16.f;
+    const int pairs = (LkR + KB - 1) / KB, steps = (LqR + 63) / 64;
+    const long wg_q = (long)BH * (Lq / 64), wg_k = (long)BH * (Lk / KB);
+    const float step_q = d == 64 ? 1.4f : 2.2f, step_k = d == 64 ? 0.9f : 1.56f;
+    const double bytes_q = 8. * BH * LqR * d, bytes_k = 16. * BH * LkR * d;   // written and read
+    Sharing s = {1, 1};
+    const float alone_q = shared_us(step_q, pairs, 1, wg_q / 512.f, 0.f, 0.), alone_k = shared_us(step_k, steps, 1, wg_k / 256.f, 0.f, 0.);
+    float best_q = alone_q, best_k = alone_k;
+    for (int n = 2; n <= 32 && n <= pairs / 2 && wg_q < 512; n *= 2) {   // (128-query workgroups do not share)
+        const float us = shared_us(step_q, pairs, n, wg_q / 512.f, d == 64 ? 0.35f : 1.f, bytes_q);
+        if (us < 0.9f * best_q) best_q = us, s.dq = n;
+    }
+    for (int n = 2; n <= 16 && n <= steps / 4 && wg_k <= 256; n *= 2) {
+        const float us = shared_us(step_k, steps, n, wg_k / 256.f, 0.35f, bytes_k);
+        if (us < 0.92f * best_k) best_k = us, s.dkv = n;
+    }
+    // the kernel that adds is paid once
+    const float gain_q = alone_q - best_q, gain_k = alone_k - best_k;
+    if (alone_q + alone_k < kHost || gain_q + gain_k < kMerge + kGain) return {1, 1};
+    if (gain_q < kGain / 2) s.dq = 1;
+    if (gain_k < kGain / 2) s.dkv = 1;
+    return s;
 }
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
@@ -809,40 +863,48 @@ size_t delta_bytes(int BH, int Lq) { return align256((size_t)BH * Lq * sizeof(fl
 
 }  // namespace
 
-// The row terms -delta, fp32 [BH][Lq] (the least that the pass needs), then (dq_splits) the sums of the workgroups that share
-// keys.
+// The row terms -delta, fp32 [BH][Lq] (the least that the pass needs), then the sums of the workgroups that share keys (dQ) and of
+// those that share queries (dV and dK).
 size_t backward_workspace_least(int BH, int Lq) { return delta_bytes(BH, Lq); }
-size_t backward_workspace_bytes(int BH, int Lq, int LqR, int LkR, int d) {
-    const int n = dq_splits(BH, Lq, LkR, d);
-    return delta_bytes(BH, Lq) + (n == 1 ? 0 : align256((size_t)n * BH * LqR * d * sizeof(float)));
+namespace {
+size_t dq_sum_bytes(int n, int BH, int LqR, int d) { return n == 1 ? 0 : align256((size_t)n * BH * LqR * d * sizeof(float)); }
+size_t dkv_sum_bytes(int n, int BH, int LkR, int d) { return n == 1 ? 0 : align256((size_t)n * 2 * BH * LkR * d * sizeof(float)); }
+}  // namespace
+size_t backward_workspace_bytes(int BH, int Lq, int Lk, int LqR, int LkR, int d) {
+    const Sharing s = sharing(BH, Lq, Lk, LqR, LkR, d);
+    return delta_bytes(BH, Lq) + dq_sum_bytes(s.dq, BH, LqR, d) + dkv_sum_bytes(s.dkv, BH, LkR, d);
 }
 
-// P, meta: as kept from the forward pass.  ws: backward_workspace_least or more; keys are shared if the sums fit (the whole is
-// less for a large grid than for a small one, and a workspace made for the largest shape has to do for all).
+// P, meta: as kept from the forward pass.  ws: backward_workspace_least or more; keys and queries are shared if all the sums fit
+// (the whole is less for a large grid than for a small one, and a workspace made for the largest shape has to do for all).
 hipError_t launch_backward(const void *dO, const void *Q, const void *K, const void *V, const void *O, const void *P,
                            const void *meta, int BH, int Lq, int Lk, int LqR, int LkR, int d, float scale, void *ws,
                            size_t ws_bytes, void *dQ, void *dK, void *dV, hipStream_t st) {
     const bool unp = LqR != Lq || LkR != Lk;
-    float *const neg_delta = (float *)ws, *const part = (float *)((char *)ws + delta_bytes(BH, Lq));
-    const int splits = ws_bytes < backward_workspace_bytes(BH, Lq, LqR, LkR, d) ? 1 : dq_splits(BH, Lq, LkR, d);
+    Sharing s = sharing(BH, Lq, Lk, LqR, LkR, d);
+    if (ws_bytes < delta_bytes(BH, Lq) + dq_sum_bytes(s.dq, BH, LqR, d) + dkv_sum_bytes(s.dkv, BH, LkR, d)) s = {1, 1};
+    float *const neg_delta = (float *)ws, *const part_q = (float *)((char *)ws + delta_bytes(BH, Lq));
+    float *const part_kv = (float *)((char *)part_q + dq_sum_bytes(s.dq, BH, LqR, d));
+    const int splits = s.dq, splits_kv = s.dkv;
     // 128-query workgroups where they fill the chip (three per compute unit at d = 64, two at d = 128), else 64-query ones
     const bool four = (long)BH * ((Lq + 127) / 128) >= 512;
     const unsigned grid_q = (unsigned)((long)BH * (four ? (Lq + 127) / 128 : Lq / 64)) * splits;
-    const unsigned grid_k = (unsigned)((long)BH * (Lk / KB));
+    const unsigned grid_k = (unsigned)((long)BH * (Lk / KB)) * splits_kv;
 #define DFSS_DQ(DD, NW, UU, SS)                                                                                          \
     hipLaunchKernelGGL((k_backward_dq<DD, NW, UU, SS>), dim3(grid_q), dim3(64 * NW), 0, st, (const __bf16 *)dO,          \
                        (const __bf16 *)V, (const __bf16 *)O, (const uint32_t *)P, (const uint32_t *)meta,               \
-                       (const __bf16 *)K, Lq, Lk, LqR, LkR, scale, (uint16_t *)dQ, neg_delta, splits, part)
-#define DFSS_DKV(DD, UU)                                                                                                 \
-    hipLaunchKernelGGL((k_backward_dkv<DD, UU>), dim3(grid_k), dim3(NT), 0, st, (const uint32_t *)P,                     \
+                       (const __bf16 *)K, Lq, Lk, LqR, LkR, scale, (uint16_t *)dQ, neg_delta, splits, part_q)
+#define DFSS_DKV(DD, UU, SS)                                                                                             \
+    hipLaunchKernelGGL((k_backward_dkv<DD, UU, SS>), dim3(grid_k), dim3(NT), 0, st, (const uint32_t *)P,                 \
                        (const uint32_t *)meta, (const __bf16 *)dO, (const __bf16 *)Q, (const __bf16 *)V, neg_delta, Lq, Lk, \
-                       LqR, LkR, scale, (uint16_t *)dK, (uint16_t *)dV)
+                       LqR, LkR, scale, (uint16_t *)dK, (uint16_t *)dV, splits_kv, part_kv)
 #define DFSS_BOTH(DD, UU)                                                \
     do {                                                                 \
         if (four) DFSS_DQ(DD, 4, UU, false);                             \
         else if (splits == 1) DFSS_DQ(DD, 2, UU, false);                 \
         else DFSS_DQ(DD, 2, UU, true);                                   \
-        DFSS_DKV(DD, UU);                                                \
+        if (splits_kv == 1) DFSS_DKV(DD, UU, false);                     \
+        else DFSS_DKV(DD, UU, true);                                     \
     } while (0)
     if (d == 64) {
         if (unp) DFSS_BOTH(64, true); else DFSS_BOTH(64, false);
@@ -852,9 +914,13 @@ hipError_t launch_backward(const void *dO, const void *Q, const void *K, const v
 #undef DFSS_BOTH
 #undef DFSS_DKV
 #undef DFSS_DQ
-    if (splits > 1) {
-        const size_t n = (size_t)BH * LqR * d;
-        hipLaunchKernelGGL(k_backward_dq_merge, dim3((unsigned)((n / 8 + NT - 1) / NT)), dim3(NT), 0, st, part, splits, n, scale, (uint16_t *)dQ);
+    if (splits > 1 || splits_kv > 1) {
+        const size_t nq = splits > 1 ? (size_t)BH * LqR * d : 0, nk = splits_kv > 1 ? (size_t)BH * LkR * d : 0;
+        const MergeJobs jobs = {{{part_q, (uint16_t *)dQ, nq, nq, splits, scale},
+                                 {part_kv, (uint16_t *)dV, nk, 2 * nk, splits_kv, 1.f},
+                                 {part_kv + nk, (uint16_t *)dK, nk, 2 * nk, splits_kv, scale}}};
+        const size_t threads = (nq + 2 * nk) / 8;
+        hipLaunchKernelGGL(k_backward_merge, dim3((unsigned)((threads + NT - 1) / NT)), dim3(NT), 0, st, jobs);
     }
     return hipGetLastError();
 }

@@ -69,9 +69,9 @@ hipError_t launch_fused_attention_split_rows(const void *Q, const void *K, const
 hipError_t launch_spmm_t(const void *vals, const void *meta, const void *X, int BH, int Lq, int Lk, int LqR, int LkR,
                          int d, void *out, hipStream_t st);
 // Backward pass through the fixed selection (P, meta as kept from the forward pass).  ws: backward_workspace_least or more,
-// 256-byte aligned; with backward_workspace_bytes workgroups may share keys.
+// 256-byte aligned; with backward_workspace_bytes workgroups may share keys and queries.
 size_t backward_workspace_least(int BH, int Lq);
-size_t backward_workspace_bytes(int BH, int Lq, int LqR, int LkR, int d);
+size_t backward_workspace_bytes(int BH, int Lq, int Lk, int LqR, int LkR, int d);
 hipError_t launch_backward(const void *dO, const void *Q, const void *K, const void *V, const void *O, const void *P,
                            const void *meta, int BH, int Lq, int Lk, int LqR, int LkR, int d, float scale, void *ws,
                            size_t ws_bytes, void *dQ, void *dK, void *dV, hipStream_t st);

@@ -178,6 +178,10 @@ def test_backward_on_grids_that_fill_the_chip(BH, Lq, Lk, d, N, M):
     (3, 100, 4100, 64, 2, 4),
     (9, 60, 4096, 64, 2, 4),       # (more than 8 tiles: one workgroup each)
     (2, 128, 256, 64, 2, 4),
+    (1, 1100, 256, 64, 2, 4),      # dV, dK: workgroups share the queries of a key tile; a partial last block of queries
+    (2, 640, 128, 128, 1, 2),      # ... d = 128
+    (3, 1000, 1500, 64, 2, 4),     # ... and the keys in dQ, no tile multiples
+    (1, 2048, 1024, 128, 2, 4),
 ])
 def test_backward_with_a_workspace_of_exactly_the_size_it_asks_for(BH, Lq, Lk, d, N, M):
     """Few queries against many keys, against the oracle; poisoned scratch of exactly dfss_backward_workspace_bytes and
@@ -247,6 +251,7 @@ def test_backward_with_a_workspace_that_holds_the_row_terms_only():
 @pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
     (2, 128, 256, 64, 2, 4), (2, 192, 128, 64, 1, 2), (2, 64, 384, 128, 2, 4),
     (2, 100, 132, 64, 2, 4), (2, 70, 260, 128, 1, 2),       # no tile multiples
+    (1, 1088, 128, 64, 2, 4), (1, 700, 260, 128, 1, 2),     # queries shared: one of the workgroups starts again
 ])
 @pytest.mark.parametrize("what", ["V", "dO", "P", "one weight"])
 def test_what_is_not_finite_reaches_the_kept_places_only(what, BH, Lq, Lk, d, N, M):
