@@ -924,8 +924,8 @@ hipError_t launch_fused_attention(const void *Q, const void *K, const void *V, c
     // workgroups and the key length (measured): four waves x 32 queries as a rule; two waves per 32-query tile
     // (64-query workgroups, twice as many, each wave half the keys) where the grid is at most one and a half
     // workgroups per compute unit and the keys number 1024 or more (2048 where the grid already gives nearly
-    // every compute unit a workgroup of its own); d = 128 always the former (the merge of the
-    // two key halves costs more than it gains there).  Full attention
+    // every compute unit a workgroup of its own); up to half a workgroup per compute unit the 16-query kernel below on
+    // short rows.  Full attention
     // (the baseline) runs the 16-query kernel below: the faster of the two at every shape measured (96 heads x 384,
     // 24 heads x 1024 .. 4096, 192 heads x 512, d = 128), the 32-query form being reachable through the test hook.
     // Few query tiles: the kernel whose waves share the keys (few_queries.hip), as long as its 16-query workgroups fit the
@@ -960,7 +960,11 @@ hipError_t launch_fused_attention(const void *Q, const void *K, const void *V, c
     // masked calls: the 32-query kernel where it measured faster -- the causal mask on 128-query workgroups (alone: its
     // form without the masking machinery, d = 64 and 128; with a key bias: the masked form, d = 64); a key bias alone
     // and block patterns stay with the kernel above
-    const bool masked32 = causal && !block_mask && (d == 64 || !key_bias) && Lq % 128 == 0 && mode != 2;
+    // (1:2 under the causal mask alone: the kernel above up to 192 workgroups of 128 queries, half the registers and the cheaper
+    // selection; 16 x 768 11.0 -> 10.4 us, 24 x 1024 13.6 -> 13.1, d = 128 16 x 768 15.3 -> 13.8, 4 x 4096 59.7 -> 55.6, 24 x 1024 19.2 ->
+    // 18.6; 2:4 5 - 10 % slower there)
+    const bool masked32 = causal && !block_mask && (d == 64 || !key_bias) && Lq % 128 == 0 && mode != 2 &&
+                          !(mode == 1 && !key_bias && (long)BH * (Lq / 128) <= 192);
     if (tiles && (!masked || masked32) && variant != DFSS_VARIANT_Q16 && variant != DFSS_VARIANT_Q16X2) {
         const long wg128 = (long)BH * (Lq / 128);
         int nw = Lq % 128 == 0 ? 4 : 2, ks = 1;
@@ -968,6 +972,19 @@ hipError_t launch_fused_attention(const void *Q, const void *K, const void *V, c
             // the key split doubles the workgroups: it pays while all of them still fit the chip at once (3 x 256
             // four-wave workgroups) and the sequence is long enough to carry the merge of the two halves
             if (mode != 2 && d == 64 && wg128 <= 384 && Lk >= (wg128 > 160 && wg128 <= 256 ? 2048 : 1024)) nw = 4, ks = 2;
+            // d = 128, where it takes more: up to 192 of them and 2048 keys (5 x 4096 x 4096 61.7 -> 54.8 us, 12 x 2048 x 2048 33.1 ->
+            // 32.4; 8 x 4096 x 4096, 256 of them, 64.4 against 65.3)
+            if (mode != 2 && d == 128 && wg128 <= 192 && Lk >= 2048) nw = 4, ks = 2;
+            // Up to 128: 64-query workgroups have a compute unit each.  Long rows: two waves per query tile (d = 128, 8 x 2048 x
+            // 2048 33.0 -> 25.7 us, 12 x 1024 x 1024 18.6 -> 15.5, 16 x 768 x 768 15.1 -> 13.0; d = 64 10.6 -> 9.1); short ones: the
+            // 16-query kernel (32 x 512 x 512 8.2 -> 7.5, 42 x 384 x 384 7.1 -> 6.4, 64 x 256 x 256 5.9 -> 5.4; d = 128 11.5 -> 10.6,
+            // 9.7 -> 8.9, 7.9 -> 7.4), whose 1:2 selection is the cheaper one, so that at d = 64 it stays ahead up to 1024 keys (16 x
+            // 768 x 768 10.7 -> 8.3, 12 x 1024 x 1024 10.6 -> 10.0; 6 x 2048 x 2048 level).  From 129 on the 128-query tiling again
+            // (45 x 384 x 384 7.1 against 8.0).
+            if (mode != 2 && Lq % 128 == 0 && wg128 <= 128) {
+                if (Lk <= (mode == 1 && d == 64 ? 1024 : 512)) nw = 0;
+                else nw = 4, ks = 2;
+            }
             if (mode != 2 && Lq % 128 != 0 && d == 64) nw = 4, ks = 2;   // 64-query workgroups either way
             // ... unless the grid is large: then 128-query workgroups, the last one of a head half empty (the kernel
             // of the unpadded lengths), beat 64-query ones (38.6 against 46.7 us at 24 heads x 2112, 19.3 against

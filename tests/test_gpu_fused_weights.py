@@ -349,6 +349,9 @@ def test_default_call_with_half_a_workgroup_left_over_on_a_large_grid(BH, Lq, Lk
     ("attention", 160, 128, 1152, 64, 2, 4, 0.125),    # keys of a block split over two waves, 18 blocks
     ("attention", 264, 128, 256, 128, 2, 4, 0.0625),
     ("causal", 136, 256, 256, 128, 2, 4, 0.0625),      # workgroups of two and of four blocks
+    ("causal", 136, 256, 256, 128, 1, 2, 0.0625),
+    ("causal", 97, 256, 384, 64, 1, 2, 0.125),         # (1:2, the first grid that the 32-query kernel takes)
+    ("causal", 96, 256, 384, 64, 1, 2, 0.125),         # (the last that it does not)
     ("lengths", 272, 128, 256, 64, 2, 4, 0.125),       # one block to four
 ])
 def test_workgroups_that_keep_level_on_their_compute_unit(path, BH, Lq, Lk, d, N, M, scale):
@@ -361,12 +364,31 @@ def test_workgroups_that_keep_level_on_their_compute_unit(path, BH, Lq, Lk, d, N
     call, mask, bias = {
         "attention": (lambda V: dfss.dfss_attention(Qd, Kd, V, s, scale), None, None),
         "causal": (lambda V: dfss.dfss_attention_causal(Qd, Kd, V, None, s, scale),
-                   np.triu(np.full((Lq, Lk), -np.inf, np.float32), 1), None),
+                   np.triu(np.full((Lq, Lk), -np.inf, np.float32), 1 + Lk - Lq), None),
         "lengths": (lambda V: dfss.dfss_attention_varlen(Qd, Kd, V, lens.to(DEV), s, scale), None,
                     synth.key_padding_bias(lens, Lk).numpy()[::16]),
     }[path]
     W = _weights_through_identity_v(call, BH, Lq, Lk, d, torch.bfloat16)
     _compare(W[::16], Qn[::16], Kn[::16], N, M, scale, key_bias=bias, mask=mask)
+
+
+@pytest.mark.parametrize("BH,Lq,Lk,d,N,M,scale", [
+    (34, 128, 512, 64, 2, 4, 0.125),       # up to half a workgroup of 128 queries per compute unit: the 16-query kernel
+    (17, 256, 1024, 64, 1, 2, 0.125),      # ... 1:2 at d = 64 up to 1024 keys
+    (34, 128, 640, 128, 1, 2, 0.0625),     # ... and from more than 512 keys on two waves per tile of 32 queries
+    (34, 128, 640, 64, 2, 4, 1.0 / 3.0),
+    (128, 128, 384, 128, 2, 4, 0.0625),    # the last such grid, and the first that is none
+    (129, 128, 384, 128, 2, 4, 0.0625),
+    (140, 128, 2048, 128, 1, 2, 0.0625),   # d = 128, 2048 keys: two waves per tile up to 192
+])
+def test_default_call_on_grids_that_leave_compute_units_idle(BH, Lq, Lk, d, N, M, scale):
+    """The tilings that dfss_attention takes for few workgroups, weight by weight against the oracle, some heads."""
+    Q, K, Qn, Kn = _int_qk(BH, Lq, Lk, d, seed=8950 + Lk + d + N)
+    s = Shape(1, BH, Lq, Lk, d, N, M)
+    Qd, Kd = Q.to(DEV), K.to(DEV)
+    W = _weights_through_identity_v(lambda V: dfss.dfss_attention(Qd, Kd, V, s, float(np.float32(scale))), BH, Lq, Lk, d, torch.bfloat16)
+    h = slice(None, None, 24)
+    assert _compare(W[h], Qn[h], Kn[h], N, M, float(np.float32(scale))) > 100
 
 
 def test_float_one_kernel_path():
