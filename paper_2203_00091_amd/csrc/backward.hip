@@ -8,6 +8,7 @@
 //
 //   k_backward_dq      dQ, and -delta for the other one; walks the keys, layout of the one-kernel forward pass
 //   k_backward_dkv     dV and dK in one pass over the queries
+//   k_backward_merge   gradients from the sums of workgroups that shared keys or queries
 //   k_spmm_t           out = A^T X for a compressed A (the public transposed product).  The contraction
 //                      runs over queries, across which the N:M structure does not run, so the tile
 //                      of A is expanded to dense bfloat16 in LDS and both operands are read with the
@@ -202,8 +203,8 @@ __global__ __launch_bounds__(NT, 2) void k_spmm_t(const uint32_t *__restrict__ A
 // The gradients.  dS is formed twice, once per direction of the sums it enters, and never written: the kept weights and
 // the metadata are read twice (2 x 1.125 B per score) instead of P twice, dS' written and read once, the metadata three
 // times (4.4 B), and the product that dS' costs a second time runs on the matrix unit.  The whole call, warm, before (dS'
-// written, one transposed product each for dV and dK) and now, 4096 x 4096 with 24 heads: 518 -> 298 us; 512 x 512 with 192
-// heads: 71 -> 51 us; d = 128, 2048 x 2048 with 64 heads: 500 -> 354 us.
+// written, one transposed product each for dV and dK) and with that, 4096 x 4096 with 24 heads: 518 -> 298 us; 512 x 512 with
+// 192 heads: 71 -> 51 us; d = 128, 2048 x 2048 with 64 heads: 500 -> 354 us.  (Now 283, 49 and 353: see where the weights come from.)
 // ------------------------------------------------------------------------------------------------
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -231,7 +232,7 @@ __device__ __forceinline__ float choose(uint32_t m, float x, float y) {
 // places of absent keys in a partial last block take the block's last key (their weights are 0).  Blocks that hold no real
 // key are not visited.
 // SPLIT: `splits` workgroups share the keys of a query tile, each a run of pairs of blocks; their sums, unscaled fp32, go to
-// `part` [split][head and query][D], and k_backward_dq_merge forms dQ.
+// `part` [split][head and query][D], and k_backward_merge forms dQ.
 // (Second number of the bounds: waves per SIMD.  At d = 128 it is what registers (four waves) and LDS (two) allow.  At d = 64
 // that would be three; the two-wave form asks for six, which the compiler reports as out of reach, because the order of
 // instructions that it arrives at on the way is the faster one: 1 - 2 % on small grids, 4 - 6 % on unpadded lengths against
@@ -527,9 +528,11 @@ __device__ __forceinline__ f32x16 expand_non_finite(u32x4 kept, bf16x16 eye, uin
 // kernel), started from -delta of the rows; dS is one multiplication per element.  Rounded to bfloat16 both tiles are the A
 // operands (row = key) of the two products, contraction index 8 m' + 4 h + x of step m = register order, against dO
 // and Q from the transposing LDS read in the same order.
-// 13 matrix instructions of 32 cycles per 32 x 32 tile at d = 64 (25 at d = 128) keep the matrix unit busy 56 % of the time
-// (4096 x 4096, 24 heads; the vector unit 31 %; d = 128, 64 heads x 2048: 53 and 21 %).  The rest is waiting: one wait for the
-// copies and one barrier per block, with P, which comes from memory, asked for one block ahead.
+// 13 matrix instructions of 32 cycles per 32 x 32 tile at d = 64 (25 at d = 128) keep the matrix unit busy 61 % of the time
+// (4096 x 4096, 24 heads, 148 us; the vector unit 34 %; d = 128, 64 heads x 2048, 196 us: 54 and 21 %).  The rest is waiting: one
+// wait for the copies and one barrier per block, with P, which comes from memory, asked for one block ahead.
+// SPLIT: `splits` workgroups share the queries of a key tile, a run of blocks each; their sums, unscaled fp32, go to `part`
+// [split][dV, dK][head and key][D], and k_backward_merge forms dV and dK.
 // UNP as above; the rows LqR .. Lq - 1 of P, whatever they hold, count as zeros.
 // What is infinite or NaN has to stay at the kept places, but the two products are formed at every place: a row of V that no
 // query kept, a row of dO, a weight that is infinite or NaN meets zeros there, and 0 times it is NaN.  Such a NaN always
