@@ -85,12 +85,13 @@ __device__ __forceinline__ uint32_t push_position(uint32_t idx, float v) {
 //              not instantiate that form, the 16-query kernel measured faster for block patterns); causal: query i
 //              sees keys 0 .. i + (Lk - Lq).  Blocks that hold nothing for the workgroup are skipped (block_list.hpp); hidden
 //              scores of the blocks that the diagonal cuts are overwritten with -1e30 by index.
-// VARLEN (unmasked kernels with KS = 1): key_len[b] keys of batch element b = head / H are real (1 <= key_len[b] <= Lk; the
+// VARLEN (unmasked kernels): key_len[b] keys of batch element b = head / H are real (1 <= key_len[b] <= Lk; the
 //   arrays are padded to Lk).  A head's workgroups walk only the blocks that hold real keys, and in the block a
 //   sequence ends in the scores of the keys past its end are overwritten by index -- no bias array is read, and every
 //   other block costs what it costs without padding.  (Block 0 always holds key 0, so the first block sets a finite
-//   reference.)
-// CAUSAL_ONLY (the same kernels): the causal mask and nothing else (query i sees keys 0 .. i + Lk - Lq), by the same two
+//   reference.  With KS = 2 the second tile of block 0 may hold padding only, but then no block follows, and the merge gives
+//   that wave's sums the factor 0.)
+// CAUSAL_ONLY (the same kernels, KS = 1): the causal mask and nothing else (query i sees keys 0 .. i + Lk - Lq), by the same two
 //   means: a workgroup walks the blocks up to the last key its last query sees, and in the blocks that the diagonal of
 //   a wave's queries cuts the hidden scores are overwritten by index.  Launch order: last row block of every head first.
 // RAGGED (the same kernels): lengths that are no tile multiples (any Lq; Lk a multiple of 4), arrays unpadded.  Absent
@@ -105,9 +106,9 @@ __global__ __launch_bounds__(64 * NW, OCC * 4 / NW) void k_fused32(const __bf16 
                                                         int Lq, int Lk, float scale, uint16_t *__restrict__ O,
                                                         const int *__restrict__ key_len) {
     static_assert(!MASKED || KS == 1, "the masked variants do not split the keys of a block over waves");
-    static_assert(!VARLEN || (KS == 1 && !MASKED), "key lengths: whole blocks per wave, no other mask");
+    static_assert(!VARLEN || !MASKED, "key lengths: no other mask");
     static_assert(!CAUSAL_ONLY || (KS == 1 && !MASKED && !VARLEN), "causal alone: whole blocks per wave, no other mask");
-    static_assert(!RAGGED || (KS == 1 && !MASKED && !VARLEN && !CAUSAL_ONLY), "ragged lengths: whole blocks per wave, no mask");
+    static_assert(!RAGGED || (!MASKED && !VARLEN && !CAUSAL_ONLY), "ragged lengths: no mask");
     constexpr int NT = 64 * NW;
     constexpr int CPR = D / 8;          // 16-byte chunks per row
     constexpr int TILE = KB * CPR;      // chunks per K (or V) block
@@ -291,7 +292,7 @@ __global__ __launch_bounds__(64 * NW, OCC * 4 / NW) void k_fused32(const __bf16 
         if constexpr (VARLEN || RAGGED) {
             if (KB * jb + KB > lk_eff) {   // the block the sequence ends in: keys from lk_eff on count as masked
                 asm volatile("" ::: "memory");   // (a branch, not selects that every block would execute)
-                const int lim = lk_eff - 1 - (KB * jb + 16 * h);   // key offsets above it are padding
+                const int lim = lk_eff - 1 - (KB * jb + 32 * kt0 + 16 * h);   // key offsets above it are padding
 #pragma unroll
                 for (int t = 0; t < KT; ++t)
 #pragma unroll
@@ -575,9 +576,25 @@ hipError_t launch_mode(const void *Q, const void *K, const void *V, const float 
     return launch_nw<MODE, 2, 1, false>(Q, K, V, nullptr, 1, nullptr, 0, BH, Lq, Lk, d, scale, O, st);
 }
 
+// Calls with key lengths and on unpadded lengths: two waves per tile of 32 queries (KS = 2, 64-query workgroups)?  By the number of
+// 128-query workgroups, us without and with: up to 128 (half of the chip idle; key lengths) 12 x 1024 x 1024 13.1 -> 11.3, 4 x 4096 x 4096 43.5 ->
+// 33.1, d = 128 18.6 -> 15.4, 61.7 -> 45.5, 24 x 512 x 512 8.5 -> 7.8 (256 keys level); d = 64 up to 384 on long rows 48 x 1024 x 1024
+// 18.1 -> 16.7, 12 x 3000 x 3000 43.9 -> 39.4 (24 x 1000 x 1000, 192 of them, 14.2 against 15.2; 16 x 1500 x 1500 level); d = 128 up to
+// 192 5 x 4000 x 4000 64.1 -> 55.0 (24 x 1000 x 1000 20.2 against 20.7; 12 x 3000 x 3000, 288 of them, 66 against 80).
+bool share_blocks(int BH, int Lq, int Lk, int d) {
+    const long wg = (long)BH * ((Lq + 127) / 128);
+    if (wg <= 128) return Lk >= 384;
+    if (d == 64) return wg <= 384 && Lk >= (wg > 160 && wg <= 256 ? 2048 : 1024);
+    return wg <= 192 && Lk >= 1500;
+}
+
 template <int MODE>
 hipError_t launch_varlen(const void *Q, const void *K, const void *V, const int *key_len, int H, int BH, int Lq, int Lk,
                          int d, float scale, void *O, hipStream_t st) {
+    // (an odd multiple of 64 queries: against two-wave workgroups 96 x 192 x 1024 17.1 -> 12.4 us, d = 128 21.4 -> 18.9)
+    const bool odd = Lq % 128 != 0 && Lk >= 384 && (long)BH * (Lq / 64) <= (d == 64 ? 768 : 288);
+    if (odd || share_blocks(BH, Lq, Lk, d))
+        return launch_nw<MODE, 4, 2, false, true>(Q, K, V, nullptr, H, nullptr, 0, BH, Lq, Lk, d, scale, O, st, key_len);
     if (Lq % 128 == 0)
         return launch_nw<MODE, 4, 1, false, true>(Q, K, V, nullptr, H, nullptr, 0, BH, Lq, Lk, d, scale, O, st, key_len);
     return launch_nw<MODE, 2, 1, false, true>(Q, K, V, nullptr, H, nullptr, 0, BH, Lq, Lk, d, scale, O, st, key_len);
@@ -599,6 +616,13 @@ hipError_t launch_fused_attention_varlen(const void *Q, const void *K, const voi
 // workgroups.
 hipError_t launch_fused_attention32_ragged(const void *Q, const void *K, const void *V, int BH, int Lq, int Lk, int d,
                                            int mode, float scale, void *O, hipStream_t st) {
+    if (share_blocks(BH, Lq, Lk, d)) {
+        if (mode == 0)
+            return launch_nw<MODE_2TO4, 4, 2, false, false, false, true>(Q, K, V, nullptr, 1, nullptr, 0, BH, Lq, Lk, d, scale, O, st);
+        if (mode == 1)
+            return launch_nw<MODE_1TO2, 4, 2, false, false, false, true>(Q, K, V, nullptr, 1, nullptr, 0, BH, Lq, Lk, d, scale, O, st);
+        return hipErrorInvalidValue;
+    }
     if (mode == 0)
         return launch_nw<MODE_2TO4, 4, 1, false, false, false, true>(Q, K, V, nullptr, 1, nullptr, 0, BH, Lq, Lk, d, scale, O, st);
     if (mode == 1)

@@ -391,6 +391,30 @@ def test_default_call_on_grids_that_leave_compute_units_idle(BH, Lq, Lk, d, N, M
     assert _compare(W[h], Qn[h], Kn[h], N, M, float(np.float32(scale))) > 100
 
 
+@pytest.mark.parametrize("path,BH,Lq,Lk,d,N,M", [
+    ("ragged", 128, 100, 500, 64, 2, 4),     # two waves per tile: a partial last block that both tiles of keys reach
+    ("ragged", 128, 70, 388, 64, 1, 2),      # ... four real keys in it, none in the second tile
+    ("ragged", 128, 66, 484, 128, 1, 2),
+    ("ragged", 130, 100, 1500, 128, 2, 4),   # ... more than 128 workgroups of 128 queries
+    ("lengths", 5, 128, 384, 64, 2, 4),      # ... sequences that end in every block, some in its first tile
+    ("lengths", 7, 192, 512, 128, 1, 2),     # ... an odd multiple of 64 queries
+])
+def test_two_waves_per_tile_on_unpadded_and_padded_lengths(path, BH, Lq, Lk, d, N, M):
+    """The keys of a block shared by two waves where the last block is partial, weight by weight against the oracle."""
+    Q, K, Qn, Kn = _int_qk(BH, Lq, Lk, d, seed=9050 + Lk + d)
+    s = Shape(BH, 1, Lq, Lk, d, N, M)
+    Qd, Kd = Q.to(DEV), K.to(DEV)
+    lens = torch.arange(BH, dtype=torch.int32) * 67 % Lk + 1
+    h = slice(None, None, 40 if BH > 40 else 1)
+    if path == "ragged":
+        W = _weights_through_identity_v(lambda V: dfss.dfss_attention_ragged(Qd, Kd, V, None, s, 0.125), BH, Lq, Lk, d, torch.bfloat16)
+        assert _compare(W[h], Qn[h], Kn[h], N, M, 0.125) > 100
+    else:
+        W = _weights_through_identity_v(lambda V: dfss.dfss_attention_varlen(Qd, Kd, V, lens.to(DEV), s, 0.125), BH, Lq, Lk, d,
+                                        torch.bfloat16)
+        _compare(W[h], Qn[h], Kn[h], N, M, 0.125, key_bias=synth.key_padding_bias(lens, Lk).numpy()[h])
+
+
 def test_float_one_kernel_path():
     """The 4-byte mode's one-kernel path (split products; integer inputs are exact in its bfloat16 pieces)."""
     BH, Lq, Lk, d = 2, 128, 256, 64
