@@ -237,7 +237,8 @@ __device__ __forceinline__ float choose(uint32_t m, float x, float y) {
 // that would be three; the two-wave form asks for six, which the compiler reports as out of reach, because the order of
 // instructions that it arrives at on the way is the faster one: 1 - 2 % on small grids, 4 - 6 % on unpadded lengths against
 // three (12 heads x 100 x 1000 20.9 and 22.0 us; 24 x 1024 x 1024 level).)
-template <int D, int NW, bool UNP, bool SPLIT>
+// PACED: the workgroups of a compute unit keep level (Pace).
+template <int D, int NW, bool UNP, bool SPLIT, bool PACED>
 __global__ __launch_bounds__(64 * NW, D == 128 ? NW / 2 : NW == 4 ? 3 : 6) void k_backward_dq(
     const __bf16 *__restrict__ dO, const __bf16 *__restrict__ V, const __bf16 *__restrict__ O,
     const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta, const __bf16 *__restrict__ K, int Lq, int Lk,
@@ -394,7 +395,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? NW / 2 : NW == 4 ? 3 : 6) void 
         }
     };
     int pair = rot;
-    Pace<> pace(visits);
+    Pace<PACED> pace(visits);
     for (int it = 0; it < visits; ++it) {
         pace.at(visits - it);
         const bool single = 2 * pair + 1 >= nblocks, last = it + 1 == visits;
@@ -549,7 +550,7 @@ struct DkvPlace {   // the kernel's LDS in 16-byte units (an access is one of a 
     static constexpr int AT_G = 0, AT_Q = XT, AT_P = 2 * XT, AT_M = AT_P + PT, AT_D = AT_M + QB, BUF = AT_D + QB / 4, AT_V = 2 * BUF;
     static constexpr int SIZE = AT_V + (V_LDS ? KB * (D / 8) : 0);
 };
-template <int D, bool UNP, bool CAREFUL, bool SPLIT>
+template <int D, bool UNP, bool CAREFUL, bool SPLIT, bool PACED>
 __device__ __forceinline__ bool dkv_pass(
     u32x4 *Smem, const int w, const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta, const __bf16 *__restrict__ dO,
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ V, const float *__restrict__ neg_delta, int Lq, int Lk,
@@ -737,7 +738,7 @@ __device__ __forceinline__ bool dkv_pass(
             if constexpr (UNP && !CAREFUL && D == 64) read_ahead<4 * DT, 2, 2, 0>();
         }
     };
-    Pace<> pace(nq);
+    Pace<PACED> pace(nq);
     for (int i = 0; i < nq; i += 2) {
         pace.at(nq - i);
         block(std::integral_constant<int, 0>{}, qb0 + i);
@@ -789,15 +790,15 @@ __device__ __forceinline__ bool dkv_pass(
     }
 }
 
-template <int D, bool UNP, bool SPLIT>
+template <int D, bool UNP, bool SPLIT, bool PACED>
 __global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void k_backward_dkv(
     const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta, const __bf16 *__restrict__ dO,
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ V, const float *__restrict__ neg_delta, int Lq, int Lk,
     int LqR, int LkR, float scale, uint16_t *__restrict__ dK, uint16_t *__restrict__ dV, int splits, float *__restrict__ part) {
     __shared__ u32x4 Smem[DkvPlace<D>::SIZE];
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    if (dkv_pass<D, UNP, false, SPLIT>(Smem, w, P, meta, dO, Q, V, neg_delta, Lq, Lk, LqR, LkR, scale, dK, dV, splits, part))
-        dkv_pass<D, UNP, true, SPLIT>(Smem, w, P, meta, dO, Q, V, neg_delta, Lq, Lk, LqR, LkR, scale, dK, dV, splits, part);
+    if (dkv_pass<D, UNP, false, SPLIT, PACED>(Smem, w, P, meta, dO, Q, V, neg_delta, Lq, Lk, LqR, LkR, scale, dK, dV, splits, part))
+        dkv_pass<D, UNP, true, SPLIT, false>(Smem, w, P, meta, dO, Q, V, neg_delta, Lq, Lk, LqR, LkR, scale, dK, dV, splits, part);
 }
 
 }  // namespace
@@ -893,21 +894,27 @@ hipError_t launch_backward(const void *dO, const void *Q, const void *K, const v
     const bool four = (long)BH * ((Lq + 127) / 128) >= 512;
     const unsigned grid_q = (unsigned)((long)BH * (four ? (Lq + 127) / 128 : Lq / 64)) * splits;
     const unsigned grid_k = (unsigned)((long)BH * (Lk / KB)) * splits_kv;
-#define DFSS_DQ(DD, NW, UU, SS)                                                                                          \
-    hipLaunchKernelGGL((k_backward_dq<DD, NW, UU, SS>), dim3(grid_q), dim3(64 * NW), 0, st, (const __bf16 *)dO,          \
+    // (workgroups that share: at the rate of one wave per SIMD, where it costs 1 - 3 %)
+    const bool level_q = splits == 1 && keep_level(grid_q, d == 128 ? 2 : four ? 3 : 4, Lk);
+    const bool level_k = splits_kv == 1 && keep_level(grid_k, d == 128 ? 2 : 3, Lq);
+#define DFSS_DQ(DD, NW, UU, SS, LL)                                                                                      \
+    hipLaunchKernelGGL((k_backward_dq<DD, NW, UU, SS, LL>), dim3(grid_q), dim3(64 * NW), 0, st, (const __bf16 *)dO,          \
                        (const __bf16 *)V, (const __bf16 *)O, (const uint32_t *)P, (const uint32_t *)meta,               \
                        (const __bf16 *)K, Lq, Lk, LqR, LkR, scale, (uint16_t *)dQ, neg_delta, splits, part_q)
-#define DFSS_DKV(DD, UU, SS)                                                                                             \
-    hipLaunchKernelGGL((k_backward_dkv<DD, UU, SS>), dim3(grid_k), dim3(NT), 0, st, (const uint32_t *)P,                 \
+#define DFSS_DKV(DD, UU, SS, LL)                                                                                         \
+    hipLaunchKernelGGL((k_backward_dkv<DD, UU, SS, LL>), dim3(grid_k), dim3(NT), 0, st, (const uint32_t *)P,                 \
                        (const uint32_t *)meta, (const __bf16 *)dO, (const __bf16 *)Q, (const __bf16 *)V, neg_delta, Lq, Lk, \
                        LqR, LkR, scale, (uint16_t *)dK, (uint16_t *)dV, splits_kv, part_kv)
 #define DFSS_BOTH(DD, UU)                                                \
     do {                                                                 \
-        if (four) DFSS_DQ(DD, 4, UU, false);                             \
-        else if (splits == 1) DFSS_DQ(DD, 2, UU, false);                 \
-        else DFSS_DQ(DD, 2, UU, true);                                   \
-        if (splits_kv == 1) DFSS_DKV(DD, UU, false);                     \
-        else DFSS_DKV(DD, UU, true);                                     \
+        if (four && level_q) DFSS_DQ(DD, 4, UU, false, true);            \
+        else if (four) DFSS_DQ(DD, 4, UU, false, false);                 \
+        else if (level_q) DFSS_DQ(DD, 2, UU, false, true);               \
+        else if (splits == 1) DFSS_DQ(DD, 2, UU, false, false);          \
+        else DFSS_DQ(DD, 2, UU, true, false);                            \
+        if (level_k) DFSS_DKV(DD, UU, false, true);                      \
+        else if (splits_kv == 1) DFSS_DKV(DD, UU, false, false);         \
+        else DFSS_DKV(DD, UU, true, false);                              \
     } while (0)
     if (d == 64) {
         if (unp) DFSS_BOTH(64, true); else DFSS_BOTH(64, false);

@@ -167,8 +167,8 @@ __device__ __forceinline__ void read_ahead() {
 // 4096, 24 heads, one-kernel forward pass: after 73, 94 and 117 us), and the last one runs by itself at the pace of a lone
 // wave, two thirds of what three reach together.  Here a wave gives up priority as it gets on -- at half, three quarters
 // and seven eighths of its steps -- so that whoever is behind goes first: 94, 100 and 106 us.  (Marks at 3/4, 7/8, 15/16: up to 2 %
-// slower, as are 1/4, 1/2, 3/4.)  It pays where a compute unit holds several workgroups of equal length; a wave by itself
-// loses up to 1 % to the test.
+// slower, as are 1/4, 1/2, 3/4.)  It pays where a compute unit holds several workgroups of equal length (keep_level in
+// dfss_kernels.hpp); a wave by itself loses up to 1 % to the test.
 template <bool ON = true>
 struct Pace {
     int half, mark;   // the steps are counted as what is left of them

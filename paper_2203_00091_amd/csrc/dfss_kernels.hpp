@@ -13,6 +13,24 @@ inline bool is_pow2(float x) {
     return frexpf(x, &e) == 0.5f;
 }
 
+// Whether the workgroups of a launch keep level on their compute units (Pace in dfss_device.hpp).  per_cu: how many a compute
+// unit holds; keys: how many each of them walks.
+// They do where all of them are resident at once, more than one to a compute unit, and where long ones fill every round, the
+// last one to `eighths` / 8 or more: who is level ends together, and what is left then starts late, on a chip filled in part.
+// us, without and with --
+//   all at once: 24 heads x 4096 x 4096, one kernel, 104 and 97
+//   one to a compute unit: 1 - 3 % slower
+//   a last round up to half full: stage 1, 1024 workgroups, 768 at a time, 8 x 4096 x 4096 37.0 and 40.5; with key lengths, 64 x 2048 x
+//     2048 61.3 and 71.4; dQ and dK, dV at d = 128, 768 of 512, 192 x 512 x 512 82.5 and 91.8
+//   two thirds full (80 x 2048 x 2048): one kernel 85.5 and 82.7, stage 1 90.6 and 94.3, backward pass 264 and 271; more (88 x 2048 x
+//     2048): 99.2 and 95.0, 99.5 and 98.6, 295 and 286
+//   whole rounds: one kernel, d = 128, two of them, 64 x 2048 x 2048 117 and 114; 512 keys: 256 x 512 x 512 37.5 and 38.1; 256 keys: 512 x
+//     256 x 256 26.6 and 27.7
+inline bool keep_level(unsigned grid, unsigned per_cu, int keys, unsigned eighths = 6) {
+    const unsigned resident = 256 * per_cu, last = grid % resident;
+    return grid > 256 && (grid <= resident || (keys >= 1024 && (last == 0 || 8 * last >= eighths * resident)));
+}
+
 // key_bias (where present): fp32 [BH / H][Lk] added to the scaled scores before the selection, or
 // nullptr for none (then H is ignored).
 // LqR, LkR (where present): the real lengths of the caller's arrays (Q, K, V, key_bias, O) when they differ from the

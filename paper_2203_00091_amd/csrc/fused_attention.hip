@@ -761,10 +761,10 @@ hipError_t launch_nq(const void *Q, const void *K, const void *V, const float *k
                      hipStream_t st) {
     const unsigned grid = (unsigned)((long)BH * ((Lq + 64 * NQ - 1) / (64 * NQ)));
     const bool pre = is_pow2(scale);
-    // More workgroups than compute units, a key bias: the ones with more blocks left go first (d = 64: 192 heads x 512 x 512 17.4 ->
-    // 16.5 us, 48 x 1024 x 1024 21.3 -> 20.0, 192 x 192 x 512 13.1 -> 12.3; d = 128 1 - 2 % slower; one to a compute unit 7 %).
+    // A key bias, several workgroups to a compute unit: the ones with more blocks left go first (d = 64: 192 heads x 512 x 512 17.4 ->
+    // 16.5 us, 48 x 1024 x 1024 21.3 -> 20.0, 192 x 192 x 512 13.1 -> 12.3; d = 128 1 - 2 % slower).
     if constexpr (MASKED && !RAGGED) {
-        if (d == 64 && key_bias && !block_mask && !causal && grid > 256) {
+        if (d == 64 && key_bias && !block_mask && !causal && keep_level(grid, NQ == 1 ? 4 : 3, Lk)) {
 #define DFSS_LAUNCH(PRE)                                                                                        \
     hipLaunchKernelGGL((k_fused<64, MODE, NQ, PRE, true, false, 1, 1, false, true>), dim3(grid), dim3(NT), 0, st, \
                        (const __bf16 *)Q, (const __bf16 *)K, (const __bf16 *)V, key_bias, H, block_mask, causal, \

@@ -530,16 +530,19 @@ hipError_t launch_nw(const void *Q, const void *K, const void *V, const float *k
                      const uint8_t *block_mask, int causal, int BH, int Lq, int Lk, int d, float scale, void *O,
                      hipStream_t st, const int *key_len = nullptr) {
     const unsigned grid = (unsigned)((long)BH * ((Lq + (RAGGED ? 32 * NW / KS - 1 : 0)) / (32 * NW / KS)));
-    // Workgroups of equal length that share a compute unit (256 of them) keep level: 24 heads x 4096 x 4096 104 -> 97 us, 48 x
-    // 1024 x 1024 19.6 -> 18.2, d = 128, 64 heads x 2048 117 -> 114.  One to a compute unit: 0.5 - 1.5 % slower with it.  The
-    // causal mask alone, where they differ in length: d = 128 73 -> 70 us, d = 64 0.5 - 1 % slower.
-    const bool paced = grid > 256 && !MASKED && (!CAUSAL_ONLY || d == 128);
+    // Workgroups of equal length that share a compute unit keep level: 24 heads x 4096 x 4096 104 -> 97 us, 48 x 1024 x 1024 19.6 ->
+    // 18.2, d = 128, 64 heads x 2048 117 -> 114.  (Resident: of two waves five by LDS at d = 64, else three of four waves; two at d =
+    // 128.)  The causal mask alone, where they differ in length, d = 128: up to 512 of them (all at once) 1 - 3 % slower, beyond that
+    // on long rows 1 - 3 % faster (64 x 2048 x 2048 68.2 -> 67.0 us, 96 x 1024 x 1024 33.7 -> 32.6, 256 x 512 x 512 33.2 and 34.7); d = 64 0.5 - 1 %
+    // slower.
+    const bool paced = CAUSAL_ONLY ? d == 128 && grid > 512 && Lk >= 1024
+                                   : !MASKED && MODE != MODE_DENSE && keep_level(grid, d == 128 ? 2 : NW == 2 ? 5 : 3, Lk, 5);
 #define DFSS_LAUNCH(DD, PP)                                                                                   \
     hipLaunchKernelGGL((k_fused32<DD, MODE, NW, KS, DFSS_OCC(DD), MASKED, VARLEN, CAUSAL_ONLY, RAGGED, PP>), dim3(grid), dim3(64 * NW), 0, st, \
                        (const __bf16 *)Q, (const __bf16 *)K, (const __bf16 *)V, key_bias, H, block_mask,      \
                        causal, Lq, Lk, scale, (uint16_t *)O, key_len)
     if (d == 64) {
-        if constexpr (!MASKED && !CAUSAL_ONLY) {
+        if constexpr (!MASKED && !CAUSAL_ONLY && MODE != MODE_DENSE) {
             if (paced) {
                 DFSS_LAUNCH(64, true);
                 return hipGetLastError();
@@ -547,7 +550,7 @@ hipError_t launch_nw(const void *Q, const void *K, const void *V, const float *k
         }
         DFSS_LAUNCH(64, false);
     } else {
-        if constexpr (!MASKED) {
+        if constexpr (!MASKED && MODE != MODE_DENSE) {
             if (paced) {
                 DFSS_LAUNCH(128, true);
                 return hipGetLastError();

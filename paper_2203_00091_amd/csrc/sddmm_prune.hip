@@ -263,7 +263,8 @@ enum { KMASK_NONE = 0, KMASK_CAUSAL = 1, KMASK_UNPADDED = 2 };
 // MASK2D (with BIAS): key_bias is an additive mask [LqR][LkR] (fp32, shared by all heads; -inf hides a key from a
 // query) instead of a per-key bias: every lane reads the 16 values of its own query's row from global memory at the
 // top of a block (the path of the per-key bias at d = 128); H is ignored.
-template <int D, int MODE, bool PRESCALE, bool BIAS, int KMASK, bool MASK2D = false>
+// PACED: the workgroups of a compute unit keep level (Pace).
+template <int D, int MODE, bool PRESCALE, bool BIAS, int KMASK, bool MASK2D = false, bool PACED = false>
 __global__ __launch_bounds__(NT, 2) void k_sddmm32(const __bf16 *__restrict__ Q, const __bf16 *__restrict__ K,
                                                    const float *__restrict__ key_bias, int H,
                                                    int Lq, int Lk, int LqR, int LkR, float scale, int ksplit,
@@ -383,7 +384,7 @@ __global__ __launch_bounds__(NT, 2) void k_sddmm32(const __bf16 *__restrict__ Q,
     u32x4 *const meta_row4 = reinterpret_cast<u32x4 *>(
         meta + (((size_t)bh * (Lq / 16) + ((q0 + lj) >> 4)) * (Lk / KB) * 16 + (lj & 15)) * 4);
 
-    Pace<> pace(blocks_per_wg);
+    Pace<PACED> pace(blocks_per_wg);
     for (int it = 0; it < blocks_per_wg; ++it) {
         pace.at(blocks_per_wg - it);
         const int jb = blk(it);
@@ -559,15 +560,26 @@ hipError_t launch32(const void *Q, const void *K, const float *key_bias, int H, 
     const int per_wg = kblocks / ksplit;
     const unsigned grid = (unsigned)((long)BH * qtiles * ksplit);
     const bool pre = is_pow2(scale);
-#define DFSS_LAUNCH(DD, PRE)                                                                             \
-    hipLaunchKernelGGL((k_sddmm32<DD, MODE, PRE, BIAS, KMASK, MASK2D>), dim3(grid), dim3(NT), 0, st,         \
+    // (plain calls: 24 x 4096 x 4096 102 -> 99 us, 1:2 94 -> 90, d = 128, 64 x 2048 x 2048 103 -> 102.  512 keys per workgroup: 2:4 at d = 64
+    // gains, 24 x 2048 x 2048 29.1 -> 28.0, 1:2, whose selection is the shorter one, does not, 96 x 1024 x 1024 26.3 and 27.5, nor d = 128, 256 x
+    // 512 x 512 32.9 and 33.7)
+    constexpr bool PACED = MODE != MODE_DENSE && !BIAS && KMASK != KMASK_CAUSAL;
+    const bool paced = PACED && keep_level(grid, d == 64 ? 3 : 2, KB * per_wg * (d == 64 && MODE == MODE_2TO4 ? 2 : 1));
+#define DFSS_LAUNCH_P(DD, PRE, PP)                                                                       \
+    hipLaunchKernelGGL((k_sddmm32<DD, MODE, PRE, BIAS, KMASK, MASK2D, PACED && PP>), dim3(grid), dim3(NT), 0, st, \
                        (const __bf16 *)Q, (const __bf16 *)K, key_bias, H, Lq, Lk, LqR, LkR, scale, ksplit, per_wg, \
                        (uint32_t *)out, (uint32_t *)meta)
+#define DFSS_LAUNCH(DD, PRE)                     \
+    do {                                         \
+        if (paced) DFSS_LAUNCH_P(DD, PRE, true); \
+        else DFSS_LAUNCH_P(DD, PRE, false);      \
+    } while (0)
     if (d == 64) {
         if (pre) DFSS_LAUNCH(64, true); else DFSS_LAUNCH(64, false);
     } else {
         if (pre) DFSS_LAUNCH(128, true); else DFSS_LAUNCH(128, false);
     }
+#undef DFSS_LAUNCH_P
 #undef DFSS_LAUNCH
     return hipGetLastError();
 }

@@ -41,7 +41,8 @@ constexpr int KB = 128;   // keys per block
 // lengths Lq (a multiple of 64) and Lk (of 128).  The weights of the absent keys are 0 (their scores were -inf); their
 // places in a partial last block of V are filled with the block's last real key, and rows past LqR are not stored.
 // SPARSE: compressed scores, turned into weights on the way; else dense weights.
-template <int D, bool SPARSE, int RB, bool UNPADDED = false>
+// PACED (compressed scores): the workgroups of a compute unit keep level (Pace).
+template <int D, bool SPARSE, int RB, bool UNPADDED = false, bool PACED = false>
 __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta,
                                               const __bf16 *__restrict__ V, int Lq, int Lk, int LqR, int LkR,
                                               uint16_t *__restrict__ O) {
@@ -199,7 +200,7 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
     if (nblocks > 1) load_a(blk(1), a_nxt);
     if constexpr (SOFTMAX) softmax_block(a_cur);
 
-    Pace<> pace(nblocks);
+    Pace<PACED> pace(nblocks);
     for (int jb = 0; jb < nblocks; ++jb) {   // jb: place in the order
         pace.at(nblocks - jb);
         const int buf = jb & 1;
@@ -453,10 +454,15 @@ hipError_t launch_av(const void *P, const void *meta, const void *V, int BH, int
                   void *O, hipStream_t st) {
     if (LqR != Lq || LkR != Lk) {   // unpadded lengths: 64-query workgroups (Lq is a multiple of 64)
         const unsigned grid = (unsigned)((long)BH * (Lq / 64));
-#define DFSS_LAUNCH(DD)                                                                                             \
-    hipLaunchKernelGGL((k_av<DD, SPARSE, 1, true>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P,     \
+        const bool paced = SPARSE && keep_level(grid, d == 64 ? 4 : 2, Lk);
+#define DFSS_LAUNCH(DD, PP)                                                                                         \
+    hipLaunchKernelGGL((k_av<DD, SPARSE, 1, true, SPARSE && PP>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P, \
                        (const uint32_t *)meta, (const __bf16 *)V, Lq, Lk, LqR, LkR, (uint16_t *)O)
-        if (d == 64) DFSS_LAUNCH(64); else DFSS_LAUNCH(128);
+        if (d == 64) {
+            if (paced) DFSS_LAUNCH(64, true); else DFSS_LAUNCH(64, false);
+        } else {
+            if (paced) DFSS_LAUNCH(128, true); else DFSS_LAUNCH(128, false);
+        }
 #undef DFSS_LAUNCH
         return hipGetLastError();
     }
@@ -464,14 +470,21 @@ hipError_t launch_av(const void *P, const void *meta, const void *V, int BH, int
     // from there on the larger tile wins, below it the finer grid does)
     bool rb2 = (Lq % 128 == 0) && ((long)BH * (Lq / 128) >= 512);
     const unsigned grid = (unsigned)((long)BH * (Lq / (rb2 ? 128 : 64)));
-#define DFSS_LAUNCH(DD, RR)                                                                                   \
-    hipLaunchKernelGGL((k_av<DD, SPARSE, RR>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P,              \
+    const bool paced = SPARSE && keep_level(grid, d == 128 ? 2 : rb2 ? 3 : 5, Lk);
+#define DFSS_LAUNCH_P(DD, RR, PP)                                                                             \
+    hipLaunchKernelGGL((k_av<DD, SPARSE, RR, false, SPARSE && PP>), dim3(grid), dim3(NT), 0, st, (const uint32_t *)P, \
                        (const uint32_t *)meta, (const __bf16 *)V, Lq, Lk, Lq, Lk, (uint16_t *)O)
+#define DFSS_LAUNCH(DD, RR)                    \
+    do {                                       \
+        if (paced) DFSS_LAUNCH_P(DD, RR, true); \
+        else DFSS_LAUNCH_P(DD, RR, false);     \
+    } while (0)
     if (d == 64) {
         if (rb2) DFSS_LAUNCH(64, 2); else DFSS_LAUNCH(64, 1);
     } else {
         if (rb2) DFSS_LAUNCH(128, 2); else DFSS_LAUNCH(128, 1);
     }
+#undef DFSS_LAUNCH_P
 #undef DFSS_LAUNCH
     return hipGetLastError();
 }

@@ -134,6 +134,14 @@ def test_forward_stages_then_backward_on_exact_scores():
     (140, 512, 256, 128, 2, 4),    # d = 128, 128-query workgroups
     (192, 300, 388, 64, 2, 4),     # no tile multiples: the last workgroup of a head half empty, and absent rows and keys
     (180, 330, 260, 128, 1, 2),
+    (512, 256, 128, 64, 2, 4),     # (dQ and dK, dV each on both sides of the rule that keeps workgroups level: a part-filled last round
+    (512, 200, 132, 64, 1, 2),     # does not, all at once do)
+    (128, 512, 256, 128, 2, 4),
+    (256, 200, 260, 128, 1, 2),
+    (90, 192, 384, 64, 2, 4),      # 64-query workgroups
+    (90, 150, 332, 64, 1, 2),
+    (70, 256, 512, 128, 1, 2),
+    (70, 230, 400, 128, 2, 4),
 ])
 def test_backward_on_grids_that_fill_the_chip(BH, Lq, Lk, d, N, M):
     """Waves that compete for the matrix unit see its results later than a lone wave does; sampled heads against the
