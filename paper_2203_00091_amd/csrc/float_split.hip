@@ -745,8 +745,10 @@ __global__ __launch_bounds__(NW * 64, (D == 64 && NW == 8) ? 4 : 2) void k_fused
                 acc[t] = mfma_split(Kh[pos], Kl[pos], qh[s], ql[s], acc[t]);
             }
         }
-        // (192 heads x 512 x 512 40.5 -> 40.0 us, d = 128 86.4 -> 81.8, 4 x 2048 x 2048, few waves, 50.1 -> 46.2)
-        read_ahead<4 * KS, 2, 2, 0, 0, 3>();
+        // (192 heads x 512 x 512 40.5 -> 40.0 us, d = 128 86.4 -> 81.8, 4 x 2048 x 2048, few waves, 50.1 -> 46.2; the dense form 57.3 -> 50.5, but
+        // with a bias 53.4 and 55.5, and with eight waves it runs out of registers)
+        constexpr bool AHEAD = PRUNE || D == 128 || RAGGED || BIAS == (NW == 8);
+        if constexpr (AHEAD) read_ahead<4 * KS, 2, 2, 0, 0, 3>();
 
         // selection: w[i] = kept score of pair i (keys 16g + 2i, +1), bit i of `second` = the later one was kept
         float w[NV];

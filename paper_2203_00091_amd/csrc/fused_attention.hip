@@ -34,8 +34,8 @@ namespace {
 
 constexpr int NT = 256;   // threads per workgroup (4 waves)
 constexpr int KB = 64;    // keys per block
-// Operands read from LDS ahead of the matrix instructions that need them, in both products (192 heads x 512 x 512 with a padding
-// bias 17.8 -> 17.4 us, d = 128, 96 heads 25.3 -> 23.4, unpadded 48 x 250 x 1000 14.7 -> 13.2; four in the first product cost
+// Operands read from LDS ahead of the matrix instructions that need them, in both products (d = 128, 96 heads x 512 x 512 with a padding
+// bias 25.3 -> 23.4, unpadded 48 x 250 x 1000 14.7 -> 13.2, block pattern 24 x 4096 x 4096 36.5 -> 34.6; four in the first product cost
 // registers: 2:4, 768 heads x 128 x 128 12.6 -> 14.6).
 constexpr int AHEAD = 2;
 constexpr float kTau = 8.0f;
@@ -157,6 +157,10 @@ __global__ __launch_bounds__(NT * G, 2) void k_fused(const __bf16 *__restrict__ 
     constexpr int DS = D / 16;          // 16-column tiles of O
     constexpr int TQ = 64 * NQ;         // queries per workgroup
     constexpr bool SPARSE = MODE != MODE_DENSE;
+    // Operands read ahead (AHEAD): where it is the faster order.  us, without and with: dense 24 heads x 4096 x 4096 106.7 and 108.3, d = 128
+    // 64 x 2048 125.6 and 127.7, general mask 16 x 1000 21.7 and 22.6; 128-query workgroups at d = 128, key bias 24 x 4096 181 and 186,
+    // unpadded 72 x 2000 172 and 184 (d = 64 level); shared rows of a block pattern, 2:4 at d = 64 24 x 4096 29.0 and 29.4.
+    constexpr bool READ_AHEAD = SPARSE && NQ == 1 && !(SPLIT > 1 && D == 64 && MODE == MODE_2TO4);
     static_assert(!RAGGED || MASKED, "ragged lengths use the masking machinery");
     static_assert(G == 1 || (MASKED && !RAGGED && NQ == 1), "key groups: block patterns on 64-query workgroups");
     static_assert(SPLIT == 1 || (MASKED && !RAGGED && NQ == 1 && G == 1), "split rows: block patterns, 64-query workgroups");
@@ -425,7 +429,7 @@ __global__ __launch_bounds__(NT * G, 2) void k_fused(const __bf16 *__restrict__ 
                         acc[qs][t] = mfma16(ak[t], bq[qs][s], c);
                     }
             }
-            read_ahead<4 * STEPS, 1, AHEAD, 0, 0, NQ>();
+            if constexpr (READ_AHEAD) read_ahead<4 * STEPS, 1, AHEAD, 0>();
         };
         if (MASKED && with_bias) {
 #pragma unroll
@@ -593,7 +597,7 @@ __global__ __launch_bounds__(NT * G, 2) void k_fused(const __bf16 *__restrict__ 
                 const bf16x8 a = __builtin_bit_cast(bf16x8, u32x4{pk[qs][0], pk[qs][1], pk[qs][2], pk[qs][3]});
                 acc_l[qs] = mfma16(a, ones8, acc_l[qs]);   // (against ones the positions do not matter: dense instruction)
             }
-            read_ahead<DS, 4, AHEAD, 1, NQ, NQ>();
+            if constexpr (READ_AHEAD) read_ahead<DS, 4, AHEAD, 1, 1>();
         } else {
             // dense: MFMA m (0/1) contracts the lane's keys 16 kb + 8 m .. +7
 #pragma unroll
