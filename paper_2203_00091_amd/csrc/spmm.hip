@@ -294,8 +294,8 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
 // V comes out of the L2 for every workgroup, one block ahead.  The workgroups start at different blocks and wrap around: the
 // rows of P are a power of two apart for the usual lengths, and workgroups in step would read the same few memory
 // channels at a time.  At d = 64 four neighbours start together and share V blocks; at d = 128 every one starts on its own.
-// (Two blocks of weights ahead at d = 64: 102 us instead of 89, as two workgroups per compute unit are left of three; a wave of
-// its own for V, 64 keys at a time, in front of two blocks of weights: 111.)
+// (Two blocks of weights ahead at d = 64 on such grids: 102 us instead of 89, as two workgroups per compute unit are left of three; a wave
+// of its own for V, 64 keys at a time, in front of two blocks of weights: 111.)
 // VB: V buffers, one if there is one block of keys.
 template <int D, int RB, int NW, int PD, bool UNPADDED, int VB = 2>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : VB == 1 ? 5 : NW == 8 ? 4 : 3) void k_spmm(
@@ -501,6 +501,9 @@ hipError_t launch_av(const void *P, const void *meta, const void *V, int BH, int
 //     flight; from a workgroup per compute unit on (32 x 2048 x 2048 31.0 against 33.5, 64 x 2048 x 2048 83.3 against 88.0; 24 x
 //     2048 x 2048 28.1 against 27.1) and 16 blocks of keys on (64 x 1024 x 1024 20.9 against 19.7)
 // A larger tile only if not more than an eighth is added to the queries.
+// d = 64, one workgroup of 64 queries per compute unit, weights that exceed the L2s (8 x 4 MB) and so come from further away: two
+//   blocks of them in flight, for which there is room (4 x 4096 x 4096 21.7 -> 18.1 us, 8 x 2048 x 2048 12.4 -> 10.7; 6 x 2048 x 2048, 24 MB, level; 16 x
+//   1024 x 1024, 16 MB, 6.5 against 6.6)
 hipError_t launch_sparse(const void *P, const void *meta, const void *V, int BH, int Lq, int Lk, int LqR, int LkR, int d,
                          void *O, hipStream_t st) {
     const bool unp = LqR != Lq || LkR != Lk;
@@ -521,7 +524,8 @@ hipError_t launch_sparse(const void *P, const void *meta, const void *V, int BH,
                                (const uint32_t *)meta, (const __bf16 *)V, Lq, Lk, LqR, LkR, (uint16_t *)O);           \
     } while (0)
     if (d == 64) {
-        if (tq == 64) DFSS_LAUNCH(64, 1, 4, 1, 2);
+        if (tq == 64 && grid <= 256 && (long)BH * Lq * Lk >= (1l << 25)) DFSS_LAUNCH(64, 1, 4, 2, 2);
+        else if (tq == 64) DFSS_LAUNCH(64, 1, 4, 1, 2);
         else if (tq == 256) DFSS_LAUNCH(64, 2, 8, 1, 2);
         else if (Lk == KB) DFSS_LAUNCH(64, 2, 4, 1, 1);   // more workgroups at a time (1024 heads x 128 x 128 10.4 -> 9.7 us)
         else DFSS_LAUNCH(64, 2, 4, 1, 2);

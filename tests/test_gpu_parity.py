@@ -237,6 +237,9 @@ def test_stage3_spmm_pairs_of_key_blocks(BH, Lq, Lk, d, N, M):
     (48, 2000, 2044, 128, 1, 2),   # d = 128: 256 queries, 16 blocks of keys; a workgroup with two waves past the last query
     (260, 256, 2176, 128, 2, 4),   # ... 17 blocks
     (230, 320, 2048, 128, 2, 4),   # (256 queries per workgroup would add a third: 128 add a fifth, 64 it is)
+    (4, 2048, 4096, 64, 2, 4),     # d = 64, few workgroups of 64 queries, long rows: two blocks of weights in flight, 32 blocks
+    (5, 3264, 2176, 64, 1, 2),     # ... 17 blocks, 255 workgroups
+    (250, 40, 4000, 64, 2, 4),     # ... no tile multiples
 ])
 def test_stage3_spmm_every_tile(BH, Lq, Lk, d, N, M):
     """Both sizes of a tile and the rule between them: the weights that stages 1 and 2 leave, some heads whole against the product in
