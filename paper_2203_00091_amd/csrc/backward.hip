@@ -823,42 +823,52 @@ namespace {
 
 // How many workgroups share the keys of a query tile (dQ) and the queries of a key tile (dV and dK); 1: none.  A tile is walked at
 // the pace of one workgroup, and a small grid leaves most of the chip idle; sharing costs the sums, written and read in fp32,
-// and the kernel that adds them.  The counts are the powers of two with the least of
-//     us per step x steps / count x (1 + slope (workgroups / chip - 1) beyond a full chip) + sums, at 5 TB/s + 4 us for that kernel
-// (a larger count has to save a tenth), where it gains 2 us or more and the two kernels take longer than their launches (one head x
-// 512 x 512, d = 64: 19.2 us, with a third launch 22.1).  Measured alone: a step of dQ, 128 keys, 1.4 us at d = 64 and 2.2 at d = 128, the
-// chip full with 512 workgroups of two waves; a step of dV and dK, 64 queries, 0.9 and 1.56 us, full with 256 of four.
-// The whole pass, before (keys shared at d = 128 up to 128 tiles) and now, us: d = 64, one head x 4096 x 4096 102 -> 37, 4 x 4096 103
-// -> 65, 4 x 2048 55 -> 33, 4 x 1024 31 -> 23, 4 x 4096 x 512 66 -> 26; d = 128, one head x 4096 122 -> 50, 4 x 4096 171 -> 114, 4 x
+// and the kernel that adds them.  The counts -- the powers of two and, for the keys, two pairs of blocks each -- are those with the least of
+//     us per step x steps / count x (1 + slope (workgroups / chip - 1) beyond a full chip) + sums, at 5 TB/s + 4 us for that kernel,
+//     the first part at least what it takes to read K and V (Q and dO), at 6 TB/s
+// (a larger count has to save a tenth; without the lower bound d = 128, 64 heads x 64 x 4096 82 us, with it 76) as long as the workgroups are all resident at once; beyond that a further round begins (d = 128, 3
+// heads x 3072 x 1536: 56 us with it, 50 without; d = 64, 16 x 1536 x 8192 180 and 166; 96 x 256 x 8192 253 and 236).
+// Shared where it gains 2 us or more and the two kernels take longer than their launches (one head x 512 x 512, d = 64: 19.2 us, with a
+// third launch 22.1).  At d = 128, where the keys weigh more, sooner (one head x 64 x 512 18.5 -> 16.5 us, x 768 23.0 -> 16.9, 48 x 64 x 512
+// 20.6 -> 20.1; 64 x 64 x 512 21.3, shared 21.8).
+// Measured alone: a step of dQ, 128 keys, 1.4 us at d = 64 and 2.2 at d = 128, the chip full with 512 workgroups of two waves (1024 and 512
+// are resident); a step of dV and dK, 64 queries, 0.9 and 1.56 us, full with 256 of four (768 and 512).
+// The whole pass, before (keys shared at d = 128 up to 128 tiles) and now, us: d = 64, one head x 4096 x 4096 102 -> 34, 4 x 4096 103
+// -> 68, 4 x 2048 55 -> 33, 4 x 1024 31 -> 23, 4 x 4096 x 512 66 -> 26; d = 128, one head x 4096 122 -> 48, 4 x 4096 171 -> 109, 4 x
 // 2048 76 -> 47; left alone, rightly: 12 x 1024 (31.4; shared by two 32.0), 24 x 512 (19.4; 25.5), 48 x 512 at d = 128 (33.9; 46.3).
+// (12 x 2048 x 2048, d = 64, would gain: 61.5, shared by two 57.4.)
 struct Sharing {
     int dq, dkv;
 };
-float shared_us(float step, int steps, int n, float fill, float slope, double sum_bytes) {
-    return step * (float)steps / (float)n * (fill * n > 1.f ? 1.f + slope * (fill * n - 1.f) : 1.f) + (n > 1 ? (float)(n * sum_bytes / 5.0e6) : 0.f);
+float shared_us(float step, int steps, int n, float fill, float slope, double sum_bytes, double read_bytes) {
+    const float work = step * (float)steps / (float)n * (fill * n > 1.f ? 1.f + slope * (fill * n - 1.f) : 1.f), read = (float)(read_bytes / 6.0e6);
+    return (n > 1 && work < read ? read : work) + (n > 1 ? (float)(n * sum_bytes / 5.0e6) : 0.f);
 }
 Sharing sharing(int BH, int Lq, int Lk, int LqR, int LkR, int d) {
-    constexpr float kMerge = 4.f, kGain = 2.f, kHost = 16.f;
+    const float kGain = d == 64 ? 6.f : 3.f, kHost = d == 64 ? 16.f : 10.f;
     const int pairs = (LkR + KB - 1) / KB, steps = (LqR + 63) / 64;
     const long wg_q = (long)BH * (Lq / 64), wg_k = (long)BH * (Lk / KB);
+    const long resident_q = d == 64 ? 1024 : 512, resident_k = d == 64 ? 768 : 512;
     const float step_q = d == 64 ? 1.4f : 2.2f, step_k = d == 64 ? 0.9f : 1.56f;
-    const double bytes_q = 8. * BH * LqR * d, bytes_k = 16. * BH * LkR * d;   // written and read
+    const double bytes_q = 8. * BH * LqR * d, bytes_k = 16. * BH * LkR * d;   // sums, written and read
+    const double read_q = 4. * BH * LkR * d, read_k = 4. * BH * LqR * d;
     Sharing s = {1, 1};
-    const float alone_q = shared_us(step_q, pairs, 1, wg_q / 512.f, 0.f, 0.), alone_k = shared_us(step_k, steps, 1, wg_k / 256.f, 0.f, 0.);
+    const float alone_q = shared_us(step_q, pairs, 1, wg_q / 512.f, 0.f, 0., 0.), alone_k = shared_us(step_k, steps, 1, wg_k / 256.f, 0.f, 0., 0.);
     float best_q = alone_q, best_k = alone_k;
-    for (int n = 2; n <= 32 && n <= pairs / 2 && wg_q < 512; n *= 2) {   // (128-query workgroups do not share)
-        const float us = shared_us(step_q, pairs, n, wg_q / 512.f, d == 64 ? 0.35f : 1.f, bytes_q);
+    const int most = pairs / 2 < 32 ? pairs / 2 : 32;
+    for (int n = 2; n <= most && wg_q < 512 && n * wg_q <= resident_q; n = n < most && 2 * n > most ? most : 2 * n) {   // (128-query workgroups do not share)
+        const float us = shared_us(step_q, pairs, n, wg_q / 512.f, d == 64 ? 0.35f : 1.f, bytes_q, read_q);
         if (us < 0.9f * best_q) best_q = us, s.dq = n;
     }
-    for (int n = 2; n <= 16 && n <= steps / 4 && wg_k <= 256; n *= 2) {
-        const float us = shared_us(step_k, steps, n, wg_k / 256.f, 0.35f, bytes_k);
+    for (int n = 2; n <= 16 && n <= steps / 4 && wg_k <= 256 && n * wg_k <= resident_k; n *= 2) {
+        const float us = shared_us(step_k, steps, n, wg_k / 256.f, 0.35f, bytes_k, read_k);
         if (us < 0.92f * best_k) best_k = us, s.dkv = n;
     }
     // the kernel that adds is paid once
     const float gain_q = alone_q - best_q, gain_k = alone_k - best_k;
-    if (alone_q + alone_k < kHost || gain_q + gain_k < kMerge + kGain) return {1, 1};
-    if (gain_q < kGain / 2) s.dq = 1;
-    if (gain_k < kGain / 2) s.dkv = 1;
+    if (alone_q + alone_k < kHost || gain_q + gain_k < kGain) return {1, 1};
+    if (gain_q < 1.f) s.dq = 1;
+    if (gain_k < 1.f) s.dkv = 1;
     return s;
 }
 

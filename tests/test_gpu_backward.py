@@ -177,23 +177,37 @@ def test_backward_on_grids_that_fill_the_chip(BH, Lq, Lk, d, N, M):
             assert np.max(np.abs(got - ref)) <= tol, (name, h)
 
 
-@pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
-    (1, 64, 512, 128, 2, 4),       # dQ: two workgroups share the keys of a query tile (d = 128: from 512 keys on)
-    (2, 128, 640, 128, 1, 2),      # ... five pairs of key blocks for two
-    (1, 1, 8192, 128, 2, 4),       # ... 32 workgroups; one query
-    (2, 70, 580, 128, 2, 4),       # ... no tile multiples; a single block in the last pair
-    (1, 64, 4096, 64, 1, 2),       # ... d = 64: from 32 pairs on
-    (3, 100, 4100, 64, 2, 4),
-    (9, 60, 4096, 64, 2, 4),       # (more than 8 tiles: one workgroup each)
-    (2, 128, 256, 64, 2, 4),
-    (1, 1100, 256, 64, 2, 4),      # dV, dK: workgroups share the queries of a key tile; a partial last block of queries
-    (2, 640, 128, 128, 1, 2),      # ... d = 128
-    (3, 1000, 1500, 64, 2, 4),     # ... and the keys in dQ, no tile multiples
-    (1, 2048, 1024, 128, 2, 4),
+def _sharing_bytes(s, keys, queries):
+    """The workspace of a backward pass whose dQ tiles are shared by `keys` workgroups, whose dV, dK tiles by `queries` (1: none):
+    the row terms, then the fp32 sums."""
+    up = lambda n: (n + 255) // 256 * 256
+    return (up(4 * s.BH * s.LqP) + (up(4 * keys * s.BH * s.Lq * s.d) if keys > 1 else 0)
+            + (up(8 * queries * s.BH * s.Lk * s.d) if queries > 1 else 0))
+
+
+@pytest.mark.parametrize("BH,Lq,Lk,d,N,M,keys,queries", [
+    (1, 64, 512, 128, 2, 4, 2, 1),      # dQ: two workgroups share the keys of a query tile
+    (2, 128, 640, 128, 1, 2, 2, 1),     # ... five pairs of key blocks for two
+    (1, 1, 8192, 128, 2, 4, 32, 1),     # ... 32 workgroups; one query
+    (2, 70, 580, 128, 2, 4, 2, 1),      # ... no tile multiples; four keys in the last block
+    (2, 70, 572, 128, 2, 4, 2, 1),      # ... a single block in the last pair
+    (2, 70, 2092, 128, 1, 2, 8, 1),     # ... 17 pairs for eight workgroups
+    (1, 64, 4096, 64, 1, 2, 16, 1),     # ... d = 64
+    (3, 100, 4100, 64, 2, 4, 16, 1),
+    (9, 60, 4096, 64, 2, 4, 16, 1),
+    (1, 100, 1400, 64, 1, 2, 5, 1),     # ... five: two pairs each, the last one three
+    (2, 128, 256, 64, 2, 4, 1, 1),      # (nobody shares)
+    (1, 1100, 256, 64, 2, 4, 1, 4),     # dV, dK: workgroups share the queries of a key tile; a partial last block of queries
+    (2, 640, 128, 128, 1, 2, 1, 2),     # ... d = 128
+    (3, 1000, 1500, 64, 2, 4, 6, 4),    # ... and the keys in dQ, no tile multiples
+    (1, 2048, 1024, 128, 2, 4, 4, 8),
+    (1, 1990, 1020, 128, 1, 2, 4, 8),
+    (1, 700, 260, 128, 2, 4, 1, 2),
 ])
-def test_backward_with_a_workspace_of_exactly_the_size_it_asks_for(BH, Lq, Lk, d, N, M):
-    """Few queries against many keys, against the oracle; poisoned scratch of exactly dfss_backward_workspace_bytes and
-    guards behind it and behind every gradient."""
+def test_backward_with_a_workspace_of_exactly_the_size_it_asks_for(BH, Lq, Lk, d, N, M, keys, queries):
+    """Few queries against many keys and the other way round, against the oracle; poisoned scratch of exactly
+    dfss_backward_workspace_bytes, which tells how many workgroups share, and guards behind it and behind every gradient."""
+    assert dfss.dfss_backward_workspace_bytes(Shape(1, BH, Lq, Lk, d, N, M)) == _sharing_bytes(Shape(1, BH, Lq, Lk, d, N, M), keys, queries)
     scale = 1.0 / math.sqrt(d)
     Q, K, V = synth.gaussian_qkv(BH, Lq, Lk, d, 1.0, seed=9900 + Lq + Lk + d)
     dO = torch.randn(BH, Lq, d, generator=torch.Generator().manual_seed(9901 + Lk)).to(torch.bfloat16)
