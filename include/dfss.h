@@ -350,8 +350,8 @@ dfss_status dfss_spmm_t(const void *vals, const void *meta, const void *X, const
  * dK, dV [B*H, Lk, d], bfloat16.  ws: device scratch of dfss_backward_workspace_bytes(), 256-byte aligned (2-byte dtype:
  * the row terms delta and, on grids too small to fill the chip, partial sums of the gradients; 4-byte dtype: dS).  With the
  * 2-byte dtype a smaller one will do as long as it holds the row terms, 4 * B*H * LqP bytes rounded up to 256: the sums are
- * then not shared out, which is slower and rounds differently (so one workspace of the largest shape's size serves smaller
- * shapes, whose own size may be larger).  A key bias of the forward pass needs no extra argument: masked entries have weight 0
+ * then shared out as far as they fit, which may be slower and rounds differently (so one workspace of the largest shape's size
+ * serves smaller shapes, whose own size may be larger).  A key bias of the forward pass needs no extra argument: masked entries have weight 0
  * and so receive and pass on no gradient.  Two kernels with the 2-byte dtype (and one that adds the partial sums): dQ and delta over the keys of a
  * query, then dV and dK over the queries of a key; each forms dS from P, the stored position codes and dO V^T in registers.
  * An infinity or a NaN reaches gradients through kept entries (and dV through dO) only: a row of V that no query kept may

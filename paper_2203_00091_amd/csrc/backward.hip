@@ -821,6 +821,11 @@ hipError_t launch_spmm_t(const void *vals, const void *meta, const void *X, int 
 
 namespace {
 
+size_t align256(size_t x) { return (x + 255) / 256 * 256; }
+size_t delta_bytes(int BH, int Lq) { return align256((size_t)BH * Lq * sizeof(float)); }
+size_t dq_sum_bytes(int n, int BH, int LqR, int d) { return n == 1 ? 0 : align256((size_t)n * BH * LqR * d * sizeof(float)); }
+size_t dkv_sum_bytes(int n, int BH, int LkR, int d) { return n == 1 ? 0 : align256((size_t)n * 2 * BH * LkR * d * sizeof(float)); }
+
 // How many workgroups share the keys of a query tile (dQ) and the queries of a key tile (dV and dK); 1: none.  A tile is walked at
 // the pace of one workgroup, and a small grid leaves most of the chip idle; sharing costs the sums, written and read in fp32,
 // and the kernel that adds them.  The counts -- the powers of two and, for the keys, two pairs of blocks each -- are those with the least of
@@ -837,6 +842,7 @@ namespace {
 // -> 68, 4 x 2048 55 -> 33, 4 x 1024 31 -> 23, 4 x 4096 x 512 66 -> 26; d = 128, one head x 4096 122 -> 48, 4 x 4096 171 -> 109, 4 x
 // 2048 76 -> 47; left alone, rightly: 12 x 1024 (31.4; shared by two 32.0), 24 x 512 (19.4; 25.5), 48 x 512 at d = 128 (33.9; 46.3).
 // (12 x 2048 x 2048, d = 64, would gain: 61.5, shared by two 57.4.)
+// room: bytes there are for the sums; the counts are those whose sums fit, and if they do not fit together, those of the part that gains more.
 struct Sharing {
     int dq, dkv;
 };
@@ -844,7 +850,7 @@ float shared_us(float step, int steps, int n, float fill, float slope, double su
     const float work = step * (float)steps / (float)n * (fill * n > 1.f ? 1.f + slope * (fill * n - 1.f) : 1.f), read = (float)(read_bytes / 6.0e6);
     return (n > 1 && work < read ? read : work) + (n > 1 ? (float)(n * sum_bytes / 5.0e6) : 0.f);
 }
-Sharing sharing(int BH, int Lq, int Lk, int LqR, int LkR, int d) {
+Sharing sharing(int BH, int Lq, int Lk, int LqR, int LkR, int d, size_t room = SIZE_MAX) {
     const float kGain = d == 64 ? 6.f : 3.f, kHost = d == 64 ? 16.f : 10.f;
     const int pairs = (LkR + KB - 1) / KB, steps = (LqR + 63) / 64;
     const long wg_q = (long)BH * (Lq / 64), wg_k = (long)BH * (Lk / KB);
@@ -856,47 +862,43 @@ Sharing sharing(int BH, int Lq, int Lk, int LqR, int LkR, int d) {
     const float alone_q = shared_us(step_q, pairs, 1, wg_q / 512.f, 0.f, 0., 0.), alone_k = shared_us(step_k, steps, 1, wg_k / 256.f, 0.f, 0., 0.);
     float best_q = alone_q, best_k = alone_k;
     const int most = pairs / 2 < 32 ? pairs / 2 : 32;
-    for (int n = 2; n <= most && wg_q < 512 && n * wg_q <= resident_q; n = n < most && 2 * n > most ? most : 2 * n) {   // (128-query workgroups do not share)
+    for (int n = 2; n <= most && wg_q < 512 && n * wg_q <= resident_q && dq_sum_bytes(n, BH, LqR, d) <= room; n = n < most && 2 * n > most ? most : 2 * n) {   // (128-query workgroups do not share)
         const float us = shared_us(step_q, pairs, n, wg_q / 512.f, d == 64 ? 0.35f : 1.f, bytes_q, read_q);
         if (us < 0.9f * best_q) best_q = us, s.dq = n;
     }
-    for (int n = 2; n <= 16 && n <= steps / 4 && wg_k <= 256 && n * wg_k <= resident_k; n *= 2) {
+    for (int n = 2; n <= 16 && n <= steps / 4 && wg_k <= 256 && n * wg_k <= resident_k && dkv_sum_bytes(n, BH, LkR, d) <= room; n *= 2) {
         const float us = shared_us(step_k, steps, n, wg_k / 256.f, 0.35f, bytes_k, read_k);
         if (us < 0.92f * best_k) best_k = us, s.dkv = n;
     }
+    float gain_q = alone_q - best_q, gain_k = alone_k - best_k;
+    if (dkv_sum_bytes(s.dkv, BH, LkR, d) > room - dq_sum_bytes(s.dq, BH, LqR, d)) {
+        if (gain_q < gain_k) s.dq = 1, gain_q = 0.f;
+        else s.dkv = 1, gain_k = 0.f;
+    }
     // the kernel that adds is paid once
-    const float gain_q = alone_q - best_q, gain_k = alone_k - best_k;
     if (alone_q + alone_k < kHost || gain_q + gain_k < kGain) return {1, 1};
     if (gain_q < 1.f) s.dq = 1;
     if (gain_k < 1.f) s.dkv = 1;
     return s;
 }
 
-size_t align256(size_t x) { return (x + 255) / 256 * 256; }
-size_t delta_bytes(int BH, int Lq) { return align256((size_t)BH * Lq * sizeof(float)); }
-
 }  // namespace
 
 // The row terms -delta, fp32 [BH][Lq] (the least that the pass needs), then the sums of the workgroups that share keys (dQ) and of
 // those that share queries (dV and dK).
 size_t backward_workspace_least(int BH, int Lq) { return delta_bytes(BH, Lq); }
-namespace {
-size_t dq_sum_bytes(int n, int BH, int LqR, int d) { return n == 1 ? 0 : align256((size_t)n * BH * LqR * d * sizeof(float)); }
-size_t dkv_sum_bytes(int n, int BH, int LkR, int d) { return n == 1 ? 0 : align256((size_t)n * 2 * BH * LkR * d * sizeof(float)); }
-}  // namespace
 size_t backward_workspace_bytes(int BH, int Lq, int Lk, int LqR, int LkR, int d) {
     const Sharing s = sharing(BH, Lq, Lk, LqR, LkR, d);
     return delta_bytes(BH, Lq) + dq_sum_bytes(s.dq, BH, LqR, d) + dkv_sum_bytes(s.dkv, BH, LkR, d);
 }
 
-// P, meta: as kept from the forward pass.  ws: backward_workspace_least or more; keys and queries are shared if all the sums fit
+// P, meta: as kept from the forward pass.  ws: backward_workspace_least or more; keys and queries are shared as far as the sums fit
 // (the whole is less for a large grid than for a small one, and a workspace made for the largest shape has to do for all).
 hipError_t launch_backward(const void *dO, const void *Q, const void *K, const void *V, const void *O, const void *P,
                            const void *meta, int BH, int Lq, int Lk, int LqR, int LkR, int d, float scale, void *ws,
                            size_t ws_bytes, void *dQ, void *dK, void *dV, hipStream_t st) {
     const bool unp = LqR != Lq || LkR != Lk;
-    Sharing s = sharing(BH, Lq, Lk, LqR, LkR, d);
-    if (ws_bytes < delta_bytes(BH, Lq) + dq_sum_bytes(s.dq, BH, LqR, d) + dkv_sum_bytes(s.dkv, BH, LkR, d)) s = {1, 1};
+    const Sharing s = sharing(BH, Lq, Lk, LqR, LkR, d, ws_bytes - delta_bytes(BH, Lq));
     float *const neg_delta = (float *)ws, *const part_q = (float *)((char *)ws + delta_bytes(BH, Lq));
     float *const part_kv = (float *)((char *)part_q + dq_sum_bytes(s.dq, BH, LqR, d));
     const int splits = s.dq, splits_kv = s.dkv;

@@ -270,6 +270,38 @@ def test_backward_with_a_workspace_that_holds_the_row_terms_only():
         run(least - 256)
 
 
+@pytest.mark.parametrize("Lq,Lk", [(2048, 1152), (1990, 1020)])
+def test_backward_shares_as_far_as_the_workspace_reaches(Lq, Lk):
+    """Shared keys and shared queries need two parts of a workspace.  One that holds fewer sums, or those of one part only, is used for
+    these; all of them give the oracle's gradients, and what is shared shows in the order of the sums."""
+    s, scale = Shape(1, 1, Lq, Lk, 128), 1.0 / math.sqrt(128)
+    g = torch.Generator().manual_seed(9960)
+    Q, K, V, dO = (torch.randn(1, L, 128, generator=g).to(DEV, torch.bfloat16) for L in (Lq, Lk, Lk, Lq))
+    P, meta = dfss.dfss_sddmm_prune(Q, K, s, scale)
+    dfss.dfss_sparse_softmax(P, s)
+    O = dfss.dfss_spmm(P, meta, V, s)
+    kidx = oracle.decode_meta(dfss.dfss_meta_to_canonical(meta, s)[0].cpu().numpy().view(np.uint16), s.LkP)[:Lq]
+    real, Ph = kidx < Lk, _np(P[0])[:Lq]
+    refs = oracle.attention_backward(*(_np(t[0]) for t in (Q, K, V, dO)), np.where(real, Ph, 0.0).astype(np.float32),
+                                     np.where(real, kidx, 0).astype(np.int32), scale)
+
+    def run(n):
+        ws = torch.full((n + 4096,), 0xFF, dtype=torch.uint8, device=DEV)
+        out = dfss.dfss_attention_backward(dO, Q, K, V, O, P, meta, s, scale, ws=ws[:n])
+        torch.cuda.synchronize()
+        assert bool((ws[n:] == 0xFF).all()), "wrote behind the workspace"
+        for got, ref in zip(out, refs):
+            assert np.max(np.abs(_np(got[0]) - ref)) <= 2.0 ** -7 * np.max(np.abs(ref)) + 1e-4      # as above
+        return out
+
+    assert dfss.dfss_backward_workspace_bytes(s) == _sharing_bytes(s, 4, 8)
+    both, queries, fewer, keys, alone = (run(n) for n in (_sharing_bytes(s, 4, 8), _sharing_bytes(s, 1, 8), _sharing_bytes(s, 1, 2),
+                                                          _sharing_bytes(s, 2, 1), _sharing_bytes(s, 1, 1)))
+    same = [[torch.equal(a, b) for a, b in zip(x, alone)] for x in (both, queries, fewer, keys)]
+    assert same == [[False, False, False], [True, False, False], [True, False, False], [False, True, True]]
+    assert torch.equal(queries[1], both[1]) and not torch.equal(fewer[1], both[1])      # eight, and two
+
+
 @pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
     (2, 128, 256, 64, 2, 4), (2, 192, 128, 64, 1, 2), (2, 64, 384, 128, 2, 4),
     (2, 100, 132, 64, 2, 4), (2, 70, 260, 128, 1, 2),       # no tile multiples
