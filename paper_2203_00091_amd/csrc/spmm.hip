@@ -297,7 +297,8 @@ __global__ __launch_bounds__(NT, 2) void k_av(const uint32_t *__restrict__ P, co
 // (Two blocks of weights ahead at d = 64 on such grids: 102 us instead of 89, as two workgroups per compute unit are left of three; a wave
 // of its own for V, 64 keys at a time, in front of two blocks of weights: 111.)
 // VB: V buffers, one if there is one block of keys.
-template <int D, int RB, int NW, int PD, bool UNPADDED, int VB = 2>
+// PACED: the workgroups of a compute unit keep level (Pace).
+template <int D, int RB, int NW, int PD, bool UNPADDED, int VB = 2, bool PACED = true>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : VB == 1 ? 5 : NW == 8 ? 4 : 3) void k_spmm(
     const uint32_t *__restrict__ P, const uint32_t *__restrict__ meta, const __bf16 *__restrict__ V, int Lq, int Lk, int LqR, int LkR,
     uint16_t *__restrict__ O) {
@@ -427,7 +428,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : VB == 1 ? 5 : NW == 8 ? 4 :
             }
         }
     };
-    Pace<> pace(nblocks);
+    Pace<PACED> pace(nblocks);
     for (int it = 0; it < nblocks; it += 2) {
         pace.at(nblocks - it);
         block(std::integral_constant<int, 0>{}, it);
@@ -514,25 +515,31 @@ hipError_t launch_sparse(const void *P, const void *meta, const void *V, int BH,
     if (fits(256) && (d == 64 ? Lk >= 512 && (long)BH * tiles(128) > 768 && (long)BH * tiles(256) <= 512 : Lk >= 2048 && (long)BH * tiles(256) >= 256))
         tq = 256;
     const unsigned grid = (unsigned)((long)BH * tiles(tq));
-#define DFSS_LAUNCH(DD, RR, WW, PP, VV)                                                                               \
+    // Workgroups keep level where there are more of them than compute units (us, without and with: d = 64 24 x 2048 x 2048 20.9 and 19.6, 24 x
+    // 4096 x 4096 92.0 and 89.3; d = 128 96 x 512 x 512 12.0 and 11.3, 64 x 1024 x 1024 20.2 and 19.6; 192 x 512 x 512 13.6 and 13.9, the other way).
+    // Up to one per compute unit they only lose by it (2 x 4096 x 4096 17.4 and 17.7, d = 128 4 x 4096 x 4096 28.5 and 28.9, 12 x 1024 x 1024 9.4 and 9.5).
+    const bool alone = grid <= 256;
+#define DFSS_LAUNCH(DD, RR, WW, PP, VV, LL)                                                                           \
     do {                                                                                                              \
         if (unp)                                                                                                      \
-            hipLaunchKernelGGL((k_spmm<DD, RR, WW, PP, true, VV>), dim3(grid), dim3(64 * WW), 0, st, (const uint32_t *)P, \
+            hipLaunchKernelGGL((k_spmm<DD, RR, WW, PP, true, VV, LL>), dim3(grid), dim3(64 * WW), 0, st, (const uint32_t *)P, \
                                (const uint32_t *)meta, (const __bf16 *)V, Lq, Lk, LqR, LkR, (uint16_t *)O);           \
         else                                                                                                          \
-            hipLaunchKernelGGL((k_spmm<DD, RR, WW, PP, false, VV>), dim3(grid), dim3(64 * WW), 0, st, (const uint32_t *)P, \
+            hipLaunchKernelGGL((k_spmm<DD, RR, WW, PP, false, VV, LL>), dim3(grid), dim3(64 * WW), 0, st, (const uint32_t *)P, \
                                (const uint32_t *)meta, (const __bf16 *)V, Lq, Lk, LqR, LkR, (uint16_t *)O);           \
     } while (0)
     if (d == 64) {
-        if (tq == 64 && grid <= 256 && (long)BH * Lq * Lk >= (1l << 25)) DFSS_LAUNCH(64, 1, 4, 2, 2);
-        else if (tq == 64) DFSS_LAUNCH(64, 1, 4, 1, 2);
-        else if (tq == 256) DFSS_LAUNCH(64, 2, 8, 1, 2);
-        else if (Lk == KB) DFSS_LAUNCH(64, 2, 4, 1, 1);   // more workgroups at a time (1024 heads x 128 x 128 10.4 -> 9.7 us)
-        else DFSS_LAUNCH(64, 2, 4, 1, 2);
+        if (tq == 64 && alone && (long)BH * Lq * Lk >= (1l << 25)) DFSS_LAUNCH(64, 1, 4, 2, 2, false);
+        else if (tq == 64 && alone) DFSS_LAUNCH(64, 1, 4, 1, 2, false);
+        else if (tq == 64) DFSS_LAUNCH(64, 1, 4, 1, 2, true);
+        else if (tq == 256) DFSS_LAUNCH(64, 2, 8, 1, 2, true);
+        else if (Lk == KB) DFSS_LAUNCH(64, 2, 4, 1, 1, true);   // more workgroups at a time (1024 heads x 128 x 128 10.4 -> 9.7 us)
+        else DFSS_LAUNCH(64, 2, 4, 1, 2, true);
     } else {
-        if (tq == 64) DFSS_LAUNCH(128, 1, 4, 1, 2);
-        else if (tq == 128) DFSS_LAUNCH(128, 2, 4, 1, 2);
-        else DFSS_LAUNCH(128, 2, 8, 2, 2);
+        if (tq == 64 && alone) DFSS_LAUNCH(128, 1, 4, 1, 2, false);
+        else if (tq == 64) DFSS_LAUNCH(128, 1, 4, 1, 2, true);
+        else if (tq == 128) DFSS_LAUNCH(128, 2, 4, 1, 2, true);
+        else DFSS_LAUNCH(128, 2, 8, 2, 2, true);
     }
 #undef DFSS_LAUNCH
     return hipGetLastError();
