@@ -346,7 +346,10 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : VB == 1 ? 5 : NW == 8 ? 4 :
             async_copy16(src, 2u * ((UNPADDED && v_row[i] > last ? last : v_row[i]) * D + v_chunk[i]), lds_v + 16u * (buf * TILE + i * THREADS));
     };
     // The wave's kept weights of a block: row r, chunk c (keys 16 c .. +15) at r * 8 + (c ^ ((r >> 1) & 7)); copy i brings rows
-    // 8 i .. +7, for which the pattern is that of copy i % 2.
+    // 8 i .. +7, for which the pattern is that of copy i % 2.  (Two lanes meet in every group of banks of the reads below; so do lane
+    // groups of V's at d = 128: conflicts in 17 and 50 % of the LDS cycles.  LDS does not bound the kernel: with chunk c at ((c >> 1) | (c & 1) << 2) ^
+    // (r & 7), free of conflicts, 23 shapes were level at d = 64 and up to 2.5 % slower at d = 128 (8 x 2048 x 2048 16.3 and 16.7 us), with V by
+    // tr_row_swizzle in addition up to 4.7 % (64 x 512 x 512 8.5 and 8.8).)
     const uint64_t p_base = uniform_address(P + ((size_t)bh * Lq + (size_t)rbp * 16) * (size_t)(Lk / 4));
     const uint32_t p_off = (uint32_t)(l >> 3) * (uint32_t)Lk + 16u * ((l & 7) ^ (l >> 4));
     const uint32_t *const m_row = meta + (((size_t)bh * (Lq / 16) + rbp) * nblocks * 16 + li) * 4 + meta_slot;
