@@ -583,7 +583,8 @@ hipError_t launch_mode(const void *Q, const void *K, const void *V, const float 
 // 128-query workgroups, us without and with: up to 128 (half of the chip idle; key lengths) 12 x 1024 x 1024 13.1 -> 11.3, 4 x 4096 x 4096 43.5 ->
 // 33.1, d = 128 18.6 -> 15.4, 61.7 -> 45.5, 24 x 512 x 512 8.5 -> 7.8 (256 keys level); d = 64 up to 384 on long rows 48 x 1024 x 1024
 // 18.1 -> 16.7, 12 x 3000 x 3000 43.9 -> 39.4 (24 x 1000 x 1000, 192 of them, 14.2 against 15.2; 16 x 1500 x 1500 level); d = 128 up to
-// 192 5 x 4000 x 4000 64.1 -> 55.0 (24 x 1000 x 1000 20.2 against 20.7; 12 x 3000 x 3000, 288 of them, 66 against 80).
+// 192 5 x 4000 x 4000 64.1 -> 55.0, 12 x 1532 x 1532 27.2 -> 26.0, key lengths 12 x 1536 x 1536 25.4 -> 23.8 (24 x 1000 x 1000 20.2 against 20.7; 12 x
+// 3000 x 3000, 288 of them, 66 against 80).  Calls without either are level between 1536 and 2048 keys (12 x 1536 x 1536 26.0 and 25.7) and begin at 2048.
 bool share_blocks(int BH, int Lq, int Lk, int d) {
     const long wg = (long)BH * ((Lq + 127) / 128);
     if (wg <= 128) return Lk >= 384;
@@ -594,8 +595,10 @@ bool share_blocks(int BH, int Lq, int Lk, int d) {
 template <int MODE>
 hipError_t launch_varlen(const void *Q, const void *K, const void *V, const int *key_len, int H, int BH, int Lq, int Lk,
                          int d, float scale, void *O, hipStream_t st) {
-    // (an odd multiple of 64 queries: against two-wave workgroups 96 x 192 x 1024 17.1 -> 12.4 us, d = 128 21.4 -> 18.9)
-    const bool odd = Lq % 128 != 0 && Lk >= 384 && (long)BH * (Lq / 64) <= (d == 64 ? 768 : 288);
+    // An odd multiple of 64 queries: against two-wave workgroups 96 x 192 x 1024 17.1 -> 12.4 us, d = 64 up to 750 of them (24 x 1472 x 1536
+    // 26 -> 19, 750 x 64 x 512 17.2 -> 16.7); d = 128 21.4 -> 18.9, 200 x 64 x 512 13.2 -> 12.0, but with more of them than compute units and
+    // short rows 96 x 192 x 384 11.2 and 11.9, 280 x 64 x 512 14.4 and 15.3 (640 keys: 15.1 and 14.6).
+    const bool odd = Lq % 128 != 0 && Lk >= 384 && (long)BH * (Lq / 64) <= (d == 64 ? 768 : Lk > 512 ? 288 : 256);
     if (odd || share_blocks(BH, Lq, Lk, d))
         return launch_nw<MODE, 4, 2, false, true>(Q, K, V, nullptr, H, nullptr, 0, BH, Lq, Lk, d, scale, O, st, key_len);
     if (Lq % 128 == 0)
