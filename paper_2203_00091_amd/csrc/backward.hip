@@ -251,6 +251,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? NW / 2 : NW == 4 ? 3 : 6) void 
     constexpr int LPT = TILE / THREADS;      // asynchronous copies per thread, block and operand
     constexpr int STEPS = D / 16;
     constexpr int DT = D / 32;
+    constexpr bool EARLY = D == 128 && (NW == 4 || SPLIT);   // operands are read ahead
     constexpr int TQ = 32 * NW;
     __shared__ u32x4 Vs[2][TILE], Kr[2][TILE], Ps[NW][32 * 8];
 
@@ -387,9 +388,9 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? NW / 2 : NW == 4 ? 3 : 6) void 
                     bf16x16, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15));
                 acc_q[dt] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(a, b, acc_q[dt], (int)codes, 0, 0);
             }
-            // (d = 128, four waves: whole pass 24 x 4096 x 4096 502 -> 500 us, 64 x 2048 level; two waves, 20 x 1500 x 1500 76.8 and 77.3; d = 64, three
-            // waves per SIMD, 3 % slower)
-            if constexpr (D == 128 && NW == 4) {
+            // (d = 128, four waves: whole pass 24 x 4096 x 4096 502 -> 500 us, 64 x 2048 level; two waves, 20 x 1500 x 1500 76.8 and 77.3, but with
+            // shared keys 5 x 2240 x 2240 68.7 -> 66.2, 2 x 2368 x 636 34.3 -> 33.3; d = 64, three waves per SIMD, 3 % slower)
+            if constexpr (EARLY) {
                 read_ahead<STEPS, 1, 2, 0>();
                 read_ahead<DT, 4, 2, 0>();
             }
@@ -410,14 +411,15 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? NW / 2 : NW == 4 ? 3 : 6) void 
         for (int i = 0; i < 4; ++i) cur.v[i] = Ps[w][lj * 8 + ((2 * i + h) ^ operand_row_swizzle<8, 32>(lj))];
         // The weights have to be in registers before their place is given to the next ones.  Two waves, on grids where a SIMD has one:
         // behind the first block, whose products hide that wait (d = 128 whole pass, 20 x 1100 x 1100 61.8 -> 60.0 us, 16 x 2000 x 2000
-        // 103 -> 99; d = 64, 24 x 1024 x 1024 35.5 -> 35.0).  Four waves: right away (24 x 4096 x 4096 274, behind it 278).
+        // 103 -> 99; d = 64, 24 x 1024 x 1024 35.5 -> 35.0).  Right away with four waves (24 x 4096 x 4096 274, behind it 278) and, together with
+        // the reads in order, where keys are shared at d = 128.
         auto ask = [&]() {
             asm volatile("" : "+v"(cur.v[0]), "+v"(cur.v[1]), "+v"(cur.v[2]), "+v"(cur.v[3]) : : "memory");
             if (!last) next_codes = load_kept(after);
         };
-        if constexpr (NW == 4) ask();
+        if constexpr (NW == 4 || EARLY) ask();
         block(std::integral_constant<int, 0>{}, cur);
-        if constexpr (NW == 2) ask();
+        if constexpr (!(NW == 4 || EARLY)) ask();
         if (single) {   // (the other buffer is free: everybody is past its use)
             __syncthreads();
             if (!last) issue_block(2 * after, 0);
