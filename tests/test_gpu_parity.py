@@ -195,14 +195,14 @@ def test_stage3_spmm(BH, Lq, Lk, d, N, M):
 
 
 @pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
-    (512, 128, 384, 64, 2, 4),    # two row blocks per wave; a pair of key blocks and a single one
-    (520, 128, 128, 128, 1, 2),   # ... a single block only
-    (5, 64, 640, 64, 1, 2),       # one row block per wave; every starting pair, the single block in the middle too
-    (7, 192, 768, 128, 2, 4),
-    (5, 64, 1152, 64, 1, 2),      # few workgroups, 9 blocks: taken in pairs from every place, the single one in the middle too
-    (9, 64, 512, 64, 2, 4),       # ... an even number of blocks: from four on
+    (512, 128, 384, 64, 2, 4),    # tiles of 128 queries, three blocks of keys
+    (520, 128, 128, 128, 1, 2),   # ... d = 128, a single block
+    (5, 64, 640, 64, 1, 2),       # tiles of 64 queries, five blocks, begun at one place or another
+    (7, 192, 768, 128, 2, 4),     # ... d = 128, six
+    (5, 64, 1152, 64, 1, 2),      # ... nine
+    (9, 64, 512, 64, 2, 4),       # ... four
 ])
-def test_stage3_spmm_pairs_of_key_blocks(BH, Lq, Lk, d, N, M):
+def test_stage3_spmm_on_random_weights_at_random_positions(BH, Lq, Lk, d, N, M):
     """The product on kept weights of random values at random positions, against the dense product in 64 bits."""
     g = torch.Generator().manual_seed(7600 + Lk + d)
     W = torch.rand(BH, Lq, Lk // 2, generator=g).to(torch.bfloat16)
@@ -264,15 +264,15 @@ def test_stage3_spmm_every_tile(BH, Lq, Lk, d, N, M):
 
 
 @pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
-    (512, 128, 3712, 64, 2, 4),   # d = 64: two row blocks per wave, 29 key blocks (an odd number)
-    (220, 256, 1536, 64, 1, 2),   # ... one, nearly four workgroups per compute unit
-    (32, 2048, 3712, 128, 1, 2),  # d = 128: two row blocks, an odd number of key blocks
-    (16, 2048, 8192, 128, 2, 4),  # ... one
+    (512, 128, 3712, 64, 2, 4),   # d = 64: tiles of 128 queries, 29 key blocks (an odd number)
+    (220, 256, 1536, 64, 1, 2),   # ... of 64, nearly four workgroups per compute unit
+    (32, 2048, 3712, 128, 1, 2),  # d = 128: 256, two blocks of weights in flight, an odd number of key blocks
+    (16, 2048, 8192, 128, 2, 4),  # ... 128
     (16, 2050, 8100, 128, 2, 4),  # ... no tile multiples
-    (16, 1000, 8100, 128, 2, 4),  # (fewer queries: the kernel that keeps to one block)
+    (16, 1000, 8100, 128, 2, 4),  # ... 64
 ])
 def test_stage3_spmm_on_weights_that_exceed_the_cache(BH, Lq, Lk, d, N, M):
-    """The kernel that streams pairs of key blocks and the sizes it is taken for: the weights that stages 1 and 2 leave,
+    """Long streams of weights, with every size of a tile: the weights that stages 1 and 2 leave,
     sampled rows of sampled heads against the product in 64 bits."""
     g = torch.Generator(device=DEV).manual_seed(7700 + Lk + d)
     Q, K, V = (torch.randn((BH, L, d), generator=g, device=DEV).to(torch.bfloat16) for L in (Lq, Lk, Lk))
