@@ -761,15 +761,17 @@ __device__ __forceinline__ bool dkv_pass(
         for (int r = 0; r < 16; ++r) {
             const int key = jblk * KB + 32 * w + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
             if (UNP && key >= LkR) continue;
+            if constexpr (SPLIT) {   // [split][dV, dK][head and key][D]; the 64-bit part of the address is the same in every lane
+                const size_t n = (size_t)(gridDim.x / splits / kblocks) * LkR * D;
+                float *const pv = part + 2 * sp * n + (size_t)bh * LkR * D;
+                const uint32_t to = (uint32_t)key * D + (lane & 31);
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) pv[to + 32 * dt] = acc_v[dt][r], pv[n + to + 32 * dt] = acc_k[dt][r];
+                continue;
+            }
             const size_t at = ((size_t)bh * LkR + key) * D + (lane & 31);
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {
-                if constexpr (SPLIT) {   // [split][dV, dK][head and key][D]
-                    const size_t n = (size_t)(gridDim.x / splits / kblocks) * LkR * D;
-                    part[2 * sp * n + at + 32 * dt] = acc_v[dt][r];
-                    part[(2 * sp + 1) * n + at + 32 * dt] = acc_k[dt][r];
-                    continue;
-                }
                 dV[at + 32 * dt] = (uint16_t)(pack_bf16x2(acc_v[dt][r], 0.f) & 0xFFFFu);
                 dK[at + 32 * dt] = (uint16_t)(pack_bf16x2(acc_k[dt][r] * scale, 0.f) & 0xFFFFu);
             }
