@@ -842,11 +842,12 @@ size_t dkv_sum_bytes(int n, int BH, int LkR, int d) { return n == 1 ? 0 : align2
 // and the kernel that adds them.  The counts -- the powers of two and, for the keys, two pairs of blocks each -- are those with the least of
 //     us per step x steps / count x (1 + slope (workgroups / chip - 1) beyond a full chip) + sums, at 5 TB/s + 4 us for that kernel,
 //     the first part at least what it takes to read K and V (Q and dO), at 6 TB/s
-// (a larger count has to save a tenth; without the lower bound d = 128, 64 heads x 64 x 4096 82 us, with it 76) as long as the workgroups are all resident at once; beyond that a further round begins (d = 128, 3
-// heads x 3072 x 1536: 56 us with it, 50 without; d = 64, 16 x 1536 x 8192 180 and 166; 96 x 256 x 8192 253 and 236).
+// (a larger count has to save a tenth; without the lower bound d = 128, 64 heads x 64 x 4096 82 us, with it 76), as long as the workgroups
+// are all resident at once; beyond that a further round begins (d = 128, 3 heads x 3072 x 1536: 56 us with it, 50 without; d = 64, 16 x
+// 1536 x 8192 180 and 166; 96 x 256 x 8192 253 and 236).
 // Shared where it gains 2 us or more and the two kernels take longer than their launches (one head x 512 x 512, d = 64: 19.2 us, with a
 // third launch 22.1).  At d = 128, where the keys weigh more, sooner (one head x 64 x 512 18.5 -> 16.5 us, x 768 23.0 -> 16.9, 48 x 64 x 512
-// 20.6 -> 20.1; 64 x 64 x 512 21.3, shared 21.8).
+// 20.6 -> 20.1; 64 x 64 x 512 21.3, shared 21.8.  On the GPU: where call after call is launched by the host, the first of these takes 18.8 and 20.6.)
 // Measured alone: a step of dQ, 128 keys, 1.4 us at d = 64 and 2.2 at d = 128, the chip full with 512 workgroups of two waves (1024 and 512
 // are resident); a step of dV and dK, 64 queries, 0.9 and 1.56 us, full with 256 of four (768 and 512).
 // The whole pass, before (keys shared at d = 128 up to 128 tiles) and now, us: d = 64, one head x 4096 x 4096 102 -> 34, 4 x 4096 103

@@ -13,8 +13,8 @@ namespace {
 constexpr int NT = 256;
 
 // A team of TPR lanes owns a row; lane t holds the 16-byte chunks t, t+TPR, ... (NCH of them).  Bound by the stream, read once and
-// written once (24 heads x 4096 x 4096, 806 MB: 6.7 TB/s); a team has RPT rows, all of their loads in flight before the first
-// is used.
+// written once (24 heads x 4096 x 4096, 806 MB: 5.6 TB/s cold, 6.9 right after stage 1, whose output is partly still in the last-level
+// cache); a team has RPT rows, all of their loads in flight before the first is used.
 // F32: the row holds fp32 values (the 4-byte mode), else bfloat16.
 template <int TPR, int NCH, bool F32, int RPT>
 __global__ __launch_bounds__(NT) void k_row_softmax(uint32_t *__restrict__ x, long rows, int cols) {
