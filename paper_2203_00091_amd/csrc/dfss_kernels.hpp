@@ -15,8 +15,8 @@ inline bool is_pow2(float x) {
 
 // Whether the workgroups of a launch keep level on their compute units (Pace in dfss_device.hpp).  per_cu: how many a compute
 // unit holds; keys: how many each of them walks.
-// They do where all of them are resident at once, more than one to a compute unit, and where long ones fill every round, the
-// last one to `eighths` / 8 or more: who is level ends together, and what is left then starts late, on a chip filled in part.
+// They do where all of them are resident at once, more than one to a compute unit, and where long ones, of `from` keys on, fill every
+// round, the last one to `eighths` / 8 or more: who is level ends together, and what is left then starts late, on a chip filled in part.
 // us, without and with --
 //   all at once: 24 heads x 4096 x 4096, one kernel, 104 and 97
 //   one to a compute unit: 1 - 3 % slower
@@ -26,9 +26,9 @@ inline bool is_pow2(float x) {
 //     2048): 99.2 and 95.0, 99.5 and 98.6, 295 and 286
 //   whole rounds: one kernel, d = 128, two of them, 64 x 2048 x 2048 117 and 114; 512 keys: 256 x 512 x 512 37.5 and 38.1; 256 keys: 512 x
 //     256 x 256 26.6 and 27.7
-inline bool keep_level(unsigned grid, unsigned per_cu, int keys, unsigned eighths = 6) {
+inline bool keep_level(unsigned grid, unsigned per_cu, int keys, unsigned eighths = 6, int from = 1024) {
     const unsigned resident = 256 * per_cu, last = grid % resident;
-    return grid > 256 && (grid <= resident || (keys >= 1024 && (last == 0 || 8 * last >= eighths * resident)));
+    return grid > 256 && (grid <= resident || (keys >= from && (last == 0 || 8 * last >= eighths * resident)));
 }
 
 // key_bias (where present): fp32 [BH / H][Lk] added to the scaled scores before the selection, or

@@ -532,11 +532,16 @@ hipError_t launch_nw(const void *Q, const void *K, const void *V, const float *k
     const unsigned grid = (unsigned)((long)BH * ((Lq + (RAGGED ? 32 * NW / KS - 1 : 0)) / (32 * NW / KS)));
     // Workgroups of equal length that share a compute unit keep level: 24 heads x 4096 x 4096 104 -> 97 us, 48 x 1024 x 1024 19.6 ->
     // 18.2, d = 128, 64 heads x 2048 117 -> 114.  (Resident: of two waves five by LDS at d = 64, else three of four waves; two at d =
-    // 128.)  The causal mask alone, where they differ in length, d = 128: up to 512 of them (all at once) 1 - 3 % slower, beyond that
-    // on long rows 1 - 3 % faster (64 x 2048 x 2048 68.2 -> 67.0 us, 96 x 1024 x 1024 33.7 -> 32.6, 256 x 512 x 512 33.2 and 34.7); d = 64 0.5 - 1 %
-    // slower.
-    const bool paced = CAUSAL_ONLY ? d == 128 && grid > 512 && Lk >= 1024
-                                   : !MASKED && MODE != MODE_DENSE && keep_level(grid, d == 128 ? 2 : NW == 2 ? 5 : 3, Lk, 5);
+    // 128.)  A last round filled in part, without and with: d = 64 from three eighths on (a third, 64 x 2048 x 2048, 69.2 and 70.3; 40 %, 67 x
+    // 2048 x 2048, 84.3 and 81.8; 51 %, 40 x 3700 x 3700, 145 and 140; 55 %, 170 x 896 x 896, 39.2 and 38.2), d = 128 from a half on (44 %, 46 x 2048 x
+    // 2048, 90.6 and 92.1; 48 %, 94 x 1024 x 1024, 51.0 and 52.2; 53 %, 49 x 2048 x 2048, 107.7 and 102.7; 52 %, 130 x 768 x 768, 44.5 and 43.1), key
+    // lengths at d = 64, where workgroups end apart anyway, from five eighths on (50 and 58 %, 72 and 76 x 2048 x 2048, 66.4 and 76, 72.5 and 76.7;
+    // 67 %, 80 x 2048 x 2048 71 and 74 but 40 x 4096 x 4096 132 and 128; 83 %, 176 x 1024 x 1024, 43.1 and 41.5).
+    // The causal mask alone, where they differ in length, d = 128: up to 512 of them (all at once) 1 - 3 % slower, beyond that on long rows
+    // 1 - 5 % faster (64 x 2048 x 2048 68.2 -> 67.0 us, 96 x 1024 x 1024 33.7 -> 32.6, 163 x 640 x 640 35.1 -> 33.8, 128 x 768 x 768 29.9 -> 28.7; 160 x 512 x
+    // 512 21.5 and 22.2, 200 x 512 x 512 27.6 and 26.2, 400 x 384 x 384 36.4 and 37.2); d = 64 0.5 - 1 % slower.
+    const bool paced = CAUSAL_ONLY ? d == 128 && grid > 512 && Lk >= 640
+                                   : !MASKED && MODE != MODE_DENSE && keep_level(grid, d == 128 ? 2 : NW == 2 ? 5 : 3, Lk, d == 128 ? 4 : VARLEN ? 5 : 3, 768);
 #define DFSS_LAUNCH(DD, PP)                                                                                   \
     hipLaunchKernelGGL((k_fused32<DD, MODE, NW, KS, DFSS_OCC(DD), MASKED, VARLEN, CAUSAL_ONLY, RAGGED, PP>), dim3(grid), dim3(64 * NW), 0, st, \
                        (const __bf16 *)Q, (const __bf16 *)K, (const __bf16 *)V, key_bias, H, block_mask,      \
