@@ -918,9 +918,14 @@ hipError_t launch_backward(const void *dO, const void *Q, const void *K, const v
     const bool four = (long)BH * ((Lq + 127) / 128) >= 512;
     const unsigned grid_q = (unsigned)((long)BH * (four ? (Lq + 127) / 128 : Lq / 64)) * splits;
     const unsigned grid_k = (unsigned)((long)BH * (Lk / KB)) * splits_kv;
-    // (workgroups that share: at the rate of one wave per SIMD, where it costs 1 - 3 %)
-    const bool level_q = splits == 1 && keep_level(grid_q, d == 128 ? 2 : four ? 3 : 4, Lk);
-    const bool level_k = splits_kv == 1 && keep_level(grid_k, d == 128 ? 2 : 3, Lq);
+    // Workgroups that keep level; not those that share: at the rate of one wave per SIMD it costs 1 - 3 %.  Two to a compute unit: also
+    // where the last round has more than one for each (whole pass without and with, 49 x 2048 x 2048 306 and 295, 100 x 1024 x 1024 165 and
+    // 161, 26 x 4096 x 4096 584 and 565; one for each, 96 x 1024 x 1024, 147 and 156).  Three: 80 x 2048 x 2048, two thirds full, 259 and 270.
+    auto level = [](unsigned grid, unsigned per_cu, int walked) {
+        return keep_level(grid, per_cu, walked, per_cu == 2 ? 4 : 6, per_cu == 2 ? 512 : 1024) && !(per_cu == 2 && grid > 512 && grid % 512 == 256);
+    };
+    const bool level_q = splits == 1 && level(grid_q, d == 128 ? 2 : four ? 3 : 4, Lk);
+    const bool level_k = splits_kv == 1 && level(grid_k, d == 128 ? 2 : 3, Lq);
 #define DFSS_DQ(DD, NW, UU, SS, LL)                                                                                      \
     hipLaunchKernelGGL((k_backward_dq<DD, NW, UU, SS, LL>), dim3(grid_q), dim3(64 * NW), 0, st, (const __bf16 *)dO,          \
                        (const __bf16 *)V, (const __bf16 *)O, (const uint32_t *)P, (const uint32_t *)meta,               \
