@@ -563,8 +563,14 @@ hipError_t launch32(const void *Q, const void *K, const float *key_bias, int H, 
     // (plain calls: 24 x 4096 x 4096 102 -> 99 us, 1:2 94 -> 90, d = 128, 64 x 2048 x 2048 103 -> 102.  512 keys per workgroup: 2:4 at d = 64
     // gains, 24 x 2048 x 2048 29.1 -> 28.0, 1:2, whose selection is the shorter one, does not, 96 x 1024 x 1024 26.3 and 27.5, nor d = 128, 256 x
     // 512 x 512 32.9 and 33.7)
+    // Keys shared, two rounds of 256 and more each, the last one three quarters full: by itself, over and over, stage 1 is level, but with the
+    // other kernels of a training step around it 192 x 512 x 512 1:2 takes 20.1 and 18.2 us (the step 104.0 and 101.6; 2:4 106.6 and 105.6, 176 x 512 x
+    // 512 101.6 and 100.1, d = 128 128 x 512 x 512 111.5 and 109.7; 48 x 1024 x 1024 102.2 and 102.8).  Not with fewer in the last round (160 x 512 x
+    // 512 1:2 13.8 and 15.3), three rounds (d = 128, 192 x 512 x 512 25.1 and 27.0) or keys that are not shared (d = 128, 256 x 512 x 512, above).
     constexpr bool PACED = MODE != MODE_DENSE && !BIAS && KMASK != KMASK_CAUSAL;
-    const bool paced = PACED && keep_level(grid, d == 64 ? 3 : 2, KB * per_wg * (d == 64 && MODE == MODE_2TO4 ? 2 : 1));
+    const unsigned per_cu = d == 64 ? 3 : 2, resident = 256 * per_cu;
+    const bool two_rounds = ksplit > 1 && KB * per_wg >= 256 && 4 * grid >= 7 * resident && grid <= 2 * resident;
+    const bool paced = PACED && (two_rounds || keep_level(grid, per_cu, KB * per_wg * (d == 64 && MODE == MODE_2TO4 ? 2 : 1)));
 #define DFSS_LAUNCH_P(DD, PRE, PP)                                                                       \
     hipLaunchKernelGGL((k_sddmm32<DD, MODE, PRE, BIAS, KMASK, MASK2D, PACED && PP>), dim3(grid), dim3(NT), 0, st, \
                        (const __bf16 *)Q, (const __bf16 *)K, key_bias, H, Lq, Lk, LqR, LkR, scale, ksplit, per_wg, \

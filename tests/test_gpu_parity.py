@@ -318,6 +318,28 @@ def _staged_attention(Qd, Kd, Vd, s, scale):
     return dfss.dfss_attention_staged(Qd, Kd, Vd, s, scale)
 
 
+@pytest.mark.parametrize("BH,Lq,Lk,d,N,M", [
+    (176, 512, 512, 64, 1, 2),    # keys shared by two, 1408 workgroups: more than seven quarters of a round of 768
+    (168, 512, 512, 64, 1, 2),    # 1344: exactly seven quarters
+    (167, 512, 512, 64, 2, 4),    # 1336: just below
+    (192, 512, 512, 64, 2, 4),    # two whole rounds
+    (128, 512, 512, 128, 2, 4),   # d = 128, rounds of 512: 1024
+    (34, 1100, 1140, 128, 1, 2),  # ... shared by three, 918, unpadded
+])
+def test_stage1_two_rounds_of_shared_keys(BH, Lq, Lk, d, N, M):
+    """Whether workgroups keep level is a matter of time only: the same bits as eight heads at a time, which do not."""
+    g = torch.Generator().manual_seed(BH)
+    Q, K = (_dev(torch.randn((BH, n, d), generator=g).to(torch.bfloat16)) for n in (Lq, Lk))
+    vals, meta = dfss.dfss_sddmm_prune(Q, K, Shape(1, BH, Lq, Lk, d, N, M), 1.0 / math.sqrt(d))
+    for h in range(0, BH, 8):
+        n = min(8, BH - h)
+        s = Shape(1, n, Lq, Lk, d, N, M)
+        v, m = dfss.dfss_sddmm_prune(Q[h:h + n].contiguous(), K[h:h + n].contiguous(), s, 1.0 / math.sqrt(d))
+        words = m.numel() // n
+        assert torch.equal(v.view(torch.int16), vals[h:h + n].contiguous().view(torch.int16)), h
+        assert torch.equal(m, meta[h * words:(h + n) * words]), h
+
+
 def _check_attention(w, heads=None):
     Q, K, V = synth.make(w)
     s = Shape(w.B, w.H, w.L, w.L, w.d, w.N, w.M)
